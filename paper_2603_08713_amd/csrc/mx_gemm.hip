@@ -27,6 +27,30 @@ int choose_shape(int64_t M, int64_t N, bool use_mbs, bool ring_ok, bool pairs_ok
     return 10;
 }
 
+// The few-row kernel's tile for M <= 64: the smallest fm that covers the rows; fn so that the launch has about one
+// workgroup per compute unit (one workgroup's wavefronts hold all of its weights in flight, so a second round costs a
+// second round trip to memory, and every workgroup reads - or, fused, quantizes - all of A).  Measured, M = 16 / K = 4096,
+// fn = 1, 2, 4: N = 4096 5.1, 5.6, 7.0 us; N = 14336 11.0, 10.5, 9.1 us (fused 17.5, 15.1, 11.3).
+struct SkinnyPlan {
+    int fm, fn, form;
+};
+SkinnyPlan plan_skinny(int64_t M, int64_t N, int64_t K, bool ring_ok, bool pairs_ok) {
+    SkinnyPlan p;
+    p.fm = M <= 16 ? 1 : M <= 32 ? 2 : 4;
+    p.form = ring_ok ? (K % 4096 == 0 ? 0 : 1) : pairs_ok ? 2 : 3;
+    const int64_t frags = (N + 15) / 16;
+    p.fn = frags > 2 * 256 ? 4 : frags > 256 ? 2 : 1;
+    // (what the forms with one LDS dword per piece have room for)
+    if (p.form == 2 && p.fn > 2) p.fn = 2;
+    if (p.form == 3) p.fn = 1;
+    return p;
+}
+// Grouped problems take the few-row kernel up to this many rows per group on average: it streams the weights once per
+// 32 rows, the main kernel once per 128 or 256 but at a quarter of the rate.  Measured (Zipf routing, rows per group 8,
+// 32, 64; few-row against main kernel): 32 groups of 2880 x 2880 35, 54, 79 against 59, 72, 91 us; 8 of 2048 x 2048 7, 9,
+// 15 against 13, 13, 13; 64 of 1024 x 1024 15, 23, 35 against 17, 25, 25.
+constexpr int64_t kFewRowsPerGroup = 32;
+
 int launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* a_mbs, const uint8_t* b_codes,
                 const uint8_t* b_scales, const uint8_t* b_mbs, int num_groups, const int64_t* row_offsets,
                 bool grouped, int64_t M, int64_t N, int64_t K, int c_dtype, void* C, int64_t ldc, bool mbs_entry,
@@ -64,11 +88,16 @@ int launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* 
                          (!use_mbs || ((!a_mbs || aligned(a_mbs, 4)) && (!b_mbs || aligned(b_mbs, 4))));
     // General form with 2-byte pieces of E8M0 bytes: rows of them on even addresses; else single bytes.
     const bool pairs_ok = K > 0 && (K % 64) == 0 && aligned(a_scales, 2) && aligned(b_scales, 2);
-    const bool skinny_ok = ring_ok && M <= 64 && K <= 8192;
+    const bool skinny_ok = K > 0 && (grouped ? M <= kFewRowsPerGroup * num_groups : M <= 64 && K <= 8192);
     int shape = choose_shape(M, N, use_mbs, ring_ok, pairs_ok, skinny_ok);
     if (force_shape >= 0) shape = force_shape;
     // (the checks below only matter for forced shapes)
-    if (shape == 5) return skinny_ok ? launch_gemm_skinny(g, use_mbs, s) : MX_EINVAL;
+    if (shape == 5) {
+        if (!skinny_ok) return MX_EINVAL;
+        if (grouped) return launch_gemm_skinny_grouped(g, use_mbs, !pairs_ok, s);
+        const SkinnyPlan p = plan_skinny(M, N, K, ring_ok, pairs_ok);
+        return launch_gemm_skinny_tile(g, use_mbs, p.fm, p.fn, p.form, s);
+    }
     if (shape == 8 || shape == 9) {
         if (!pairs_ok) return MX_EINVAL;
         return use_mbs ? launch_gemm_mbs_general(g, shape - 8, false, s) : launch_gemm_wide_general(g, shape - 8, false, s);
@@ -102,7 +131,8 @@ int launch_gemm_quantize_a(const void* a_bf16, int64_t lda, int rule, int a_use_
     g.C = C;
     g.M = M; g.N = N; g.K = K; g.ldc = ldc;
     g.c_bf16 = c_dtype == MX_OUT_BF16;
-    return launch_gemm_skinny_fused(g, a_bf16, lda, rule, a_use_mbs != 0, static_cast<hipStream_t>(stream));
+    const SkinnyPlan p = plan_skinny(M, N, K, true, true);
+    return launch_gemm_skinny_fused_tile(g, a_bf16, lda, rule, a_use_mbs != 0, p.fm, p.fn, p.form, static_cast<hipStream_t>(stream));
 }
 
 }  // namespace
@@ -142,7 +172,7 @@ int mx_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int a_has_mbs, int b_
     if (!out || cap <= 0 || M < 0 || N < 0 || K < 0 || (K % mx::kBlock) != 0) return MX_EINVAL;
     const bool use_mbs = a_has_mbs || b_has_mbs;
     const bool ring_ok = !grouped && K > 0 && (K % 512) == 0, pairs_ok = K > 0 && (K % 64) == 0;
-    const int shape = mx::choose_shape(M, N, use_mbs, ring_ok, pairs_ok, ring_ok && M <= 64 && K <= 8192);
+    const int shape = mx::choose_shape(M, N, use_mbs, ring_ok, pairs_ok, K > 0 && !grouped && M <= 64 && K <= 8192);
     const char* sides = a_has_mbs && b_has_mbs ? "MBS words on A and B" : a_has_mbs ? "MBS words on A" : b_has_mbs ? "MBS words on B" : "no MBS";
     const char* what;
     switch (shape) {

@@ -53,9 +53,16 @@ int launch_gemm_mbs_ring(const GemmArgs& g, int variant, hipStream_t s);
 // 128 x 128 tiles only).
 int launch_gemm_mbs_general(const GemmArgs& g, int tile, bool bytes, hipStream_t s);
 int launch_gemm_wide_general(const GemmArgs& g, int tile, bool bytes, hipStream_t s);
-// Few activation rows (M <= 64, K <= 8192, otherwise the same conditions), defined in mx_gemm_skinny.hip.
-int launch_gemm_skinny(const GemmArgs& g, bool use_mbs, hipStream_t s);
-int launch_gemm_skinny_fused(const GemmArgs& g, const void* x_bf16, int64_t ldx, int rule, bool a_mbs, hipStream_t s);
+// Few activation rows (mx_gemm_skinny.h): M <= 64, not grouped; fm, fn = fragments of 16 rows of A and of B per
+// workgroup, form as there (mx_gemm_skinny.hip).
+int launch_gemm_skinny_tile(const GemmArgs& g, bool use_mbs, int fm, int fn, int form, hipStream_t s);
+// The same with A given as bf16 [M, ldx] and quantized inside the kernel (mx_gemm_skinny_fused.hip): rule, MBS-Static words
+// if a_mbs; the a_* members of g are not used.  Also requires K % 512 == 0, x 16-byte aligned, ldx % 8 == 0 and the rows
+// of x to span less than 2 GiB.
+int launch_gemm_skinny_fused_tile(const GemmArgs& g, const void* x_bf16, int64_t ldx, int rule, bool a_mbs, int fm, int fn,
+                                  int form, hipStream_t s);
+// Grouped problems with few rows per group (mx_gemm_skinny_grouped.hip).
+int launch_gemm_skinny_grouped(const GemmArgs& g, bool use_mbs, bool bytes, hipStream_t s);
 // The few-row kernel for operands in the 8-bit or 6-bit element formats (a_elem, b_elem: mx_elem_t), under the same
 // conditions, defined in mx_gemm_skinny_f8.hip; an operand without MBS words has a null a_mbs / b_mbs.
 int launch_gemm_skinny_elem(const GemmArgs& g, int a_elem, int b_elem, hipStream_t s);
