@@ -128,42 +128,51 @@ def forced(**choices):
 
 
 def _forced(name):
-    return getattr(_dev, "choices", {}).get(name)
+    choices = getattr(_dev, "choices", None)
+    return choices.get(name) if choices else None
 
 
 def gemm_plan(M: int, N: int, K: int, a_has_mbs: bool = True, b_has_mbs: bool = True, grouped: bool = False) -> str:
     """The kernel the dispatcher of mx_gemm / mx_gemm_mbs / mx_gemm_mbs_grouped picks for a problem with aligned
     arrays (host only; reported by the benchmark beside its timings)."""
     buf = ctypes.create_string_buffer(512)
-    _check(load_library().mx_internal_gemm_plan(M, N, K, int(a_has_mbs), int(b_has_mbs), int(grouped), buf, 512),
+    _check((_lib or load_library()).mx_internal_gemm_plan(M, N, K, int(a_has_mbs), int(b_has_mbs), int(grouped), buf, 512),
            "mx_internal_gemm_plan")
     return buf.value.decode()
 
 
-def _quantize_call(where, x, rows, K, ldx, rule, use_mbs, codes, scales, mbs, public):
-    hw = _forced("quantize_hw")
-    if hw is None:
-        _check(public(), where)
-    else:
-        _check(load_library().mx_internal_quantize(_ptr(x), rows, K, ldx, rule, int(use_mbs), int(hw), _ptr(codes),
-                                                   _ptr(scales), _ptr(mbs), _stream()), where + " (mx_internal_quantize)")
+def _quantize_forced(where, hw, x, rows, K, ldx, rule, use_mbs, codes, scales, mbs):
+    _check((_lib or load_library()).mx_internal_quantize(_ptr(x), rows, K, ldx, rule, int(use_mbs), int(hw), _ptr(codes),
+                                               _ptr(scales), _ptr(mbs), _stream()), where + " (mx_internal_quantize)")
 
 
-def _gemm_call(where, a, b, grouped, num_groups, row_offsets, M, N, K, code, out, ldc, mbs_entry, public):
-    shape = _forced("gemm_shape")
-    if shape is None:
-        _check(public(), where)
-    else:
-        _check(load_library().mx_internal_gemm(_ptr(a[0]), _ptr(a[1]), _ptr(a[2]), _ptr(b[0]), _ptr(b[1]), _ptr(b[2]),
-                                               int(grouped), int(num_groups), _ptr(row_offsets), M, N, K, code, _ptr(out),
-                                               ldc, int(mbs_entry), int(shape), _stream()), where + " (mx_internal_gemm)")
+def _gemm_forced(where, shape, a, b, grouped, num_groups, row_offsets, M, N, K, code, out, ldc, mbs_entry):
+    _check((_lib or load_library()).mx_internal_gemm(_ptr(a[0]), _ptr(a[1]), _ptr(a[2]), _ptr(b[0]), _ptr(b[1]), _ptr(b[2]),
+                                           int(grouped), int(num_groups), _ptr(row_offsets), M, N, K, code, _ptr(out),
+                                           ldc, int(mbs_entry), int(shape), _stream()), where + " (mx_internal_gemm)")
 
 
 # ---- helpers ---------------------------------------------------------------------------------------
-def _torch():
-    import torch
+# The marshalling stands in front of kernels of a few microseconds, so it is kept short: a call costs about 6 us of host
+# time, 3.5 to 4.3 of which are the C call with its launch (13 us when every call imported torch again, built a Stream object to
+# read its handle, 3 us by itself, compared shapes as tuples and went through closures).
+_torch_module = None
+_stream_handle = _stream_device = None  # torch's calls for the current stream's handle and the current device, if it has them
+_out_dtypes = {}                        # what a caller may pass as an output type -> (type code, torch dtype)
 
-    return torch
+
+def _torch():
+    global _torch_module, _stream_handle, _stream_device
+    if _torch_module is None:
+        import torch
+
+        _stream_handle = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        _stream_device = getattr(torch._C, "_cuda_getDevice", None)
+        for names, value in (((MX_OUT_F32, "f32", "fp32", torch.float32), (MX_OUT_F32, torch.float32)),
+                             ((MX_OUT_BF16, "bf16", torch.bfloat16), (MX_OUT_BF16, torch.bfloat16))):
+            _out_dtypes.update((name, value) for name in names)
+        _torch_module = torch
+    return _torch_module
 
 
 def _rule(rule) -> int:
@@ -175,7 +184,10 @@ def _elem(elem) -> int:
 
 
 def _stream() -> int:
-    return _torch().cuda.current_stream().cuda_stream
+    torch = _torch_module or _torch()
+    if _stream_handle is None or _stream_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _stream_handle(_stream_device())
 
 
 def _ptr(t) -> Optional[int]:
@@ -188,34 +200,45 @@ def _check(status: int, where: str):
 
 
 def _rows_ld(x):
-    torch = _torch()
-    if x.dim() != 2 or x.dtype != torch.bfloat16 or not x.is_cuda:
+    torch = _torch_module or _torch()
+    if x.dtype is not torch.bfloat16 or x.dim() != 2 or not x.is_cuda:
         raise TypeError("expected a 2-D bf16 CUDA tensor")
-    if x.shape[1] > 1 and x.stride(1) != 1:
+    rows, K = x.shape
+    ld, inner = x.stride()
+    if inner != 1 and K > 1:
         raise ValueError("innermost dimension must be contiguous")
-    return x.shape[0], x.shape[1], (x.stride(0) if x.shape[0] > 1 else max(x.stride(0), x.shape[1]))
+    return rows, K, (ld if rows > 1 else max(ld, K))
 
 
 def _u8(t, shape, name):
-    torch = _torch()
-    if t.dtype != torch.uint8 or not t.is_cuda or not t.is_contiguous() or tuple(t.shape) != tuple(shape):
-        raise TypeError("%s must be a contiguous uint8 CUDA tensor of shape %s" % (name, tuple(shape)))
+    if t.dtype is not _torch_module.uint8 or t.shape != shape or not t.is_cuda or not t.is_contiguous():
+        raise TypeError("%s must be a contiguous uint8 CUDA tensor of shape %s" % (name, shape))
     return t
 
 
-def _alloc_outputs(x, rows, K, codes, scales, mbs, want_mbs):
-    torch = _torch()
+def _outputs(x, rows, K, code_bytes, codes, scales, mbs, want_mbs):
+    torch = _torch_module
+    shape = (rows, code_bytes)
     if codes is None:
-        codes = torch.empty((rows, K // 2), dtype=torch.uint8, device=x.device)
+        codes = torch.empty(shape, dtype=torch.uint8, device=x.device)
+    else:
+        _u8(codes, shape, "codes")
+    shape = (rows, K // 32)
     if scales is None:
-        scales = torch.empty((rows, K // 32), dtype=torch.uint8, device=x.device)
-    if want_mbs and mbs is None:
-        mbs = torch.empty((rows, (K + 127) // 128), dtype=torch.uint8, device=x.device)
-    _u8(codes, (rows, K // 2), "codes")
-    _u8(scales, (rows, K // 32), "scales")
+        scales = torch.empty(shape, dtype=torch.uint8, device=x.device)
+    else:
+        _u8(scales, shape, "scales")
     if want_mbs:
-        _u8(mbs, (rows, (K + 127) // 128), "mbs")
+        shape = (rows, (K + 127) // 128)
+        if mbs is None:
+            mbs = torch.empty(shape, dtype=torch.uint8, device=x.device)
+        else:
+            _u8(mbs, shape, "mbs")
     return codes, scales, mbs
+
+
+def _alloc_outputs(x, rows, K, codes, scales, mbs, want_mbs):
+    return _outputs(x, rows, K, K // 2, codes, scales, mbs, want_mbs)
 
 
 # ---- entry points ----------------------------------------------------------------------------------
@@ -223,16 +246,24 @@ def mx_quantize(x, rule="ocp", codes=None, scales=None):
     """bf16 [rows, K] -> (codes uint8 [rows, K/2], scales uint8 [rows, K/32]) with `rule`, no MBS."""
     rows, K, ldx = _rows_ld(x)
     codes, scales, _ = _alloc_outputs(x, rows, K, codes, scales, None, False)
-    _quantize_call("mx_quantize", x, rows, K, ldx, _rule(rule), False, codes, scales, None,
-                   lambda: load_library().mx_quantize(_ptr(x), rows, K, ldx, _rule(rule), _ptr(codes), _ptr(scales), _stream()))
+    hw = _forced("quantize_hw")
+    if hw is not None:
+        _quantize_forced("mx_quantize", hw, x, rows, K, ldx, _rule(rule), False, codes, scales, None)
+    else:
+        _check((_lib or load_library()).mx_quantize(x.data_ptr(), rows, K, ldx, _rule(rule), codes.data_ptr(),
+                                                    scales.data_ptr(), _stream()), "mx_quantize")
     return codes, scales
 
 
 def mx_quantize_oas(x, codes=None, scales=None):
     rows, K, ldx = _rows_ld(x)
     codes, scales, _ = _alloc_outputs(x, rows, K, codes, scales, None, False)
-    _quantize_call("mx_quantize_oas", x, rows, K, ldx, MX_RULE_OAS, False, codes, scales, None,
-                   lambda: load_library().mx_quantize_oas(_ptr(x), rows, K, ldx, _ptr(codes), _ptr(scales), _stream()))
+    hw = _forced("quantize_hw")
+    if hw is not None:
+        _quantize_forced("mx_quantize_oas", hw, x, rows, K, ldx, MX_RULE_OAS, False, codes, scales, None)
+    else:
+        _check((_lib or load_library()).mx_quantize_oas(x.data_ptr(), rows, K, ldx, codes.data_ptr(), scales.data_ptr(),
+                                                        _stream()), "mx_quantize_oas")
     return codes, scales
 
 
@@ -240,9 +271,12 @@ def mx_quantize_mbs(x, rule="oas", codes=None, scales=None, mbs=None):
     """MBS-Static quantization -> (codes, scales, mbs uint8 [rows, ceil(K/128)])."""
     rows, K, ldx = _rows_ld(x)
     codes, scales, mbs = _alloc_outputs(x, rows, K, codes, scales, mbs, True)
-    _quantize_call("mx_quantize_mbs", x, rows, K, ldx, _rule(rule), True, codes, scales, mbs,
-                   lambda: load_library().mx_quantize_mbs(_ptr(x), rows, K, ldx, _rule(rule), _ptr(codes), _ptr(scales),
-                                                          _ptr(mbs), _stream()))
+    hw = _forced("quantize_hw")
+    if hw is not None:
+        _quantize_forced("mx_quantize_mbs", hw, x, rows, K, ldx, _rule(rule), True, codes, scales, mbs)
+    else:
+        _check((_lib or load_library()).mx_quantize_mbs(x.data_ptr(), rows, K, ldx, _rule(rule), codes.data_ptr(),
+                                                        scales.data_ptr(), mbs.data_ptr(), _stream()), "mx_quantize_mbs")
     return codes, scales, mbs
 
 
@@ -254,7 +288,7 @@ def mx_quantize_mbs_pair(x0, x1, rule="oas", out0=None, out1=None):
         raise ValueError("the two tensors must share K")
     o0 = _alloc_outputs(x0, rows0, K, *(out0 or (None, None, None)), True)
     o1 = _alloc_outputs(x1, rows1, K, *(out1 or (None, None, None)), True)
-    _check(load_library().mx_quantize_mbs_pair(_ptr(x0), rows0, ld0, _ptr(o0[0]), _ptr(o0[1]), _ptr(o0[2]),
+    _check((_lib or load_library()).mx_quantize_mbs_pair(_ptr(x0), rows0, ld0, _ptr(o0[0]), _ptr(o0[1]), _ptr(o0[2]),
                                                _ptr(x1), rows1, ld1, _ptr(o1[0]), _ptr(o1[1]), _ptr(o1[2]),
                                                K, _rule(rule), _stream()), "mx_quantize_mbs_pair")
     return o0, o1
@@ -265,7 +299,7 @@ def mx_quantize_mbs_dynamic(x, rule="oas", cand_first=0, cand_count=16, cand_str
     """MBS-Dynamic quantization (searched word per 1x128 window) -> (codes, scales, mbs)."""
     rows, K, ldx = _rows_ld(x)
     codes, scales, mbs = _alloc_outputs(x, rows, K, codes, scales, mbs, True)
-    _check(load_library().mx_quantize_mbs_dynamic(_ptr(x), rows, K, ldx, _rule(rule), int(cand_first),
+    _check((_lib or load_library()).mx_quantize_mbs_dynamic(_ptr(x), rows, K, ldx, _rule(rule), int(cand_first),
                                                   int(cand_count), int(cand_stride), _ptr(codes), _ptr(scales),
                                                   _ptr(mbs), _stream()), "mx_quantize_mbs_dynamic")
     return codes, scales, mbs
@@ -278,7 +312,7 @@ def mx_mbs_lut_build(lut=None):
         lut = torch.empty((2, 64, 16), dtype=torch.int16, device="cuda")
     if lut.dtype != torch.int16 or not lut.is_cuda or not lut.is_contiguous() or lut.numel() != 2048:
         raise TypeError("lut must be a contiguous int16 CUDA tensor of 2048 elements")
-    _check(load_library().mx_mbs_lut_build(_ptr(lut), _stream()), "mx_mbs_lut_build")
+    _check((_lib or load_library()).mx_mbs_lut_build(_ptr(lut), _stream()), "mx_mbs_lut_build")
     return lut
 
 
@@ -289,7 +323,7 @@ def mx_quantize_mbs_dynamic_lut(x, lut, rule="oas", keep_static=True, codes=None
     if lut.dtype != torch.int16 or not lut.is_cuda or not lut.is_contiguous() or lut.numel() != 2048:
         raise TypeError("lut must be a contiguous int16 CUDA tensor of 2048 elements")
     codes, scales, mbs = _alloc_outputs(x, rows, K, codes, scales, mbs, True)
-    _check(load_library().mx_quantize_mbs_dynamic_lut(_ptr(x), rows, K, ldx, _rule(rule), _ptr(lut), int(bool(keep_static)),
+    _check((_lib or load_library()).mx_quantize_mbs_dynamic_lut(_ptr(x), rows, K, ldx, _rule(rule), _ptr(lut), int(bool(keep_static)),
                                                       _ptr(codes), _ptr(scales), _ptr(mbs), _stream()),
            "mx_quantize_mbs_dynamic_lut")
     return codes, scales, mbs
@@ -300,69 +334,81 @@ def mx_quantize_mbs_dynamic_lut_static(x, codes, scales, mbs, rule="oas", keep_s
     caller passes the three output tensors ([rows, K/2], [rows, K/32], [rows, ceil(K/128)], uint8)."""
     rows, K, ldx = _rows_ld(x)
     _alloc_outputs(x, rows, K, codes, scales, mbs, True)  # given all three, this only checks them
-    _check(load_library().mx_quantize_mbs_dynamic_lut_static(_ptr(x), rows, K, ldx, _rule(rule), int(bool(keep_static)),
+    _check((_lib or load_library()).mx_quantize_mbs_dynamic_lut_static(_ptr(x), rows, K, ldx, _rule(rule), int(bool(keep_static)),
                                                              _ptr(codes), _ptr(scales), _ptr(mbs), _stream()),
            "mx_quantize_mbs_dynamic_lut_static")
     return codes, scales, mbs
 
 
 def _out_dtype(dtype) -> Tuple[int, object]:
-    torch = _torch()
-    if dtype in (MX_OUT_F32, "f32", "fp32", torch.float32):
-        return MX_OUT_F32, torch.float32
-    if dtype in (MX_OUT_BF16, "bf16", torch.bfloat16):
-        return MX_OUT_BF16, torch.bfloat16
-    raise ValueError("output dtype must be fp32 or bf16")
+    if _torch_module is None:
+        _torch()
+    try:
+        return _out_dtypes[dtype]
+    except (KeyError, TypeError):
+        raise ValueError("output dtype must be fp32 or bf16") from None
+
+
+def _matrix(rows, cols, out_dtype, out, device, what):
+    """The output matrix (allocated if not given), its type code and its leading dimension."""
+    code, tdt = _out_dtype(out_dtype)
+    if out is None:
+        out = _torch_module.empty((rows, cols), dtype=tdt, device=device)
+    if out.dtype is not tdt or out.shape != (rows, cols):
+        raise TypeError(what)
+    ld, inner = out.stride()
+    if inner != 1 and cols > 1:
+        raise TypeError(what)
+    return code, out, (ld if rows > 1 else max(ld, cols))
 
 
 def mx_dequantize(codes, scales, mbs=None, out_dtype="f32", out=None):
-    torch = _torch()
-    rows, K = codes.shape[0], codes.shape[1] * 2
-    code, tdt = _out_dtype(out_dtype)
-    if out is None:
-        out = torch.empty((rows, K), dtype=tdt, device=codes.device)
-    if out.dtype != tdt or out.dim() != 2 or tuple(out.shape) != (rows, K) or (K > 1 and out.stride(1) != 1):
-        raise TypeError("out must be [rows, K] of the requested dtype with a contiguous last dimension")
-    ldo = out.stride(0) if rows > 1 else max(out.stride(0), K)
-    _check(load_library().mx_dequantize(_ptr(codes), _ptr(scales), _ptr(mbs), rows, K, code, _ptr(out), ldo,
-                                        _stream()), "mx_dequantize")
+    shape = codes.shape
+    rows, K = shape[0], shape[1] * 2
+    code, out, ldo = _matrix(rows, K, out_dtype, out, codes.device,
+                             "out must be [rows, K] of the requested dtype with a contiguous last dimension")
+    _check((_lib or load_library()).mx_dequantize(codes.data_ptr(), scales.data_ptr(), _ptr(mbs), rows, K, code,
+                                                  out.data_ptr(), ldo, _stream()), "mx_dequantize")
     return out
 
 
 def _c_tensor(M, N, out_dtype, out, device):
-    torch = _torch()
-    code, tdt = _out_dtype(out_dtype)
-    if out is None:
-        out = torch.empty((M, N), dtype=tdt, device=device)
-    if out.dtype != tdt or tuple(out.shape) != (M, N) or (N > 1 and out.stride(1) != 1):
-        raise TypeError("C must be [M, N] of the requested dtype with a contiguous last dimension")
-    ldc = out.stride(0) if M > 1 else max(out.stride(0), N)
-    return code, out, ldc
+    return _matrix(M, N, out_dtype, out, device, "C must be [M, N] of the requested dtype with a contiguous last dimension")
 
 
 def mx_gemm(a_codes, a_scales, b_codes, b_scales, out_dtype="f32", out=None):
     """Plain MXFP4 GEMM: C[M,N] = A[M,K] . B[N,K]^T."""
-    M, K = a_codes.shape[0], a_codes.shape[1] * 2
-    N = b_codes.shape[0]
-    if b_codes.shape[1] * 2 != K:
+    a_shape, b_shape = a_codes.shape, b_codes.shape
+    M, half, N = a_shape[0], a_shape[1], b_shape[0]
+    if b_shape[1] != half:
         raise ValueError("A and B disagree on K")
     code, out, ldc = _c_tensor(M, N, out_dtype, out, a_codes.device)
-    _gemm_call("mx_gemm", (a_codes, a_scales, None), (b_codes, b_scales, None), False, 0, None, M, N, K, code, out, ldc, False,
-               lambda: load_library().mx_gemm(_ptr(a_codes), _ptr(a_scales), _ptr(b_codes), _ptr(b_scales), M, N, K, code,
-                                              _ptr(out), ldc, _stream()))
+    shape = _forced("gemm_shape")
+    if shape is not None:
+        _gemm_forced("mx_gemm", shape, (a_codes, a_scales, None), (b_codes, b_scales, None), False, 0, None, M, N, 2 * half,
+                     code, out, ldc, False)
+    else:
+        _check((_lib or load_library()).mx_gemm(a_codes.data_ptr(), a_scales.data_ptr(), b_codes.data_ptr(),
+                                                b_scales.data_ptr(), M, N, 2 * half, code, out.data_ptr(), ldc, _stream()),
+               "mx_gemm")
     return out
 
 
 def mx_gemm_mbs(a_codes, a_scales, a_mbs, b_codes, b_scales, b_mbs, out_dtype="f32", out=None):
     """GEMM with the per-macro-block MBS correction; a_mbs / b_mbs may be None."""
-    M, K = a_codes.shape[0], a_codes.shape[1] * 2
-    N = b_codes.shape[0]
-    if b_codes.shape[1] * 2 != K:
+    a_shape, b_shape = a_codes.shape, b_codes.shape
+    M, half, N = a_shape[0], a_shape[1], b_shape[0]
+    if b_shape[1] != half:
         raise ValueError("A and B disagree on K")
     code, out, ldc = _c_tensor(M, N, out_dtype, out, a_codes.device)
-    _gemm_call("mx_gemm_mbs", (a_codes, a_scales, a_mbs), (b_codes, b_scales, b_mbs), False, 0, None, M, N, K, code, out, ldc,
-               True, lambda: load_library().mx_gemm_mbs(_ptr(a_codes), _ptr(a_scales), _ptr(a_mbs), _ptr(b_codes),
-                                                        _ptr(b_scales), _ptr(b_mbs), M, N, K, code, _ptr(out), ldc, _stream()))
+    shape = _forced("gemm_shape")
+    if shape is not None:
+        _gemm_forced("mx_gemm_mbs", shape, (a_codes, a_scales, a_mbs), (b_codes, b_scales, b_mbs), False, 0, None, M, N,
+                     2 * half, code, out, ldc, True)
+    else:
+        _check((_lib or load_library()).mx_gemm_mbs(a_codes.data_ptr(), a_scales.data_ptr(), _ptr(a_mbs), b_codes.data_ptr(),
+                                                    b_scales.data_ptr(), _ptr(b_mbs), M, N, 2 * half, code, out.data_ptr(),
+                                                    ldc, _stream()), "mx_gemm_mbs")
     return out
 
 
@@ -373,25 +419,15 @@ def elem_code_bytes(elem, K: int) -> int:
 
 def mx_quantize_elem(x, elem="e4m3", rule="oas", use_mbs=True, codes=None, scales=None, mbs=None):
     """Quantize into an 8-bit (codes one per byte) or 6-bit (packed) MX element format, with or without MBS words."""
-    torch = _torch()
     rows, K, ldx = _rows_ld(x)
-    if codes is None:
-        codes = torch.empty((rows, elem_code_bytes(elem, K)), dtype=torch.uint8, device=x.device)
-    if scales is None:
-        scales = torch.empty((rows, K // 32), dtype=torch.uint8, device=x.device)
-    if use_mbs and mbs is None:
-        mbs = torch.empty((rows, (K + 127) // 128), dtype=torch.uint8, device=x.device)
-    _u8(codes, (rows, elem_code_bytes(elem, K)), "codes")
-    _u8(scales, (rows, K // 32), "scales")
-    if use_mbs:
-        _u8(mbs, (rows, (K + 127) // 128), "mbs")
+    codes, scales, mbs = _outputs(x, rows, K, elem_code_bytes(elem, K), codes, scales, mbs, use_mbs)
     hw = _forced("quantize_elem_hw")
     if hw is None:
-        _check(load_library().mx_quantize_elem(_elem(elem), _ptr(x), rows, K, ldx, _rule(rule), int(bool(use_mbs)),
+        _check((_lib or load_library()).mx_quantize_elem(_elem(elem), _ptr(x), rows, K, ldx, _rule(rule), int(bool(use_mbs)),
                                                _ptr(codes), _ptr(scales), _ptr(mbs) if use_mbs else None, _stream()),
                "mx_quantize_elem")
     else:
-        _check(load_library().mx_internal_quantize_elem(_elem(elem), _ptr(x), rows, K, ldx, _rule(rule), int(bool(use_mbs)),
+        _check((_lib or load_library()).mx_internal_quantize_elem(_elem(elem), _ptr(x), rows, K, ldx, _rule(rule), int(bool(use_mbs)),
                                                         int(hw), _ptr(codes), _ptr(scales), _ptr(mbs) if use_mbs else None,
                                                         _stream()), "mx_quantize_elem (mx_internal_quantize_elem)")
     return codes, scales, (mbs if use_mbs else None)
@@ -401,16 +437,9 @@ def mx_quantize_elem_mbs_dynamic(x, elem, rule="oas", cand_first=0, cand_count=1
                                  mbs=None):
     """MBS-Dynamic into an 8-bit or 6-bit element format: the word of every 1x128 window searched among the static
     word and cand_count candidates for the least squared error.  Returns (codes, scales, mbs)."""
-    torch = _torch()
     rows, K, ldx = _rows_ld(x)
-    dev = x.device
-    codes = torch.empty((rows, elem_code_bytes(elem, K)), dtype=torch.uint8, device=dev) if codes is None else codes
-    scales = torch.empty((rows, K // 32), dtype=torch.uint8, device=dev) if scales is None else scales
-    mbs = torch.empty((rows, (K + 127) // 128), dtype=torch.uint8, device=dev) if mbs is None else mbs
-    _u8(codes, (rows, elem_code_bytes(elem, K)), "codes")
-    _u8(scales, (rows, K // 32), "scales")
-    _u8(mbs, (rows, (K + 127) // 128), "mbs")
-    _check(load_library().mx_quantize_elem_mbs_dynamic(_elem(elem), _ptr(x), rows, K, ldx, _rule(rule), int(cand_first),
+    codes, scales, mbs = _outputs(x, rows, K, elem_code_bytes(elem, K), codes, scales, mbs, True)
+    _check((_lib or load_library()).mx_quantize_elem_mbs_dynamic(_elem(elem), _ptr(x), rows, K, ldx, _rule(rule), int(cand_first),
                                                        int(cand_count), int(cand_stride), _ptr(codes), _ptr(scales),
                                                        _ptr(mbs), _stream()), "mx_quantize_elem_mbs_dynamic")
     return codes, scales, mbs
@@ -419,17 +448,12 @@ def mx_quantize_elem_mbs_dynamic(x, elem, rule="oas", cand_first=0, cand_count=1
 def mx_dequantize_elem(elem, codes, scales, mbs=None, out_dtype="f32", out=None):
     """Dequantize codes of an 8-bit (one per byte) or 6-bit (packed) MX element format to fp32 or bf16.  K is taken
     from the scale array."""
-    torch = _torch()
     rows, K = codes.shape[0], scales.shape[1] * 32
     if codes.shape[1] != elem_code_bytes(elem, K):
         raise ValueError("the code array does not have the row length of its format")
-    code, dt = _out_dtype(out_dtype)
-    if out is None:
-        out = torch.empty((rows, K), dtype=dt, device=codes.device)
-    if out.dtype != dt or out.dim() != 2 or tuple(out.shape) != (rows, K) or (K > 1 and out.stride(1) != 1):
-        raise TypeError("out must be [rows, K] of the requested dtype with a contiguous last dimension")
-    ldo = out.stride(0) if rows > 1 else max(out.stride(0), K)
-    _check(load_library().mx_dequantize_elem(_elem(elem), _ptr(codes), _ptr(scales), _ptr(mbs), rows, K, code, _ptr(out),
+    code, out, ldo = _matrix(rows, K, out_dtype, out, codes.device,
+                             "out must be [rows, K] of the requested dtype with a contiguous last dimension")
+    _check((_lib or load_library()).mx_dequantize_elem(_elem(elem), _ptr(codes), _ptr(scales), _ptr(mbs), rows, K, code, _ptr(out),
                                              ldo, _stream()), "mx_dequantize_elem")
     return out
 
@@ -441,13 +465,14 @@ def mx_gemm_mbs_elem(a_elem, a_codes, a_scales, a_mbs, b_elem, b_codes, b_scales
     if b_scales.shape[1] * 32 != K or a_codes.shape[1] != elem_code_bytes(a_elem, K) or b_codes.shape[1] != elem_code_bytes(b_elem, K):
         raise ValueError("A and B disagree on K, or a code array does not have the row length of its format")
     code, out, ldc = _c_tensor(M, N, out_dtype, out, a_codes.device)
-    if _forced("gemm_elem"):
-        _check(load_library().mx_internal_gemm_elem(_elem(a_elem), _ptr(a_codes), _ptr(a_scales), _ptr(a_mbs), _elem(b_elem),
+    force = _forced("gemm_elem")
+    if force:
+        _check((_lib or load_library()).mx_internal_gemm_elem(_elem(a_elem), _ptr(a_codes), _ptr(a_scales), _ptr(a_mbs), _elem(b_elem),
                                                     _ptr(b_codes), _ptr(b_scales), _ptr(b_mbs), M, N, K, code, _ptr(out),
-                                                    ldc, int(_forced("gemm_elem")), _stream()),
+                                                    ldc, int(force), _stream()),
                "mx_gemm_mbs_elem (mx_internal_gemm_elem)")
     else:
-        _check(load_library().mx_gemm_mbs_elem(_elem(a_elem), _ptr(a_codes), _ptr(a_scales), _ptr(a_mbs), _elem(b_elem),
+        _check((_lib or load_library()).mx_gemm_mbs_elem(_elem(a_elem), _ptr(a_codes), _ptr(a_scales), _ptr(a_mbs), _elem(b_elem),
                                                _ptr(b_codes), _ptr(b_scales), _ptr(b_mbs), M, N, K, code, _ptr(out), ldc,
                                                _stream()), "mx_gemm_mbs_elem")
     return out
@@ -457,7 +482,7 @@ def mx_gemm_mbs_elem_grouped(a_elem, a_codes, a_scales, a_mbs, b_elem, b_codes, 
                              out_dtype="f32", out=None):
     """Grouped GEMM for operands in 8-bit or 6-bit element formats: rows row_offsets[e]..row_offsets[e+1]-1 of A
     times B_e^T, B stacked [G*N, ...]."""
-    torch = _torch()
+    torch = _torch_module or _torch()
     M, K = a_codes.shape[0], a_scales.shape[1] * 32
     if row_offsets.dtype != torch.int64 or not row_offsets.is_cuda or not row_offsets.is_contiguous():
         raise TypeError("row_offsets must be a contiguous int64 CUDA tensor")
@@ -466,7 +491,7 @@ def mx_gemm_mbs_elem_grouped(a_elem, a_codes, a_scales, a_mbs, b_elem, b_codes, 
             or b_codes.shape[1] != elem_code_bytes(b_elem, K)):
         raise ValueError("B must hold num_groups stacked [N, K] weights in its format's row length")
     code, out, ldc = _c_tensor(M, N, out_dtype, out, a_codes.device)
-    _check(load_library().mx_gemm_mbs_elem_grouped(_elem(a_elem), _ptr(a_codes), _ptr(a_scales), _ptr(a_mbs), _elem(b_elem),
+    _check((_lib or load_library()).mx_gemm_mbs_elem_grouped(_elem(a_elem), _ptr(a_codes), _ptr(a_scales), _ptr(a_mbs), _elem(b_elem),
                                                    _ptr(b_codes), _ptr(b_scales), _ptr(b_mbs), G, _ptr(row_offsets), M, N, K,
                                                    code, _ptr(out), ldc, _stream()), "mx_gemm_mbs_elem_grouped")
     return out
@@ -479,7 +504,7 @@ def mx_gemm_mbs_quantize_a(a, rule, b_codes, b_scales, b_mbs, out_dtype="f32", o
     if b_codes.shape[1] * 2 != K:
         raise ValueError("A and B disagree on K")
     code, out, ldc = _c_tensor(M, N, out_dtype, out, a.device)
-    _check(load_library().mx_gemm_mbs_quantize_a(_ptr(a), lda, _rule(rule), int(bool(a_use_mbs)), _ptr(b_codes),
+    _check((_lib or load_library()).mx_gemm_mbs_quantize_a(_ptr(a), lda, _rule(rule), int(bool(a_use_mbs)), _ptr(b_codes),
                                                  _ptr(b_scales), _ptr(b_mbs), M, N, K, code, _ptr(out), ldc,
                                                  _stream()), "mx_gemm_mbs_quantize_a")
     return out
@@ -488,7 +513,7 @@ def mx_gemm_mbs_quantize_a(a, rule, b_codes, b_scales, b_mbs, out_dtype="f32", o
 def mx_gemm_mbs_grouped(a_codes, a_scales, a_mbs, b_codes, b_scales, b_mbs, row_offsets, N, out_dtype="f32",
                         out=None):
     """Grouped GEMM: rows row_offsets[e]..row_offsets[e+1]-1 of A times B_e^T, B stacked [G*N, K]."""
-    torch = _torch()
+    torch = _torch_module or _torch()
     M, K = a_codes.shape[0], a_codes.shape[1] * 2
     if row_offsets.dtype != torch.int64 or not row_offsets.is_cuda or not row_offsets.is_contiguous():
         raise TypeError("row_offsets must be a contiguous int64 CUDA tensor")
@@ -496,9 +521,13 @@ def mx_gemm_mbs_grouped(a_codes, a_scales, a_mbs, b_codes, b_scales, b_mbs, row_
     if b_codes.shape[0] != G * N or b_codes.shape[1] * 2 != K:
         raise ValueError("B must hold num_groups stacked [N, K] weights")
     code, out, ldc = _c_tensor(M, N, out_dtype, out, a_codes.device)
-    _gemm_call("mx_gemm_mbs_grouped", (a_codes, a_scales, a_mbs), (b_codes, b_scales, b_mbs), True, G, row_offsets, M, N, K,
-               code, out, ldc, True,
-               lambda: load_library().mx_gemm_mbs_grouped(_ptr(a_codes), _ptr(a_scales), _ptr(a_mbs), _ptr(b_codes),
-                                                          _ptr(b_scales), _ptr(b_mbs), G, _ptr(row_offsets), M, N, K, code,
-                                                          _ptr(out), ldc, _stream()))
+    shape = _forced("gemm_shape")
+    if shape is not None:
+        _gemm_forced("mx_gemm_mbs_grouped", shape, (a_codes, a_scales, a_mbs), (b_codes, b_scales, b_mbs), True, G, row_offsets,
+                     M, N, K, code, out, ldc, True)
+    else:
+        _check((_lib or load_library()).mx_gemm_mbs_grouped(a_codes.data_ptr(), a_scales.data_ptr(), _ptr(a_mbs),
+                                                            b_codes.data_ptr(), b_scales.data_ptr(), _ptr(b_mbs), G,
+                                                            row_offsets.data_ptr(), M, N, K, code, out.data_ptr(), ldc,
+                                                            _stream()), "mx_gemm_mbs_grouped")
     return out

@@ -1,3 +1,4 @@
+import gc
 import os
 import sys
 
@@ -18,3 +19,11 @@ def oracle():
 
     _oracle.build()
     return _oracle
+
+
+@pytest.fixture(autouse=True, scope="module")
+def _no_garbage_left_for_the_next_module():
+    """Tensors that a test left in reference cycles (tracebacks) are freed here and not at some allocation of a later
+    test that watches the allocator."""
+    yield
+    gc.collect()
