@@ -12,7 +12,7 @@ namespace {
 
 // force_shape (mx_internal_gemm only; the public entry points pass -1 = automatic): 2 / 6 / 7 = fast form without
 // MBS on 256x256 / 256x128 / 128x128 tiles, 3 / 4 = fast form with MBS on 256x128 / 128x128 tiles, 5 = few-row
-// kernel, 8 / 9 = general form (2-byte pieces) on 256x128 / 128x128 tiles, 10 = general form (single bytes) on
+// kernel, 8 / 9 = general form (row pieces through registers) on 256x128 / 128x128 tiles, 10 = general form (single bytes) on
 // 128x128 tiles.
 // Which kernel form and tile shape (the codes above) takes a problem.  Tiles run in rounds of one per compute
 // unit: rounds x tile area / efficiency (the small tile reaches about 0.8 of the large tile's rate per output
@@ -86,7 +86,7 @@ int launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* 
     // Fast form: K in whole groups of four macro blocks and aligned per-row arrays.
     const bool ring_ok = !grouped && K > 0 && (K % 512) == 0 && aligned(a_scales, 16) && aligned(b_scales, 16) &&
                          (!use_mbs || ((!a_mbs || aligned(a_mbs, 4)) && (!b_mbs || aligned(b_mbs, 4))));
-    // General form with 2-byte pieces of E8M0 bytes: rows of them on even addresses; else single bytes.
+    // General form with row pieces through registers: rows of E8M0 bytes on even addresses; else single bytes.
     const bool pairs_ok = K > 0 && (K % 64) == 0 && aligned(a_scales, 2) && aligned(b_scales, 2);
     const bool skinny_ok = K > 0 && (grouped ? M <= kFewRowsPerGroup * num_groups : M <= 64 && K <= 8192);
     int shape = choose_shape(M, N, use_mbs, ring_ok, pairs_ok, skinny_ok);
@@ -181,8 +181,8 @@ int mx_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int a_has_mbs, int b_
                                               : "gemm_ring_kernel, fast form, 256x128 tile, 8 wavefronts of 128x32"; break;
         case 4: what = "gemm_ring_kernel, fast form, 128x128 tile, 8 wavefronts of 64x32"; break;
         case 5: what = "gemm_skinny_kernel (few rows)"; break;
-        case 8: what = use_mbs ? "gemm_ring_kernel, general form (2-byte scale pieces), 256x128 tile, 8 wavefronts" : "gemm_ring_kernel, general form (2-byte scale pieces), 256x128 tile, 4 wavefronts"; break;
-        case 9: what = "gemm_ring_kernel, general form (2-byte scale pieces), 128x128 tile"; break;
+        case 8: what = use_mbs ? "gemm_ring_kernel, general form (row pieces through registers), 256x128 tile, 8 wavefronts" : "gemm_ring_kernel, general form (row pieces through registers), 256x128 tile, 4 wavefronts"; break;
+        case 9: what = "gemm_ring_kernel, general form (row pieces through registers), 128x128 tile"; break;
         default: what = "gemm_ring_kernel, general form (single scale bytes), 128x128 tile"; break;
     }
     snprintf(out, (size_t)cap, "%s; %s", what, sides);

@@ -1,7 +1,7 @@
 // The main GEMM kernel template in its general forms: any K, rows of E8M0 bytes and MBS words at any address,
-// and grouped problems (mixture of experts).  E8M0 bytes travel as 2-byte pieces (K % 64 == 0, even addresses) or
-// as single bytes, MBS words as single bytes, which costs texture-address time the fast form does not spend,
-// so the fast form keeps every problem it can take.  This file holds the kernels with MBS (compiled with the
+// and grouped problems (mixture of experts).  A row's E8M0 bytes and MBS words travel in the fast form's pieces, but
+// through registers (K % 64 == 0, even addresses), or as single bytes direct to LDS, which costs texture-address time;
+// the fast form, whose loads need no registers, keeps every problem it can take.  This file holds the kernels with MBS (compiled with the
 // VGPR form of the matrix instructions, as in mx_gemm_mbs.hip); those without are in mx_gemm_wide.hip.
 #include "mx_gemm_ring.h"
 

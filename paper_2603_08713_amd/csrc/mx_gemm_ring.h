@@ -141,8 +141,8 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
         const int row = ((i * NW + w) * 16 + (l >> 2)) - (i * NW * 16 < TM ? 0 : TM);  // row within its operand
         code_off[i] = row * row_bytes + (((l & 3) ^ ((row >> 2) & 3)) * 16);
     }
-    // Per-row loads, fast form: load i of wavefront w serves row (i * NW + w) * 64 + l with the 16 E8M0 bytes, or
-    // the 4 MBS words, of a group of four stages; rows past the tile are padding and read zero.
+    // Per-row loads (not in single bytes): load i of wavefront w serves row (i * NW + w) * 64 + l with the 16 E8M0
+    // bytes, or the 4 MBS words, of a group of four stages; rows past the tile are padding and read zero.
     int scale_off[kRowDma], m8_off[kRowDma];
     bool row_is_a[kRowDma];
 #pragma unroll
@@ -153,13 +153,21 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
         scale_off[i] = grow >= kRows ? kOob : row * scale_bytes;
         m8_off[i] = grow >= kRows ? kOob : row * nmac;
     }
-    // General forms: E8M0 load i of wavefront w serves rows (i * NW + w) * 8 .. + 7, lane l pair l % 8 of the
-    // group's 8 pairs of bytes of row l / 8 (or rows (i * NW + w) * 4 .. + 3, lane l byte l % 16 of row l / 16);
+    // Single bytes: E8M0 load i of wavefront w serves rows (i * NW + w) * 4 .. + 3, lane l byte l % 16 of row l / 16;
     // MBS load i serves rows (i * NW + w) * 16 .. + 15, lane l word l % 4 of row l / 4.
     const int gen_code_col = ((l & 3) ^ ((l >> 4) & 3)) * 16;  // this lane's chunk of the 64-byte stage piece
-    const int gen_scale_col = S::kBytes ? l & 15 : (l & 7) * 2;
-    const int gen_scale_off = (S::kBytes ? w * 4 + (l >> 4) : w * 8 + (l >> 3)) * scale_bytes + gen_scale_col;
+    const int gen_scale_col = l & 15, gen_scale_off = (w * 4 + (l >> 4)) * scale_bytes + gen_scale_col;
     const int gen_m8_off = (w * 16 + (l >> 2)) * nmac + (l & 3), gen_m8_col = l & 3;
+    // Form 1: the groups of four stages that K fills, and the slot of a group (the partial last one has its own).
+    const int nwhole = K / (kRingGroup * kRingStageK);
+    auto group_slot = [&](int grp) { return S::kRegs && grp >= nwhole ? 2 : grp & 1; };
+    // A row's E8M0 bytes and MBS words on their way through registers (form 1): requested in one stage with a barrier,
+    // written in the next.  Loads into registers serve rows at any address and cost the texture-address unit one
+    // pass per row and group; fetched direct to LDS in 2-byte and 1-byte pieces, as this form once did, they cost nine
+    // passes of 64 clocks per wavefront and group, three times what the codes cost.  Without MBS words that was what
+    // bound the kernel (1777 x 5001 x 2880, quantizer and GEMM: 55 -> 46 us); with them the vector work hides most of it.
+    v4i reg_scale[kRowDma];
+    uint32_t reg_m8[kRowDma];
 
     // A stage or group past the end of K is never used; its loads (the pipeline issues them regardless, into
     // slots that are no longer read) fetch the last one again, so that no address leaves the operands.
@@ -181,15 +189,18 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
     };
     auto dma_scale = [&](int grp, auto i_) {  // load i of the E8M0 bytes of stages 4 grp .. 4 grp + 3
         constexpr int i = decltype(i_)::value;
-        if constexpr (S::kGen) {
-            constexpr int kPer = S::kScaleRowsPerLoad;
+        if constexpr (S::kRegs) {
+            const __amdgpu_buffer_rsrc_t rsrc = row_is_a[i] ? opa.scales : opb.scales;
+            reg_scale[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, grp < nwhole ? scale_off[i] : kOob, grp * 16, 0);
+        } else if constexpr (S::kBytes) {
+            constexpr int kPer = 4;
             constexpr bool is_a = i * NW * kPer < TM;
             uint8_t* dst = smem + S::kScaleBase + (grp & 1) * S::kScaleGroup + (i * NW + w) * 256;
             // (the row goes into the per-lane offset, which is what the hardware checks against the valid rows)
             const int in_range = gen_scale_off + (i * NW * kPer - (is_a ? 0 : TM)) * scale_bytes;
             const int voff = grp * 16 + gen_scale_col < scale_bytes ? in_range : kOob;  // past K: zero
             const __amdgpu_buffer_rsrc_t rsrc = is_a ? opa.scales : opb.scales;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)dst, S::kBytes ? 1 : 2, voff, grp * 16, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)dst, 1, voff, grp * 16, 0, 0);
         } else {
             uint8_t* dst = smem + S::kScaleBase + (grp & 1) * S::kScaleGroup + (i * NW + w) * 1024;
             const int voff = scale_off[i];
@@ -199,7 +210,10 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
     };
     auto dma_m8 = [&](int grp, auto i_) {  // load i of the MBS words of stages 4 grp .. 4 grp + 3
         constexpr int i = decltype(i_)::value;
-        if constexpr (S::kGen) {
+        if constexpr (S::kRegs) {
+            const __amdgpu_buffer_rsrc_t rsrc = row_is_a[i] ? opa.mbs : opb.mbs;
+            reg_m8[i] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, grp < nwhole ? m8_off[i] : kOob, grp * 4, 0);
+        } else if constexpr (S::kBytes) {
             constexpr bool is_a = i * NW * 16 < TM;
             uint8_t* dst = smem + S::kM8Base + (grp & 1) * S::kM8Group + (i * NW + w) * 256;
             const int in_range = gen_m8_off + (i * NW * 16 - (is_a ? 0 : TM)) * nmac;
@@ -212,6 +226,56 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
             const __amdgpu_buffer_rsrc_t rsrc = row_is_a[i] ? opa.mbs : opb.mbs;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)dst, 4, voff, min(grp, ngroups - 1) * 4, 0, 0);
         }
+    };
+    // form 1: what has arrived in registers to its group's slot
+    auto put_scale = [&](int slot, const v4i (&v)[kRowDma]) {
+#pragma unroll
+        for (int i = 0; i < kRowDma; ++i)
+            *reinterpret_cast<v4i*>(smem + S::kScaleBase + slot * S::kScaleGroup + (i * NT + tid) * 16) = v[i];
+    };
+    auto put_m8 = [&](int slot, const uint32_t (&v)[kRowDma]) {
+        if constexpr (kMbs) {
+#pragma unroll
+            for (int i = 0; i < kRowDma; ++i)
+                *reinterpret_cast<uint32_t*>(smem + S::kM8Base + slot * S::kM8Group + (i * NT + tid) * 4) = v[i];
+        }
+    };
+    // form 1: the partial last group of K, zeros behind its end: a row's last 16 bytes (requested ahead of everything
+    // else), shifted down by those of the group before when they have arrived; rows of fewer than 16 bytes (K < 512) are
+    // put together byte by byte.
+    v4i tail_scale[kRowDma];
+    uint32_t tail_m8[kRowDma];
+    const int tail_bytes = scale_bytes - nwhole * 16, tail_words = nmac - nwhole * 4;  // 0 .. 15, 0 .. 4
+    auto fetch_tail = [&]() {
+#pragma unroll
+        for (int i = 0; i < kRowDma; ++i) {
+            const __amdgpu_buffer_rsrc_t rs = row_is_a[i] ? opa.scales : opb.scales, rw = row_is_a[i] ? opa.mbs : opb.mbs;
+            const bool piece = nwhole > 0 && tail_bytes > 0;
+            tail_scale[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, piece ? scale_off[i] : kOob, piece ? scale_bytes - 16 : 0, 0);
+            tail_m8[i] = 0;
+            if constexpr (kMbs) tail_m8[i] = __builtin_amdgcn_raw_buffer_load_b32(rw, piece ? m8_off[i] : kOob, piece ? nmac - 4 : 0, 0);
+        }
+    };
+    auto put_tail = [&]() {
+#pragma unroll
+        for (int i = 0; i < kRowDma; ++i) {
+            unsigned __int128 v = 0;
+            if (nwhole > 0) {
+                __builtin_memcpy(&v, &tail_scale[i], 16);
+                v >>= ((16 - tail_bytes) & 15) * 8;
+                tail_m8[i] >>= ((4 - tail_words) & 3) * 8;
+            } else {
+                const __amdgpu_buffer_rsrc_t rs = row_is_a[i] ? opa.scales : opb.scales, rw = row_is_a[i] ? opa.mbs : opb.mbs;
+                for (int b = 0; b < tail_bytes; ++b)
+                    v |= (unsigned __int128)(uint8_t)__builtin_amdgcn_raw_buffer_load_b8(rs, scale_off[i], b, 0) << (b * 8);
+                if constexpr (kMbs)
+                    for (int b = 0; b < tail_words; ++b)
+                        tail_m8[i] |= (uint32_t)(uint8_t)__builtin_amdgcn_raw_buffer_load_b8(rw, m8_off[i], b, 0) << (b * 8);
+            }
+            __builtin_memcpy(&tail_scale[i], &v, 16);
+        }
+        put_scale(2, tail_scale);
+        put_m8(2, tail_m8);
     };
     // MBS words of stage s -> fp32 sigma = 1/F, F = 1 + m8/256 exact, reciprocal within an ulp.  Thread p serves
     // row p (whose words its own wavefront has loaded, so its own wait covers them); threads past the last row
@@ -226,14 +290,14 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
     // parity turns the slot's address into a constant of the LDS instruction)
     auto load_words = [&](int s, RawWords& r, auto gp_) {
         constexpr int gp = decltype(gp_)::value;
-        const uint32_t* raw = reinterpret_cast<const uint32_t*>(smem + S::kM8Base + (gp < 0 ? (s / kRingGroup) & 1 : gp) * S::kM8Group);
+        const uint32_t* raw = reinterpret_cast<const uint32_t*>(smem + S::kM8Base + (gp < 0 ? group_slot(s / kRingGroup) : gp) * S::kM8Group);
 #pragma unroll
         for (int i = 0; i < kConv; ++i) {
             const int q = i * NT + tid;  // (a side without words reads zero and stores sigma = 1, which nobody reads)
             const int p = (kRows % NT == 0 || q < kRows) ? q : 0;
-            // fast form: a row's four words in one dword; general form: one word per dword, [row][4]
-            r.first[i] = S::kGen ? raw[p * kRingGroup + s % kRingGroup] : raw[p];
-            r.second[i] = S::kGen ? raw[p * kRingGroup + s % kRingGroup + 1] : r.first[i];
+            // a row's four words in one dword; single bytes: one word per dword, [row][4]
+            r.first[i] = S::kBytes ? raw[p * kRingGroup + s % kRingGroup] : raw[p];
+            r.second[i] = S::kBytes ? raw[p * kRingGroup + s % kRingGroup + 1] : r.first[i];
         }
     };
     auto store_sigma = [&](int s, const uint32_t (&words)[kConv]) {
@@ -242,7 +306,7 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
         for (int i = 0; i < kConv; ++i) {
             const int q = i * NT + tid;
             const bool live = kRows % NT == 0 || q < kRows;
-            const uint32_t m8 = S::kGen ? words[i] & 0xFFu : (words[i] >> (8 * (s % kRingGroup))) & 0xFFu;
+            const uint32_t m8 = S::kBytes ? words[i] & 0xFFu : (words[i] >> (8 * (s % kRingGroup))) & 0xFFu;
             float* dst = live ? sig + (live ? q : 0) : reinterpret_cast<float*>(smem + S::kDummy);
             *dst = __builtin_amdgcn_rcpf(1.0f + (float)m8 * (1.0f / 256.0f));
         }
@@ -255,7 +319,7 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
         const uint8_t* tab = smem + S::kRcpBase;
 #pragma unroll
         for (int i = 0; i < kConv; ++i) {
-            const uint32_t at = S::kGen ? (words[i] & 0xFFu) << 2 : ((words[i] >> (8 * (s % kRingGroup))) & 0xFFu) << 2;
+            const uint32_t at = S::kBytes ? (words[i] & 0xFFu) << 2 : ((words[i] >> (8 * (s % kRingGroup))) & 0xFFu) << 2;
             val[i] = *reinterpret_cast<const float*>(tab + at);
         }
     };
@@ -326,7 +390,7 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
             asm volatile("" : "+v"(code_base[o][kk][1]));
         }
     }
-    const int lane_scale = S::kBytes ? lr * 64 + lh * 8 : S::kGen ? lr * 32 + lh * 4 : lr * 16 + lh * 2;
+    const int lane_scale = S::kBytes ? lr * 64 + lh * 8 : lr * 16 + lh * 2;
 
     // LDS read `idx` of the kReads that fetch the fragments of a stage in ring slot `slot`: per fragment (A's
     // FM, then B's FN) the two 16-byte code pieces and the 16-bit scale pair.
@@ -343,18 +407,16 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
             else f.n[q][part] = v;
         } else {
             const int row0 = is_m ? (wm * FM + q) * 32 : TM + (wn * FN + q) * 32;  // in the A-then-B row space
-            // fast form: [row][16 bytes of the group]; general forms: [row][8 pairs], one pair per dword, or
-            // [row][16 bytes], one byte per dword (the lane's two bytes come as two dwords and are packed)
+            // [row][16 bytes of the group]; single bytes: one byte per dword (the lane's two bytes come as two dwords
+            // and are packed)
             uint32_t v;
-            const uint8_t* grp_base = smem + S::kScaleBase + (gp < 0 ? (s / kRingGroup) & 1 : gp) * S::kScaleGroup;
+            const uint8_t* grp_base = smem + S::kScaleBase + (gp < 0 ? group_slot(s / kRingGroup) : gp) * S::kScaleGroup;
             if constexpr (S::kBytes) {
                 // (a plain vector type: before a read through HIP's uint2 the compiler waits for every
                 // outstanding direct-to-LDS load)
                 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
                 const u32x2 two = *reinterpret_cast<const u32x2*>(grp_base + (s % kRingGroup) * 16 + lane_scale + row0 * 64);
                 v = (two.x & 0xFFu) | ((two.y & 0xFFu) << 8);
-            } else if constexpr (S::kGen) {
-                v = *(lds_half_ptr_t)(grp_base + (s % kRingGroup) * 8 + lane_scale + row0 * 32);
             } else {
                 v = *(lds_half_ptr_t)(grp_base + (s % kRingGroup) * 4 + lane_scale + row0 * 16);
             }
@@ -416,19 +478,30 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
     };
 
     // ---- prologue: fill the ring, fetch the operands of stage 0 --------------------------------------
+    if constexpr (S::kRegs) fetch_tail();
+    uint32_t first_m8[kRowDma];  // form 1: the words of group 0 (reg_m8 takes those of group 1)
     static_for<Sched::prologue_count()>([&](auto n_) {
         constexpr LoadItem it = Sched::prologue_item(decltype(n_)::value);
         using Index = std::integral_constant<int, it.index>;
         if constexpr (it.kind == kLoadCode) dma_code(it.what, Index{});
         else if constexpr (it.kind == kLoadScale) dma_scale(it.what, Index{});
         else dma_m8(it.what, Index{});
+        if constexpr (S::kRegs && it.kind == kLoadWords && it.what == 0) first_m8[it.index] = reg_m8[it.index];
     });
     if constexpr (kSigmaLut) {
         static_assert(NT >= 256, "one thread per table entry");
         if (tid < 256) reinterpret_cast<float*>(smem + S::kRcpBase)[tid] = __builtin_amdgcn_rcpf(1.0f + (float)tid * (1.0f / 256.0f));
         __builtin_amdgcn_s_waitcnt(kWaitLds);  // the barrier below publishes the table
     }
-    __builtin_amdgcn_s_waitcnt(wait_imm(Sched::prologue_wait_first()));
+    // (form 1: the compiler may issue group 1's words, which go to a register, earlier than the schedule has them; they are
+    // not counted on to be among the youngest)
+    __builtin_amdgcn_s_waitcnt(wait_imm(Sched::prologue_wait_first() - (S::kRegs && kMbs ? kM8Dma : 0)));
+    if constexpr (S::kRegs) {
+        put_scale(0, reg_scale);
+        put_m8(0, first_m8);
+        put_tail();
+        __builtin_amdgcn_s_waitcnt(kWaitLds);
+    }
     bare_barrier();
     Frags f0, f1;
     Frags alt;  // the second register set of A fragment 0 (kSnake: m[0], scl_m[0]) or of the B fragment (kDoubleB: n[0], scl_n[0])
@@ -439,7 +512,7 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
         read_sigma_m(0, std::integral_constant<int, 0>{});
         read_sigma_n(0, std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
     }
-    static_for<kReads>([&](auto idx_) { read_item(f0, 0, std::integral_constant<int, 0>{}, idx_, std::integral_constant<int, 0>{}); });
+    static_for<kReads>([&](auto idx_) { read_item(f0, 0, std::integral_constant<int, 0>{}, idx_, std::integral_constant<int, S::kRegs ? -1 : 0>{}); });
 
     // ---- the matrix instructions of one stage ---------------------------------------------------------
     // Plain: instruction t is half kk = t / (FM FN) of fragment pair (i, j); the two halves of a pair are
@@ -524,7 +597,14 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
         // barrier every wavefront has finished stage s - 1.  (Stages past the last request keep the barrier.)
         if constexpr (Sched::has_barrier(kPhase)) {
             __builtin_amdgcn_s_waitcnt(wait_imm(Sched::wait_count(kPhase)));
+            if constexpr (S::kRegs && kIssue && kPhase == 3) {
+                // the E8M0 bytes requested two stages ago: this barrier publishes them
+                put_scale((s / kRingGroup + 1) & 1, reg_scale);
+                __builtin_amdgcn_s_waitcnt(kWaitLds);
+            }
             bare_barrier();
+            // the words requested two stages ago: this thread alone reads them, from the next stage on
+            if constexpr (S::kRegs && kIssue && kPhase == 1) put_m8((s / kRingGroup + 1) & 1, reg_m8);
         }
         // a stage without a barrier converts the words of the stages s + 2 and s + 3 at its end (published by the
         // next stage's barrier, into the tables that the stages s - 2 and s - 1 were read from)
@@ -730,6 +810,7 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
     // Stages whose iteration still has a stage s + 4 to request, rounded up to whole groups (the extra ones
     // fetch the last stage again into slots that are no longer read); the rest runs without loads.
     const int n_issue = (max(nstages - kRingSlots, 0) + kRingGroup - 1) / kRingGroup * kRingGroup;
+    constexpr bool kSkipLast = S::kRegs && (!kMbs || (kSurface && kCouples % 2 == 0));
     auto run = [&](auto late_) {
         using Yes = std::integral_constant<bool, true>;
         using No = std::integral_constant<bool, false>;
@@ -767,6 +848,11 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
             stage(s, fa, fb, P0{}, late_, No{}, Gx{});
             stage(s + 1, fb, fa, P1{}, late_, No{}, Gx{});
             stage(s + 2, fa, fb, P2{}, late_, No{}, Gx{});
+            // (a last stage wholly past the end of K is left out; what is folded in behind the loop does not depend on
+            // the stage's parity here.  K = 2880: 23 stages instead of 24)
+            if constexpr (kSkipLast) {
+                if (s + 3 >= nmac) break;
+            }
             stage(s + 3, fb, fa, P3{}, late_, No{}, Gx{});
         }
     };

@@ -38,39 +38,42 @@ constexpr int kSigmaSlots = 4;                  // as many as ring slots: a stag
 // kSides: which operands carry MBS words (0 none, 1 A only, 2 B only, 3 both).
 // kForm: 0 = fast form, which wants K % 512 == 0 and 16-byte (E8M0) / 4-byte (MBS) aligned rows, so that a row's
 // bytes of four stages travel as one piece per lane.  1, 2 = general forms for everything else, grouped problems
-// included: E8M0 bytes travel as 2-byte pieces (1: any K % 64 == 0, rows of E8M0 bytes on even addresses; one
-// piece per lane and pair of blocks) or as single bytes (2: any K % 32 == 0, any address), MBS words as single
-// bytes, each piece in an LDS dword of its own; the last stage may be partly empty and the stage count is
-// padded to whole groups with stages that read zeros.
+// included; the last stage may be partly empty and the stage count is padded to whole groups with stages that read
+// zeros.  1 (any K % 64 == 0, rows of E8M0 bytes on even addresses): the same 16-byte and 4-byte pieces, one row per
+// lane, but through registers - a load into registers takes any address, a direct-to-LDS load of 16 bytes does not -
+// and the thread writes them to LDS; K's last group, where it is not whole, is fetched in the prologue into a slot of
+// its own.  2 (any K % 32 == 0, any address): E8M0 bytes and MBS words travel direct to LDS as single bytes, each in
+// an LDS dword of its own.
 template <int NWM_, int NWN_, int FM_, int FN_, int kSides_, int kForm_ = 0>
 struct RingShape {
     static constexpr int NWM = NWM_, NWN = NWN_, FM = FM_, FN = FN_, kSides = kSides_;
-    static constexpr bool kMbs = kSides != 0, kGen = kForm_ != 0, kBytes = kForm_ == 2;
+    static constexpr bool kMbs = kSides != 0, kGen = kForm_ != 0, kBytes = kForm_ == 2, kRegs = kForm_ == 1;
     // (couples of A fragments against one B fragment at a time; instantiated with one and with two B fragments)
     static constexpr bool kSurface = kSides == 3 && FM_ % 2 == 0 && (FN_ == 1 || FN_ == 2);
     static constexpr int NW = NWM * NWN, NT = NW * kWave;
     static constexpr int TM = NWM * FM * 32, TN = NWN * FN * 32;
     static constexpr int kRows = TM + TN;             // rows of A followed by rows of B
     static constexpr int kCodeDma = kRows / 16 / NW;  // per wavefront and stage: 16 rows x 64 B per load
-    // per wavefront and group of four stages: E8M0 bytes (fast: one row per lane; general: 8 rows x 8 pairs or
-    // 4 rows x 16 bytes per load) and MBS words (fast: one row per lane; general: 16 rows x 4 words per load)
+    // per wavefront and group of four stages: E8M0 bytes (one row per lane; single bytes: 4 rows x 16 bytes per
+    // load) and MBS words (one row per lane; single bytes: 16 rows x 4 words per load)
     static constexpr int kRowDma = ceil_div(kRows, kWave * NW);
-    static constexpr int kScaleRowsPerLoad = kBytes ? 4 : 8;  // general forms
-    static constexpr int kScaleDma = kGen ? kRows / kScaleRowsPerLoad / NW : kRowDma;
-    static constexpr int kM8Dma = kGen ? kRows / 16 / NW : kRowDma;
+    static constexpr int kScaleDma = kBytes ? kRows / 4 / NW : kRowDma;
+    static constexpr int kM8Dma = kBytes ? kRows / 16 / NW : kRowDma;
     static constexpr int kRowsPadded = kRowDma * NW * kWave;
     static constexpr int kCodesStage = kRows * kRingRowStage;
-    static constexpr int kScaleGroup = kBytes ? kRows * 64 : kGen ? kRows * 32 : kRowsPadded * 16;
-    static constexpr int kM8Group = !kMbs ? 0 : kGen ? kRows * 16 : kRowsPadded * 4;
+    static constexpr int kScaleGroup = kBytes ? kRows * 64 : kRowsPadded * 16;
+    static constexpr int kM8Group = !kMbs ? 0 : kBytes ? kRows * 16 : kRowsPadded * 4;
+    // group g sits in slot g % 2; with kRegs K's last, partial group in slot 2
+    static constexpr int kGroupSlots = kRegs ? 3 : 2;
     static constexpr int kSigmaStage = kMbs ? kRows * 4 : 0;
     // The small arrays come first: their addresses then fit the 16-bit constant of an LDS instruction.
     static constexpr int kM8Base = 0;
-    static constexpr int kSigmaBase = kM8Base + 2 * kM8Group;
+    static constexpr int kSigmaBase = kM8Base + kGroupSlots * kM8Group;
     // the 256 values sigma can take, 1 / (1 + m8 / 256) in fp32 (kernels that look sigma up instead of computing it)
     static constexpr int kRcpBase = kSigmaBase + kSigmaSlots * kSigmaStage;
     static constexpr int kRcpBytes = kMbs ? 1024 : 0;
     static constexpr int kScaleBase = (kRcpBase + kRcpBytes + 16383) / 16384 * 16384;
-    static constexpr int kDummy = kScaleBase + 2 * kScaleGroup;  // target of padding stores
+    static constexpr int kDummy = kScaleBase + kGroupSlots * kScaleGroup;  // target of padding stores
     static constexpr int kCodesBase = kDummy + 256;
     static constexpr int kLdsBytes = kCodesBase + kRingSlots * kCodesStage;
     static_assert(kCodesBase % 64 == 0 && kCodesBase < 65536, "code rows stay 64-byte aligned; small arrays below 64 KiB");
