@@ -77,8 +77,9 @@ __global__ __launch_bounds__(F8Shape<kFast>::NT) void gemm_f8_kernel(GemmArgs g)
     // walked in bands of kF8GroupM tile-rows so that concurrent workgroups share panels in its L2
     // (grouped: the launch took an upper bound of the tile-rows; the tiles are dealt out over the real number)
     int tiles_m = g.tiles_m;
+    GroupLane groups;
     if constexpr (!kFast || kRegs) {
-        if (g.num_groups > 0) tiles_m = grouped_tile_rows(g.row_offsets, g.num_groups, TM, (int)(threadIdx.x & 63));
+        if (g.num_groups > 0) tiles_m = grouped_tile_rows(g.row_offsets, g.num_groups, TM, (int)(threadIdx.x & 63), groups);
     }
     const int total = tiles_m * g.tiles_n;
     const int per_xcd = (total + 7) / 8;
@@ -96,7 +97,7 @@ __global__ __launch_bounds__(F8Shape<kFast>::NT) void gemm_f8_kernel(GemmArgs g)
     if constexpr (!kFast || kRegs) {
         if (g.num_groups > 0) {
             GroupOfTileRow gr;
-            if (!grouped_find(g.row_offsets, g.num_groups, TM, (int)(threadIdx.x & 63), tm, gr)) return;
+            if (!grouped_find(g.row_offsets, g.num_groups, TM, (int)(threadIdx.x & 63), tm, groups, gr)) return;
             a_row0 = gr.lo + (int64_t)(tm - gr.first) * TM;
             a_end = gr.hi;
             b_row0 = (int64_t)gr.group * g.N + (int64_t)tn * TN;

@@ -92,8 +92,9 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
     // tiles, walked in bands of kRingGroupM tile-rows so that concurrent workgroups share panels in its L2
     // (grouped: the launch took an upper bound of the tile-rows; the tiles are dealt out over the real number)
     int tiles_m = g.tiles_m;
+    GroupLane groups;
     if constexpr (S::kGen) {
-        if (g.num_groups > 0) tiles_m = grouped_tile_rows(g.row_offsets, g.num_groups, TM, (int)(threadIdx.x & 63));
+        if (g.num_groups > 0) tiles_m = grouped_tile_rows(g.row_offsets, g.num_groups, TM, (int)(threadIdx.x & 63), groups);
     }
     const int total = tiles_m * g.tiles_n;
     const int per_xcd = (total + 7) / 8;
@@ -111,7 +112,7 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
     if constexpr (S::kGen) {
         if (g.num_groups > 0) {
             GroupOfTileRow gr;
-            if (!grouped_find(g.row_offsets, g.num_groups, TM, (int)(threadIdx.x & 63), tm, gr)) return;
+            if (!grouped_find(g.row_offsets, g.num_groups, TM, (int)(threadIdx.x & 63), tm, groups, gr)) return;
             a_row0 = gr.lo + (int64_t)(tm - gr.first) * TM;
             a_end = gr.hi;
             b_row0 = (int64_t)gr.group * g.N + (int64_t)tn * TN;
@@ -599,12 +600,12 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
             __builtin_amdgcn_s_waitcnt(wait_imm(Sched::wait_count(kPhase)));
             if constexpr (S::kRegs && kIssue && kPhase == 3) {
                 // the E8M0 bytes requested two stages ago: this barrier publishes them
-                put_scale((s / kRingGroup + 1) & 1, reg_scale);
+                put_scale(kGp < 0 ? (s / kRingGroup + 1) & 1 : 1 - kGp, reg_scale);
                 __builtin_amdgcn_s_waitcnt(kWaitLds);
             }
             bare_barrier();
             // the words requested two stages ago: this thread alone reads them, from the next stage on
-            if constexpr (S::kRegs && kIssue && kPhase == 1) put_m8((s / kRingGroup + 1) & 1, reg_m8);
+            if constexpr (S::kRegs && kIssue && kPhase == 1) put_m8(kGp < 0 ? (s / kRingGroup + 1) & 1 : 1 - kGp, reg_m8);
         }
         // a stage without a barrier converts the words of the stages s + 2 and s + 3 at its end (published by the
         // next stage's barrier, into the tables that the stages s - 2 and s - 1 were read from)
@@ -827,7 +828,9 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
         if constexpr (kTwoGroups) {
             // two groups per turn: which of the two slots a group's E8M0 bytes and MBS words sit in is then a
             // constant of the LDS instructions that read them, which saves the vector ALUs the address additions
-            for (; s + 8 <= n_issue; s += 8) {
+            // (form 1: a partial last group has a slot of its own and is first read in the stage before it)
+            const int n_paired = S::kRegs ? min(n_issue, (nwhole - 1) * kRingGroup) : n_issue;
+            for (; s + 8 <= n_paired; s += 8) {
                 stage(s, fa, fb, P0{}, late_, Yes{}, G0{});
                 stage(s + 1, fb, fa, P1{}, late_, Yes{}, G0{});
                 stage(s + 2, fa, fb, P2{}, late_, Yes{}, G0{});
