@@ -83,9 +83,9 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
     // first pair; with words on one operand the B fragment alone has two.
     constexpr bool kDoubleAll = kSurface && !kSnake, kDoubleB = kMbs && !kSurface && FN == 1;
     // The loop over the stages that issue loads takes two groups of four stages per turn (see run below).
-    constexpr bool kTwoGroups = kSnake && !S::kGen;
+    constexpr bool kTwoGroups = kSnake;
     // sigma = 1 / (1 + m8 / 256) read from a table of its 256 values instead of computed per row and stage
-    constexpr bool kSigmaLut = kSnake && !S::kGen;
+    constexpr bool kSigmaLut = kSnake;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
 
     // ---- which tile: workgroups are dealt round-robin to the 8 XCDs; each XCD gets a contiguous run of
