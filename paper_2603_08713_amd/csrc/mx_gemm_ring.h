@@ -811,7 +811,8 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
     // Stages whose iteration still has a stage s + 4 to request, rounded up to whole groups (the extra ones
     // fetch the last stage again into slots that are no longer read); the rest runs without loads.
     const int n_issue = (max(nstages - kRingSlots, 0) + kRingGroup - 1) / kRingGroup * kRingGroup;
-    constexpr bool kSkipLast = S::kRegs && (!kMbs || (kSurface && kCouples % 2 == 0));
+    constexpr bool kSkip = S::kRegs;
+    static_assert(!kSkip || !kMbs || kSurface, "the product left over is folded in with the last stage's parity below");
     auto run = [&](auto late_) {
         using Yes = std::integral_constant<bool, true>;
         using No = std::integral_constant<bool, false>;
@@ -848,14 +849,13 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
             stage(s + 3, fb, fa, P3{}, late_, Yes{}, Gx{});
         }
         for (; s < nstages; s += 4) {  // nstages is a multiple of the group
+            // (stages wholly past the end of K are left out.  K = 2880: 23 stages instead of 24, 1088: 9 instead of 12)
             stage(s, fa, fb, P0{}, late_, No{}, Gx{});
+            if (kSkip && s + 1 >= nmac) break;
             stage(s + 1, fb, fa, P1{}, late_, No{}, Gx{});
+            if (kSkip && s + 2 >= nmac) break;
             stage(s + 2, fa, fb, P2{}, late_, No{}, Gx{});
-            // (a last stage wholly past the end of K is left out; what is folded in behind the loop does not depend on
-            // the stage's parity here.  K = 2880: 23 stages instead of 24)
-            if constexpr (kSkipLast) {
-                if (s + 3 >= nmac) break;
-            }
+            if (kSkip && s + 3 >= nmac) break;
             stage(s + 3, fb, fa, P3{}, late_, No{}, Gx{});
         }
     };
@@ -864,11 +864,16 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
     if constexpr (kSurface) issue_surface(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
     if (NW == 8 || w % 4 < 2) run(std::integral_constant<int, 0>{});
     else run(std::integral_constant<int, 1>{});
-    // (the last stage is the fourth of its group: parity 1)
+    // (the last stage is the fourth of its group, parity 1, unless stages past the end of K were left out)
     if constexpr (kDefer) retire(std::integral_constant<int, 1>{}, std::integral_constant<int, kPairs - 1>{});
     if constexpr (kSurface) {
-        fold(std::integral_constant<int, 1>{}, std::integral_constant<int, kPairs - 1>{}, std::integral_constant<int, 0>{});
-        fold(std::integral_constant<int, 1>{}, std::integral_constant<int, kPairs - 1>{}, std::integral_constant<int, 1>{});
+        auto fold_last = [&](auto par_) {
+            fold(par_, std::integral_constant<int, kPairs - 1>{}, std::integral_constant<int, 0>{});
+            fold(par_, std::integral_constant<int, kPairs - 1>{}, std::integral_constant<int, 1>{});
+        };
+        // (with an even number of couples a stage the two are the same)
+        if (kSkip && kCouples % 2 == 1 && nmac % 2 == 1) fold_last(std::integral_constant<int, 0>{});
+        else fold_last(std::integral_constant<int, 1>{});
     }
 
     // ---- epilogue ------------------------------------------------------------------------------------
