@@ -56,11 +56,12 @@ namespace mx {
 namespace {
 
 // kFmtA / kFmtB: the matrix instruction's format selector of tensor A / B (0 = E4M3, 1 = E5M2).  kRegs: the fast form
-// for rows of E8M0 bytes and MBS words at any address, grouped problems and any K % 64 == 0 from 512 on.
-template <int kFmtA, int kFmtB, bool kMbs, bool kFast, bool kRegs = false>
-__global__ __launch_bounds__(F8Shape<kFast>::NT) void gemm_f8_kernel(GemmArgs g) {
+// for rows of E8M0 bytes and MBS words at any address, grouped problems and any K % 64 == 0 from 512 on.  kSmall: 128 x 128
+// tiles (instantiated with kRegs, which takes every K and address from 512 on).
+template <int kFmtA, int kFmtB, bool kMbs, bool kFast, bool kRegs = false, bool kSmall = false>
+__global__ __launch_bounds__((F8Shape<kFast, kSmall>::NT)) void gemm_f8_kernel(GemmArgs g) {
     static_assert(kFast || !kRegs, "kRegs is a variant of the fast form");
-    using S = F8Shape<kFast>;
+    using S = F8Shape<kFast, kSmall>;
     constexpr int FM = S::FM, FN = S::FN, TM = S::TM, TN = S::TN, NW = S::NW, kCodeDma = S::kCodeDma;
     // 6-bit codes (format selectors 2, 3) come packed, 24 bytes per block; both operands have the same width
     constexpr bool kSix = kFmtA >= 2;
@@ -70,7 +71,7 @@ __global__ __launch_bounds__(F8Shape<kFast>::NT) void gemm_f8_kernel(GemmArgs g)
     constexpr int kRowStage = kSix ? 96 : kF8RowStage;  // code bytes per row and stage
     // loads a wavefront makes per stage: what the stage's wait counts (a count that assumed more would let the
     // youngest loads of the stage it is about to read stay in flight)
-    using Sched = F8Schedule<kSixPlanes ? kF8Six : kFast ? kF8Fast : kF8General, kMbs>;
+    using Sched = F8Schedule<kSixPlanes ? kF8Six : kFast ? kF8Fast : kF8General, kMbs, kSmall>;
     constexpr int kLoads = Sched::kLoads;
     static_assert(kLoads == S::kLoads - (kFast || kMbs ? 0 : 2) && Sched::kCodeDma == kCodeDma, "the schedule describes this kernel");
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -689,19 +690,9 @@ __global__ __launch_bounds__(F8Shape<kFast>::NT) void gemm_f8_kernel(GemmArgs g)
     else flush(std::integral_constant<bool, false>{});
 }
 
-template <int kFmtA, int kFmtB, bool kMbs, bool kFast, bool kRegs = false>
-int launch_f8_kernel(const GemmArgs& g, unsigned blocks, hipStream_t s) {
-    using S = F8Shape<kFast>;
-    auto* fn = gemm_f8_kernel<kFmtA, kFmtB, kMbs, kFast, kRegs>;
-    static LdsOptIn opt_in;  // one per kernel instantiation
-    if (int st = opt_in.ensure(reinterpret_cast<const void*>(fn), S::kLdsBytes)) return st;
-    hipLaunchKernelGGL(fn, dim3(blocks), dim3(S::NT), S::kLdsBytes, s, g);
-    return launch_status();
-}
-
-template <int kFmtA, int kFmtB>
-int launch_f8(GemmArgs g, bool use_mbs, bool force_general, hipStream_t s) {
-    using S = F8Shape<true>;
+template <int kFmtA, int kFmtB, bool kMbs, bool kFast, bool kRegs = false, bool kSmall = false>
+int launch_f8_kernel(GemmArgs g, hipStream_t s) {
+    using S = F8Shape<kFast, kSmall>;
     // grouped: every group may end with a partial tile-row, so this is an upper bound (the surplus exits)
     const int64_t tiles_m = g.num_groups > 0 ? g.M / S::TM + g.num_groups : (g.M + S::TM - 1) / S::TM;
     const int64_t tiles_n = (g.N + S::TN - 1) / S::TN;
@@ -709,16 +700,38 @@ int launch_f8(GemmArgs g, bool use_mbs, bool force_general, hipStream_t s) {
     g.tiles_m = (int)tiles_m;
     g.tiles_n = (int)tiles_n;
     const unsigned blocks = (unsigned)(((tiles_m * tiles_n + 7) / 8) * 8);
+    auto* fn = gemm_f8_kernel<kFmtA, kFmtB, kMbs, kFast, kRegs, kSmall>;
+    static LdsOptIn opt_in;  // one per kernel instantiation
+    if (int st = opt_in.ensure(reinterpret_cast<const void*>(fn), S::kLdsBytes)) return st;
+    hipLaunchKernelGGL(fn, dim3(blocks), dim3(S::NT), S::kLdsBytes, s, g);
+    return launch_status();
+}
+
+// Tiles run in rounds of one per compute unit: rounds x tile area / efficiency, the 128 x 128 tile taken at 0.8 of
+// the large one's rate per output, as in the MXFP4 kernels.  1024 x 4096 x 4096 in E2M3, 128 large tiles or 256 small ones, with the
+// quantizer: 38.6 and 29.6 us; 78 x 6795 x 1792 in E5M2 29.8 and 17.8 us.  A grouped problem's rounds are not known here: large tiles.
+inline bool f8_small_tile(const GemmArgs& g) {
+    if (g.num_groups > 0 || g.K < 512) return false;
+    const int64_t cols = (g.N + 127) / 128, big = (g.M + 255) / 256 * cols, small = (g.M + 127) / 128 * cols;
+    return (double)((small + 255) / 256) / 0.8 < 2.0 * (double)((big + 255) / 256);
+}
+
+template <int kFmtA, int kFmtB>
+int launch_f8_small(const GemmArgs& g, bool use_mbs, hipStream_t s) {
+    return use_mbs ? launch_f8_kernel<kFmtA, kFmtB, true, true, true, true>(g, s) : launch_f8_kernel<kFmtA, kFmtB, false, true, true, true>(g, s);
+}
+
+template <int kFmtA, int kFmtB>
+int launch_f8(const GemmArgs& g, bool use_mbs, bool force_general, hipStream_t s) {
     // Fast form: E8M0 bytes and MBS words travel per group of four stages, as 16-byte pieces and dwords, direct to LDS
     // where the addresses allow it and through registers elsewhere (grouped problems: a group's rows start anywhere).
     // The general form is left with rows that are shorter than one piece.
     const bool fast = !force_general && g.num_groups == 0 && (g.K % 512) == 0 && aligned(g.a_scales, 16) && aligned(g.b_scales, 16) &&
                       (!g.a_mbs || aligned(g.a_mbs, 4)) && (!g.b_mbs || aligned(g.b_mbs, 4));
-    if (fast)
-        return use_mbs ? launch_f8_kernel<kFmtA, kFmtB, true, true>(g, blocks, s) : launch_f8_kernel<kFmtA, kFmtB, false, true>(g, blocks, s);
+    if (fast) return use_mbs ? launch_f8_kernel<kFmtA, kFmtB, true, true>(g, s) : launch_f8_kernel<kFmtA, kFmtB, false, true>(g, s);
     if (!force_general && g.K >= 512)
-        return use_mbs ? launch_f8_kernel<kFmtA, kFmtB, true, true, true>(g, blocks, s) : launch_f8_kernel<kFmtA, kFmtB, false, true, true>(g, blocks, s);
-    return use_mbs ? launch_f8_kernel<kFmtA, kFmtB, true, false>(g, blocks, s) : launch_f8_kernel<kFmtA, kFmtB, false, false>(g, blocks, s);
+        return use_mbs ? launch_f8_kernel<kFmtA, kFmtB, true, true, true>(g, s) : launch_f8_kernel<kFmtA, kFmtB, false, true, true>(g, s);
+    return use_mbs ? launch_f8_kernel<kFmtA, kFmtB, true, false>(g, s) : launch_f8_kernel<kFmtA, kFmtB, false, false>(g, s);
 }
 
 }  // namespace

@@ -1,4 +1,4 @@
-// Tile shape and load schedule of the GEMM kernel for 8-bit and 6-bit operands (mx_gemm_f8.hip): what the kernel
+// Tile shape and load schedule of the GEMM kernel for 8-bit and 6-bit operands (mx_gemm_f8.h): what the kernel
 // keeps in LDS, which loads a wavefront issues in a stage, in which order, and how many of its youngest loads may
 // still be in flight when a stage starts.  Plain constexpr C++ with no device code, so that a host program can
 // replay the schedule of every form and check it (tests/schedule_check.cpp).
@@ -30,10 +30,11 @@ constexpr int kF8Slots = 3;
 constexpr int kF8RowStage = kMacro;  // code bytes per row and stage (8-bit)
 constexpr int kF8GroupM = 4;         // tile-rows walked together for L2 reuse
 
-template <bool kFast_>
+// kSmall: 128 x 128 tiles (eight wavefronts of 64 x 32) instead of 256 x 128 (64 x 64)
+template <bool kFast_, bool kSmall_ = false>
 struct F8Shape {
     static constexpr bool kFast = kFast_;
-    static constexpr int NWM = 4, NWN = 2, FM = 2, FN = 2, NW = NWM * NWN, NT = NW * kWave;
+    static constexpr int NWM = kSmall_ ? 2 : 4, NWN = kSmall_ ? 4 : 2, FM = 2, FN = kSmall_ ? 1 : 2, NW = NWM * NWN, NT = NW * kWave;
     static constexpr int TM = NWM * FM * 32, TN = NWN * FN * 32, kRows = TM + TN;
     static constexpr int kCodeDma = kRows / 8 / NW;                     // per wavefront and stage: 8 rows x 128 B per load
     static constexpr int kRegLoads = kFast ? 0 : FM + FN + 2;           // general form: E8M0 dwords and MBS words per lane and stage
@@ -52,7 +53,7 @@ struct F8Shape {
     static_assert((TM / 8) % NW == 0 && (TN / 8) % NW == 0, "operand fixed per load index");
     static_assert(kRows % kWave == 0 && TM % kWave == 0, "fast form: a wavefront's rows belong to one operand");
     static_assert(kLdsBytes <= 160 * 1024 && NW * kStageRegion <= kLdsBytes, "LDS capacity of a gfx950 compute unit");
-    static_assert(kCodeDma <= 2 * FM * FN - 2 && 3 * kLoads + 4 < 64, "vmcnt is a 6-bit counter");
+    static_assert(kCodeDma <= 2 * FM * FN && 3 * kLoads + 4 < 64, "vmcnt is a 6-bit counter");
 };
 
 // ---- load schedule ----------------------------------------------------------------------------------------------
@@ -64,9 +65,9 @@ struct F8LoadItem {
     int kind, what, index;
 };
 
-template <int kForm, bool kMbs>
+template <int kForm, bool kMbs, bool kSmall = false>
 struct F8Schedule {
-    using S = F8Shape<kForm != kF8General>;
+    using S = F8Shape<kForm != kF8General, kSmall>;
     static constexpr int kCodeDma = S::kCodeDma, kGroup = S::kGroup;
     static constexpr int kRegScales = kForm == kF8General ? S::FM + S::FN : 0;
     static constexpr int kRegWords = kForm == kF8General && kMbs ? 2 : 0;

@@ -161,16 +161,16 @@ void check_all(const char* name) {
     for (int nstages : {4, 8, 12, 16, 64, 256}) check<S>(name, nstages);
 }
 
-// ---- the kernel for 8-bit and 6-bit operands (mx_gemm_f8.hip), same rules ------------------------------------
+// ---- the kernel for 8-bit and 6-bit operands (mx_gemm_f8.h), same rules ------------------------------------
 struct F8Issued {
     mx::F8LoadItem item;  // absolute
     int at_stage;
     bool repeat;          // past the end of K the kernel fetches the last stage, group or plane again
 };
 
-template <int kForm, bool kMbs>
+template <int kForm, bool kMbs, bool kSmall = false>
 void check_f8(const char* name, int nstages) {
-    using Sched = mx::F8Schedule<kForm, kMbs>;
+    using Sched = mx::F8Schedule<kForm, kMbs, kSmall>;
     constexpr int C = Sched::kCodeDma;
     constexpr bool kGroups = kForm != mx::kF8General, kSix = kForm == mx::kF8Six;
     std::vector<F8Issued> issued;
@@ -263,7 +263,10 @@ void check_f8_all(const char* name) {
     if (kForm == mx::kF8General)
         for (int nstages : {1, 2, 3, 4, 5, 7, 12, 61, 256}) check_f8<kForm, kMbs>(name, nstages);
     else
-        for (int nstages : {4, 8, 12, 16, 20, 64, 256}) check_f8<kForm, kMbs>(name, nstages);
+        for (int nstages : {4, 8, 12, 16, 20, 64, 256}) {
+            check_f8<kForm, kMbs>(name, nstages);
+            check_f8<kForm, kMbs, true>(name, nstages);  // 128 x 128 tiles
+        }
 }
 
 }  // namespace
