@@ -13,15 +13,19 @@ namespace {
 // force_shape (mx_internal_gemm only; the public entry points pass -1 = automatic): 2 / 6 / 7 = fast form without
 // MBS on 256x256 / 256x128 / 128x128 tiles, 3 / 4 = fast form with MBS on 256x128 / 128x128 tiles, 5 = few-row
 // kernel, 8 / 9 = general form (row pieces through registers) on 256x128 / 128x128 tiles, 10 = general form (single bytes) on
-// 128x128 tiles.
+// 128x128 tiles, 11 / 12 = fast form with MBS on both operands / general form with MBS on 64x128 tiles.
 // Which kernel form and tile shape (the codes above) takes a problem.  Tiles run in rounds of one per compute
 // unit: rounds x tile area / efficiency (the small tile reaches about 0.8 of the large tile's rate per output
-// with MBS, 0.85 / 0.72 without; measured) picks the tile.
-int choose_shape(int64_t M, int64_t N, bool use_mbs, bool ring_ok, bool pairs_ok, bool skinny_ok) {
+// with MBS, 0.85 / 0.72 without; measured) picks the tile.  With words on both operands, ungrouped, 64 x 128 tiles
+// take what they cover in one round: twice the compute units have work, and a tile of few rows is bound by a stage's serial chain
+// and not by its arithmetic.  GEMM alone, 64 x 128 against 128 x 128: 333 x 4096 x 4096 14.0 and 17.6 us, 512 x 4096 x 4096 14.1
+// and 17.8, 333 x 4000 x 2880 11.1 and 13.7; past one round 800 x 4096 x 4096 20.4 and 19.1, 1024 x 4096 x 2880 17.7 and 15.9.
+int choose_shape(int64_t M, int64_t N, bool use_mbs, bool ring_ok, bool pairs_ok, bool skinny_ok, bool tile64_ok) {
     const int64_t t256x128 = ((M + 255) / 256) * ((N + 127) / 128), t128 = ((M + 127) / 128) * ((N + 127) / 128);
     const double big = 2.0 * ((t256x128 + 255) / 256) / (use_mbs ? 1.0 : 0.85),
                  small = ((t128 + 255) / 256) / (use_mbs ? 0.8 : 0.72);
     if (skinny_ok) return 5;
+    if (tile64_ok && ((M + 63) / 64) * ((N + 127) / 128) <= 256 && (ring_ok || pairs_ok)) return ring_ok ? 11 : 12;
     if (ring_ok) return use_mbs ? (big <= small ? 3 : 4) : 2;  // (without MBS the launcher also has 256 x 256 tiles)
     if (pairs_ok) return big <= small ? 8 : 9;
     return 10;
@@ -89,7 +93,8 @@ int launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* 
     // General form with row pieces through registers: rows of E8M0 bytes on even addresses; else single bytes.
     const bool pairs_ok = K > 0 && (K % 64) == 0 && aligned(a_scales, 2) && aligned(b_scales, 2);
     const bool skinny_ok = K > 0 && (grouped ? M <= kFewRowsPerGroup * num_groups : M <= 64 && K <= 8192);
-    int shape = choose_shape(M, N, use_mbs, ring_ok, pairs_ok, skinny_ok);
+    const bool tile64_ok = !grouped && a_mbs && b_mbs && mbs_entry;
+    int shape = choose_shape(M, N, use_mbs, ring_ok, pairs_ok, skinny_ok, tile64_ok);
     if (force_shape >= 0) shape = force_shape;
     // (the checks below only matter for forced shapes)
     if (shape == 5) {
@@ -97,6 +102,10 @@ int launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* 
         if (grouped) return launch_gemm_skinny_grouped(g, use_mbs, !pairs_ok, s);
         const SkinnyPlan p = plan_skinny(M, N, K, ring_ok, pairs_ok);
         return launch_gemm_skinny_tile(g, use_mbs, p.fm, p.fn, p.form, s);
+    }
+    if (shape == 11 || shape == 12) {
+        if (!use_mbs || (shape == 11 ? !ring_ok || !a_mbs || !b_mbs : !pairs_ok)) return MX_EINVAL;
+        return shape == 11 ? launch_gemm_mbs_ring(g, 2, s) : launch_gemm_mbs_general(g, 2, false, s);
     }
     if (shape == 8 || shape == 9) {
         if (!pairs_ok) return MX_EINVAL;
@@ -172,7 +181,8 @@ int mx_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int a_has_mbs, int b_
     if (!out || cap <= 0 || M < 0 || N < 0 || K < 0 || (K % mx::kBlock) != 0) return MX_EINVAL;
     const bool use_mbs = a_has_mbs || b_has_mbs;
     const bool ring_ok = !grouped && K > 0 && (K % 512) == 0, pairs_ok = K > 0 && (K % 64) == 0;
-    const int shape = mx::choose_shape(M, N, use_mbs, ring_ok, pairs_ok, K > 0 && !grouped && M <= 64 && K <= 8192);
+    const int shape = mx::choose_shape(M, N, use_mbs, ring_ok, pairs_ok, K > 0 && !grouped && M <= 64 && K <= 8192,
+                                       !grouped && a_has_mbs && b_has_mbs);
     const char* sides = a_has_mbs && b_has_mbs ? "MBS words on A and B" : a_has_mbs ? "MBS words on A" : b_has_mbs ? "MBS words on B" : "no MBS";
     const char* what;
     switch (shape) {
@@ -181,6 +191,8 @@ int mx_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int a_has_mbs, int b_
                                               : "gemm_ring_kernel, fast form, 256x128 tile, 8 wavefronts of 128x32"; break;
         case 4: what = "gemm_ring_kernel, fast form, 128x128 tile, 8 wavefronts of 64x32"; break;
         case 5: what = "gemm_skinny_kernel (few rows)"; break;
+        case 11: what = "gemm_ring_kernel, fast form, 64x128 tile, 4 wavefronts of 64x32"; break;
+        case 12: what = "gemm_ring_kernel, general form (row pieces through registers), 64x128 tile, 4 wavefronts of 64x32"; break;
         case 8: what = use_mbs ? "gemm_ring_kernel, general form (row pieces through registers), 256x128 tile, 8 wavefronts" : "gemm_ring_kernel, general form (row pieces through registers), 256x128 tile, 4 wavefronts"; break;
         case 9: what = "gemm_ring_kernel, general form (row pieces through registers), 128x128 tile"; break;
         default: what = "gemm_ring_kernel, general form (single scale bytes), 128x128 tile"; break;

@@ -19,6 +19,8 @@ namespace mx {
 // for that operand: the one-sided variants fold a product in with one multiply-add per output instead of two
 // operations.
 int launch_gemm_mbs_ring(const GemmArgs& g, int variant, hipStream_t s) {
+    // 64 x 128 tiles, four wavefronts (words on both operands)
+    if (variant == 2) return launch_ring<RingShape<1, 4, 2, 1, 3>>(g, s);
     if (variant == 1) {  // 128 x 128 tiles
         if (g.a_mbs && g.b_mbs) return launch_ring<RingShape<2, 4, 2, 1, 3>>(g, s);
         if (g.a_mbs) return launch_ring<RingShape<2, 4, 2, 1, 1>>(g, s);

@@ -80,7 +80,8 @@ struct RingShape {
     static constexpr int kStageRegion = 32 * (FN * 32 * 4 + 16);  // per wavefront, epilogue staging
     static_assert(NW == 4 || NW == 8, "one or two wavefronts per SIMD");
     static_assert((TM / 16) % NW == 0 && (TN / 16) % NW == 0, "16-row code loads: operand fixed per load index");
-    static_assert(!kGen || (TM % 128 == 0 && TN % 128 == 0 && kRows % (16 * NW) == 0), "general forms: operand fixed per load index");
+    static_assert(!kBytes || (TM % 128 == 0 && TN % 128 == 0 && kRows % (16 * NW) == 0), "single bytes: operand fixed per load index");
+    static_assert(TM % kWave == 0 && TN % kWave == 0, "a wavefront's rows belong to one operand");
     static_assert(kLdsBytes <= 160 * 1024, "LDS capacity of a gfx950 compute unit");
     static_assert(NW * kStageRegion <= kLdsBytes, "epilogue staging fits the LDS of the main loop");
     static_assert(FM * FN * 16 <= 256, "accumulators fill at most the accumulation registers");

@@ -290,6 +290,8 @@ int main() {
     SHAPE(4, 2, 2, 2, 3, 1);
     SHAPE(2, 4, 2, 1, 3, 1);
     SHAPE(2, 4, 2, 1, 3, 2);
+    SHAPE(1, 4, 2, 1, 3);
+    SHAPE(1, 4, 2, 1, 3, 1);
     // the forms of the kernel for 8-bit and 6-bit operands, with and without MBS words
     check_f8_all<mx::kF8General, false>("F8Schedule<general, no MBS>");
     check_f8_all<mx::kF8General, true>("F8Schedule<general, MBS>");
