@@ -598,15 +598,15 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
         // barrier every wavefront has finished stage s - 1.  (Stages past the last request keep the barrier.)
         if constexpr (Sched::has_barrier(kPhase)) {
             __builtin_amdgcn_s_waitcnt(wait_imm(Sched::wait_count(kPhase)));
-            if constexpr (S::kRegs && kIssue && kPhase == 3) {
-                // the E8M0 bytes requested two stages ago: this barrier publishes them
-                put_scale(kGp < 0 ? (s / kRingGroup + 1) & 1 : 1 - kGp, reg_scale);
-                __builtin_amdgcn_s_waitcnt(kWaitLds);
-            }
             bare_barrier();
             // the words requested two stages ago: this thread alone reads them, from the next stage on
             if constexpr (S::kRegs && kIssue && kPhase == 1) put_m8(kGp < 0 ? (s / kRingGroup + 1) & 1 : 1 - kGp, reg_m8);
         }
+        // form 1: the E8M0 bytes requested in the stage before (the compiler waits for them and lets the codes fly), written in the
+        // middle of the stage so that the next one's barrier, which publishes them, does not wait for the LDS
+        auto put_next_scale = [&]() {
+            if constexpr (S::kRegs && kIssue && kPhase == 2) put_scale(kGp < 0 ? (s / kRingGroup + 1) & 1 : 1 - kGp, reg_scale);
+        };
         // a stage without a barrier converts the words of the stages s + 2 and s + 3 at its end (published by the
         // next stage's barrier, into the tables that the stages s - 2 and s - 1 were read from)
         constexpr bool kConvert = kMbs && !Sched::has_barrier(kPhase);
@@ -625,6 +625,7 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
         auto slip = [&](auto t_) {  // after matrix instruction t: LDS reads and loads whose turn it is
             constexpr int t = decltype(t_)::value;
             if constexpr (!kMbs) {
+                if constexpr (t == kMfmas / 2) put_next_scale();
                 static_for<kReads>([&](auto r_) {
                     if constexpr ((decltype(r_)::value * kMfmas) / kReads == t) read_item(next, s + 1, NextSlot{}, r_, NextGp{});
                 });
@@ -692,6 +693,7 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
                             if constexpr ((decltype(n_)::value * 2) / kN == shadow) issue_load(s, phase_, n_);
                         });
                     }
+                    if constexpr (shadow == 0) put_next_scale();
                     if constexpr (shadow == 0 && kConvert && kSigmaLut) {
                         lookup_sigma(s + 2, words.first, looked_up[0]);
                         lookup_sigma(s + 3, words.second, looked_up[1]);
@@ -730,6 +732,7 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
                 __builtin_amdgcn_sched_barrier(0);
                 // (two register sets: the next stage's fragments are requested behind the first pair)
                 if constexpr (kDoubleAll && q == 0) static_for<kReads>([&](auto idx_) { read_item(next, s + 1, NextSlot{}, idx_, NextGp{}); });
+                if constexpr (q == 0) put_next_scale();
                 if constexpr (q % 2 == 1) {
                     constexpr int shadow = q / 2;
                     if constexpr (shadow + 1 < kShadows) issue_surface(Par{}, std::integral_constant<int, shadow + 1>{});
@@ -862,7 +865,7 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
     // (with one wavefront per SIMD every stalled load stalls the matrix pipeline: half of the wavefronts issue
     // theirs one slot later; with two per SIMD the second copy of the loop is not worth its registers)
     if constexpr (kSurface) issue_surface(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
-    if (NW == 8 || w % 4 < 2) run(std::integral_constant<int, 0>{});
+    if (NW == 8 || kMbs || w % 4 < 2) run(std::integral_constant<int, 0>{});
     else run(std::integral_constant<int, 1>{});
     // (the last stage is the fourth of its group, parity 1, unless stages past the end of K were left out)
     if constexpr (kDefer) retire(std::integral_constant<int, 1>{}, std::integral_constant<int, kPairs - 1>{});
