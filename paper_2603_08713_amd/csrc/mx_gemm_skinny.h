@@ -37,6 +37,7 @@
 #pragma once
 
 #include "mx_gemm_shared.h"
+#include "mx_gemm_skinny_schedule.h"
 #include "mx_quantize_math.h"
 
 namespace mx {
@@ -53,8 +54,6 @@ struct SkinnyArgs {
 
 namespace {
 
-constexpr int kSkinnyMacs = 4;  // macro blocks per chunk
-
 // what a wavefront keeps in LDS
 template <int NW, int FM, int FN, bool kFused, int kForm>
 struct SkinnyShape {
@@ -63,9 +62,10 @@ struct SkinnyShape {
     static constexpr int kCodes = FN * 4096;  // [fragment][16 rows][256 B]; at the end its partial results
     static constexpr int kPiece = kForm == 2 ? 2 : 1;  // bytes of an E8M0 piece in the forms 2 and 3
     // E8M0 bytes and MBS words of a chunk: loads, bytes of LDS
-    static constexpr int kScaleLoads = kForm == 0 ? 1 : kForm == 1 ? FN : kForm == 2 ? 2 * FN : 4 * FN;
+    using Sched = SkinnySchedule<FM, FN, kForm>;
+    static constexpr int kScaleLoads = Sched::kScaleLoads;
     static constexpr int kScaleBytes = kForm == 0 ? 1024 : kScaleLoads * 256;
-    static constexpr int kWordLoads = kForm == 0 ? 1 : kForm == 1 ? (FN + 1) / 2 : FN;
+    static constexpr int kWordLoads = Sched::kWordLoads;
     static constexpr int kSigma = FM * 256;                   // sigma_A [macro block of the chunk][FM * 16]
     // A's way from the layout it is fetched (or quantized) in into the operand's: codes of a macro block [block][row][16 B]
     // (the blocks 320 bytes apart: bank conflicts) and its E8M0 bytes, [block][row] or (not fused) [macro block][row][4]
@@ -216,6 +216,7 @@ template <int NW, int FM, int FN, bool kFused, int kForm, bool kSingle>
 __device__ __forceinline__ void skinny_tile(const SkinnyArgs& args, uint8_t* smem, int64_t m0, int64_t m_end, int64_t n0,
                                             int64_t n_end, int64_t c_n0) {
     using S = SkinnyShape<NW, FM, FN, kFused, kForm>;
+    using Sched = typename S::Sched;
     const GemmArgs& g = args.g;
     const int K = (int)g.K, nmac = (K + kMacro - 1) / kMacro;
     const int row_bytes = K >> 1, scale_bytes = K >> 5;
@@ -250,7 +251,7 @@ __device__ __forceinline__ void skinny_tile(const SkinnyArgs& args, uint8_t* sme
     auto issue_codes = [&](int mac, auto j_) {
         constexpr int j = decltype(j_)::value;
         const int stride = opaque(row_bytes);
-        static_for<4>([&](auto i_) {
+        static_for<Sched::kCodeLoads>([&](auto i_) {
             constexpr int i = decltype(i_)::value;
             const int piece = piece0 ^ (4 * i);
             int voff = lane_row_off + (j * 16 + 4 * i) * stride + piece * 16;
@@ -347,26 +348,26 @@ __device__ __forceinline__ void skinny_tile(const SkinnyArgs& args, uint8_t* sme
         });
     };
     // fused: unit u = two macro blocks of fragment u / 2; load b of a macro block: lane l fetches piece l % 4 of block b of
-    // row l / 4
-    typedef v4i RawUnit[2][4];
+    // row l / 4.  (The wait for the weights counts these loads: both go by unit_macs.)
+    typedef v4i RawUnit[2][Sched::kRawLoads];
     const int x_off = (l >> 2) * (int)args.ldx * 2 + (l & 3) * 16;
     auto load_raw = [&](RawUnit& raw, int mac, auto u_) {
-        constexpr int f = decltype(u_)::value / 2, t0 = decltype(u_)::value % 2 * 2;
+        constexpr int f = decltype(u_)::value / 2, h = decltype(u_)::value % 2, t0 = h * 2;
         const int stride = opaque((int)args.ldx * 2);
         static_for<2>([&](auto t_) {
             constexpr int t = decltype(t_)::value;
             const int voff = x_off + f * 16 * stride;
-            if (kForm == 0 || mac + t0 + t < last) static_for<4>([&](auto b_) {
+            if (t < Sched::unit_macs(last - mac, h)) static_for<Sched::kRawLoads>([&](auto b_) {
                 constexpr int b = decltype(b_)::value;
                 raw[t][b] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(opx, voff, (mac + t0 + t) * 256 + b * 64, 0));
             });
         });
     };
     auto quantize_raw = [&](RawUnit& raw, v4i (&codes)[kSkinnyMacs], uint32_t& scales, int count, auto f_, auto h_) {
-        constexpr int f = decltype(f_)::value, t0 = decltype(h_)::value * 2;
+        constexpr int f = decltype(f_)::value, h = decltype(h_)::value, t0 = h * 2;
         static_for<2>([&](auto t_) {
             constexpr int t = decltype(t_)::value;
-            if (kForm != 0 && t0 + t >= count) return;
+            if (t >= Sched::unit_macs(count, h)) return;
             const MacroQuant m = quantize_macro(raw[t], args.carry, args.a_mbs, l);
             // through LDS into the operand's layout (the wavefront's LDS operations run in order: no wait between them)
             static_for<4>([&](auto b_) {
@@ -442,6 +443,18 @@ __device__ __forceinline__ void skinny_tile(const SkinnyArgs& args, uint8_t* sme
         asm volatile("" : "+v"(acc[f][j]));  // (keeps the compiler from moving the sums behind the next branch, products alive)
     };
 
+    // fused: the weights of a chunk of `count` macro blocks have landed
+    auto wait_weights = [&](int count) {
+        if constexpr (Sched::weights_wait(1) == Sched::weights_wait(kSkinnyMacs)) {
+            wait_loads_but<Sched::weights_wait(kSkinnyMacs)>();
+        } else {  // (uniform over the wavefront)
+            if (count >= 4) wait_loads_but<Sched::weights_wait(4)>();
+            else if (count == 3) wait_loads_but<Sched::weights_wait(3)>();
+            else if (count == 2) wait_loads_but<Sched::weights_wait(2)>();
+            else wait_loads_but<Sched::weights_wait(1)>();
+        }
+    };
+
     // Everything is requested before anything waits, the activations first: loads return in order, and bringing the
     // activations into the operand's layout (fused: quantizing them) is to run while the weights are on their way.
     if constexpr (kFused) {
@@ -469,11 +482,7 @@ __device__ __forceinline__ void skinny_tile(const SkinnyArgs& args, uint8_t* sme
                         else if (more) load_raw(raw[h], mac + kSkinnyMacs, h_);
                         __builtin_amdgcn_sched_barrier(0);
                     });
-                    if constexpr (f == 0) {
-                        // (what is younger than the weights are the loads of the next unit pair)
-                        if constexpr (FM > 1) wait_loads_but<16>();
-                        else wait_loads();
-                    }
+                    if constexpr (f == 0) wait_weights(count);
                     static_for<FN>([&](auto j_) {
                         Weights d;
                         read_weights(d, mac, j_);

@@ -9,6 +9,8 @@
 //      far apart as the barriers allow), or that holds a stage not yet consumed;
 //   3. everything that is read was loaded, exactly once, and no load asks for a stage past the end of K;
 //   4. every wait count fits the 6-bit counter.
+// The few-row kernel has no barrier (a wavefront reads only what it loaded itself): 1 without publication, 2, 3 and 4, for
+// every number of macro blocks that a wavefront's share of K can have.
 // Prints one line per case; exits 1 at the first violation.  Compiled and run by tests/test_gemm_schedule.py.
 #include <cstdio>
 #include <cstdlib>
@@ -18,6 +20,7 @@
 
 #include "mx_gemm_f8_schedule.h"
 #include "mx_gemm_schedule.h"
+#include "mx_gemm_skinny_schedule.h"
 
 namespace {
 
@@ -269,6 +272,126 @@ void check_f8_all(const char* name) {
         }
 }
 
+// ---- the few-row kernel (mx_gemm_skinny.h) ------------------------------------------------------------------
+// Loads of one wavefront whose share of K is `macs` macro blocks, in chunks of four.
+enum SkinnyKind { kSkinnyA = 0, kSkinnySmall = 1, kSkinnyCodes = 2 };
+
+struct SkinnyCase {  // (plain numbers: the replay is compiled once)
+    int fm, fn;
+    bool fused;
+    int small_loads, code_loads, raw_loads;
+    int (*unit_macs)(int, int);
+    int (*weights_wait)(int);
+};
+
+void check_skinny(const char* name, const SkinnyCase& k, int macs) {
+    constexpr int kMacs = mx::kSkinnyMacs;
+    const int FM = k.fused ? k.fm : 1, FN = k.fn;  // (quantized: all fragments of A at once)
+    struct Load {
+        int kind, chunk, fragment;  // activations, fused: fragment = 2 * fragment of A + half
+        int mac;                    // activations, fused: macro block of the chunk
+    };
+    std::vector<Load> issued;
+    size_t landed = 0;
+    std::map<std::pair<int, int>, int> in_slot, readers_left;  // (kind, fragment) -> chunk that LDS holds or will; reads to come
+    auto wait = [&](int n) {
+        if (n < 0 || n > 63) fail(name, macs, "wait count outside the 6-bit counter", n);
+        const size_t keep = (size_t)n < issued.size() ? issued.size() - (size_t)n : 0;
+        if (keep > landed) landed = keep;
+    };
+    auto to_lds = [&](int kind, int chunk, int fragment, int count) {
+        if (readers_left[{kind, fragment}] > 0) fail(name, macs, "weights requested into LDS that is still to be read", kind, chunk, fragment);
+        in_slot[{kind, fragment}] = chunk;
+        readers_left[{kind, fragment}] = kind == kSkinnySmall ? FM * FN : FM;
+        for (int i = 0; i < count; ++i) issued.push_back({kind, chunk, fragment, -1});
+    };
+    auto from_lds = [&](int kind, int chunk, int fragment) {
+        if (in_slot.count({kind, fragment}) == 0 || in_slot[{kind, fragment}] != chunk) fail(name, macs, "weights of another chunk are read", kind, chunk, fragment);
+        for (size_t n = landed; n < issued.size(); ++n)
+            if (issued[n].kind == kind && issued[n].chunk == chunk && issued[n].fragment == fragment)
+                fail(name, macs, "weights are read before a wait has retired their load", kind, chunk, fragment);
+        --readers_left[{kind, fragment}];
+    };
+    auto weights = [&](int chunk, int j) {
+        to_lds(kSkinnyCodes, chunk, j, k.code_loads);
+    };
+    auto small = [&](int chunk) { to_lds(kSkinnySmall, chunk, 0, k.small_loads); };
+    // fused: a unit of activations; only macro blocks of the share are fetched
+    auto raw = [&](int chunk, int f, int half) {
+        const int left = macs - chunk * kMacs;
+        for (int t = 0; t < k.unit_macs(left, half); ++t) {
+            if (2 * half + t >= left) fail(name, macs, "activations past the share of K are fetched", chunk, f, half);
+            for (int b = 0; b < k.raw_loads; ++b) issued.push_back({kSkinnyA, chunk, 2 * f + half, 2 * half + t});
+        }
+    };
+    // registers: whoever uses them waits for exactly the youngest of them (the compiler's wait), and all older ones have landed too
+    auto use = [&](int chunk, int fragment) {
+        for (size_t n = issued.size(); n > landed; --n)
+            if (issued[n - 1].kind == kSkinnyA && issued[n - 1].chunk == chunk && issued[n - 1].fragment == fragment) landed = n;
+    };
+    const int chunks = (macs + kMacs - 1) / kMacs;
+    if (k.fused) {
+        raw(0, 0, 0);
+        raw(0, 0, 1);
+    } else {
+        issued.push_back({kSkinnyA, 0, 0, 0});
+    }
+    small(0);
+    for (int j = 0; j < FN; ++j) weights(0, j);
+    for (int c = 0; c < chunks; ++c) {
+        const int count = macs - c * kMacs < kMacs ? macs - c * kMacs : kMacs;
+        const bool more = c + 1 < chunks;
+        for (int f = 0; f < FM; ++f) {
+            if (k.fused) {
+                for (int half = 0; half < 2; ++half) {
+                    use(c, 2 * f + half);
+                    for (int t = 0; t < k.unit_macs(count, half); ++t) {
+                        int found = 0;
+                        for (const Load& l : issued) found += l.kind == kSkinnyA && l.chunk == c && l.fragment == 2 * f + half && l.mac == 2 * half + t;
+                        if (found != k.raw_loads) fail(name, macs, "activations that are quantized were not fetched once", c, f, 2 * half + t);
+                    }
+                    if (f + 1 < FM) raw(c, f + 1, half);
+                    else if (more) raw(c + 1, 0, half);
+                }
+                if (f == 0) wait(k.weights_wait(count));
+            } else {
+                use(c, 0);
+                wait(0);
+            }
+            for (int j = 0; j < FN; ++j) {
+                from_lds(kSkinnyCodes, c, j);
+                from_lds(kSkinnySmall, c, 0);
+                if (f + 1 == FM && more) {
+                    weights(c + 1, j);
+                    if (j == FN - 1) small(c + 1);
+                }
+            }
+        }
+        if (!k.fused && more) issued.push_back({kSkinnyA, c + 1, 0, 0});
+    }
+    std::printf("ok %s macs=%d; weights' wait %d\n", name, macs, k.fused ? k.weights_wait(macs < kMacs ? macs : kMacs) : 0);
+}
+
+template <int FM, int FN, int kForm, bool kFused>
+void check_skinny_form(const char* name) {
+    using Sched = mx::SkinnySchedule<FM, FN, kForm>;
+    const SkinnyCase k = {FM, FN, kFused, Sched::kScaleLoads + Sched::kWordLoads, Sched::kCodeLoads, Sched::kRawLoads, Sched::unit_macs, Sched::weights_wait};
+    // eight wavefronts share K <= 8192: at most two chunks; form 0 whole chunks only
+    for (int macs = kForm == 0 ? 4 : 1; macs <= 8; macs += kForm == 0 ? 4 : 1) check_skinny(name, k, macs);
+}
+
+template <int FM, int FN>
+void check_skinny_all() {
+    char name[64];
+    auto named = [&](int form, const char* a) { std::snprintf(name, sizeof name, "SkinnySchedule<%d, %d, %d> %s", FM, FN, form, a); return name; };
+    check_skinny_form<FM, FN, 0, true>(named(0, "fused"));
+    check_skinny_form<FM, FN, 1, true>(named(1, "fused"));
+    check_skinny_form<FM, FN, 0, false>(named(0, "quantized"));
+    check_skinny_form<FM, FN, 1, false>(named(1, "quantized"));
+    check_skinny_form<FM, FN, 2, false>(named(2, "quantized"));
+    check_skinny_form<FM, FN, 3, false>(named(3, "quantized"));
+}
+
 }  // namespace
 
 #define SHAPE(...) check_all<mx::RingShape<__VA_ARGS__>>("RingShape<" #__VA_ARGS__ ">")
@@ -299,6 +422,16 @@ int main() {
     check_f8_all<mx::kF8Fast, true>("F8Schedule<fast, MBS>");
     check_f8_all<mx::kF8Six, false>("F8Schedule<six, no MBS>");
     check_f8_all<mx::kF8Six, true>("F8Schedule<six, MBS>");
+    // the few-row kernel: fragments of 16 rows of A and of B
+    check_skinny_all<1, 1>();
+    check_skinny_all<1, 2>();
+    check_skinny_all<1, 4>();
+    check_skinny_all<2, 1>();
+    check_skinny_all<2, 2>();
+    check_skinny_all<2, 4>();
+    check_skinny_all<4, 1>();
+    check_skinny_all<4, 2>();
+    check_skinny_all<4, 4>();
     std::printf("all schedules hold\n");
     return 0;
 }

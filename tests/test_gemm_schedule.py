@@ -1,8 +1,8 @@
 """The load / wait schedules of the GEMM kernels, replayed on the host (no GPU).
 
 tests/schedule_check.cpp includes the kernels' own schedule headers (plain constexpr C++: mx_gemm_schedule.h for the
-main kernel template, mx_gemm_f8_schedule.h for the kernel on 8-bit and 6-bit operands) and replays prologue and
-stages for every instantiated tile shape and form; this file compiles and runs it, checks that its list of shapes is
+main kernel template, mx_gemm_f8_schedule.h for the kernel on 8-bit and 6-bit operands, mx_gemm_skinny_schedule.h for the
+few-row kernel) and replays prologue and stages for every instantiated tile shape and form; this file compiles and runs it, checks that its list of shapes is
 the list the sources instantiate, and plants mistakes in copies of the headers to see that the replay catches them."""
 import os
 import re
@@ -16,7 +16,7 @@ CSRC = os.path.join(ROOT, "paper_2603_08713_amd", "csrc")
 CHECK = os.path.join(ROOT, "tests", "schedule_check.cpp")
 
 
-HEADERS = ("mx_constants.h", "mx_gemm_schedule.h", "mx_gemm_f8_schedule.h")
+HEADERS = ("mx_constants.h", "mx_gemm_schedule.h", "mx_gemm_f8_schedule.h", "mx_gemm_skinny_schedule.h")
 
 
 def build_and_run(tmp_path, include_dir, name="check"):
@@ -39,6 +39,11 @@ def test_every_instantiated_shape_holds(tmp_path):
     # the kernel for 8-bit and 6-bit operands: its three forms, with and without MBS words
     forms = set(re.findall(r"ok (F8Schedule<[a-zA-Z, ]*>)", out.stdout))
     assert forms == {"F8Schedule<%s, %s>" % (f, m) for f in ("general", "fast", "six") for m in ("MBS", "no MBS")}, forms
+    # the few-row kernel's fused form: shares of one to eight macro blocks in every tile
+    for fm in (1, 2, 4):
+        for fn in (1, 2, 4):
+            macs = re.findall(r"ok SkinnySchedule<%d, %d, 1> fused macs=(\d)" % (fm, fn), out.stdout)
+            assert macs == list("12345678"), (fm, fn, macs)
 
 
 MUTATIONS = [
@@ -92,6 +97,22 @@ F8_MUTATIONS = [
 ]
 
 
+SKINNY_MUTATIONS = [
+    # the wait for the weights counts the activations of four macro blocks whatever the chunk has (a mistake this kernel once had)
+    ("return FM == 1 ? 0 : kRawLoads * (unit_macs(left, 0) + unit_macs(left, 1));", "return FM == 1 ? 0 : 16;", "read before a wait"),
+    # ... of three at least
+    ("return FM == 1 ? 0 : kRawLoads * (unit_macs(left, 0) + unit_macs(left, 1));",
+     "return FM == 1 ? 0 : kRawLoads * (2 + (unit_macs(left, 1) ? unit_macs(left, 1) : 1));", "read before a wait"),
+    # one load too many may fly
+    ("return FM == 1 ? 0 : kRawLoads * (unit_macs(left, 0) + unit_macs(left, 1));",
+     "return FM == 1 ? 0 : 1 + kRawLoads * (unit_macs(left, 0) + unit_macs(left, 1));", "read before a wait"),
+    # one fragment of A: nothing is younger than the weights, unless there is another chunk
+    ("return FM == 1 ? 0 : kRawLoads", "return kRawLoads", "read before a wait"),
+    # a unit fetches what lies past the share
+    ("return kForm == 0 || n > 2 ? 2 : n < 0 ? 0 : n;", "return n > 0 ? 2 : 0;", "past the share"),
+]
+
+
 def run_mutant(tmp_path, header, old, new, expect):
     """Replay with `old` replaced by `new` in a copy of `header` (the other headers copied as they are).  A mutant that
     a static_assert of the headers rejects counts as caught; any other compile error is a mistake of the test."""
@@ -125,6 +146,11 @@ def test_replay_catches_planted_mistakes_in_the_8_bit_kernel(tmp_path, old, new,
 @pytest.mark.parametrize("old,new,expect", MUTATIONS)
 def test_replay_catches_planted_mistakes(tmp_path, old, new, expect):
     run_mutant(tmp_path, "mx_gemm_schedule.h", old, new, expect)
+
+
+@pytest.mark.parametrize("old,new,expect", SKINNY_MUTATIONS)
+def test_replay_catches_planted_mistakes_in_the_few_row_kernel(tmp_path, old, new, expect):
+    run_mutant(tmp_path, "mx_gemm_skinny_schedule.h", old, new, expect)
 
 
 def test_unmutated_copy_of_the_headers_holds(tmp_path):

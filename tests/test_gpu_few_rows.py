@@ -82,3 +82,21 @@ def test_grouped_few_rows(mx, oracle, K, shift):
             if not mbs:
                 ra[2] = rb[2] = None
             close(out[lo:hi], oracle.gemm(tuple(ra), tuple(rb)), (K, shift, mbs, e))
+
+
+# N: the kernel's one, two and four fragments of B; K: shares of one, two, three and four macro blocks per wavefront (the last
+# wavefronts of some have fewer, or none), then a whole chunk and one, two and four of another
+@pytest.mark.parametrize("M,N", [(17, 250), (33, 4113), (64, 8209), (32, 100), (16, 4100)])
+@pytest.mark.parametrize("K", [512, 1024, 1536, 2560, 3072, 4096, 4608, 5120, 6656, 8192])
+def test_fused_waits_for_weights_from_memory(mx, M, N, K):
+    """mx_gemm_mbs_quantize_a bit for bit the quantizer and the GEMM, on weights that no cache holds any more: what a wait lets
+    fly then has not arrived when it is read."""
+    rng = np.random.default_rng(M + K)
+    x = torch.from_numpy(rng.standard_normal((M, K)).astype(np.float32)).cuda().to(torch.bfloat16)
+    w = [dev(t) for t in random_operand(rng, N, K)]
+    want = mx.mx_gemm_mbs(*mx.mx_quantize_mbs(x, "oas"), *w, "f32")
+    evict = torch.empty(1 << 29, dtype=torch.uint8, device="cuda")
+    for i in range(3):
+        evict.fill_(i)
+        got = mx.mx_gemm_mbs_quantize_a(x, "oas", *w, "f32")
+        assert torch.equal(got, want), (M, N, K, i)
