@@ -518,7 +518,7 @@ def moe_extras(mx, torch, synth, np, metrics, args):
         "mxfp8_mxfp6_grouped": elem_grouped,
         "workload": "32 experts of 2880x2880 N(0,0.02^2), 8192 tokens x 2880 (Student-t(4), 1%% channels x20) routed top-4, "
                     "P(e) ~ (e+1)^-1.1; %d rows in expert order" % rows,
-        "kernel": mx.gemm_plan(rows, dim, dim, True, True, True),
+        "kernel": mx.gemm_plan(rows, dim, dim, True, True, True, len(loads)),
         "grouped_gemm_mbs_tflops": round(tg, 1), "grouped_gemm_mbs_frac_of_peak": round(tg / metrics.MFMA_FP4_PEAK_TFLOPS, 4),
         "grouped_gemm_plain_tflops": round(tp, 1), "mbs_overhead": round(metrics.overhead_fraction(tp, tg), 4),
         "step_tflops": round(flops / (ms_s * 1e-3) / 1e12, 1), "ms_per_step": round(ms_s, 4),

@@ -132,11 +132,12 @@ def _forced(name):
     return choices.get(name) if choices else None
 
 
-def gemm_plan(M: int, N: int, K: int, a_has_mbs: bool = True, b_has_mbs: bool = True, grouped: bool = False) -> str:
-    """The kernel the dispatcher of mx_gemm / mx_gemm_mbs / mx_gemm_mbs_grouped picks for a problem with aligned
-    arrays (host only; reported by the benchmark beside its timings)."""
+def gemm_plan(M: int, N: int, K: int, a_has_mbs: bool = True, b_has_mbs: bool = True, grouped: bool = False,
+              num_groups: int = 1) -> str:
+    """The kernel the dispatcher of mx_gemm / mx_gemm_mbs / mx_gemm_mbs_grouped (of num_groups groups) picks for a problem
+    with aligned arrays (host only; reported by the benchmark beside its timings)."""
     buf = ctypes.create_string_buffer(512)
-    _check((_lib or load_library()).mx_internal_gemm_plan(M, N, K, int(a_has_mbs), int(b_has_mbs), int(grouped), buf, 512),
+    _check((_lib or load_library()).mx_internal_gemm_plan(M, N, K, int(a_has_mbs), int(b_has_mbs), int(num_groups) if grouped else 0, buf, 512),
            "mx_internal_gemm_plan")
     return buf.value.decode()
 

@@ -55,6 +55,11 @@ SkinnyPlan plan_skinny(int64_t M, int64_t N, int64_t K, bool ring_ok, bool pairs
 // 15 against 13, 13, 13; 64 of 1024 x 1024 15, 23, 35 against 17, 25, 25.
 constexpr int64_t kFewRowsPerGroup = 32;
 
+// Whether the few-row kernel takes a problem (num_groups: 0 = not grouped).
+bool takes_few_rows(int64_t M, int64_t K, int64_t num_groups) {
+    return K > 0 && (num_groups > 0 ? M <= kFewRowsPerGroup * num_groups : M <= 64 && K <= 8192);
+}
+
 int launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* a_mbs, const uint8_t* b_codes,
                 const uint8_t* b_scales, const uint8_t* b_mbs, int num_groups, const int64_t* row_offsets,
                 bool grouped, int64_t M, int64_t N, int64_t K, int c_dtype, void* C, int64_t ldc, bool mbs_entry,
@@ -92,7 +97,7 @@ int launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* 
                          (!use_mbs || ((!a_mbs || aligned(a_mbs, 4)) && (!b_mbs || aligned(b_mbs, 4))));
     // General form with row pieces through registers: rows of E8M0 bytes on even addresses; else single bytes.
     const bool pairs_ok = K > 0 && (K % 64) == 0 && aligned(a_scales, 2) && aligned(b_scales, 2);
-    const bool skinny_ok = K > 0 && (grouped ? M <= kFewRowsPerGroup * num_groups : M <= 64 && K <= 8192);
+    const bool skinny_ok = takes_few_rows(M, K, g.num_groups);
     const bool tile64_ok = !grouped && a_mbs && b_mbs && mbs_entry;
     int shape = choose_shape(M, N, use_mbs, ring_ok, pairs_ok, skinny_ok, tile64_ok);
     if (force_shape >= 0) shape = force_shape;
@@ -177,11 +182,11 @@ int mx_gemm_mbs_grouped(const uint8_t* a_codes, const uint8_t* a_scales, const u
                            row_offsets, true, M_total, N, K, (int)c_dtype, C, ldc, true, stream);
 }
 
-int mx_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int a_has_mbs, int b_has_mbs, int grouped, char* out, int cap) {
-    if (!out || cap <= 0 || M < 0 || N < 0 || K < 0 || (K % mx::kBlock) != 0) return MX_EINVAL;
-    const bool use_mbs = a_has_mbs || b_has_mbs;
+int mx_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int a_has_mbs, int b_has_mbs, int num_groups, char* out, int cap) {
+    if (!out || cap <= 0 || M < 0 || N < 0 || K < 0 || (K % mx::kBlock) != 0 || num_groups < 0) return MX_EINVAL;
+    const bool use_mbs = a_has_mbs || b_has_mbs, grouped = num_groups > 0;
     const bool ring_ok = !grouped && K > 0 && (K % 512) == 0, pairs_ok = K > 0 && (K % 64) == 0;
-    const int shape = mx::choose_shape(M, N, use_mbs, ring_ok, pairs_ok, K > 0 && !grouped && M <= 64 && K <= 8192,
+    const int shape = mx::choose_shape(M, N, use_mbs, ring_ok, pairs_ok, mx::takes_few_rows(M, K, num_groups),
                                        !grouped && a_has_mbs && b_has_mbs);
     const char* sides = a_has_mbs && b_has_mbs ? "MBS words on A and B" : a_has_mbs ? "MBS words on A" : b_has_mbs ? "MBS words on B" : "no MBS";
     const char* what;
@@ -190,7 +195,7 @@ int mx_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int a_has_mbs, int b_
         case 3: what = a_has_mbs && b_has_mbs ? "gemm_ring_kernel, fast form, 256x128 tile, 8 wavefronts of 64x64"
                                               : "gemm_ring_kernel, fast form, 256x128 tile, 8 wavefronts of 128x32"; break;
         case 4: what = "gemm_ring_kernel, fast form, 128x128 tile, 8 wavefronts of 64x32"; break;
-        case 5: what = "gemm_skinny_kernel (few rows)"; break;
+        case 5: what = grouped ? "gemm_skinny_grouped_kernel (few rows per group)" : "gemm_skinny_kernel (few rows)"; break;
         case 11: what = "gemm_ring_kernel, fast form, 64x128 tile, 4 wavefronts of 64x32"; break;
         case 12: what = "gemm_ring_kernel, general form (row pieces through registers), 64x128 tile, 4 wavefronts of 64x32"; break;
         case 8: what = use_mbs ? "gemm_ring_kernel, general form (row pieces through registers), 256x128 tile, 8 wavefronts" : "gemm_ring_kernel, general form (row pieces through registers), 256x128 tile, 4 wavefronts"; break;

@@ -31,8 +31,9 @@ int mx_internal_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint
                      void* C, int64_t ldc, int mbs_entry, int force_shape, void* stream);
 
 // Which kernel the dispatcher of mx_gemm / mx_gemm_mbs / mx_gemm_mbs_grouped picks for a problem whose arrays meet the
-// fast form's alignment (host only, nothing is launched): a NUL-terminated description into out[cap].
-int mx_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int a_has_mbs, int b_has_mbs, int grouped, char* out, int cap);
+// fast form's alignment (host only, nothing is launched): a NUL-terminated description into out[cap].  num_groups: 0 = not
+// grouped.
+int mx_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int a_has_mbs, int b_has_mbs, int num_groups, char* out, int cap);
 
 // mx_gemm_mbs_elem with the kernel chosen by the caller.  force: 0 = as mx_gemm_mbs_elem, 1 = the main kernel's
 // general form also where the fast form applies, 2 = the main kernel also where the few-row kernel applies, 3 = the

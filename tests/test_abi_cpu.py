@@ -99,6 +99,13 @@ def test_gemm_plan_names_the_kernel_a_problem_takes(lib):
     assert "single scale bytes" in plan(512, 512, 2016)             # K % 64 == 32
     assert lib.mx_internal_gemm_plan(8, 8, 48, 1, 1, 0, ctypes.create_string_buffer(8), 8) == -1   # K % 32
     assert lib.mx_internal_gemm_plan(8, 8, 64, 1, 1, 0, None, 0) == -1
+    # grouped: the choice goes by the rows per group
+    assert "few rows per group" in plan(32 * 32, 2880, 2880, grouped=32)
+    assert "general form" in plan(32 * 32 + 1, 2880, 2880, grouped=32)
+    import paper_2603_08713_amd as mx
+
+    assert "few rows per group" in mx.gemm_plan(256, 2880, 2880, grouped=True, num_groups=32)
+    assert "few rows" in mx.gemm_plan(16, 4096, 4096) and "few rows" not in mx.gemm_plan(65, 4096, 4096)
 
 
 def test_version_and_status_strings(lib):
