@@ -7,6 +7,8 @@
 
 #include <stdio.h>
 
+#include <algorithm>
+
 namespace mx {
 namespace {
 
@@ -55,9 +57,34 @@ SkinnyPlan plan_skinny(int64_t M, int64_t N, int64_t K, bool ring_ok, bool pairs
 // 15 against 13, 13, 13; 64 of 1024 x 1024 15, 23, 35 against 17, 25, 25.
 constexpr int64_t kFewRowsPerGroup = 32;
 
+// Whether the few-row kernel takes a problem that is not grouped and has at most 64 rows.  With K % 512 == 0 and aligned
+// arrays (forms 0 and 1): always.  In the forms 2 and 3 a workgroup has LDS for 32 and 16 columns only, so many columns
+// are many rounds, and each costs a round trip to memory, while the main kernel's 64 x 128 (without words on both sides
+// 128 x 128) tiles cover 32768 columns in one round.  More than one round is therefore priced against the main kernel, in
+// us, by what both take on the device with weights from memory.  Few-row and main kernel at M = 1, 32, 64, words on both sides:
+//   K = 2880   N =  8192  5.8, 7.2, 9.6      and 15.9, 17.1, 17.9;   N = 28672  18.1, 23.8, 32.2   and 17.9, 19.1, 20.0
+//   K = 1088   N =  8192  4.4, 5.3, 6.7      and 7.2, 7.4, 7.7;      N = 28672  12.8, 15.8, 20.8   and 9.1, 9.4, 9.8
+//   K = 4128   N =  4096  6.3, 9.4, 13.1     and 25.7, 25.8, 25.9;   N = 28672  27.3, 45.8, 78.2   and 33.6, 34.6, 35.8
+// Over K of 64 to 8160, N of 1024 to 57344 and 1 to 64 rows the few-row kernel is chosen where it is at most 4 % slower, the
+// main kernel where it is at most a third slower: the prices lean to the kernel that had all of these problems before.
+bool few_rows_pay(int64_t M, int64_t N, int64_t K, const SkinnyPlan& p, bool use_mbs) {
+    if (p.form <= 1) return true;
+    const bool bytes = p.form == 3;
+    const int64_t rounds = ((N + 15) / 16 + p.fn * 256 - 1) / (p.fn * 256), tile_rounds = ((N + 127) / 128 + 255) / 256;
+    if (rounds == 1) return true;
+    const int at = p.fm == 1 ? 0 : p.fm == 2 ? 1 : 2;
+    static const double kRound[2][3] = {{1.6, 2.2, 2.8}, {0.8, 1.1, 1.4}}, kRoundPerK[2][3] = {{0.92e-3, 1.14e-3, 1.6e-3}, {0.6e-3, 1.15e-3, 2.0e-3}};
+    const double few = 1.7 + rounds * (kRound[bytes][at] + kRoundPerK[bytes][at] * K);
+    const double tile = bytes ? (use_mbs ? 4.5 + 6.2e-3 * K : 3.5 + 5.2e-3 * K)
+                              : (use_mbs ? std::max(4.3, 1.5 + 5.5e-3 * K) : std::max(4.0, 1.4 + 4.7e-3 * K));
+    // (a further round of the tiles starts while the one before ends, where two workgroups fit a compute unit)
+    return few <= tile * (bytes ? tile_rounds : 0.5 + 0.5 * tile_rounds);
+}
 // Whether the few-row kernel takes a problem (num_groups: 0 = not grouped).
-bool takes_few_rows(int64_t M, int64_t K, int64_t num_groups) {
-    return K > 0 && (num_groups > 0 ? M <= kFewRowsPerGroup * num_groups : M <= 64 && K <= 8192);
+bool takes_few_rows(int64_t M, int64_t N, int64_t K, int64_t num_groups, bool ring_ok, bool pairs_ok, bool use_mbs) {
+    if (K == 0) return false;
+    if (num_groups > 0) return M <= kFewRowsPerGroup * num_groups;
+    return M <= 64 && K <= 8192 && few_rows_pay(M, N, K, plan_skinny(M, N, K, ring_ok, pairs_ok), use_mbs);
 }
 
 int launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* a_mbs, const uint8_t* b_codes,
@@ -97,13 +124,13 @@ int launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* 
                          (!use_mbs || ((!a_mbs || aligned(a_mbs, 4)) && (!b_mbs || aligned(b_mbs, 4))));
     // General form with row pieces through registers: rows of E8M0 bytes on even addresses; else single bytes.
     const bool pairs_ok = K > 0 && (K % 64) == 0 && aligned(a_scales, 2) && aligned(b_scales, 2);
-    const bool skinny_ok = takes_few_rows(M, K, g.num_groups);
+    const bool skinny_ok = takes_few_rows(M, N, K, g.num_groups, ring_ok, pairs_ok, use_mbs);
     const bool tile64_ok = !grouped && a_mbs && b_mbs && mbs_entry;
     int shape = choose_shape(M, N, use_mbs, ring_ok, pairs_ok, skinny_ok, tile64_ok);
     if (force_shape >= 0) shape = force_shape;
     // (the checks below only matter for forced shapes)
     if (shape == 5) {
-        if (!skinny_ok) return MX_EINVAL;
+        if (K == 0 || (!grouped && (M > 64 || K > 8192))) return MX_EINVAL;
         if (grouped) return launch_gemm_skinny_grouped(g, use_mbs, !pairs_ok, s);
         const SkinnyPlan p = plan_skinny(M, N, K, ring_ok, pairs_ok);
         return launch_gemm_skinny_tile(g, use_mbs, p.fm, p.fn, p.form, s);
@@ -186,7 +213,7 @@ int mx_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int a_has_mbs, int b_
     if (!out || cap <= 0 || M < 0 || N < 0 || K < 0 || (K % mx::kBlock) != 0 || num_groups < 0) return MX_EINVAL;
     const bool use_mbs = a_has_mbs || b_has_mbs, grouped = num_groups > 0;
     const bool ring_ok = !grouped && K > 0 && (K % 512) == 0, pairs_ok = K > 0 && (K % 64) == 0;
-    const int shape = mx::choose_shape(M, N, use_mbs, ring_ok, pairs_ok, mx::takes_few_rows(M, K, num_groups),
+    const int shape = mx::choose_shape(M, N, use_mbs, ring_ok, pairs_ok, mx::takes_few_rows(M, N, K, num_groups, ring_ok, pairs_ok, use_mbs),
                                        !grouped && a_has_mbs && b_has_mbs);
     const char* sides = a_has_mbs && b_has_mbs ? "MBS words on A and B" : a_has_mbs ? "MBS words on A" : b_has_mbs ? "MBS words on B" : "no MBS";
     const char* what;

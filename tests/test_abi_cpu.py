@@ -105,6 +105,10 @@ def test_gemm_plan_names_the_kernel_a_problem_takes(lib):
     import paper_2603_08713_amd as mx
 
     assert "few rows per group" in mx.gemm_plan(256, 2880, 2880, grouped=True, num_groups=32)
+    # few rows, K % 512 != 0: the few-row kernel as far as its rounds of narrow workgroups are cheaper than the main kernel's tiles
+    for M, N, K, few in ((64, 8192, 1088, 1), (64, 28672, 1088, 0), (1, 14336, 2880, 1), (64, 14336, 2880, 1), (32, 28672, 2880, 0),
+                         (64, 4096, 4128, 1), (64, 28672, 4128, 0), (16, 28672, 4128, 1), (64, 28672, 4096, 1), (1, 1 << 30, 32, 0)):
+        assert ("few rows" in plan(M, N, K)) == bool(few), (M, N, K)
     assert "few rows" in mx.gemm_plan(16, 4096, 4096) and "few rows" not in mx.gemm_plan(65, 4096, 4096)
 
 
