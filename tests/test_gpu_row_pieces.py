@@ -60,6 +60,29 @@ def test_mxfp4(mx, oracle, shape, K, shift):
             close(got[~nan], want[~nan], (K, am, bm))
 
 
+@pytest.mark.parametrize("K", [64, 128, 192, 256, 320, 384, 448])
+def test_mxfp4_short_rows(mx, oracle, K):
+    """Rows of fewer than 16 E8M0 bytes, one of every length, that start on every second even address; a NaN block in the first
+    and in the last place of a row."""
+    rng = np.random.default_rng(K)
+    M, N = 133, 129
+    a, b = operand(rng, M, K), operand(rng, N, K)
+    a[1][3, -1] = a[1][132, 0] = b[1][1, 0] = b[1][128, -1] = 255
+    nan = np.zeros((M, N), bool)
+    nan[[3, 132]] = True
+    nan[:, [1, 128]] = True
+    da, db = [dev(a[0])] + [dev(t, 2) for t in a[1:]], [dev(b[0])] + [dev(t, 2) for t in b[1:]]
+    for shape in (8, 9, 12):
+        for mbs in (True, False):
+            if shape == 12 and not mbs:
+                continue
+            with mx.forced(gemm_shape=shape):
+                got = mx.mx_gemm_mbs(da[0], da[1], da[2] if mbs else None, db[0], db[1], db[2] if mbs else None, "f32").cpu().numpy()
+            want = oracle.gemm((a[0], a[1], a[2] if mbs else None), (b[0], b[1], b[2] if mbs else None))
+            assert np.array_equal(np.isnan(got), nan), (shape, mbs)
+            close(got[~nan], want[~nan], (K, shape, mbs))
+
+
 @pytest.mark.parametrize("M,N,K", [(65, 130, 512), (64, 128, 1024), (193, 300, 1536), (129, 4097, 2560)])
 def test_mxfp4_64_row_tiles(mx, oracle, M, N, K):
     """The 64 x 128 tile of the fast form, which few tiles take: against the oracle, bit for bit the 128 x 128 tile's result,
