@@ -52,9 +52,11 @@ SkinnyPlan plan_skinny(int64_t M, int64_t N, int64_t K, bool ring_ok, bool pairs
     return p;
 }
 // Grouped problems take the few-row kernel up to this many rows per group on average: it streams the weights once per
-// 32 rows, the main kernel once per 128 or 256 but at a quarter of the rate.  Measured (Zipf routing, rows per group 8,
-// 32, 64; few-row against main kernel): 32 groups of 2880 x 2880 35, 54, 79 against 59, 72, 91 us; 8 of 2048 x 2048 7, 9,
-// 15 against 13, 13, 13; 64 of 1024 x 1024 15, 23, 35 against 17, 25, 25.
+// 32 rows, the main kernel once per 128 or 256 but at a quarter of the rate.  Measured (Zipf routing, rows per group 8 and
+// 32; few-row against main kernel): 32 groups of 2880 x 2880 38, 54 against 64, 82 us; 8 of 2048 x 2048 7.8, 8.8
+// against 13, 13; 64 of 1024 x 1024 16, 24 against 19, 26; at 64 rows per group 79, 15, 35 against 91, 13, 25.  All rows
+// in one group, 8, 16 and 32 per group on average: 32 of 2880 x 2880 13, 22, 35 against 16, 17, 19; 64 of 1024 x 1024 7, 11, 17
+// against 9, 9, 9.  The launch cannot know the routing: it goes by what routers produce and loses up to half there.
 constexpr int64_t kFewRowsPerGroup = 32;
 
 // Whether the few-row kernel takes a problem that is not grouped and has at most 64 rows.  With K % 512 == 0 and aligned

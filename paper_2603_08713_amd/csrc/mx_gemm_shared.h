@@ -61,7 +61,15 @@ int launch_gemm_skinny_tile(const GemmArgs& g, bool use_mbs, int fm, int fn, int
 // of x to span less than 2 GiB.
 int launch_gemm_skinny_fused_tile(const GemmArgs& g, const void* x_bf16, int64_t ldx, int rule, bool a_mbs, int fm, int fn,
                                   int form, hipStream_t s);
-// Grouped problems with few rows per group (mx_gemm_skinny_grouped.hip).
+// Grouped problems with few rows per group (mx_gemm_skinny_grouped.hip): the rows and columns of a workgroup's tile, and an upper
+// bound of the workgroups: at most one partial tile-row per group that has rows.
+constexpr int few_rows_tile(bool bytes) { return bytes ? 16 : 32; }
+inline int64_t few_rows_blocks(int64_t M, int64_t N, int64_t num_groups, bool bytes) {
+    const int64_t t = few_rows_tile(bytes), busy = num_groups < M ? num_groups : M;
+    return (M + busy * (t - 1)) / t * ((N + t - 1) / t);
+}
+// (a launch has less than 2^32 work-items, a workgroup up to 256)
+constexpr int64_t kFewRowsMaxBlocks = ((int64_t)1 << 24) - 1;
 int launch_gemm_skinny_grouped(const GemmArgs& g, bool use_mbs, bool bytes, hipStream_t s);
 // The few-row kernel for operands in the 8-bit or 6-bit element formats (a_elem, b_elem: mx_elem_t), under the same
 // conditions, defined in mx_gemm_skinny_f8.hip; an operand without MBS words has a null a_mbs / b_mbs.

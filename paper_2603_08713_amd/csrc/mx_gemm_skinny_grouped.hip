@@ -4,45 +4,39 @@
 namespace mx {
 namespace {
 
-// A workgroup owns 16 FN columns of one group's C and walks over the group's rows, at most 16 kMaxFM at a time; g.tiles_m
-// workgroups share the rows of a group and a column tile.  (No workgroup looks its tile-row up in a prefix sum over the
-// groups, as the main kernel does: that is a round trip to memory and a scan in front of a tile that takes a few us.)
+// A workgroup owns up to 16 kMaxFM rows of one group and 16 FN columns of its C; every wavefront finds the group of its
+// tile-row as the main kernel does (grouped_find).  The launch takes an upper bound of the tile-rows, the surplus exits.
+// The lookup is a scan in front of a tile that takes a few us, but it spreads a group's rows over as many workgroups as
+// they need.  A fixed number of workgroups for every group (four for an average of 32 rows) was up to 0.4 us faster where none has
+// more than its workgroups take, and far slower where one group has all rows: 64 groups of 1024 x 1024, 1024 rows 46.3 us instead
+// of 10.7, 32 of 2880 x 2880, 1024 rows 56.6 instead of 34.6 (Zipf routing: 18.9 and 19.1, 58.0 and 54.4).  Workgroups without a lookup for each group's first rows and the rest behind them: up to 18 %
+// slower than this, because the largest group's rows start last.
 template <int NW, int kMaxFM, int FN, int kForm, bool kSingle>
 __global__ __launch_bounds__(NW * kWave) void gemm_skinny_grouped_kernel(SkinnyArgs args) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const GemmArgs& g = args.g;
     // column tiles innermost: a group's tiles spread over all XCDs, whatever its share of the rows
-    const int tn = (int)(blockIdx.x % (unsigned)g.tiles_n), rest = (int)(blockIdx.x / (unsigned)g.tiles_n);
-    const int part = rest % g.tiles_m, e = rest / g.tiles_m;
-    const int64_t lo = g.row_offsets[e], hi = g.row_offsets[e + 1];
-    const int64_t b0 = (int64_t)e * g.N + (int64_t)tn * (16 * FN), b_end = (int64_t)(e + 1) * g.N;
-    for (int64_t m0 = lo + part * (16 * kMaxFM); m0 < hi;) {
-        const int64_t m_end = min(hi, m0 + 16 * kMaxFM);
-        if (kMaxFM == 1 || m_end - m0 <= 16) {
-            skinny_tile<NW, 1, FN, false, kForm, kSingle>(args, smem, m0, m_end, b0, b_end, (int64_t)tn * (16 * FN));
-        } else if constexpr (kMaxFM == 2) {
-            skinny_tile<NW, 2, FN, false, kForm, kSingle>(args, smem, m0, m_end, b0, b_end, (int64_t)tn * (16 * FN));
-        } else if constexpr (kMaxFM == 4) {
-            skinny_tile<NW, 4, FN, false, kForm, kSingle>(args, smem, m0, m_end, b0, b_end, (int64_t)tn * (16 * FN));
-        }
-        m0 += g.tiles_m * (16 * kMaxFM);
-        if (m0 < hi) __syncthreads();  // the partial results have been read before the next weights land on them
+    const int tn = (int)(blockIdx.x % (unsigned)g.tiles_n), tm = (int)(blockIdx.x / (unsigned)g.tiles_n);
+    const int lane = (int)(threadIdx.x & 63);
+    GroupOfTileRow gr;
+    const GroupLane first = group_lane(g.row_offsets, g.num_groups, 16 * kMaxFM, lane, 0);
+    if (!grouped_find(g.row_offsets, g.num_groups, 16 * kMaxFM, lane, tm, first, gr)) return;
+    const int64_t m0 = gr.lo + (int64_t)(tm - gr.first) * (16 * kMaxFM), m_end = min(gr.hi, m0 + 16 * kMaxFM);
+    const int64_t c_n0 = (int64_t)tn * (16 * FN), b0 = (int64_t)gr.group * g.N + c_n0, b_end = (int64_t)(gr.group + 1) * g.N;
+    if (kMaxFM == 1 || m_end - m0 <= 16) {
+        skinny_tile<NW, 1, FN, false, kForm, kSingle>(args, smem, m0, m_end, b0, b_end, c_n0);
+    } else if constexpr (kMaxFM == 2) {
+        skinny_tile<NW, 2, FN, false, kForm, kSingle>(args, smem, m0, m_end, b0, b_end, c_n0);
     }
 }
-
-// Workgroups that share a group's rows: enough for groups with a few times the average (measured, average 32 rows, 1, 2, 4
-// parts: 8 groups of 2048 x 2048 14.0, 11.2, 9.0 us, 64 of 1024 x 1024 39.9, 23.5, 24.9), but workgroups without rows
-// cost their launch (average 1 row, 32 groups of 2880 x 2880: 21.3, 21.4, 22.6).
-int64_t parts_of(int64_t rows, int64_t groups) { return rows > 16 * groups ? 4 : rows > 8 * groups ? 2 : 1; }
 
 template <int NW, int kMaxFM, int FN, int kForm>
 int launch(SkinnyArgs a, hipStream_t s) {
     GemmArgs& g = a.g;
-    const int64_t tiles_n = (g.N + 16 * FN - 1) / (16 * FN), parts = parts_of(g.M, g.num_groups);
-    const int64_t blocks = tiles_n * g.num_groups * parts;
-    if (blocks > (int64_t)1 << 30) return MX_EINVAL;
-    g.tiles_m = (int)parts;
-    g.tiles_n = (int)tiles_n;
+    static_assert(NW <= 4 && kMaxFM * 16 == few_rows_tile(kForm == 3) && FN * 16 == few_rows_tile(kForm == 3), "as few_rows_blocks counts");
+    const int64_t blocks = few_rows_blocks(g.M, g.N, g.num_groups, kForm == 3);
+    if (blocks > kFewRowsMaxBlocks) return MX_EINVAL;
+    g.tiles_n = (int)((g.N + 16 * FN - 1) / (16 * FN));
     using S = SkinnyShape<NW, kMaxFM, FN, false, kForm>;
     auto launch = [&](auto single_) {
         auto* fn = gemm_skinny_grouped_kernel<NW, kMaxFM, FN, kForm, decltype(single_)::value>;
@@ -58,9 +52,9 @@ int launch(SkinnyArgs a, hipStream_t s) {
 }  // namespace
 
 // K > 0; scale arrays 2-byte aligned and K % 64 == 0, or `bytes`.  Few wavefronts per workgroup, so that several workgroups
-// are resident per compute unit and one streams while another starts or adds up (8 wavefronts: 52 us at the case below);
-// 32 columns and up to 32 rows each.  Measured, 32 groups of 2880 x 2880 with 256 rows (Zipf): 35 us = 4.0 TB/s of weight
-// bytes with 3 wavefronts, 36 with 4; 64 groups of 1024 x 1024 with 512 rows 15.5 with 3, 15.9 with 4, and 8 of 2048 x 2048
+// are resident per compute unit and one streams while another starts or adds up; 32 columns and up to 32 rows each.  32 groups
+// of 2880 x 2880 with 256 rows (Zipf) take 38 us, 3.7 TB/s of weight bytes.  Measured with a fixed number of workgroups per group:
+// the same 35 us with 3 wavefronts, 36 with 4, 52 with 8; 64 groups of 1024 x 1024 with 512 rows 15.5 with 3, 15.9 with 4, and 8 of 2048 x 2048
 // with 64 rows 9.1 and 7.2: the fewer K elements, the more wavefronts to share them.
 int launch_gemm_skinny_grouped(const GemmArgs& g, bool use_mbs, bool bytes, hipStream_t s) {
     SkinnyArgs a = {};

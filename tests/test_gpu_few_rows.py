@@ -84,6 +84,25 @@ def test_grouped_few_rows(mx, oracle, K, shift):
             close(out[lo:hi], oracle.gemm(tuple(ra), tuple(rb)), (K, shift, mbs, e))
 
 
+@pytest.mark.parametrize("K,shift", [(320, 0), (96, 1)])
+@pytest.mark.parametrize("hot", [0, 63, 64, 129])
+def test_grouped_few_rows_most_in_one_group(mx, oracle, K, shift, hot):
+    """More groups than lanes, nearly all rows in one of them: its tile-rows are found behind and in front of empty groups."""
+    rng = np.random.default_rng(K + hot)
+    G, N = 130, 40
+    sizes = np.where(np.arange(G) % 7 == 3, 1, 0)
+    sizes[hot] = 16 * 45 + 1
+    offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    M = int(offsets[-1])
+    assert "few rows" in mx.gemm_plan(M, N, K, grouped=True, num_groups=G)
+    a, b = random_operand(rng, M, K), random_operand(rng, G * N, K)
+    da, db = [dev(a[0])] + [dev(t, shift) for t in a[1:]], [dev(b[0])] + [dev(t, shift) for t in b[1:]]
+    out = mx.mx_gemm_mbs_grouped(*da, *db, torch.from_numpy(offsets).cuda(), N, "f32")
+    for e in np.flatnonzero(sizes):
+        lo, hi = offsets[e], offsets[e + 1]
+        close(out[lo:hi], oracle.gemm(tuple(t[lo:hi] for t in a), tuple(t[e * N:(e + 1) * N] for t in b)), (K, hot, e))
+
+
 # N: the kernel's one, two and four fragments of B; K: shares of one, two, three and four macro blocks per wavefront (the last
 # wavefronts of some have fewer, or none), then a whole chunk and one, two and four of another
 @pytest.mark.parametrize("M,N", [(17, 250), (33, 4113), (64, 8209), (32, 100), (16, 4100)])
