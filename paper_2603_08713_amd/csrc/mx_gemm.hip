@@ -85,7 +85,7 @@ bool few_rows_pay(int64_t M, int64_t N, int64_t K, const SkinnyPlan& p, bool use
 // Whether the few-row kernel takes a problem (num_groups: 0 = not grouped).
 bool takes_few_rows(int64_t M, int64_t N, int64_t K, int64_t num_groups, bool ring_ok, bool pairs_ok, bool use_mbs) {
     if (K == 0) return false;
-    if (num_groups > 0) return M <= kFewRowsPerGroup * num_groups;
+    if (num_groups > 0) return M <= kFewRowsPerGroup * num_groups && few_rows_blocks(M, N, num_groups, !pairs_ok) <= kFewRowsMaxBlocks;
     return M <= 64 && K <= 8192 && few_rows_pay(M, N, K, plan_skinny(M, N, K, ring_ok, pairs_ok), use_mbs);
 }
 

@@ -102,6 +102,9 @@ def test_gemm_plan_names_the_kernel_a_problem_takes(lib):
     # grouped: the choice goes by the rows per group
     assert "few rows per group" in plan(32 * 32, 2880, 2880, grouped=32)
     assert "general form" in plan(32 * 32 + 1, 2880, 2880, grouped=32)
+    # ... and by what fits a launch of fewer than 2^32 work-items
+    assert "few rows per group" in plan(2048, 1 << 22, 64, grouped=64) and "general form" in plan(2048, 1 << 23, 64, grouped=64)
+    assert "few rows per group" in plan(64, 1 << 21, 32, grouped=64) and "single scale bytes" in plan(64, 1 << 23, 32, grouped=64)
     import paper_2603_08713_amd as mx
 
     assert "few rows per group" in mx.gemm_plan(256, 2880, 2880, grouped=True, num_groups=32)
