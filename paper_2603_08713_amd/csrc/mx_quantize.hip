@@ -244,14 +244,20 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(QuantArgs q) {
 // comparison - once cost every lane another 34.  So the candidates are taken four at a time: a lane's four sums of
 // squares are exchanged over its quad so that each lane ends with the block sum of one of them, and the four lanes do
 // the rest for one candidate each.  F < 2 lets the shared exponent take two values only, so that it is a comparison
-// and two selects.  14336 x 4096, 16 candidates: 200 -> 165 us, the same bytes.
+// and two selects.  14336 x 4096, 16 candidates: 200 -> 165 us, the same bytes.  Short lists are priced one word at a time, by every
+// lane (kFour false): a pass over four costs what three words do that way, and what the lanes share out has to be set up and
+// the chosen word evaluated again.  14336 x 4096, list of 1, 4, 5, 7, 8, 9, 10, 13 words, one at a time: 41, 65, 76, 97, 108, 119, 131, 166
+// us; four at a time 73, 73, 100, 100, 100, 131, 130, 165 (3333 x 2880: the same order at each).
 struct DynArgs {
     QuantArgs q;
     int cand_first, cand_count, cand_stride;
 };
+// Words in the list: the static word is in front of the candidates unless the first of them is the static word.
+__host__ __device__ __forceinline__ int listed_lead(const DynArgs& d) {
+    return (((uint32_t)d.cand_first * (uint32_t)d.cand_stride & 255u) != 0 || d.cand_count == 0) ? 1 : 0;
+}
 
-// Word i of the list that is searched, as a distance from the static word: the static word, then the candidates (where
-// the first candidate is the static word, it is not listed twice).
+// Word i of the list that is searched, as a distance from the static word.
 __device__ __forceinline__ uint32_t listed_step(const DynArgs& d, int lead, int i) {
     return i < lead ? 0u : (uint32_t)(d.cand_first + i - lead) * (uint32_t)d.cand_stride & 255u;
 }
@@ -328,11 +334,67 @@ __device__ __forceinline__ float squared_error(const float (&x)[8], float mult, 
     return acc;
 }
 
-__global__ __launch_bounds__(kThreads) void quantize_dynamic_kernel(DynArgs d) {
+// The search four words at a time: place in the list of the word with the least cost, the earlier one where costs are equal
+__device__ __forceinline__ int search_four(const DynArgs& d, int lead, int n_listed, const float (&xf)[8], uint32_t amax,
+                                           bool counts, uint32_t e128, uint32_t m_static, uint32_t lane) {
 #pragma clang fp contract(off)
+    // The block's shared exponent is e0 until the scaled absmax reaches `next`, then e0 + 1.  A block that does not
+    // count searches with zeros.
+    const float amaxf = __uint_as_float(amax << 16);
+    const uint32_t e0 = ((__float_as_uint(amaxf) + d.q.carry) >> 23) - 2u;
+    const float next = __uint_as_float(((e0 + 3u) << 23) - d.q.carry);
+    const float pow0 = __uint_as_float(counts ? (254u - e0) << 23 : 0x3F800000u);  // 2^(127 - E)
+    const float pow1 = __uint_as_float(counts ? (253u - e0) << 23 : 0x3F800000u);
+    const float rescale0 = __uint_as_float(counts ? (127u + 2u * (e0 - e128)) << 23 : 0x3F800000u);
+    const float rescale1 = __uint_as_float(counts ? (129u + 2u * (e0 - e128)) << 23 : 0x3F800000u);
+    float xs[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) xs[i] = counts ? xf[i] : 0.0f;
+    // Of four listed words this lane prices word `mine`: its place in the quad, counted backwards in odd quads, so
+    // that the mirrored exchanges between quads meet lanes with the same word.
+    const uint32_t mine = (lane & 3u) ^ ((lane & 4u) ? 3u : 0u);
+    const bool p0 = mine & 1u, p1 = mine & 2u;
+    float best_cost = __builtin_inff();
+    int best_i = 0;
+    uint32_t left[4] = {0, 0, 0, 0};
+    for (int i = 0; i < n_listed; i += 4) {
+        float F[4], acc[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t step = listed_step(d, lead, i + k);
+            F[k] = __uint_as_float(0x3F800000u | (((m_static + step) << 15) & 0x7F8000u));
+            acc[k] = squared_error(xs, F[k] * (amaxf * F[k] >= next ? pow1 : pow0), left[k]);
+        }
+        float s01 = (p0 ? acc[1] : acc[0]) + dpp_quad_xor1_f(p0 ? acc[0] : acc[1]);
+        float s23 = (p0 ? acc[3] : acc[2]) + dpp_quad_xor1_f(p0 ? acc[2] : acc[3]);
+        float cost = (p1 ? s23 : s01) + dpp_quad_xor2_f(p1 ? s01 : s23);
+        const float f01 = p0 ? F[1] : F[0], f23 = p0 ? F[3] : F[2], f = p1 ? f23 : f01;
+        cost = cost * (amaxf * f >= next ? rescale1 : rescale0);
+        cost = cost + dpp_half_mirror_f(cost);
+        cost = cost + dpp_mirror_f(cost);
+        cost = cost * __builtin_amdgcn_rcpf(f * f);
+        const int at = i + (int)mine;
+        if (cost < best_cost && at < n_listed) {
+            best_cost = cost;
+            best_i = at;
+        }
+    }
+    // the least of the quad's four, the earlier word where costs are equal
+    auto take = [&](float other_cost, int other_i) {
+        if (other_cost < best_cost || (other_cost == best_cost && other_i < best_i)) {
+            best_cost = other_cost;
+            best_i = other_i;
+        }
+    };
+    take(dpp_quad_xor1_f(best_cost), (int)dpp_quad_xor1((uint32_t)best_i));
+    take(dpp_quad_xor2_f(best_cost), (int)dpp_quad_xor2((uint32_t)best_i));
+    return best_i;
+}
+
+template <bool kFour>
+__global__ __launch_bounds__(kThreads) void quantize_dynamic_kernel(DynArgs d) {
     const QuantArgs& q = d.q;
-    const int lead = (((uint32_t)d.cand_first * (uint32_t)d.cand_stride & 255u) != 0 || d.cand_count == 0) ? 1 : 0;
-    const int n_listed = d.cand_count + lead;
+    const int lead = listed_lead(d), n_listed = d.cand_count + lead;
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(blockIdx.x * (kThreads / kWave) + (threadIdx.x >> 6));
     const uint32_t nwaves = gridDim.x * (kThreads / kWave);
@@ -370,58 +432,25 @@ __global__ __launch_bounds__(kThreads) void quantize_dynamic_kernel(DynArgs d) {
         const bool searchable = !nf && e128 >= 64u && e128 <= 249u;
         const bool counts = amax != 0 && (amax >> 7) + 30u >= e128;
 
-        // The block's shared exponent is e0 until the scaled absmax reaches `next`, then e0 + 1.  A block that does not
-        // count searches with zeros.
-        const float amaxf = __uint_as_float(amax << 16);
-        const uint32_t e0 = ((__float_as_uint(amaxf) + q.carry) >> 23) - 2u;
-        const float next = __uint_as_float(((e0 + 3u) << 23) - q.carry);
-        const float pow0 = __uint_as_float(counts ? (254u - e0) << 23 : 0x3F800000u);  // 2^(127 - E)
-        const float pow1 = __uint_as_float(counts ? (253u - e0) << 23 : 0x3F800000u);
-        const float rescale0 = __uint_as_float(counts ? (127u + 2u * (e0 - e128)) << 23 : 0x3F800000u);
-        const float rescale1 = __uint_as_float(counts ? (129u + 2u * (e0 - e128)) << 23 : 0x3F800000u);
-        float xs[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) xs[i] = counts ? xf[i] : 0.0f;
-        // Of four listed words this lane prices word `mine`: its place in the quad, counted backwards in odd quads, so
-        // that the mirrored exchanges between quads meet lanes with the same word.
-        const uint32_t mine = (lane & 3u) ^ ((lane & 4u) ? 3u : 0u);
-        const bool p0 = mine & 1u, p1 = mine & 2u;
-        float best_cost = __builtin_inff();
-        int best_i = 0;
-        uint32_t left[4] = {0, 0, 0, 0};
-        for (int i = 0; i < n_listed; i += 4) {
-            float F[4], acc[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const uint32_t step = listed_step(d, lead, i + k);
-                F[k] = __uint_as_float(0x3F800000u | (((m_static + step) << 15) & 0x7F8000u));
-                acc[k] = squared_error(xs, F[k] * (amaxf * F[k] >= next ? pow1 : pow0), left[k]);
-            }
-            float s01 = (p0 ? acc[1] : acc[0]) + dpp_quad_xor1_f(p0 ? acc[0] : acc[1]);
-            float s23 = (p0 ? acc[3] : acc[2]) + dpp_quad_xor1_f(p0 ? acc[2] : acc[3]);
-            float cost = (p1 ? s23 : s01) + dpp_quad_xor2_f(p1 ? s01 : s23);
-            const float f01 = p0 ? F[1] : F[0], f23 = p0 ? F[3] : F[2], f = p1 ? f23 : f01;
-            cost = cost * (amaxf * f >= next ? rescale1 : rescale0);
-            cost = cost + dpp_half_mirror_f(cost);
-            cost = cost + dpp_mirror_f(cost);
-            cost = cost * __builtin_amdgcn_rcpf(f * f);
-            const int at = i + (int)mine;
-            if (cost < best_cost && at < n_listed) {
-                best_cost = cost;
-                best_i = at;
+        Candidate best;
+        uint32_t m_best = m_static;
+        if constexpr (kFour) {
+            const int best_i = search_four(d, lead, n_listed, xf, amax, counts, e128, m_static, lane);
+            m_best = searchable ? (m_static + listed_step(d, lead, best_i)) & 255u : m_static;
+            best = eval_candidate(xf, amax, counts, e128, m_best, q.carry);
+        } else {
+            best = eval_candidate(xf, amax, counts, e128, m_static, q.carry);
+            for (int i = 1; i < n_listed; ++i) {
+                const uint32_t step = listed_step(d, lead, i);
+                if (step == 0) continue;  // the static word again: it cannot beat itself (uniform over the launch)
+                const uint32_t m = searchable ? (m_static + step) & 255u : m_static;
+                const Candidate cand = eval_candidate(xf, amax, counts, e128, m, q.carry);
+                if (cand.cost < best.cost) {
+                    best = cand;
+                    m_best = m;
+                }
             }
         }
-        // the least of the quad's four, the earlier word where costs are equal
-        auto take = [&](float other_cost, int other_i) {
-            if (other_cost < best_cost || (other_cost == best_cost && other_i < best_i)) {
-                best_cost = other_cost;
-                best_i = other_i;
-            }
-        };
-        take(dpp_quad_xor1_f(best_cost), (int)dpp_quad_xor1((uint32_t)best_i));
-        take(dpp_quad_xor2_f(best_cost), (int)dpp_quad_xor2((uint32_t)best_i));
-        const uint32_t m_best = searchable ? (m_static + listed_step(d, lead, best_i)) & 255u : m_static;
-        const Candidate best = eval_candidate(xf, amax, counts, e128, m_best, q.carry);
 
         // the fp32 route gave valid codes unless some block of this wavefront lies outside its range
         // (Inf/NaN, or an absmax exponent field outside [24, 249]); then the all-integer path redoes the
@@ -749,7 +778,10 @@ int launch_quantize_dynamic(const void* x, int64_t rows, int64_t K, int64_t ldx,
     int64_t blocks = ((int64_t)d.q.total_chunks + (kThreads / kWave) - 1) / (kThreads / kWave);
     const int64_t max_blocks = 1 << 20;
     if (blocks > max_blocks) blocks = max_blocks;
-    hipLaunchKernelGGL(quantize_dynamic_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, static_cast<hipStream_t>(stream), d);
+    const int n = cand_count + listed_lead(d);
+    const bool one_at_a_time = n <= 7 || n == 9;  // (see the kernel)
+    hipLaunchKernelGGL(one_at_a_time ? quantize_dynamic_kernel<false> : quantize_dynamic_kernel<true>, dim3((unsigned)blocks), dim3(kThreads),
+                       0, static_cast<hipStream_t>(stream), d);
     return launch_status();
 }
 

@@ -1,4 +1,4 @@
-"""The MBS-Dynamic search takes listed words four at a time: lists of every length about a multiple of four, with the static
+"""The MBS-Dynamic search takes listed words four at a time, lists of up to seven words and of nine one at a time: lists of every length about a multiple of four, with the static
 word among the candidates (listed once) and not (listed in front of them), on whole and ragged rows."""
 import pytest
 
