@@ -43,7 +43,8 @@ struct SkinnyPlan {
 SkinnyPlan plan_skinny(int64_t M, int64_t N, int64_t K, bool ring_ok, bool pairs_ok) {
     SkinnyPlan p;
     p.fm = M <= 16 ? 1 : M <= 32 ? 2 : 4;
-    p.form = ring_ok ? (K % 4096 == 0 ? 0 : 1) : pairs_ok ? 2 : 3;
+    // (K % 512 == 0: shares of whole chunks where a wavefront's share comes out as a multiple of four macro blocks)
+    p.form = ring_ok ? (((K / kMacro + 7) / 8) % 4 == 0 ? 0 : 1) : pairs_ok ? 2 : 3;
     const int64_t frags = (N + 15) / 16;
     p.fn = frags > 2 * 256 ? 4 : frags > 256 ? 2 : 1;
     // (what the forms with one LDS dword per piece have room for)

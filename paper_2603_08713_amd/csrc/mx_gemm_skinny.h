@@ -18,8 +18,9 @@
 // and the four sigma_A values come from a small LDS table per wavefront.
 //
 // How the E8M0 bytes and MBS words of a chunk travel depends on the alignment of a row's bytes (kForm):
-//   0  every wavefront's share of K is whole chunks, scale rows 16-byte and word rows 4-byte aligned: a row's 16 E8M0
-//      bytes as one piece, its four words as one dword (one load of each kind per chunk)
+//   0  every wavefront's share of K is whole chunks (eight wavefronts: K of 3584, 4096, 7680 and 8192), scale rows 16-byte
+//      and word rows 4-byte aligned: a row's 16 E8M0 bytes as one piece, its four words as one dword (one load of each
+//      kind per chunk)
 //   1  K % 512 == 0, the same alignment of the arrays: a macro block's four E8M0 bytes as one dword, words as the two
 //      aligned dwords that hold the chunk's four
 //   2  K % 64 == 0, scale arrays on even addresses: E8M0 bytes in pairs, words one by one, each piece in an LDS dword of
@@ -212,7 +213,9 @@ constexpr int kSingleChunkK(int waves) { return waves * kSkinnyMacs * kMacro; }
 
 // Rows m0 .. m_end - 1 (at most 16 FM of them) of A against weight rows n0 .. n_end - 1 (at most 16 FN) of B; C starts
 // at row m0 and column c_n0.  smem: the workgroup's LDS.
-template <int NW, int FM, int FN, bool kFused, int kForm, bool kSingle>
+// kWords: false = no MBS words on either side: nothing is fetched, kept or multiplied for them.  (A choice at compile time: a
+// branch between a matrix instruction and the use of its result got no wait for that result from the compiler.)
+template <int NW, int FM, int FN, bool kFused, int kForm, bool kSingle, bool kWords = true>
 __device__ __forceinline__ void skinny_tile(const SkinnyArgs& args, uint8_t* smem, int64_t m0, int64_t m_end, int64_t n0,
                                             int64_t n_end, int64_t c_n0) {
     using S = SkinnyShape<NW, FM, FN, kFused, kForm>;
@@ -265,7 +268,7 @@ __device__ __forceinline__ void skinny_tile(const SkinnyArgs& args, uint8_t* sme
         uint8_t* wdst = mine + S::kWordBase;
         if constexpr (kForm == 0) {
             __builtin_amdgcn_raw_ptr_buffer_load_lds(opb.scales, (lds_ptr_t)sdst, 16, l < S::kRows ? l * scale_bytes : kOob, mac * 4, 0, 0);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(opb.mbs, (lds_ptr_t)wdst, 4, l < S::kRows ? l * nmac : kOob, mac, 0, 0);
+            if constexpr (kWords) __builtin_amdgcn_raw_ptr_buffer_load_lds(opb.mbs, (lds_ptr_t)wdst, 4, l < S::kRows ? l * nmac : kOob, mac, 0, 0);
         } else if constexpr (kForm == 1) {
             static_for<S::kScaleLoads>([&](auto i_) {  // 16 rows x 4 macro blocks
                 constexpr int i = decltype(i_)::value;
@@ -273,7 +276,7 @@ __device__ __forceinline__ void skinny_tile(const SkinnyArgs& args, uint8_t* sme
                 uint8_t* dst = sdst + i * 256;
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(opb.scales, (lds_ptr_t)dst, 4, voff, mac * 4, 0, 0);
             });
-            static_for<S::kWordLoads>([&](auto i_) {  // 32 rows x 2 dwords
+            if constexpr (kWords) static_for<S::kWordLoads>([&](auto i_) {  // 32 rows x 2 dwords
                 constexpr int i = decltype(i_)::value;
                 const int from = mac & ~3, row = i * 32 + (l >> 1);
                 const int voff = row < S::kRows && from + (l & 1) * 4 < nmac ? row * nmac + (l & 1) * 4 : kOob;
@@ -288,7 +291,7 @@ __device__ __forceinline__ void skinny_tile(const SkinnyArgs& args, uint8_t* sme
                 uint8_t* dst = sdst + i * 256;
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(opb.scales, (lds_ptr_t)dst, S::kPiece, voff, mac * 4, 0, 0);
             });
-            static_for<S::kWordLoads>([&](auto i_) {  // 16 rows x 4 words
+            if constexpr (kWords) static_for<S::kWordLoads>([&](auto i_) {  // 16 rows x 4 words
                 constexpr int i = decltype(i_)::value;
                 const int voff = mac + (l & 3) < nmac ? (i * 16 + (l >> 2)) * nmac + (l & 3) : kOob;
                 uint8_t* dst = wdst + i * 256;
@@ -309,6 +312,7 @@ __device__ __forceinline__ void skinny_tile(const SkinnyArgs& args, uint8_t* sme
             constexpr int f = decltype(f_)::value;
             static_for<kSkinnyMacs>([&](auto t_) {
                 constexpr int t = decltype(t_)::value;
+                if (kForm != 0 && mac + t >= last) return;  // (even out of range a load costs the texture-address unit its turn)
                 int voff = a_row * row_bytes + a_piece * 16 + f * 16 * stride;
                 if constexpr (kForm != 0) voff = (mac + t) * 64 + a_piece * 16 < code_end ? voff : kOob;
                 ac[f][t] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(opa.codes, voff, (mac + t) * 64, 0));
@@ -327,19 +331,21 @@ __device__ __forceinline__ void skinny_tile(const SkinnyArgs& args, uint8_t* sme
                     a_scale[f] |= (uint32_t)(uint8_t)__builtin_amdgcn_raw_buffer_load_b8(opa.scales, k + b < scale_bytes ? at + b : kOob, mac * 4, 0) << (8 * b);
                 });
             }
-            a_word[f] = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(opa.mbs, mac + a_piece < nmac ? (f * 16 + a_row) * nmac + a_piece : kOob, mac, 0);
+            a_word[f] = 0;
+            if constexpr (kWords) a_word[f] = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(opa.mbs, mac + a_piece < nmac ? (f * 16 + a_row) * nmac + a_piece : kOob, mac, 0);
         });
     };
-    auto place_a = [&]() {
+    auto place_a = [&](int count) {
         static_for<FM>([&](auto f_) {
             constexpr int f = decltype(f_)::value;
             static_for<kSkinnyMacs>([&](auto t_) {
                 constexpr int t = decltype(t_)::value;
+                if (kForm != 0 && t >= count) return;
                 lds_store128(exchange + a_piece * 320 + a_row * 16, ac[f][t]);
                 ac[f][t] = *reinterpret_cast<const v4i*>(exchange + q * 320 + r * 16);
             });
             lds_store32(exchange + S::kExchangeScales + a_piece * 64 + a_row * 4, a_scale[f]);
-            lds_store32(sig_a + a_piece * (FM * 16) + f * 16 + a_row, __float_as_uint(__builtin_amdgcn_rcpf(1.0f + (float)a_word[f] * (1.0f / 256.0f))));
+            if constexpr (kWords) lds_store32(sig_a + a_piece * (FM * 16) + f * 16 + a_row, __float_as_uint(__builtin_amdgcn_rcpf(1.0f + (float)a_word[f] * (1.0f / 256.0f))));
             as[f] = 0;
             static_for<kSkinnyMacs>([&](auto t_) {
                 constexpr int t = decltype(t_)::value;
@@ -437,9 +443,13 @@ __device__ __forceinline__ void skinny_tile(const SkinnyArgs& args, uint8_t* sme
         const v4f zero = {0.f, 0.f, 0.f, 0.f};
         const v4f p = mfma_fp4(a_codes, d.codes[t], zero, a_scale, d.scale[t]);  // D[4 q + i][r]: m = 4 q + i, n = r
         // F = 1 + m8/256 is exact, the reciprocal within an ulp; m8 = 0 (also: no words) gives exactly 1
-        const float sn = __builtin_amdgcn_rcpf(1.0f + (float)d.word[t] * (1.0f / 256.0f));
-        const v4f sm = *reinterpret_cast<const v4f*>(sig_a + t * (FM * 16) + f * 16 + q * 4);
-        acc[f][j] += p * (sm * sn);
+        if constexpr (kWords) {
+            const float sn = __builtin_amdgcn_rcpf(1.0f + (float)d.word[t] * (1.0f / 256.0f));
+            const v4f sm = *reinterpret_cast<const v4f*>(sig_a + t * (FM * 16) + f * 16 + q * 4);
+            acc[f][j] += p * (sm * sn);
+        } else {
+            acc[f][j] += p;
+        }
         asm volatile("" : "+v"(acc[f][j]));  // (keeps the compiler from moving the sums behind the next branch, products alive)
     };
 
@@ -509,7 +519,7 @@ __device__ __forceinline__ void skinny_tile(const SkinnyArgs& args, uint8_t* sme
             for (int mac = first; mac < last; mac += kSkinnyMacs) {
                 const bool more = !kSingle && mac + kSkinnyMacs < last;
                 const int count = min(last - mac, kSkinnyMacs);
-                place_a();
+                place_a(count);
                 wait_loads();
                 static_for<FN>([&](auto j_) {
                     Weights d;
@@ -559,7 +569,7 @@ __device__ __forceinline__ void skinny_tile(const SkinnyArgs& args, uint8_t* sme
 
 // M <= 16 FM rows, or (not fused) any number of them in tile-rows of 16 FM: g.tiles_m tile-rows.  Workgroups are dealt
 // round-robin to the XCDs; the tile-rows of one column tile go to one XCD, so that its weights cross the fabric once.
-template <int NW, int FM, int FN, bool kFused, int kForm, bool kSingle>
+template <int NW, int FM, int FN, bool kFused, int kForm, bool kSingle, bool kWords>
 __global__ __launch_bounds__(NW * kWave) void gemm_skinny_kernel(SkinnyArgs args) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const GemmArgs& g = args.g;
@@ -571,7 +581,7 @@ __global__ __launch_bounds__(NW * kWave) void gemm_skinny_kernel(SkinnyArgs args
         if (tn >= g.tiles_n) return;
     }
     const int64_t m0 = (int64_t)tm * (16 * FM), n0 = (int64_t)tn * (16 * FN);
-    skinny_tile<NW, FM, FN, kFused, kForm, kSingle>(args, smem, m0, g.M, n0, g.N, n0);
+    skinny_tile<NW, FM, FN, kFused, kForm, kSingle, kWords>(args, smem, m0, g.M, n0, g.N, n0);
 }
 
 template <int NW, int FM, int FN, bool kFused, int kForm>
@@ -583,15 +593,20 @@ int launch_skinny_variant(SkinnyArgs a, hipStream_t s) {
     g.tiles_m = (int)tiles_m;
     g.tiles_n = (int)tiles_n;
     using S = SkinnyShape<NW, FM, FN, kFused, kForm>;
-    auto launch = [&](auto single_) {
-        auto* fn = gemm_skinny_kernel<NW, FM, FN, kFused, kForm, decltype(single_)::value>;
+    auto launch = [&](auto single_, auto words_) {
+        auto* fn = gemm_skinny_kernel<NW, FM, FN, kFused, kForm, decltype(single_)::value, decltype(words_)::value>;
         static LdsOptIn opt_in;  // one per kernel instantiation
         if (int st = opt_in.ensure(reinterpret_cast<const void*>(fn), S::kLdsBytes)) return st;
         hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(S::NT), S::kLdsBytes, s, a);
         return launch_status();
     };
-    if (g.K <= kSingleChunkK(NW)) return launch(std::integral_constant<bool, true>{});
-    return launch(std::integral_constant<bool, false>{});
+    using Yes = std::integral_constant<bool, true>;
+    using No = std::integral_constant<bool, false>;
+    const bool single = g.K <= kSingleChunkK(NW);
+    if constexpr (!kFused) {
+        if (!g.a_mbs && !g.b_mbs) return single ? launch(Yes{}, No{}) : launch(No{}, No{});
+    }
+    return single ? launch(Yes{}, Yes{}) : launch(No{}, Yes{});
 }
 
 }  // namespace

@@ -106,7 +106,7 @@ def test_grouped_few_rows_most_in_one_group(mx, oracle, K, shift, hot):
 # N: the kernel's one, two and four fragments of B; K: shares of one, two, three and four macro blocks per wavefront (the last
 # wavefronts of some have fewer, or none), then a whole chunk and one, two and four of another
 @pytest.mark.parametrize("M,N", [(17, 250), (33, 4113), (64, 8209), (32, 100), (16, 4100)])
-@pytest.mark.parametrize("K", [512, 1024, 1536, 2560, 3072, 4096, 4608, 5120, 6656, 8192])
+@pytest.mark.parametrize("K", [512, 1024, 1536, 2560, 3072, 3584, 4096, 4608, 5120, 6656, 7680, 8192])
 def test_fused_waits_for_weights_from_memory(mx, M, N, K):
     """mx_gemm_mbs_quantize_a bit for bit the quantizer and the GEMM, on weights that no cache holds any more: what a wait lets
     fly then has not arrived when it is read."""
