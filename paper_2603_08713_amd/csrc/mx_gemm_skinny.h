@@ -476,8 +476,7 @@ __device__ __forceinline__ void skinny_tile(const SkinnyArgs& args, uint8_t* sme
             issue_small(first);
             static_for<FN>([&](auto j_) { issue_codes(first, j_); });
             __builtin_amdgcn_sched_barrier(0);
-            for (int mac = first; mac < last; mac += kSkinnyMacs) {
-                const bool more = !kSingle && mac + kSkinnyMacs < last;
+            auto chunk = [&](int mac, auto more) __attribute__((always_inline)) {
                 const int count = min(last - mac, kSkinnyMacs);
                 // fragment by fragment of A: quantize its four macro blocks, request the next activations, multiply
                 static_for<FM>([&](auto f_) {
@@ -506,7 +505,20 @@ __device__ __forceinline__ void skinny_tile(const SkinnyArgs& args, uint8_t* sme
                         __builtin_amdgcn_sched_barrier(0);
                     });
                 });
-                if (kSingle) break;
+            };
+            using Yes = std::integral_constant<bool, true>;
+            using No = std::integral_constant<bool, false>;
+            // K <= 8192 is one chunk or two.  Up to 32 rows they are written out: where a loop's two ends meet the compiler's own waits
+            // for activations count as if nothing else were in flight, and the weights land before anything is quantized (1 x
+            // 4096 x 8192 12.7 -> 12.0 us, 16 x 14336 x 6144 18.3 -> 17.4, 32 x 28672 x 5120 44.3 -> 42.2).  With 64 rows the weights'
+            // share of the time is small and the loop's smaller code is faster (64 x 14336 x 8192 48.9 -> 47.1).
+            if (kSingle || (FM <= 2 && first + kSkinnyMacs >= last)) {
+                chunk(first, No{});
+            } else if constexpr (FM <= 2) {
+                chunk(first, Yes{});
+                chunk(first + kSkinnyMacs, No{});
+            } else {
+                for (int mac = first; mac < last; mac += kSkinnyMacs) chunk(mac, mac + kSkinnyMacs < last);
             }
         }
     } else {
@@ -600,6 +612,7 @@ int launch_skinny_variant(SkinnyArgs a, hipStream_t s) {
         hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(S::NT), S::kLdsBytes, s, a);
         return launch_status();
     };
+    if (kFused && g.K > 2 * kSingleChunkK(NW)) return MX_EUNSUPPORTED;  // (the kernel takes two chunks at most)
     using Yes = std::integral_constant<bool, true>;
     using No = std::integral_constant<bool, false>;
     const bool single = g.K <= kSingleChunkK(NW);
