@@ -368,7 +368,7 @@ def mx_dequantize(codes, scales, mbs=None, out_dtype="f32", out=None):
     rows, K = shape[0], shape[1] * 2
     code, out, ldo = _matrix(rows, K, out_dtype, out, codes.device,
                              "out must be [rows, K] of the requested dtype with a contiguous last dimension")
-    _check((_lib or load_library()).mx_dequantize(codes.data_ptr(), scales.data_ptr(), _ptr(mbs), rows, K, code,
+    _check((_lib or load_library()).mx_dequantize(codes.data_ptr(), _ptr(scales), _ptr(mbs), rows, K, code,
                                                   out.data_ptr(), ldo, _stream()), "mx_dequantize")
     return out
 
@@ -389,9 +389,8 @@ def mx_gemm(a_codes, a_scales, b_codes, b_scales, out_dtype="f32", out=None):
         _gemm_forced("mx_gemm", shape, (a_codes, a_scales, None), (b_codes, b_scales, None), False, 0, None, M, N, 2 * half,
                      code, out, ldc, False)
     else:
-        _check((_lib or load_library()).mx_gemm(a_codes.data_ptr(), a_scales.data_ptr(), b_codes.data_ptr(),
-                                                b_scales.data_ptr(), M, N, 2 * half, code, out.data_ptr(), ldc, _stream()),
-               "mx_gemm")
+        _check((_lib or load_library()).mx_gemm(a_codes.data_ptr(), _ptr(a_scales), b_codes.data_ptr(), _ptr(b_scales),
+                                                M, N, 2 * half, code, out.data_ptr(), ldc, _stream()), "mx_gemm")
     return out
 
 
@@ -407,8 +406,8 @@ def mx_gemm_mbs(a_codes, a_scales, a_mbs, b_codes, b_scales, b_mbs, out_dtype="f
         _gemm_forced("mx_gemm_mbs", shape, (a_codes, a_scales, a_mbs), (b_codes, b_scales, b_mbs), False, 0, None, M, N,
                      2 * half, code, out, ldc, True)
     else:
-        _check((_lib or load_library()).mx_gemm_mbs(a_codes.data_ptr(), a_scales.data_ptr(), _ptr(a_mbs), b_codes.data_ptr(),
-                                                    b_scales.data_ptr(), _ptr(b_mbs), M, N, 2 * half, code, out.data_ptr(),
+        _check((_lib or load_library()).mx_gemm_mbs(a_codes.data_ptr(), _ptr(a_scales), _ptr(a_mbs), b_codes.data_ptr(),
+                                                    _ptr(b_scales), _ptr(b_mbs), M, N, 2 * half, code, out.data_ptr(),
                                                     ldc, _stream()), "mx_gemm_mbs")
     return out
 
@@ -527,8 +526,8 @@ def mx_gemm_mbs_grouped(a_codes, a_scales, a_mbs, b_codes, b_scales, b_mbs, row_
         _gemm_forced("mx_gemm_mbs_grouped", shape, (a_codes, a_scales, a_mbs), (b_codes, b_scales, b_mbs), True, G, row_offsets,
                      M, N, K, code, out, ldc, True)
     else:
-        _check((_lib or load_library()).mx_gemm_mbs_grouped(a_codes.data_ptr(), a_scales.data_ptr(), _ptr(a_mbs),
-                                                            b_codes.data_ptr(), b_scales.data_ptr(), _ptr(b_mbs), G,
+        _check((_lib or load_library()).mx_gemm_mbs_grouped(a_codes.data_ptr(), _ptr(a_scales), _ptr(a_mbs),
+                                                            b_codes.data_ptr(), _ptr(b_scales), _ptr(b_mbs), G,
                                                             row_offsets.data_ptr(), M, N, K, code, out.data_ptr(), ldc,
                                                             _stream()), "mx_gemm_mbs_grouped")
     return out

@@ -115,6 +115,25 @@ def test_gemm_plan_names_the_kernel_a_problem_takes(lib):
     assert "few rows" in mx.gemm_plan(16, 4096, 4096) and "few rows" not in mx.gemm_plan(65, 4096, 4096)
 
 
+def test_binding_leaves_missing_scales_to_the_library(monkeypatch):
+    """An operand without its scale array: the library's own status, and nothing at all for an empty product."""
+    import torch
+
+    import paper_2603_08713_amd as mx
+    from paper_2603_08713_amd import binding
+
+    monkeypatch.setattr(binding, "_stream", lambda: 0)
+    codes, scales = torch.zeros((4, 32), dtype=torch.uint8), torch.zeros((4, 2), dtype=torch.uint8)
+    for a_scales, b_scales in ((None, scales), (scales, None)):
+        for call in (lambda a: mx.mx_gemm(a, a_scales, codes, b_scales), lambda a: mx.mx_gemm_mbs(a, a_scales, None, codes, b_scales, None)):
+            with pytest.raises(mx.MxError):
+                call(codes)
+            assert call(codes[:0]).shape == (0, 4)
+    with pytest.raises(mx.MxError):
+        mx.mx_dequantize(codes, None)
+    assert mx.mx_dequantize(codes[:0], None).shape == (0, 64)
+
+
 def test_version_and_status_strings(lib):
     assert lib.mx_version() >= 100
     seen = set()
