@@ -346,8 +346,11 @@ def _out_dtype(dtype) -> Tuple[int, object]:
         _torch()
     try:
         return _out_dtypes[dtype]
-    except (KeyError, TypeError):
-        raise ValueError("output dtype must be fp32 or bf16") from None
+    except (KeyError, TypeError):  # what is equal to one of the names without hashing like it (a 0-d array or tensor)
+        for name, value in _out_dtypes.items():
+            if dtype == name:
+                return value
+    raise ValueError("output dtype must be fp32 or bf16")
 
 
 def _matrix(rows, cols, out_dtype, out, device, what):

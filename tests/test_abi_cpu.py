@@ -115,6 +115,22 @@ def test_gemm_plan_names_the_kernel_a_problem_takes(lib):
     assert "few rows" in mx.gemm_plan(16, 4096, 4096) and "few rows" not in mx.gemm_plan(65, 4096, 4096)
 
 
+def test_binding_output_type_names():
+    """Whatever equals a type code, a name or a torch dtype names the output type, hashable or not."""
+    import numpy as np
+    import torch
+
+    import paper_2603_08713_amd as mx
+    from paper_2603_08713_amd import binding
+
+    for code, dtype, names in ((mx.MX_OUT_F32, torch.float32, ("f32", "fp32", torch.float32)), (mx.MX_OUT_BF16, torch.bfloat16, ("bf16", torch.bfloat16))):
+        for name in names + (code, float(code), np.int64(code), np.array(code), torch.tensor(code)):
+            assert binding._out_dtype(name) == (code, dtype), name
+    for name in ("f16", 7, None, torch.float16, [], np.array(9)):
+        with pytest.raises(ValueError):
+            binding._out_dtype(name)
+
+
 def test_binding_leaves_missing_scales_to_the_library(monkeypatch):
     """An operand without its scale array: the library's own status, and nothing at all for an empty product."""
     import torch
