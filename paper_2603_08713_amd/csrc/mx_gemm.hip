@@ -1,7 +1,7 @@
 // Block-scaled MXFP4 GEMM  C = A * B^T  with the Macro Block Scaling correction, for gfx950: argument checks and
 // the choice of kernel.  The kernels are the main template (mx_gemm_ring.h: fast form in mx_gemm_wide.hip and
 // mx_gemm_mbs.hip, general forms in mx_gemm_general.hip and mx_gemm_wide.hip) and the few-row kernel
-// (mx_gemm_skinny.hip).
+// (mx_gemm_skinny.h; mx_gemm_skinny.hip, mx_gemm_skinny_fused.hip, mx_gemm_skinny_grouped.hip).
 #include "mx_gemm_shared.h"
 #include "mx_internal.h"
 
@@ -153,7 +153,7 @@ int launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* 
     return launch_gemm_mbs_ring(g, shape == 4, s);
 }
 
-// Few-row GEMM with A given as bf16 and quantized inside the kernel (mx_gemm_skinny.hip).
+// Few-row GEMM with A given as bf16 and quantized inside the kernel (mx_gemm_skinny_fused.hip).
 int launch_gemm_quantize_a(const void* a_bf16, int64_t lda, int rule, int a_use_mbs, const uint8_t* b_codes,
                            const uint8_t* b_scales, const uint8_t* b_mbs, int64_t M, int64_t N, int64_t K, int c_dtype,
                            void* C, int64_t ldc, void* stream) {

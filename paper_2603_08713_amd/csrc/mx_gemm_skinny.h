@@ -33,8 +33,7 @@
 // figures of one of the macro block's four blocks; codes and E8M0 bytes go through a small piece of LDS into the
 // matrix instruction's layout.  MBS word, scale byte and codes follow the quantizer's arithmetic to the bit.
 //
-// Grouped form (mixture of experts with few rows per expert): a workgroup belongs to one group and walks over its
-// rows 16, 32 or 64 at a time.
+// Grouped form (mixture of experts with few rows per expert): a workgroup has up to 32 rows of one group.
 #pragma once
 
 #include "mx_gemm_shared.h"
@@ -45,10 +44,9 @@ namespace mx {
 
 struct SkinnyArgs {
     GemmArgs g;
-    // fused form only: bf16 activations [M, ldx], the scale rule and whether MBS-Static words are formed
+    // fused form only: bf16 activations [M, ldx], the scale rule's carry and whether MBS-Static words are formed
     const uint16_t* x;
     int64_t ldx;
-    int rule;
     uint32_t carry;
     int a_mbs;
 };
@@ -579,31 +577,19 @@ __device__ __forceinline__ void skinny_tile(const SkinnyArgs& args, uint8_t* sme
     }
 }
 
-// M <= 16 FM rows, or (not fused) any number of them in tile-rows of 16 FM: g.tiles_m tile-rows.  Workgroups are dealt
-// round-robin to the XCDs; the tile-rows of one column tile go to one XCD, so that its weights cross the fabric once.
+// M <= 16 FM rows; a workgroup per column tile.
 template <int NW, int FM, int FN, bool kFused, int kForm, bool kSingle, bool kWords>
 __global__ __launch_bounds__(NW * kWave) void gemm_skinny_kernel(SkinnyArgs args) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    const GemmArgs& g = args.g;
-    int tn = (int)blockIdx.x, tm = 0;
-    if constexpr (!kFused) {
-        const int k = (int)(blockIdx.x >> 3);
-        tn = (int)(blockIdx.x & 7) + 8 * (k / g.tiles_m);
-        tm = k % g.tiles_m;
-        if (tn >= g.tiles_n) return;
-    }
-    const int64_t m0 = (int64_t)tm * (16 * FM), n0 = (int64_t)tn * (16 * FN);
-    skinny_tile<NW, FM, FN, kFused, kForm, kSingle, kWords>(args, smem, m0, g.M, n0, g.N, n0);
+    const int64_t n0 = (int64_t)blockIdx.x * (16 * FN);
+    skinny_tile<NW, FM, FN, kFused, kForm, kSingle, kWords>(args, smem, 0, args.g.M, n0, args.g.N, n0);
 }
 
 template <int NW, int FM, int FN, bool kFused, int kForm>
-int launch_skinny_variant(SkinnyArgs a, hipStream_t s) {
-    GemmArgs& g = a.g;
-    const int64_t tiles_n = (g.N + 16 * FN - 1) / (16 * FN), tiles_m = (g.M + 16 * FM - 1) / (16 * FM);
-    const int64_t blocks = kFused ? tiles_n : (tiles_n + 7) / 8 * 8 * tiles_m;
-    if (blocks > (int64_t)1 << 30) return MX_EINVAL;
-    g.tiles_m = (int)tiles_m;
-    g.tiles_n = (int)tiles_n;
+int launch_skinny_variant(const SkinnyArgs& a, hipStream_t s) {
+    const GemmArgs& g = a.g;
+    const int64_t blocks = (g.N + 16 * FN - 1) / (16 * FN);
+    if (g.M > 16 * FM || blocks > (int64_t)1 << 30) return MX_EINVAL;
     using S = SkinnyShape<NW, FM, FN, kFused, kForm>;
     auto launch = [&](auto single_, auto words_) {
         auto* fn = gemm_skinny_kernel<NW, FM, FN, kFused, kForm, decltype(single_)::value, decltype(words_)::value>;

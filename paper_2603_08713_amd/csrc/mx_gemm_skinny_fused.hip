@@ -19,7 +19,6 @@ int launch_gemm_skinny_fused_tile(const GemmArgs& g, const void* x, int64_t ldx,
     a.g.a_codes = a.g.a_scales = a.g.a_mbs = nullptr;
     a.x = static_cast<const uint16_t*>(x);
     a.ldx = ldx;
-    a.rule = rule;
     a.carry = rule_carry(rule);
     a.a_mbs = a_mbs ? 1 : 0;
     switch (fm * 8 + fn) {
