@@ -243,33 +243,20 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
     };
     // form 1: the partial last group of K, zeros behind its end: a row's last 16 bytes (requested ahead of everything
     // else), shifted down by those of the group before when they have arrived.  Rows of fewer than 16 bytes (K < 512) come as
-    // the dwords and the pair that they have, all requested at once (byte by byte, each waited for, 128 x 4096 x 448 took 7.2
-    // us instead of 5.0).
+    // the dwords and the pair that they have, all requested at once when they are put together (byte by byte, each waited for, 128 x
+    // 4096 x 448 took 7.2 us instead of 5.2).  Not ahead of everything else: a branch for them in front of the prologue gains
+    // short rows 3 % and costs longer ones (32 groups of 2880 x 2880, 32768 rows, 256 x 128 tiles) 1.2 %.
     v4i tail_scale[kRowDma];
-    uint32_t tail_m8[kRowDma], tail_pair[kRowDma], tail_m8_pair[kRowDma], tail_m8_byte[kRowDma];
+    uint32_t tail_m8[kRowDma];
     const int tail_bytes = scale_bytes - nwhole * 16, tail_words = nmac - nwhole * 4;  // 0 .. 15, 0 .. 4
     auto fetch_tail = [&]() {
 #pragma unroll
         for (int i = 0; i < kRowDma; ++i) {
             const __amdgpu_buffer_rsrc_t rs = row_is_a[i] ? opa.scales : opb.scales, rw = row_is_a[i] ? opa.mbs : opb.mbs;
-            tail_m8[i] = tail_pair[i] = tail_m8_pair[i] = tail_m8_byte[i] = 0;
-            if (nwhole > 0) {
-                const bool piece = tail_bytes > 0;
-                tail_scale[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, piece ? scale_off[i] : kOob, piece ? scale_bytes - 16 : 0, 0);
-                if constexpr (kMbs) tail_m8[i] = __builtin_amdgcn_raw_buffer_load_b32(rw, piece ? m8_off[i] : kOob, piece ? nmac - 4 : 0, 0);
-            } else {
-                tail_scale[i] = v4i{0, 0, 0, 0};
-                static_for<3>([&](auto d_) {
-                    constexpr int d = decltype(d_)::value;
-                    tail_scale[i][d] = __builtin_amdgcn_raw_buffer_load_b32(rs, tail_bytes >= 4 * d + 4 ? scale_off[i] + 4 * d : kOob, 0, 0);
-                });
-                tail_pair[i] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (tail_bytes & 2) ? scale_off[i] + (tail_bytes & ~3) : kOob, 0, 0);
-                if constexpr (kMbs) {
-                    tail_m8[i] = __builtin_amdgcn_raw_buffer_load_b32(rw, tail_words == 4 ? m8_off[i] : kOob, 0, 0);
-                    tail_m8_pair[i] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rw, (tail_words & 2) ? m8_off[i] : kOob, 0, 0);
-                    tail_m8_byte[i] = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(rw, (tail_words & 1) ? m8_off[i] + (tail_words & 2) : kOob, 0, 0);
-                }
-            }
+            const bool piece = nwhole > 0 && tail_bytes > 0;
+            tail_scale[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, piece ? scale_off[i] : kOob, piece ? scale_bytes - 16 : 0, 0);
+            tail_m8[i] = 0;
+            if constexpr (kMbs) tail_m8[i] = __builtin_amdgcn_raw_buffer_load_b32(rw, piece ? m8_off[i] : kOob, piece ? nmac - 4 : 0, 0);
         }
     };
     auto put_tail = [&]() {
@@ -281,9 +268,21 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
                 v >>= ((16 - tail_bytes) & 15) * 8;
                 tail_m8[i] >>= ((4 - tail_words) & 3) * 8;
             } else {
-                __builtin_memcpy(&v, &tail_scale[i], 16);
-                v |= (unsigned __int128)tail_pair[i] << ((tail_bytes & ~3) * 8);
-                tail_m8[i] |= tail_m8_pair[i] | tail_m8_byte[i] << ((tail_words & 2) * 8);
+                const __amdgpu_buffer_rsrc_t rs = row_is_a[i] ? opa.scales : opb.scales, rw = row_is_a[i] ? opa.mbs : opb.mbs;
+                uint32_t d[3], pair, word = 0, word_pair = 0, word_byte = 0;
+                static_for<3>([&](auto n_) {
+                    constexpr int n = decltype(n_)::value;
+                    d[n] = __builtin_amdgcn_raw_buffer_load_b32(rs, tail_bytes >= 4 * n + 4 ? scale_off[i] + 4 * n : kOob, 0, 0);
+                });
+                pair = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (tail_bytes & 2) ? scale_off[i] + (tail_bytes & ~3) : kOob, 0, 0);
+                if constexpr (kMbs) {
+                    word = __builtin_amdgcn_raw_buffer_load_b32(rw, tail_words == 4 ? m8_off[i] : kOob, 0, 0);
+                    word_pair = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rw, (tail_words & 2) ? m8_off[i] : kOob, 0, 0);
+                    word_byte = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(rw, (tail_words & 1) ? m8_off[i] + (tail_words & 2) : kOob, 0, 0);
+                }
+                __builtin_memcpy(&v, d, 12);
+                v |= (unsigned __int128)pair << ((tail_bytes & ~3) * 8);
+                tail_m8[i] = word | word_pair | word_byte << ((tail_words & 2) * 8);
             }
             __builtin_memcpy(&tail_scale[i], &v, 16);
         }
