@@ -1,6 +1,7 @@
 """The few-row GEMM kernel at the edges of its tiles, chunks and forms, against the CPU oracle: shares of K that are
 whole chunks of four macro blocks, parts of one and none at all; the four ways E8M0 bytes and MBS words travel (by K and by
-the alignment of the arrays); grouped problems with empty groups, groups of one row and of several tile-rows."""
+the alignment of the arrays); grouped problems with empty groups, groups of one row and of several tile-rows, and with
+nearly all rows in one group; the form with the activations quantized inside, bit for bit the quantizer and the GEMM."""
 import numpy as np
 import pytest
 
@@ -57,6 +58,21 @@ def test_few_rows_every_form(mx, oracle, M, N, K, shift):
         assert torch.equal(c16, out.to(torch.bfloat16))
         big[1:M + 1, 1:N + 1] = -3.0
         assert bool((big == -3.0).all())
+
+
+@pytest.mark.parametrize("M,N,K,shift", [(33, 8209, 4096, 1), (64, 8300, 1088, 0), (17, 8193, 64, 2), (64, 12301, 1056, 0)])
+def test_few_rows_in_more_than_one_round(mx, oracle, M, N, K, shift):
+    """Pairs and single bytes with more columns than one round of workgroups covers, where the dispatcher goes by price: the few-row
+    kernel and the one it takes."""
+    rng = np.random.default_rng(M + K)
+    a, b = random_operand(rng, M, K), random_operand(rng, N, K)
+    da, db = [dev(a[0])] + [dev(t, shift) for t in a[1:]], [dev(b[0])] + [dev(t, shift) for t in b[1:]]
+    for words in (True, False):
+        want = oracle.gemm((a[0], a[1], a[2] if words else None), (b[0], b[1], b[2] if words else None))
+        args = (da[0], da[1], da[2] if words else None, db[0], db[1], db[2] if words else None, "f32")
+        close(mx.mx_gemm_mbs(*args), want, (M, N, K, words))
+        with mx.forced(gemm_shape=5):
+            close(mx.mx_gemm_mbs(*args), want, (M, N, K, words, "few rows"))
 
 
 @pytest.mark.parametrize("K,shift", [(512, 0), (2880, 0), (2240, 1), (4096, 2), (96, 0)])
