@@ -31,20 +31,21 @@
 // (K % 512 == 0, 16-byte aligned E8M0 rows, 4-byte aligned MBS rows) therefore fetches them per group of four
 // stages: a row's 16 E8M0 bytes as one 16-byte piece into one of two LDS buffers, its four MBS words as one dword
 // into a register of the thread that owns the row.  That thread turns the word of stage s + 1 into
-// sigma = 1 / (1 + m8 / 256) during stage s, into one of two LDS tables that the barrier publishes.  The general
-// form (any K % 64 == 0 from 128 on) fetches one dword of E8M0 bytes and one MBS word per lane and stage into registers and
+// sigma = 1 / (1 + m8 / 256) during stage s, into one of two LDS tables that the barrier publishes.  Rows at any address,
+// grouped problems and any K % 64 == 0 from 512 on take the same pieces through registers (kRegs).  The general form is left with
+// K % 64 == 0 from 128 to 448, whose rows are shorter than a piece: it fetches one dword of E8M0 bytes and one MBS word per lane and stage into registers and
 // keeps a sigma table per wavefront.
 //
 // 6-bit operands (E2M3, E3M2; codes packed 32 to 24 bytes) run the fast form of the same template.  As for FP4, a
 // lane half holds one whole block per instruction (instruction kk: block kk + 2 h) with the lane's own E8M0
 // byte.  A stage is 96 bytes of a row; so that no 128-byte line of memory is fetched twice, the ring slots hold
 // planes instead of stages: slot L = bytes 128 L .. + 127 of the 384 that a group of four stages takes of each
-// row, loaded during stage L + 1 of the group before.  Details at the places marked kSix.  Their general form (any
-// K % 64 == 0 from 128 on) keeps a stage per ring slot like the 8-bit one: the 96 bytes of a row sit in places 0 .. 5 of the
+// row, loaded during stage L + 1 of the group before.  Details at the places marked kSix.  Their general form (K < 512)
+// keeps a stage per ring slot like the 8-bit one: the 96 bytes of a row sit in places 0 .. 5 of the
 // row's eight 16-byte places, a quarter of the lanes of a code load fetch nothing, and a stage's bytes straddle the
 // 128-byte lines of memory, so half of the lines are fetched twice (from the L2).
 //
-// Grouped problems (mx_gemm_mbs_elem_grouped) run the general form: a tile-row belongs to one group, whose rows of
+// Grouped problems (mx_gemm_mbs_elem_grouped) run with kRegs (K < 512: in the general form): a tile-row belongs to one group, whose rows of
 // A and C and whose weight the workgroup looks up in row_offsets.
 #pragma once
 
@@ -93,7 +94,7 @@ __global__ __launch_bounds__((F8Shape<kFast, kSmall>::NT)) void gemm_f8_kernel(G
     const int band_rows = min(tiles_m - first_m, kF8GroupM);
     const int tm = first_m + (linear % band) % band_rows;
     const int tn = (linear % band) / band_rows;
-    // Rows of A and C this tile covers and the rows of B it multiplies with.  Grouped (general form only): tile-rows
+    // Rows of A and C this tile covers and the rows of B it multiplies with.  Grouped (kRegs and general form only): tile-rows
     // are counted group by group; group e owns rows row_offsets[e] .. row_offsets[e + 1] - 1 and the e-th of the
     // stacked [N, K] weights.
     int64_t a_row0 = (int64_t)tm * TM, a_end = g.M, b_row0 = (int64_t)tn * TN, b_end = g.N;

@@ -24,7 +24,7 @@ int launch_gemm_elem(int a_elem, const uint8_t* a_codes, const uint8_t* a_scales
     const size_t esz = c_dtype == MX_OUT_F32 ? 4 : 2;
     if (!aligned(C, esz)) return MX_EALIGN;
     const bool a8 = a_elem == MX_ELEM_E4M3 || a_elem == MX_ELEM_E5M2, b8 = b_elem == MX_ELEM_E4M3 || b_elem == MX_ELEM_E5M2;
-    // K in whole macro blocks, or ending with half of one (the general form; rows of E8M0 bytes then start on even
+    // K in whole macro blocks, or ending with half of one (rows of E8M0 bytes then start on even
     // addresses only)
     const bool half_tail = (K % kMacro) != 0;
     if (a8 != b8 || K == 0 || (K % (kMacro / 2)) != 0 || K < kMacro || !aligned(a_codes, 16) || !aligned(b_codes, 16) ||
