@@ -708,13 +708,16 @@ int launch_f8_kernel(GemmArgs g, hipStream_t s) {
     return launch_status();
 }
 
-// Tiles run in rounds of one per compute unit: rounds x tile area / efficiency, the 128 x 128 tile taken at 0.8 of
-// the large one's rate per output, as in the MXFP4 kernels.  1024 x 4096 x 4096 in E2M3, 128 large tiles or 256 small ones, with the
-// quantizer: 38.6 and 29.6 us; 78 x 6795 x 1792 in E5M2 29.8 and 17.8 us.  A grouped problem's rounds are not known here: large tiles.
-inline bool f8_small_tile(const GemmArgs& g) {
+// Tiles run in rounds of one per compute unit: rounds x tile area / efficiency, the 128 x 128 tile taken at 0.75 of
+// the large one's rate per output, 0.55 without words (it reads as many bytes a stage for half the products).  GEMM alone, rounds of large
+// and of small tiles, K = 1536 and 4096, us large and small: 1 and 1 (2048 x 2048) E4M3 16.9, 13.2 and 34.0, 26.7, without words 12.5, 10.7
+// and 26.3, 21.1; 2 and 2 (896 x 9344) 33.2, 25.6 and 72.2, 57.6, without 27.5, 23.4 and 56.4, 48.3; 2 and 3 (600 x 19200)
+// 34.5, 37.3 and 78.1, 84.4, without 27.9, 34.3 and 58.3, 71.2; 3 and 4 (384 x 38400) 52.9, 51.3 and 116, 112, without 43.0, 45.4 and
+// 88.3, 97.0; the 6-bit formats the same within 5 %.  A grouped problem's rounds are not known here: large tiles.
+inline bool f8_small_tile(const GemmArgs& g, bool use_mbs) {
     if (g.num_groups > 0 || g.K < 512) return false;
     const int64_t cols = (g.N + 127) / 128, big = (g.M + 255) / 256 * cols, small = (g.M + 127) / 128 * cols;
-    return (double)((small + 255) / 256) / 0.8 < 2.0 * (double)((big + 255) / 256);
+    return (double)((small + 255) / 256) / (use_mbs ? 0.75 : 0.55) < 2.0 * (double)((big + 255) / 256);
 }
 
 template <int kFmtA, int kFmtB>

@@ -49,7 +49,7 @@ int launch_gemm_elem(int a_elem, const uint8_t* a_codes, const uint8_t* a_scales
                            (!a_mbs || aligned(a_mbs, 4)) && (!b_mbs || aligned(b_mbs, 4));
     if (force == 3 && !skinny_ok) return MX_EINVAL;
     if (skinny_ok && (force == 0 || force == 3)) return launch_gemm_skinny_elem(g, a_elem, b_elem, s);
-    const bool small_tile = !force_general && f8_small_tile(g);
+    const bool small_tile = !force_general && f8_small_tile(g, use_mbs);
     if (!a8) {
         if (small_tile) return launch_gemm_six_small(g, a_elem == MX_ELEM_E3M2, b_elem == MX_ELEM_E3M2, use_mbs, s);
         return launch_gemm_six(g, a_elem == MX_ELEM_E3M2, b_elem == MX_ELEM_E3M2, use_mbs, force_general, s);
