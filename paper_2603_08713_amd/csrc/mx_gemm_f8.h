@@ -633,7 +633,7 @@ __global__ __launch_bounds__((F8Shape<kFast, kSmall>::NT)) void gemm_f8_kernel(G
         constexpr int lanes_per_row = kCols * esz / 16, rows_per_pass = kWave / lanes_per_row;
         const int rd_row = l / lanes_per_row, rd_chunk = l % lanes_per_row;
         const int64_t n = n0 + rd_chunk * per;
-        const bool whole = g.vec_store16 && n + per <= g.N;
+        const bool whole = n + per <= g.N;
         static_for<FM>([&](auto i_) {
             constexpr int i = decltype(i_)::value;
             static_for<FN * 4>([&](auto q_) {
@@ -653,34 +653,17 @@ __global__ __launch_bounds__((F8Shape<kFast, kSmall>::NT)) void gemm_f8_kernel(G
                 if (m < a_end && n < g.N) {
                     uint8_t* o = static_cast<uint8_t*>(g.C) + (m * g.ldc + n) * esz;
                     if (whole) {
-                        __builtin_nontemporal_store(v, reinterpret_cast<v4i*>(o));
+                        // (any element: the device serves 16-byte stores at any address; element by element 818 x 3907 x 1152 in
+                        // E2M3 with the quantizer took 22.4 us instead of 15.8)
+                        if (g.vec_store16) __builtin_nontemporal_store(v, reinterpret_cast<v4i*>(o));
+                        else *reinterpret_cast<v4i_any*>(o) = v;
                     } else {
-                        // rows of C that start on 8-byte but not on 16-byte boundaries: the halves of the piece that
-                        // lie inside the row go out as 8-byte stores, the rest element by element
 #pragma unroll
-                        for (int half = 0; half < 2; ++half) {
-                            if (g.vec_store8 && n + (half + 1) * (per / 2) <= g.N) {
-                                typedef int v2i_t __attribute__((ext_vector_type(2)));
-                                reinterpret_cast<v2i_t*>(o)[half] = v2i_t{v[2 * half], v[2 * half + 1]};
-                                continue;
+                        for (int e = 0; e < per; ++e)
+                            if (n + e < g.N) {
+                                if constexpr (kBf16) reinterpret_cast<uint16_t*>(o)[e] = (uint16_t)((uint32_t)v[e / 2] >> (e % 2 * 16));
+                                else reinterpret_cast<int*>(o)[e] = v[e];
                             }
-                            if constexpr (kBf16) {
-                                // (rows on 4-byte boundaries: two elements at a time where both lie inside the row)
-#pragma unroll
-                                for (int d = 2 * half; d < 2 * half + 2; ++d) {
-                                    if (g.vec_store4 && n + 2 * d + 1 < g.N) {
-                                        reinterpret_cast<int*>(o)[d] = v[d];
-                                    } else {
-                                        if (n + 2 * d < g.N) reinterpret_cast<uint16_t*>(o)[2 * d] = (uint16_t)(uint32_t)v[d];
-                                        if (n + 2 * d + 1 < g.N) reinterpret_cast<uint16_t*>(o)[2 * d + 1] = (uint16_t)((uint32_t)v[d] >> 16);
-                                    }
-                                }
-                            } else {
-#pragma unroll
-                                for (int e = 2 * half; e < 2 * half + 2; ++e)
-                                    if (n + e < g.N) reinterpret_cast<int*>(o)[e] = v[e];
-                            }
-                        }
                     }
                 }
             });

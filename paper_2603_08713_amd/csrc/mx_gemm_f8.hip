@@ -39,8 +39,6 @@ int launch_gemm_elem(int a_elem, const uint8_t* a_codes, const uint8_t* a_scales
     g.num_groups = grouped ? num_groups : 0;
     g.c_bf16 = c_dtype == MX_OUT_BF16;
     g.vec_store16 = aligned(C, 16) && (ldc * esz) % 16 == 0;
-    g.vec_store8 = aligned(C, 8) && (ldc * esz) % 8 == 0;
-    g.vec_store4 = aligned(C, 4) && (ldc * esz) % 4 == 0;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bool use_mbs = a_mbs || b_mbs;
     const bool force_general = force == 1;

@@ -37,9 +37,7 @@ struct GemmArgs {
     int num_groups;              // 0 = plain GEMM
     int tiles_m, tiles_n;        // tile grid (tiles_m is an upper bound in grouped mode)
     int c_bf16;
-    int vec_store16;             // C rows allow 16-byte vector stores
-    int vec_store8;              // C rows allow 8-byte vector stores
-    int vec_store4;              // C rows allow 4-byte stores (bf16 output: two elements at a time)
+    int vec_store16;             // every row of C starts on a 16-byte boundary
 };
 
 // Main kernels (mx_gemm_ring.h), fast form: K % 512 == 0 and aligned scale and MBS arrays, not grouped; without MBS
@@ -82,6 +80,7 @@ namespace {
 
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v4i_any __attribute__((ext_vector_type(4), aligned(2)));  // in memory, on any element of C
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float v32f __attribute__((ext_vector_type(32)));
