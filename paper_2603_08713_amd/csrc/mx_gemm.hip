@@ -14,23 +14,26 @@ namespace {
 
 // force_shape (mx_internal_gemm only; the public entry points pass -1 = automatic): 2 / 6 / 7 = fast form without
 // MBS on 256x256 / 256x128 / 128x128 tiles, 3 / 4 = fast form with MBS on 256x128 / 128x128 tiles, 5 = few-row
-// kernel, 8 / 9 = general form (row pieces through registers) on 256x128 / 128x128 tiles, 10 = general form (single bytes) on
-// 128x128 tiles, 11 / 12 = fast form with MBS on both operands / general form with MBS on 64x128 tiles.
+// kernel, 8 / 9 = general form (row pieces through registers) on 256x128 / 128x128 tiles, 10 = general form (single bytes, any K:
+// K = 0) on 128x128 tiles, 11 / 12 = fast form with MBS on both operands / general form with MBS on 64x128 tiles.
 // Which kernel form and tile shape (the codes above) takes a problem.  Tiles run in rounds of one per compute
 // unit: rounds x tile area / efficiency (the small tile reaches about 0.8 of the large tile's rate per output
 // with MBS, 0.85 / 0.72 without; measured) picks the tile.  With words on both operands, ungrouped, 64 x 128 tiles
 // take what they cover in one round: twice the compute units have work, and a tile of few rows is bound by a stage's serial chain
 // and not by its arithmetic.  GEMM alone, 64 x 128 against 128 x 128: 333 x 4096 x 4096 14.0 and 17.6 us, 512 x 4096 x 4096 14.1
 // and 17.8, 333 x 4000 x 2880 11.1 and 13.7; past one round 800 x 4096 x 4096 20.4 and 19.1, 1024 x 4096 x 2880 17.7 and 15.9.
-int choose_shape(int64_t M, int64_t N, bool use_mbs, bool ring_ok, bool pairs_ok, bool skinny_ok, bool tile64_ok) {
+//
+// The general form fetches a row's pieces through registers, which any K % 32 == 0 at any address can use: it costs what the fast form
+// does, where single bytes (K % 64 = 32 once took them) keep the texture-address unit busy three times as long as the codes and leave
+// LDS for 128 x 128 tiles only.  With the quantizer: 305 x 1205 x 1632 21.8 -> 13.3 us, 5680 x 1130 x 6880 110 -> 75.
+int choose_shape(int64_t M, int64_t N, int64_t K, bool use_mbs, bool ring_ok, bool skinny_ok, bool tile64_ok) {
     const int64_t t256x128 = ((M + 255) / 256) * ((N + 127) / 128), t128 = ((M + 127) / 128) * ((N + 127) / 128);
     const double big = 2.0 * ((t256x128 + 255) / 256) / (use_mbs ? 1.0 : 0.85),
                  small = ((t128 + 255) / 256) / (use_mbs ? 0.8 : 0.72);
     if (skinny_ok) return 5;
-    if (tile64_ok && ((M + 63) / 64) * ((N + 127) / 128) <= 256 && (ring_ok || pairs_ok)) return ring_ok ? 11 : 12;
+    if (tile64_ok && ((M + 63) / 64) * ((N + 127) / 128) <= 256 && K > 0) return ring_ok ? 11 : 12;
     if (ring_ok) return use_mbs ? (big <= small ? 3 : 4) : 2;  // (without MBS the launcher also has 256 x 256 tiles)
-    if (pairs_ok) return big <= small ? 8 : 9;
-    return 10;
+    return K == 0 ? 10 : big <= small ? 8 : 9;
 }
 
 // The few-row kernel's tile for M <= 64: the smallest fm that covers the rows; fn so that the launch has about one
@@ -67,7 +70,7 @@ constexpr int64_t kFewRowsPerGroup = 32;
 // us, by what both take on the device with weights from memory.  Few-row and main kernel at M = 1, 32, 64, words on both sides:
 //   K = 2880   N =  8192  5.8, 7.2, 9.6      and 15.9, 17.1, 17.9;   N = 28672  18.1, 23.8, 32.2   and 17.9, 19.1, 20.0
 //   K = 1088   N =  8192  4.4, 5.3, 6.7      and 7.2, 7.4, 7.7;      N = 28672  12.8, 15.8, 20.8   and 9.1, 9.4, 9.8
-//   K = 4128   N =  4096  6.3, 9.4, 13.1     and 25.7, 25.8, 25.9;   N = 28672  27.3, 45.8, 78.2   and 33.6, 34.6, 35.8
+//   K = 4128   N =  4096  5.8, 8.0, 11.5      and 18.1, 20.5, 19.8;   N = 28672  23.4, 41.1, 67.1   and 26.5, 27.3, 28.9
 // Over K of 64 to 8160, N of 1024 to 57344 and 1 to 64 rows the few-row kernel is chosen where it is at most 4 % slower, the
 // main kernel where it is at most a third slower: the prices lean to the kernel that had all of these problems before.
 bool few_rows_pay(int64_t M, int64_t N, int64_t K, const SkinnyPlan& p, bool use_mbs) {
@@ -78,10 +81,10 @@ bool few_rows_pay(int64_t M, int64_t N, int64_t K, const SkinnyPlan& p, bool use
     const int at = p.fm == 1 ? 0 : p.fm == 2 ? 1 : 2;
     static const double kRound[2][3] = {{1.6, 2.2, 2.8}, {0.8, 1.1, 1.4}}, kRoundPerK[2][3] = {{0.92e-3, 1.14e-3, 1.6e-3}, {0.6e-3, 1.15e-3, 2.0e-3}};
     const double few = 1.7 + rounds * (kRound[bytes][at] + kRoundPerK[bytes][at] * K);
-    const double tile = bytes ? (use_mbs ? 4.5 + 6.2e-3 * K : 3.5 + 5.2e-3 * K)
-                              : (use_mbs ? std::max(4.3, 1.5 + 5.5e-3 * K) : std::max(4.0, 1.4 + 4.7e-3 * K));
+    const double tile = use_mbs ? std::max(4.3, 1.5 + 5.5e-3 * K) : std::max(4.0, 1.4 + 4.7e-3 * K);
     // (a further round of the tiles starts while the one before ends, where two workgroups fit a compute unit)
-    return few <= tile * (bytes ? tile_rounds : 0.5 + 0.5 * tile_rounds);
+    // (single bytes: the quarter is what the few-row prices above are too high for one row and long K)
+    return few <= tile * (bytes ? 1.25 : 1.0) * (0.5 + 0.5 * tile_rounds);
 }
 // Whether the few-row kernel takes a problem (num_groups: 0 = not grouped).
 bool takes_few_rows(int64_t M, int64_t N, int64_t K, int64_t num_groups, bool ring_ok, bool pairs_ok, bool use_mbs) {
@@ -123,11 +126,11 @@ int launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* 
     // Fast form: K in whole groups of four macro blocks and aligned per-row arrays.
     const bool ring_ok = !grouped && K > 0 && (K % 512) == 0 && aligned(a_scales, 16) && aligned(b_scales, 16) &&
                          (!use_mbs || ((!a_mbs || aligned(a_mbs, 4)) && (!b_mbs || aligned(b_mbs, 4))));
-    // General form with row pieces through registers: rows of E8M0 bytes on even addresses; else single bytes.
+    // (few-row kernel: pairs of E8M0 bytes; else single ones)
     const bool pairs_ok = K > 0 && (K % 64) == 0 && aligned(a_scales, 2) && aligned(b_scales, 2);
     const bool skinny_ok = takes_few_rows(M, N, K, g.num_groups, ring_ok, pairs_ok, use_mbs);
     const bool tile64_ok = !grouped && a_mbs && b_mbs && mbs_entry;
-    int shape = choose_shape(M, N, use_mbs, ring_ok, pairs_ok, skinny_ok, tile64_ok);
+    int shape = choose_shape(M, N, K, use_mbs, ring_ok, skinny_ok, tile64_ok);
     if (force_shape >= 0) shape = force_shape;
     // (the checks below only matter for forced shapes)
     if (shape == 5) {
@@ -137,11 +140,11 @@ int launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* 
         return launch_gemm_skinny_tile(g, use_mbs, p.fm, p.fn, p.form, s);
     }
     if (shape == 11 || shape == 12) {
-        if (!use_mbs || (shape == 11 ? !ring_ok || !a_mbs || !b_mbs : !pairs_ok)) return MX_EINVAL;
+        if (!use_mbs || (shape == 11 ? !ring_ok || !a_mbs || !b_mbs : K == 0)) return MX_EINVAL;
         return shape == 11 ? launch_gemm_mbs_ring(g, 2, s) : launch_gemm_mbs_general(g, 2, false, s);
     }
     if (shape == 8 || shape == 9) {
-        if (!pairs_ok) return MX_EINVAL;
+        if (K == 0) return MX_EINVAL;
         return use_mbs ? launch_gemm_mbs_general(g, shape - 8, false, s) : launch_gemm_wide_general(g, shape - 8, false, s);
     }
     if (shape == 10) return use_mbs ? launch_gemm_mbs_general(g, 1, true, s) : launch_gemm_wide_general(g, 1, true, s);
@@ -214,7 +217,7 @@ int mx_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int a_has_mbs, int b_
     if (!out || cap <= 0 || M < 0 || N < 0 || K < 0 || (K % mx::kBlock) != 0 || num_groups < 0) return MX_EINVAL;
     const bool use_mbs = a_has_mbs || b_has_mbs, grouped = num_groups > 0;
     const bool ring_ok = !grouped && K > 0 && (K % 512) == 0, pairs_ok = K > 0 && (K % 64) == 0;
-    const int shape = mx::choose_shape(M, N, use_mbs, ring_ok, pairs_ok, mx::takes_few_rows(M, N, K, num_groups, ring_ok, pairs_ok, use_mbs),
+    const int shape = mx::choose_shape(M, N, K, use_mbs, ring_ok, mx::takes_few_rows(M, N, K, num_groups, ring_ok, pairs_ok, use_mbs),
                                        !grouped && a_has_mbs && b_has_mbs);
     const char* sides = a_has_mbs && b_has_mbs ? "MBS words on A and B" : a_has_mbs ? "MBS words on A" : b_has_mbs ? "MBS words on B" : "no MBS";
     const char* what;
@@ -226,9 +229,9 @@ int mx_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int a_has_mbs, int b_
         case 5: what = grouped ? "gemm_skinny_grouped_kernel (few rows per group)" : "gemm_skinny_kernel (few rows)"; break;
         case 11: what = "gemm_ring_kernel, fast form, 64x128 tile, 4 wavefronts of 64x32"; break;
         case 12: what = "gemm_ring_kernel, general form (row pieces through registers), 64x128 tile, 4 wavefronts of 64x32"; break;
+        case 10: what = "gemm_ring_kernel, general form (single scale bytes), 128x128 tile"; break;
         case 8: what = use_mbs ? "gemm_ring_kernel, general form (row pieces through registers), 256x128 tile, 8 wavefronts" : "gemm_ring_kernel, general form (row pieces through registers), 256x128 tile, 4 wavefronts"; break;
-        case 9: what = "gemm_ring_kernel, general form (row pieces through registers), 128x128 tile"; break;
-        default: what = "gemm_ring_kernel, general form (single scale bytes), 128x128 tile"; break;
+        default: what = "gemm_ring_kernel, general form (row pieces through registers), 128x128 tile"; break;
     }
     snprintf(out, (size_t)cap, "%s; %s", what, sides);
     return MX_OK;

@@ -1,13 +1,13 @@
 // The main GEMM kernel template in its general forms: any K, rows of E8M0 bytes and MBS words at any address,
 // and grouped problems (mixture of experts).  A row's E8M0 bytes and MBS words travel in the fast form's pieces, but
-// through registers (K % 64 == 0, even addresses), or as single bytes direct to LDS, which costs texture-address time;
+// through registers (K > 0), or as single bytes direct to LDS, which costs texture-address time;
 // the fast form, whose loads need no registers, keeps every problem it can take.  This file holds the kernels with MBS (compiled with the
 // VGPR form of the matrix instructions, as in mx_gemm_mbs.hip); those without are in mx_gemm_wide.hip.
 #include "mx_gemm_ring.h"
 
 namespace mx {
 
-// K % 64 == 0, K > 0, E8M0 arrays 2-byte aligned (or `bytes`); the caller has checked these.  A null MBS array reads as
+// K > 0 (or `bytes`); the caller has checked this.  A null MBS array reads as
 // words of zero (sigma = 1, which multiplies exactly), so one instantiation serves one-sided MBS as well.
 // tile: 0 = 256 x 128, 1 = 128 x 128, 2 = 64 x 128.  bytes: E8M0 bytes one at a time (any K % 32 == 0, any address; 128 x 128
 // tiles only: one LDS dword per byte does not fit beside the larger tile).

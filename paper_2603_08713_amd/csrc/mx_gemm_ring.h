@@ -159,7 +159,9 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
     const int gen_code_col = ((l & 3) ^ ((l >> 4) & 3)) * 16;  // this lane's chunk of the 64-byte stage piece
     const int gen_scale_col = l & 15, gen_scale_off = (w * 4 + (l >> 4)) * scale_bytes + gen_scale_col;
     const int gen_m8_off = (w * 16 + (l >> 2)) * nmac + (l & 3), gen_m8_col = l & 3;
-    // Form 1: the groups of four stages that K fills, and the slot of a group (the partial last one has its own).
+    // Form 1 takes any K % 32 == 0: a chunk of codes is one E8M0 block, so the blocks of the last stage that do not exist are chunks
+    // past the end of the row, and their E8M0 bytes are zeros like the rest of a partial group.
+    // The groups of four stages that K fills, and the slot of a group (the partial last one has its own).
     const int nwhole = K / (kRingGroup * kRingStageK);
     auto group_slot = [&](int grp) { return S::kRegs && grp >= nwhole ? 2 : grp & 1; };
     // A row's E8M0 bytes and MBS words on their way through registers (form 1): requested in one stage with a barrier,
@@ -243,7 +245,7 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
     };
     // form 1: the partial last group of K, zeros behind its end: a row's last 16 bytes (requested ahead of everything
     // else), shifted down by those of the group before when they have arrived.  Rows of fewer than 16 bytes (K < 512) come as
-    // the dwords and the pair that they have, all requested at once when they are put together (byte by byte, each waited for, 128 x
+    // the dwords, the pair and the byte that they have, all requested at once when they are put together (byte by byte, each waited for, 128 x
     // 4096 x 448 took 7.2 us instead of 5.2).  Not ahead of everything else: a branch for them in front of the prologue gains
     // short rows 3 % and costs longer ones (32 groups of 2880 x 2880, 32768 rows, 256 x 128 tiles) 1.2 %.
     v4i tail_scale[kRowDma];
@@ -269,19 +271,20 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
                 tail_m8[i] >>= ((4 - tail_words) & 3) * 8;
             } else {
                 const __amdgpu_buffer_rsrc_t rs = row_is_a[i] ? opa.scales : opb.scales, rw = row_is_a[i] ? opa.mbs : opb.mbs;
-                uint32_t d[3], pair, word = 0, word_pair = 0, word_byte = 0;
+                uint32_t d[3], pair, byte, word = 0, word_pair = 0, word_byte = 0;
                 static_for<3>([&](auto n_) {
                     constexpr int n = decltype(n_)::value;
                     d[n] = __builtin_amdgcn_raw_buffer_load_b32(rs, tail_bytes >= 4 * n + 4 ? scale_off[i] + 4 * n : kOob, 0, 0);
                 });
                 pair = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (tail_bytes & 2) ? scale_off[i] + (tail_bytes & ~3) : kOob, 0, 0);
+                byte = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(rs, (tail_bytes & 1) ? scale_off[i] + (tail_bytes & ~1) : kOob, 0, 0);
                 if constexpr (kMbs) {
                     word = __builtin_amdgcn_raw_buffer_load_b32(rw, tail_words == 4 ? m8_off[i] : kOob, 0, 0);
                     word_pair = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rw, (tail_words & 2) ? m8_off[i] : kOob, 0, 0);
                     word_byte = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(rw, (tail_words & 1) ? m8_off[i] + (tail_words & 2) : kOob, 0, 0);
                 }
                 __builtin_memcpy(&v, d, 12);
-                v |= (unsigned __int128)pair << ((tail_bytes & ~3) * 8);
+                v |= (unsigned __int128)pair << ((tail_bytes & ~3) * 8) | (unsigned __int128)byte << ((tail_bytes & ~1) * 8);
                 tail_m8[i] = word | word_pair | word_byte << ((tail_words & 2) * 8);
             }
             __builtin_memcpy(&tail_scale[i], &v, 16);

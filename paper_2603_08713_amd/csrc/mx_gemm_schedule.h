@@ -39,10 +39,10 @@ constexpr int kSigmaSlots = 4;                  // as many as ring slots: a stag
 // kForm: 0 = fast form, which wants K % 512 == 0 and 16-byte (E8M0) / 4-byte (MBS) aligned rows, so that a row's
 // bytes of four stages travel as one piece per lane.  1, 2 = general forms for everything else, grouped problems
 // included; the last stage may be partly empty and the stage count is padded to whole groups with stages that read
-// zeros.  1 (any K % 64 == 0, rows of E8M0 bytes on even addresses): the same 16-byte and 4-byte pieces, one row per
+// zeros.  1 (any K % 32 == 0, K > 0, any address): the same 16-byte and 4-byte pieces, one row per
 // lane, but through registers - a load into registers takes any address, a direct-to-LDS load of 16 bytes does not -
 // and the thread writes them to LDS; K's last group, where it is not whole, is fetched in the prologue into a slot of
-// its own.  2 (any K % 32 == 0, any address): E8M0 bytes and MBS words travel direct to LDS as single bytes, each in
+// its own.  2 (any K, 0 among them, any address): E8M0 bytes and MBS words travel direct to LDS as single bytes, each in
 // an LDS dword of its own.
 template <int NWM_, int NWN_, int FM_, int FN_, int kSides_, int kForm_ = 0>
 struct RingShape {

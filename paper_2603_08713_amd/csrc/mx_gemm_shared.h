@@ -47,8 +47,7 @@ const char* describe_gemm_wide(int64_t M, int64_t N);  // what launch_gemm_wide(
 int launch_gemm_mbs_ring(const GemmArgs& g, int variant, hipStream_t s);
 // The same kernels in their general forms (any K % 32 == 0, any alignment of the scale arrays, grouped or not),
 // defined in mx_gemm_general.hip (with MBS) and mx_gemm_wide.hip (without).  tile: 0 = 256 x 128, 1 = 128 x 128;
-// bytes: E8M0 bytes fetched one at a time (needed when K % 64 != 0 or a scale array sits on an odd address;
-// 128 x 128 tiles only).
+// bytes: E8M0 bytes fetched one at a time (needed when K = 0; 128 x 128 tiles only).
 int launch_gemm_mbs_general(const GemmArgs& g, int tile, bool bytes, hipStream_t s);
 int launch_gemm_wide_general(const GemmArgs& g, int tile, bool bytes, hipStream_t s);
 // Few activation rows (mx_gemm_skinny.h): M <= 64, not grouped; fm, fn = fragments of 16 rows of A and of B per
