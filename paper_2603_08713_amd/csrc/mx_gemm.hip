@@ -16,6 +16,32 @@ namespace {
 // MBS on 256x256 / 256x128 / 128x128 tiles, 3 / 4 = fast form with MBS on 256x128 / 128x128 tiles, 5 = few-row
 // kernel, 8 / 9 = general form (row pieces through registers) on 256x128 / 128x128 tiles, 10 = general form (single bytes, any K:
 // K = 0) on 128x128 tiles, 11 / 12 = fast form with MBS on both operands / general form with MBS on 64x128 tiles.
+// Grouped problems with words: what the kernels take, in us, from rows, groups and the number of macro blocks; the launch cannot know the
+// routing, so a group is taken to end half a tile-row short and every group to have rows.  Fitted to Zipf and equal routings over 8, 32
+// and 64 groups of 768, 1536 and 2880 squared with 4 to 4096 rows per group.
+struct GroupedPrices {
+    double big, small, few;  // 256 x 128 tiles, 64 x 128 tiles, the few-row kernel
+};
+GroupedPrices grouped_prices(int64_t M, int64_t N, int64_t K, int64_t num_groups) {
+    const double busy = (double)std::min(num_groups, M), st = (double)((K + kMacro - 1) / kMacro), cols = (double)((N + 127) / 128);
+    const double weights_mb = busy * N * K * 0.54e-6;
+    const double x256 = (M / 256.0 + 0.5 * busy) * cols / 256.0, x64 = (M / 64.0 + 0.5 * busy) * cols / 256.0;
+    GroupedPrices p;
+    p.big = std::max(1.0, x256) * (4.7 + 0.82 * st);
+    p.small = 2.5 + std::max(std::max(x64, 1.2) * (1.2 + 0.29 * st), weights_mb / 3.4);  // (two workgroups share a compute unit)
+    p.few = std::max(2.0 + 0.3 * st + (M / 32.0 + 0.5 * busy) * ((N + 31) / 32) * std::max(0.005, 0.36e-3 * st), weights_mb / 4.2);
+    return p;
+}
+// 64 x 128 tiles for a grouped problem with words: up to 128 rows per group they leave less empty than 256 x 128 tiles, and two of
+// their workgroups fit a compute unit; above, where they are cheaper by more than the prices are wrong.  GEMM alone, Zipf routing,
+// 256 x 128 (or 128 x 128, where those were taken) and 64 x 128: 64 groups of 1536 x 1536, 4096 rows 55.6 and 32.3 us, 8192 rows 57.9 and
+// 45.8; 64 of 2880 x 2880, 4096 rows 157 and 111; 8 of 768 x 768, 1024 rows 7.4 and 6.4; past the line 32 of 1536 x 1536, 16384 rows
+// 55 and 63, 8 of 2880 x 2880, 2048 rows 24 and 32.
+bool grouped_small_tile(int64_t M, int64_t N, int64_t K, int64_t num_groups) {
+    const GroupedPrices p = grouped_prices(M, N, K, num_groups);
+    return M <= 128 * num_groups || p.small < 0.85 * p.big;
+}
+
 // Which kernel form and tile shape (the codes above) takes a problem.  Tiles run in rounds of one per compute
 // unit: rounds x tile area / efficiency (the small tile reaches about 0.8 of the large tile's rate per output
 // with MBS, 0.85 / 0.72 without; measured) picks the tile.  With words on both operands, ungrouped, 64 x 128 tiles
@@ -26,11 +52,12 @@ namespace {
 // The general form fetches a row's pieces through registers, which any K % 32 == 0 at any address can use: it costs what the fast form
 // does, where single bytes (K % 64 = 32 once took them) keep the texture-address unit busy three times as long as the codes and leave
 // LDS for 128 x 128 tiles only.  With the quantizer: 305 x 1205 x 1632 21.8 -> 13.3 us, 5680 x 1130 x 6880 110 -> 75.
-int choose_shape(int64_t M, int64_t N, int64_t K, bool use_mbs, bool ring_ok, bool skinny_ok, bool tile64_ok) {
+int choose_shape(int64_t M, int64_t N, int64_t K, int64_t num_groups, bool use_mbs, bool ring_ok, bool skinny_ok, bool tile64_ok) {
     const int64_t t256x128 = ((M + 255) / 256) * ((N + 127) / 128), t128 = ((M + 127) / 128) * ((N + 127) / 128);
     const double big = 2.0 * ((t256x128 + 255) / 256) / (use_mbs ? 1.0 : 0.85),
                  small = ((t128 + 255) / 256) / (use_mbs ? 0.8 : 0.72);
     if (skinny_ok) return 5;
+    if (num_groups > 0 && use_mbs && K > 0) return grouped_small_tile(M, N, K, num_groups) ? 12 : 8;
     if (tile64_ok && ((M + 63) / 64) * ((N + 127) / 128) <= 256 && K > 0) return ring_ok ? 11 : 12;
     if (ring_ok) return use_mbs ? (big <= small ? 3 : 4) : 2;  // (without MBS the launcher also has 256 x 256 tiles)
     return K == 0 ? 10 : big <= small ? 8 : 9;
@@ -55,10 +82,10 @@ SkinnyPlan plan_skinny(int64_t M, int64_t N, int64_t K, bool ring_ok, bool pairs
     if (p.form == 3) p.fn = 1;
     return p;
 }
-// Grouped problems take the few-row kernel up to this many rows per group on average: it streams the weights once per
-// 32 rows, the main kernel once per 128 or 256 but at a quarter of the rate.  Measured (Zipf routing, rows per group 8 and
-// 32; few-row against main kernel): 32 groups of 2880 x 2880 38, 54 against 64, 82 us; 8 of 2048 x 2048 7.8, 8.8
-// against 13, 13; 64 of 1024 x 1024 16, 24 against 19, 26; at 64 rows per group 79, 15, 35 against 91, 13, 25.  All rows
+// Grouped problems may take the few-row kernel up to this many rows per group on average: it streams the weights once per
+// 32 rows.  From K = 512 on, with words, it competes with the main kernel's 64 x 128 tiles (grouped_prices).  Zipf routing, 8, 16 and 32 rows
+// per group, few-row kernel and tiles: 32 groups of 2880 x 2880 34.9, 43.4, 54.2 and 43.1, 46.2, 48.8 us; 64 of 1536 x 1536 22.0, 25.8,
+// 33.0 and 22.3, 24.4, 25.5; 64 of 768 x 768 9.0, 11.7, 14.7 and 8.3, 8.4, 8.5.  All rows
 // in one group, 8, 16 and 32 per group on average: 32 of 2880 x 2880 13, 22, 35 against 16, 17, 19; 64 of 1024 x 1024 7, 11, 17
 // against 9, 9, 9.  The launch cannot know the routing: it goes by what routers produce and loses up to half there.
 constexpr int64_t kFewRowsPerGroup = 32;
@@ -89,7 +116,12 @@ bool few_rows_pay(int64_t M, int64_t N, int64_t K, const SkinnyPlan& p, bool use
 // Whether the few-row kernel takes a problem (num_groups: 0 = not grouped).
 bool takes_few_rows(int64_t M, int64_t N, int64_t K, int64_t num_groups, bool ring_ok, bool pairs_ok, bool use_mbs) {
     if (K == 0) return false;
-    if (num_groups > 0) return M <= kFewRowsPerGroup * num_groups && few_rows_blocks(M, N, num_groups, !pairs_ok) <= kFewRowsMaxBlocks;
+    if (num_groups > 0) {
+        if (M > kFewRowsPerGroup * num_groups || few_rows_blocks(M, N, num_groups, !pairs_ok) > kFewRowsMaxBlocks) return false;
+        if (K < 512 || !use_mbs) return true;
+        const GroupedPrices p = grouped_prices(M, N, K, num_groups);
+        return p.few <= 1.02 * p.small;
+    }
     return M <= 64 && K <= 8192 && few_rows_pay(M, N, K, plan_skinny(M, N, K, ring_ok, pairs_ok), use_mbs);
 }
 
@@ -130,7 +162,7 @@ int launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* 
     const bool pairs_ok = K > 0 && (K % 64) == 0 && aligned(a_scales, 2) && aligned(b_scales, 2);
     const bool skinny_ok = takes_few_rows(M, N, K, g.num_groups, ring_ok, pairs_ok, use_mbs);
     const bool tile64_ok = !grouped && a_mbs && b_mbs && mbs_entry;
-    int shape = choose_shape(M, N, K, use_mbs, ring_ok, skinny_ok, tile64_ok);
+    int shape = choose_shape(M, N, K, g.num_groups, use_mbs, ring_ok, skinny_ok, tile64_ok);
     if (force_shape >= 0) shape = force_shape;
     // (the checks below only matter for forced shapes)
     if (shape == 5) {
@@ -217,7 +249,7 @@ int mx_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int a_has_mbs, int b_
     if (!out || cap <= 0 || M < 0 || N < 0 || K < 0 || (K % mx::kBlock) != 0 || num_groups < 0) return MX_EINVAL;
     const bool use_mbs = a_has_mbs || b_has_mbs, grouped = num_groups > 0;
     const bool ring_ok = !grouped && K > 0 && (K % 512) == 0, pairs_ok = K > 0 && (K % 64) == 0;
-    const int shape = mx::choose_shape(M, N, K, use_mbs, ring_ok, mx::takes_few_rows(M, N, K, num_groups, ring_ok, pairs_ok, use_mbs),
+    const int shape = mx::choose_shape(M, N, K, num_groups, use_mbs, ring_ok, mx::takes_few_rows(M, N, K, num_groups, ring_ok, pairs_ok, use_mbs),
                                        !grouped && a_has_mbs && b_has_mbs);
     const char* sides = a_has_mbs && b_has_mbs ? "MBS words on A and B" : a_has_mbs ? "MBS words on A" : b_has_mbs ? "MBS words on B" : "no MBS";
     const char* what;
