@@ -57,12 +57,12 @@ namespace mx {
 namespace {
 
 // kFmtA / kFmtB: the matrix instruction's format selector of tensor A / B (0 = E4M3, 1 = E5M2).  kRegs: the fast form
-// for rows of E8M0 bytes and MBS words at any address, grouped problems and any K % 64 == 0 from 512 on.  kSmall: 128 x 128
-// tiles (instantiated with kRegs, which takes every K and address from 512 on).
-template <int kFmtA, int kFmtB, bool kMbs, bool kFast, bool kRegs = false, bool kSmall = false>
-__global__ __launch_bounds__((F8Shape<kFast, kSmall>::NT)) void gemm_f8_kernel(GemmArgs g) {
+// for rows of E8M0 bytes and MBS words at any address, grouped problems and any K % 64 == 0 from 512 on.  kTile: see
+// F8Shape (1 and 2 are instantiated with kRegs, which takes every K and address from 512 on).
+template <int kFmtA, int kFmtB, bool kMbs, bool kFast, bool kRegs = false, int kTile = 0>
+__global__ __launch_bounds__((F8Shape<kFast, kTile>::NT)) void gemm_f8_kernel(GemmArgs g) {
     static_assert(kFast || !kRegs, "kRegs is a variant of the fast form");
-    using S = F8Shape<kFast, kSmall>;
+    using S = F8Shape<kFast, kTile>;
     constexpr int FM = S::FM, FN = S::FN, TM = S::TM, TN = S::TN, NW = S::NW, kCodeDma = S::kCodeDma;
     // 6-bit codes (format selectors 2, 3) come packed, 24 bytes per block; both operands have the same width
     constexpr bool kSix = kFmtA >= 2;
@@ -72,7 +72,7 @@ __global__ __launch_bounds__((F8Shape<kFast, kSmall>::NT)) void gemm_f8_kernel(G
     constexpr int kRowStage = kSix ? 96 : kF8RowStage;  // code bytes per row and stage
     // loads a wavefront makes per stage: what the stage's wait counts (a count that assumed more would let the
     // youngest loads of the stage it is about to read stay in flight)
-    using Sched = F8Schedule<kSixPlanes ? kF8Six : kFast ? kF8Fast : kF8General, kMbs, kSmall>;
+    using Sched = F8Schedule<kSixPlanes ? kF8Six : kFast ? kF8Fast : kF8General, kMbs, kTile>;
     constexpr int kLoads = Sched::kLoads;
     static_assert(kLoads == S::kLoads - (kFast || kMbs ? 0 : 2) && Sched::kCodeDma == kCodeDma, "the schedule describes this kernel");
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -210,6 +210,7 @@ __global__ __launch_bounds__((F8Shape<kFast, kSmall>::NT)) void gemm_f8_kernel(G
             return;
         }
         uint8_t* dst = smem + (owns ? S::kSmallBase + (grp & 1) * S::kScaleGroup + w * 1024 : S::kSpare);
+        static_assert(kRegs || !kFast || S::kSpareBytes == 1024, "a piece of 1 KiB goes there");
         __builtin_amdgcn_raw_ptr_buffer_load_lds(own_scales, (lds_ptr_t)dst, 16, own_scale_off, gg * 16, 0, 0);
         own_m8[decltype(mod3_)::value] = __builtin_amdgcn_raw_buffer_load_b32(own_mbs, own_m8_off, gg * 4, 0);
     };
@@ -220,7 +221,7 @@ __global__ __launch_bounds__((F8Shape<kFast, kSmall>::NT)) void gemm_f8_kernel(G
                        a2 = __builtin_amdgcn_alignbit(w3, w2, bits), a3 = w3 >> bits;
         const bool one = early & 4u, two = early & 8u;
         const uint32_t b0 = one ? a1 : a0, b1 = one ? a2 : a1, b2 = one ? a3 : a2, b3 = one ? 0u : a3;
-        uint8_t* dst = smem + (owns ? S::kSmallBase + (grp & 1) * S::kScaleGroup + tid * 16 : S::kSpare + l * 16);
+        uint8_t* dst = smem + (owns ? S::kSmallBase + (grp & 1) * S::kScaleGroup + tid * 16 : S::kSpare + l * 16 % S::kSpareBytes);
         *reinterpret_cast<v4i*>(dst) = v4i{(int)(two ? b2 : b0), (int)(two ? b3 : b1), (int)(two ? 0u : b2), (int)(two ? 0u : b3)};
     };
     // General form: E8M0 dwords and MBS words of stage st into the registers of ring slot `slot`.
@@ -481,6 +482,15 @@ __global__ __launch_bounds__((F8Shape<kFast, kSmall>::NT)) void gemm_f8_kernel(G
         auto issue_next = [&](auto i_) __attribute__((always_inline)) {
             if constexpr (!kSixPlanes || p > 0) issue_code(code_soff, CodeSlot{}, i_);
         };
+        // behind matrix instruction t: load t, or, with more loads than instructions, its share of them
+        constexpr int kInstr = 2 * FM * FN;
+        auto issue_behind = [&](auto t_) __attribute__((always_inline)) {
+            constexpr int t = decltype(t_)::value;
+            if constexpr (kCodeDma <= kInstr) issue_next(t_);
+            else static_for<kCodeDma>([&](auto n_) __attribute__((always_inline)) {
+                if constexpr (decltype(n_)::value * kInstr / kCodeDma == t) issue_next(n_);
+            });
+        };
 
         // sigma of this lane's output row per A fragment; of its 16 output columns per B fragment, kept as four
         // registers: lane l holds the value of column 8 gq + 4 h + l % 4, and the multiply fetches column i from
@@ -507,10 +517,10 @@ __global__ __launch_bounds__((F8Shape<kFast, kSmall>::NT)) void gemm_f8_kernel(G
                 for (int e = 0; e < 16; ++e) zero[e] = 0.f;
                 prod[q % 2] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[j][0], fa[i][0], zero, kFmtB, kFmtA, 0,
                                                                                 (int)scl_b[j], 0, (int)scl_a[i]);
-                issue_next(std::integral_constant<int, 2 * q>{});
+                issue_behind(std::integral_constant<int, 2 * q>{});
                 prod[q % 2] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[j][1], fa[i][1], prod[q % 2], kFmtB, kFmtA,
                                                                                 kSel1, (int)scl_b[j], kSel1, (int)scl_a[i]);
-                issue_next(std::integral_constant<int, 2 * q + 1>{});
+                issue_behind(std::integral_constant<int, 2 * q + 1>{});
                 if constexpr (i == FM - 1) {
                     read_frag(Next{}, IsB{}, std::integral_constant<int, j>{}, std::integral_constant<int, 0>{});
                     read_frag(Next{}, IsB{}, std::integral_constant<int, j>{}, std::integral_constant<int, 1>{});
@@ -547,7 +557,7 @@ __global__ __launch_bounds__((F8Shape<kFast, kSmall>::NT)) void gemm_f8_kernel(G
                 constexpr int t = decltype(t_)::value, kk = t / (FM * FN), i = t % (FM * FN) / FN, j = t % FN;
                 acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[j][kk], fa[i][kk], acc[i][j], kFmtB, kFmtA, kSel1 * kk,
                                                                              (int)scl_b[j], kSel1 * kk, (int)scl_a[i]);
-                issue_next(t_);
+                issue_behind(t_);
                 if constexpr (i == FM - 1) read_frag(Next{}, IsB{}, std::integral_constant<int, j>{}, std::integral_constant<int, kk>{});
                 if constexpr (j == FN - 1) read_frag(Next{}, IsA{}, std::integral_constant<int, i>{}, std::integral_constant<int, kk>{});
                 if constexpr (kFast && t == 2 * FM * FN - 1) read_scales_fast(s + 1);
@@ -674,9 +684,9 @@ __global__ __launch_bounds__((F8Shape<kFast, kSmall>::NT)) void gemm_f8_kernel(G
     else flush(std::integral_constant<bool, false>{});
 }
 
-template <int kFmtA, int kFmtB, bool kMbs, bool kFast, bool kRegs = false, bool kSmall = false>
+template <int kFmtA, int kFmtB, bool kMbs, bool kFast, bool kRegs = false, int kTile = 0>
 int launch_f8_kernel(GemmArgs g, hipStream_t s) {
-    using S = F8Shape<kFast, kSmall>;
+    using S = F8Shape<kFast, kTile>;
     // grouped: every group may end with a partial tile-row, so this is an upper bound (the surplus exits)
     const int64_t tiles_m = g.num_groups > 0 ? g.M / S::TM + g.num_groups : (g.M + S::TM - 1) / S::TM;
     const int64_t tiles_n = (g.N + S::TN - 1) / S::TN;
@@ -684,28 +694,48 @@ int launch_f8_kernel(GemmArgs g, hipStream_t s) {
     g.tiles_m = (int)tiles_m;
     g.tiles_n = (int)tiles_n;
     const unsigned blocks = (unsigned)(((tiles_m * tiles_n + 7) / 8) * 8);
-    auto* fn = gemm_f8_kernel<kFmtA, kFmtB, kMbs, kFast, kRegs, kSmall>;
+    auto* fn = gemm_f8_kernel<kFmtA, kFmtB, kMbs, kFast, kRegs, kTile>;
     static LdsOptIn opt_in;  // one per kernel instantiation
     if (int st = opt_in.ensure(reinterpret_cast<const void*>(fn), S::kLdsBytes)) return st;
     hipLaunchKernelGGL(fn, dim3(blocks), dim3(S::NT), S::kLdsBytes, s, g);
     return launch_status();
 }
 
-// Tiles run in rounds of one per compute unit: rounds x tile area / efficiency, the 128 x 128 tile taken at 0.75 of
+// The tile of F8Shape for a problem; the small ones take K >= 512.
+// One round of 64 x 128 tiles takes them: a stage's serial chain bounds such a problem, and it is shortest there.  GEMM alone, 128 x 128
+// and 64 x 128 tiles, us: 512 x 4096 x 4096 in E4M3 24.0 and 19.7, without words 18.8 and 15.3, in E2M3 23.0 and 20.0; 1024 x 2048 x 576
+// 8.3 and 7.2; two rounds 512 x 8192 x 2048 15.0 and 16.9.
+// Otherwise tiles run in rounds of one per compute unit: rounds x tile area / efficiency, the 128 x 128 tile taken at 0.75 of
 // the large one's rate per output, 0.55 without words (it reads as many bytes a stage for half the products).  GEMM alone, rounds of large
 // and of small tiles, K = 1536 and 4096, us large and small: 1 and 1 (2048 x 2048) E4M3 16.9, 13.2 and 34.0, 26.7, without words 12.5, 10.7
 // and 26.3, 21.1; 2 and 2 (896 x 9344) 33.2, 25.6 and 72.2, 57.6, without 27.5, 23.4 and 56.4, 48.3; 2 and 3 (600 x 19200)
 // 34.5, 37.3 and 78.1, 84.4, without 27.9, 34.3 and 58.3, 71.2; 3 and 4 (384 x 38400) 52.9, 51.3 and 116, 112, without 43.0, 45.4 and
-// 88.3, 97.0; the 6-bit formats the same within 5 %.  A grouped problem's rounds are not known here: large tiles.
-inline bool f8_small_tile(const GemmArgs& g, bool use_mbs) {
-    if (g.num_groups > 0 || g.K < 512) return false;
-    const int64_t cols = (g.N + 127) / 128, big = (g.M + 255) / 256 * cols, small = (g.M + 127) / 128 * cols;
-    return (double)((small + 255) / 256) / (use_mbs ? 0.75 : 0.55) < 2.0 * (double)((big + 255) / 256);
+// 88.3, 97.0; the 6-bit formats the same within 5 %.
+// Grouped: the launch cannot know the routing, so every group is taken to have rows and to end half a tile-row short, and what the
+// three tiles take, in us, is fitted to Zipf routings over 8, 32 and 64 groups of 768, 1536 and 2880 squared in E4M3 and E2M3 (just past a
+// round costs most of a second one; two workgroups of 64 x 128 share a compute unit, so they have no rounds to speak of).  256 x 128, 128 x 128
+// and 64 x 128 in E4M3: 64 groups of 1536 x 1536 with 1024, 8192 and 16384 rows 56.9, 49.0, 40.8; 74.4, 65.6, 68.3; 93.7, 102.5, 115.2.
+inline int f8_tile(const GemmArgs& g, bool use_mbs) {
+    if (g.K < 512) return 0;
+    const int64_t cols = (g.N + 127) / 128;
+    if (g.num_groups > 0) {
+        const double st = (double)((g.K + kMacro - 1) / kMacro), busy = (double)(g.num_groups < g.M ? g.num_groups : g.M);
+        auto rounds = [&](double rows) { return (g.M / rows + 0.5 * busy) * cols / 256.0; };
+        // (between 1 and 1.1 the estimate cannot tell one round from two)
+        auto whole = [](double x) { return x <= 1.0 ? 1.0 : x <= 1.1 ? 1.4 : x < 1.8 ? 1.8 : x; };
+        const double x0 = rounds(256.0), x2 = rounds(64.0);
+        const double t0 = x0 <= 1.1 ? 5.5 + 1.06 * st : whole(x0) * (3.8 + 1.39 * st), t1 = whole(rounds(128.0)) * (2.6 + 0.88 * st),
+                     t2 = 3.0 + (x2 < 1.0 ? 1.0 : x2) * (0.7 * st - 0.3);
+        return t0 < t1 && t0 < t2 ? 0 : t1 < t2 ? 1 : 2;
+    }
+    const int64_t big = (g.M + 255) / 256 * cols, small = (g.M + 127) / 128 * cols;
+    if ((g.M + 63) / 64 * cols <= 256) return 2;
+    return (double)((small + 255) / 256) / (use_mbs ? 0.75 : 0.55) < 2.0 * (double)((big + 255) / 256) ? 1 : 0;
 }
 
-template <int kFmtA, int kFmtB>
+template <int kFmtA, int kFmtB, int kTile>
 int launch_f8_small(const GemmArgs& g, bool use_mbs, hipStream_t s) {
-    return use_mbs ? launch_f8_kernel<kFmtA, kFmtB, true, true, true, true>(g, s) : launch_f8_kernel<kFmtA, kFmtB, false, true, true, true>(g, s);
+    return use_mbs ? launch_f8_kernel<kFmtA, kFmtB, true, true, true, kTile>(g, s) : launch_f8_kernel<kFmtA, kFmtB, false, true, true, kTile>(g, s);
 }
 
 template <int kFmtA, int kFmtB>

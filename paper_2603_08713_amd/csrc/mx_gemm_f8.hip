@@ -6,7 +6,7 @@ namespace mx {
 namespace {
 
 // force: 0 = automatic, 1 = the main kernel's general form, 2 = the main kernel in the form the problem allows, 3 = the
-// few-row kernel
+// few-row kernel, 16 / 17 / 18 = the main kernel on 256 x 128 / 128 x 128 / 64 x 128 tiles
 int launch_gemm_elem(int a_elem, const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* a_mbs, int b_elem,
                      const uint8_t* b_codes, const uint8_t* b_scales, const uint8_t* b_mbs, int num_groups,
                      const int64_t* row_offsets, bool grouped, int64_t M, int64_t N, int64_t K, int c_dtype, void* C,
@@ -43,17 +43,27 @@ int launch_gemm_elem(int a_elem, const uint8_t* a_codes, const uint8_t* a_scales
     const bool use_mbs = a_mbs || b_mbs;
     const bool force_general = force == 1;
     // few activation rows: the weights are streamed once, nothing is staged (mx_gemm_skinny_f8.hip)
+    // Taken where its rows and its rounds of workgroups are few, against one round of 64 x 128 tiles of the main kernel.  E4M3, few-row
+    // kernel and tiles, us, K = 512, 1536, 3072: 16 rows, N = 8192 5.3, 7.2, 10.9 and 5.9, 9.2, 16.3, N = 14336 7.5, 11.7, 17.3 and 5.9,
+    // 10.1, 17.9; 32 rows, N = 4096 4.8, 7.0, 9.5 and 5.4, 9.3, 14.6, N = 8192 7.5, 10.7, 15.8 and 5.8, 9.3, 16.8; 64 rows, N = 4096 7.0,
+    // 9.8, 13.4 and 5.7, 9.5, 14.9, N = 8192 12.5, 17.6, 25.7 and 5.9, 9.8, 18.4, N = 14336 22.7, 33.0, 48.7 and 6.3, 11.3, 19.4.  Without
+    // words the tiles are faster: 64 rows, N = 4096, K = 3072 and 8192 13.0, 27.0 and 11.4, 35.9.  6-bit within 10 %.
+    const int64_t few_work = (M <= 16 ? 1 : M <= 32 ? 2 : 4) * ((N + 4351) / 4352);
+    const bool few_pays = few_work <= 2 || (few_work <= 4 && K >= (use_mbs ? 2560 : 5120));
     const bool skinny_ok = !grouped && M <= 64 && (K % 512) == 0 && K <= 8192 && aligned(a_scales, 16) && aligned(b_scales, 16) &&
                            (!a_mbs || aligned(a_mbs, 4)) && (!b_mbs || aligned(b_mbs, 4));
     if (force == 3 && !skinny_ok) return MX_EINVAL;
-    if (skinny_ok && (force == 0 || force == 3)) return launch_gemm_skinny_elem(g, a_elem, b_elem, s);
-    const bool small_tile = !force_general && f8_small_tile(g, use_mbs);
+    if (skinny_ok && ((force == 0 && few_pays) || force == 3)) return launch_gemm_skinny_elem(g, a_elem, b_elem, s);
+    if (force > 18 || (force > 16 && K < 512)) return MX_EINVAL;
+    const int tile = force >= 16 ? force - 16 : force_general ? 0 : f8_tile(g, use_mbs);
     if (!a8) {
-        if (small_tile) return launch_gemm_six_small(g, a_elem == MX_ELEM_E3M2, b_elem == MX_ELEM_E3M2, use_mbs, s);
+        if (tile == 2) return launch_gemm_six_tiny(g, a_elem == MX_ELEM_E3M2, b_elem == MX_ELEM_E3M2, use_mbs, s);
+        if (tile == 1) return launch_gemm_six_small(g, a_elem == MX_ELEM_E3M2, b_elem == MX_ELEM_E3M2, use_mbs, s);
         return launch_gemm_six(g, a_elem == MX_ELEM_E3M2, b_elem == MX_ELEM_E3M2, use_mbs, force_general, s);
     }
     const bool a5 = a_elem == MX_ELEM_E5M2, b5 = b_elem == MX_ELEM_E5M2;
-    if (small_tile) return launch_gemm_eight_small(g, a5, b5, use_mbs, s);
+    if (tile == 2) return launch_gemm_eight_tiny(g, a5, b5, use_mbs, s);
+    if (tile == 1) return launch_gemm_eight_small(g, a5, b5, use_mbs, s);
     if (!a5 && !b5) return launch_f8<0, 0>(g, use_mbs, force_general, s);
     if (!a5 && b5) return launch_f8<0, 1>(g, use_mbs, force_general, s);
     if (a5 && !b5) return launch_f8<1, 0>(g, use_mbs, force_general, s);

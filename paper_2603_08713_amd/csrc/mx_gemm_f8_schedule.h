@@ -30,11 +30,12 @@ constexpr int kF8Slots = 3;
 constexpr int kF8RowStage = kMacro;  // code bytes per row and stage (8-bit)
 constexpr int kF8GroupM = 4;         // tile-rows walked together for L2 reuse
 
-// kSmall: 128 x 128 tiles (eight wavefronts of 64 x 32) instead of 256 x 128 (64 x 64)
-template <bool kFast_, bool kSmall_ = false>
+// kTile: 0 = 256 x 128 tiles (eight wavefronts of 64 x 64), 1 = 128 x 128 (eight of 64 x 32), 2 = 64 x 128 (four of 64 x 32; LDS for
+// two workgroups on a compute unit)
+template <bool kFast_, int kTile_ = 0>
 struct F8Shape {
     static constexpr bool kFast = kFast_;
-    static constexpr int NWM = kSmall_ ? 2 : 4, NWN = kSmall_ ? 4 : 2, FM = 2, FN = kSmall_ ? 1 : 2, NW = NWM * NWN, NT = NW * kWave;
+    static constexpr int NWM = kTile_ == 0 ? 4 : kTile_ == 1 ? 2 : 1, NWN = kTile_ == 0 ? 2 : 4, FM = 2, FN = kTile_ == 0 ? 2 : 1, NW = NWM * NWN, NT = NW * kWave;
     static constexpr int TM = NWM * FM * 32, TN = NWN * FN * 32, kRows = TM + TN;
     static constexpr int kCodeDma = kRows / 8 / NW;                     // per wavefront and stage: 8 rows x 128 B per load
     static constexpr int kRegLoads = kFast ? 0 : FM + FN + 2;           // general form: E8M0 dwords and MBS words per lane and stage
@@ -47,13 +48,15 @@ struct F8Shape {
     static constexpr int kScaleGroup = kRows * 16, kSigmaTable = kRows * 4;
     static constexpr int kSigmaBase = kSmallBase + (kFast ? 2 * kScaleGroup : 0);
     static constexpr int kSigmaWave = (FM + FN) * 32 * 4;
-    static constexpr int kSpare = kSigmaBase + 2 * kSigmaTable;         // fast form: 1 KiB nobody reads
-    static constexpr int kLdsBytes = kFast ? kSpare + 1024 : kSigmaBase + NW * kSigmaWave;
+    static constexpr int kSpare = kSigmaBase + 2 * kSigmaTable;         // fast form: 1 KiB (64 x 128 tiles: 256 bytes) nobody reads
+    static constexpr int kSpareBytes = kTile_ == 2 ? 256 : 1024;
+    static constexpr int kLdsBytes = kFast ? kSpare + kSpareBytes : kSigmaBase + NW * kSigmaWave;
     static constexpr int kStageRegion = 32 * (FN * 32 * 4 + 16);        // per wavefront, epilogue staging
     static_assert((TM / 8) % NW == 0 && (TN / 8) % NW == 0, "operand fixed per load index");
     static_assert(kRows % kWave == 0 && TM % kWave == 0, "fast form: a wavefront's rows belong to one operand");
     static_assert(kLdsBytes <= 160 * 1024 && NW * kStageRegion <= kLdsBytes, "LDS capacity of a gfx950 compute unit");
-    static_assert(kCodeDma <= 2 * FM * FN && 3 * kLoads + 4 < 64, "vmcnt is a 6-bit counter");
+    static_assert(kTile_ != 2 || 2 * kLdsBytes <= 160 * 1024, "two workgroups per compute unit");
+    static_assert(3 * kLoads + 4 < 64, "vmcnt is a 6-bit counter");
 };
 
 // ---- load schedule ----------------------------------------------------------------------------------------------
@@ -65,9 +68,9 @@ struct F8LoadItem {
     int kind, what, index;
 };
 
-template <int kForm, bool kMbs, bool kSmall = false>
+template <int kForm, bool kMbs, int kTile = 0>
 struct F8Schedule {
-    using S = F8Shape<kForm != kF8General, kSmall>;
+    using S = F8Shape<kForm != kF8General, kTile>;
     static constexpr int kCodeDma = S::kCodeDma, kGroup = S::kGroup;
     static constexpr int kRegScales = kForm == kF8General ? S::FM + S::FN : 0;
     static constexpr int kRegWords = kForm == kF8General && kMbs ? 2 : 0;

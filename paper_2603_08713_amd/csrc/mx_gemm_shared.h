@@ -71,6 +71,8 @@ int launch_gemm_skinny_grouped(const GemmArgs& g, bool use_mbs, bool bytes, hipS
 // The few-row kernel for operands in the 8-bit or 6-bit element formats (a_elem, b_elem: mx_elem_t), under the same
 // conditions, defined in mx_gemm_skinny_f8.hip; an operand without MBS words has a null a_mbs / b_mbs.
 int launch_gemm_eight_small(const GemmArgs& g, bool a5, bool b5, bool use_mbs, hipStream_t s);
+int launch_gemm_eight_tiny(const GemmArgs& g, bool a5, bool b5, bool use_mbs, hipStream_t s);
+int launch_gemm_six_tiny(const GemmArgs& g, bool a32, bool b32, bool use_mbs, hipStream_t s);
 int launch_gemm_six_small(const GemmArgs& g, bool a32, bool b32, bool use_mbs, hipStream_t s);
 int launch_gemm_six(const GemmArgs& g, bool a32, bool b32, bool use_mbs, bool force_general, hipStream_t s);
 int launch_gemm_skinny_elem(const GemmArgs& g, int a_elem, int b_elem, hipStream_t s);

@@ -37,7 +37,8 @@ int mx_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int a_has_mbs, int b_
 
 // mx_gemm_mbs_elem with the kernel chosen by the caller.  force: 0 = as mx_gemm_mbs_elem, 1 = the main kernel's
 // general form also where the fast form applies, 2 = the main kernel also where the few-row kernel applies, 3 = the
-// few-row kernel (MX_EINVAL where it does not apply).
+// few-row kernel (MX_EINVAL where it does not apply), 16 / 17 / 18 = the main kernel on 256 x 128 / 128 x 128 / 64 x 128 tiles (the
+// last two: K >= 512).
 int mx_internal_gemm_elem(mx_elem_t a_elem, const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* a_mbs_or_null,
                           mx_elem_t b_elem, const uint8_t* b_codes, const uint8_t* b_scales, const uint8_t* b_mbs_or_null,
                           int64_t M, int64_t N, int64_t K, mx_dtype_t c_dtype, void* C, int64_t ldc, int force,

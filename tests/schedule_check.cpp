@@ -171,7 +171,7 @@ struct F8Issued {
     bool repeat;          // past the end of K the kernel fetches the last stage, group or plane again
 };
 
-template <int kForm, bool kMbs, bool kSmall = false>
+template <int kForm, bool kMbs, int kSmall = 0>
 void check_f8(const char* name, int nstages) {
     using Sched = mx::F8Schedule<kForm, kMbs, kSmall>;
     constexpr int C = Sched::kCodeDma;
@@ -268,7 +268,8 @@ void check_f8_all(const char* name) {
     else
         for (int nstages : {4, 8, 12, 16, 20, 64, 256}) {
             check_f8<kForm, kMbs>(name, nstages);
-            check_f8<kForm, kMbs, true>(name, nstages);  // 128 x 128 tiles
+            check_f8<kForm, kMbs, 1>(name, nstages);  // 128 x 128 tiles
+            check_f8<kForm, kMbs, 2>(name, nstages);  // 64 x 128 tiles
         }
 }
 
