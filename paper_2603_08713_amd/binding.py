@@ -1,7 +1,8 @@
-"""ctypes binding of ``libmx4.so`` (C ABI in ``include/mx4.h``), same names as the C entry points.
+"""Binding of ``libmx4.so`` (C ABI in ``include/mx4.h``), same names as the C entry points.
 
 Marshalling only: tensors in, ``data_ptr()`` + sizes + the current HIP stream out.  Output tensors
-are allocated with torch when the caller does not pass them.  Nothing is computed here.
+are allocated with torch when the caller does not pass them.  Nothing is computed here.  Calls that bring plain CUDA
+tensors and all outputs are marshalled natively (csrc_host/marshal.cpp); what that declines goes through ctypes below.
 """
 from __future__ import annotations
 
@@ -13,6 +14,7 @@ from typing import Optional, Tuple
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libmx4.so")
+_MARSHAL_PATH = os.path.join(_HERE, "_marshal.so")
 
 MX_RULE_OCP, MX_RULE_FLOOR, MX_RULE_OAS = 0, 1, 2
 MX_OUT_F32, MX_OUT_BF16 = 0, 1
@@ -154,16 +156,16 @@ def _gemm_forced(where, shape, a, b, grouped, num_groups, row_offsets, M, N, K, 
 
 
 # ---- helpers ---------------------------------------------------------------------------------------
-# The marshalling stands in front of kernels of a few microseconds, so it is kept short: a call costs about 6 us of host
-# time, 3.5 to 4.3 of which are the C call with its launch (13 us when every call imported torch again, built a Stream object to
-# read its handle, 3 us by itself, compared shapes as tuples and went through closures).
+# The marshalling stands in front of kernels of a few microseconds, so it is kept short: natively a call costs about 3.3 us of host
+# time, nearly all of it the launch; through ctypes and the checks below 5.5 (quantizer and GEMM in a row 7.2 and 13.7).
 _torch_module = None
 _stream_handle = _stream_device = None  # torch's calls for the current stream's handle and the current device, if it has them
+_native = None                          # the native marshaller, once torch is there
 _out_dtypes = {}                        # what a caller may pass as an output type -> (type code, torch dtype)
 
 
 def _torch():
-    global _torch_module, _stream_handle, _stream_device
+    global _torch_module, _stream_handle, _stream_device, _native
     if _torch_module is None:
         import torch
 
@@ -172,8 +174,37 @@ def _torch():
         for names, value in (((MX_OUT_F32, "f32", "fp32", torch.float32), (MX_OUT_F32, torch.float32)),
                              ((MX_OUT_BF16, "bf16", torch.bfloat16), (MX_OUT_BF16, torch.bfloat16))):
             _out_dtypes.update((name, value) for name in names)
+        _native = _load_native()
         _torch_module = torch
     return _torch_module
+
+
+# (in the order in which csrc_host/marshal.cpp keeps the addresses)
+_NATIVE_CALLS = ("mx_quantize", "mx_quantize_mbs", "mx_quantize_mbs_pair", "mx_quantize_mbs_dynamic", "mx_quantize_elem", "mx_dequantize", "mx_gemm",
+                 "mx_gemm_mbs", "mx_gemm_mbs_grouped", "mx_gemm_mbs_quantize_a", "mx_gemm_mbs_elem", "mx_gemm_mbs_elem_grouped")
+
+
+def _load_native():
+    """The native marshaller (the build step makes it beside libmx4.so); without it every call goes through ctypes."""
+    if not os.path.exists(_MARSHAL_PATH):
+        return None
+    import importlib.machinery
+    import importlib.util
+
+    L = load_library()
+    loader = importlib.machinery.ExtensionFileLoader("_marshal", _MARSHAL_PATH)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_marshal", _MARSHAL_PATH, loader=loader))
+    loader.exec_module(module)
+    module.use(*(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in _NATIVE_CALLS))
+    return module
+
+
+def _done(status, where: str) -> bool:
+    """Whether the native marshaller has made the call (None: it declined)."""
+    if status is None:
+        return False
+    _check(status, where)
+    return True
 
 
 def _rule(rule) -> int:
@@ -245,6 +276,9 @@ def _alloc_outputs(x, rows, K, codes, scales, mbs, want_mbs):
 # ---- entry points ----------------------------------------------------------------------------------
 def mx_quantize(x, rule="ocp", codes=None, scales=None):
     """bf16 [rows, K] -> (codes uint8 [rows, K/2], scales uint8 [rows, K/32]) with `rule`, no MBS."""
+    if _native is not None and scales is not None and not getattr(_dev, "choices", None) and _done(
+            _native.quantize(x, rule, codes, scales), "mx_quantize"):
+        return codes, scales
     rows, K, ldx = _rows_ld(x)
     codes, scales, _ = _alloc_outputs(x, rows, K, codes, scales, None, False)
     hw = _forced("quantize_hw")
@@ -270,6 +304,9 @@ def mx_quantize_oas(x, codes=None, scales=None):
 
 def mx_quantize_mbs(x, rule="oas", codes=None, scales=None, mbs=None):
     """MBS-Static quantization -> (codes, scales, mbs uint8 [rows, ceil(K/128)])."""
+    if _native is not None and mbs is not None and not getattr(_dev, "choices", None) and _done(
+            _native.quantize_mbs(x, rule, codes, scales, mbs), "mx_quantize_mbs"):
+        return codes, scales, mbs
     rows, K, ldx = _rows_ld(x)
     codes, scales, mbs = _alloc_outputs(x, rows, K, codes, scales, mbs, True)
     hw = _forced("quantize_hw")
@@ -283,6 +320,9 @@ def mx_quantize_mbs(x, rule="oas", codes=None, scales=None, mbs=None):
 
 def mx_quantize_mbs_pair(x0, x1, rule="oas", out0=None, out1=None):
     """MBS-Static quantization of two tensors with the same K in one launch -> ((codes, scales, mbs), (...))."""
+    if _native is not None and type(out0) is tuple and type(out1) is tuple and _done(
+            _native.quantize_mbs_pair(x0, x1, rule, *out0, *out1), "mx_quantize_mbs_pair"):
+        return out0, out1
     rows0, K, ld0 = _rows_ld(x0)
     rows1, K1, ld1 = _rows_ld(x1)
     if K != K1:
@@ -298,6 +338,9 @@ def mx_quantize_mbs_pair(x0, x1, rule="oas", out0=None, out1=None):
 def mx_quantize_mbs_dynamic(x, rule="oas", cand_first=0, cand_count=16, cand_stride=16, codes=None, scales=None,
                             mbs=None):
     """MBS-Dynamic quantization (searched word per 1x128 window) -> (codes, scales, mbs)."""
+    if _native is not None and mbs is not None and not getattr(_dev, "choices", None) and _done(
+            _native.quantize_mbs_dynamic(x, rule, cand_first, cand_count, cand_stride, codes, scales, mbs), "mx_quantize_mbs_dynamic"):
+        return codes, scales, mbs
     rows, K, ldx = _rows_ld(x)
     codes, scales, mbs = _alloc_outputs(x, rows, K, codes, scales, mbs, True)
     _check((_lib or load_library()).mx_quantize_mbs_dynamic(_ptr(x), rows, K, ldx, _rule(rule), int(cand_first),
@@ -367,6 +410,8 @@ def _matrix(rows, cols, out_dtype, out, device, what):
 
 
 def mx_dequantize(codes, scales, mbs=None, out_dtype="f32", out=None):
+    if _native is not None and out is not None and _done(_native.dequantize(codes, scales, mbs, out_dtype, out), "mx_dequantize"):
+        return out
     shape = codes.shape
     rows, K = shape[0], shape[1] * 2
     code, out, ldo = _matrix(rows, K, out_dtype, out, codes.device,
@@ -382,6 +427,9 @@ def _c_tensor(M, N, out_dtype, out, device):
 
 def mx_gemm(a_codes, a_scales, b_codes, b_scales, out_dtype="f32", out=None):
     """Plain MXFP4 GEMM: C[M,N] = A[M,K] . B[N,K]^T."""
+    if _native is not None and out is not None and not getattr(_dev, "choices", None) and _done(
+            _native.gemm(a_codes, a_scales, b_codes, b_scales, out_dtype, out), "mx_gemm"):
+        return out
     a_shape, b_shape = a_codes.shape, b_codes.shape
     M, half, N = a_shape[0], a_shape[1], b_shape[0]
     if b_shape[1] != half:
@@ -399,6 +447,9 @@ def mx_gemm(a_codes, a_scales, b_codes, b_scales, out_dtype="f32", out=None):
 
 def mx_gemm_mbs(a_codes, a_scales, a_mbs, b_codes, b_scales, b_mbs, out_dtype="f32", out=None):
     """GEMM with the per-macro-block MBS correction; a_mbs / b_mbs may be None."""
+    if _native is not None and out is not None and not getattr(_dev, "choices", None) and _done(
+            _native.gemm_mbs(a_codes, a_scales, a_mbs, b_codes, b_scales, b_mbs, out_dtype, out), "mx_gemm_mbs"):
+        return out
     a_shape, b_shape = a_codes.shape, b_codes.shape
     M, half, N = a_shape[0], a_shape[1], b_shape[0]
     if b_shape[1] != half:
@@ -422,6 +473,9 @@ def elem_code_bytes(elem, K: int) -> int:
 
 def mx_quantize_elem(x, elem="e4m3", rule="oas", use_mbs=True, codes=None, scales=None, mbs=None):
     """Quantize into an 8-bit (codes one per byte) or 6-bit (packed) MX element format, with or without MBS words."""
+    if _native is not None and scales is not None and not getattr(_dev, "choices", None) and _done(
+            _native.quantize_elem(x, elem, rule, use_mbs, codes, scales, mbs), "mx_quantize_elem"):
+        return codes, scales, (mbs if use_mbs else None)
     rows, K, ldx = _rows_ld(x)
     codes, scales, mbs = _outputs(x, rows, K, elem_code_bytes(elem, K), codes, scales, mbs, use_mbs)
     hw = _forced("quantize_elem_hw")
@@ -464,6 +518,9 @@ def mx_dequantize_elem(elem, codes, scales, mbs=None, out_dtype="f32", out=None)
 def mx_gemm_mbs_elem(a_elem, a_codes, a_scales, a_mbs, b_elem, b_codes, b_scales, b_mbs, out_dtype="f32", out=None):
     """GEMM with the MBS correction for operands in 8-bit or (packed) 6-bit MX element formats; a_mbs / b_mbs may
     be None.  K is taken from the scale arrays."""
+    if _native is not None and out is not None and not getattr(_dev, "choices", None) and _done(
+            _native.gemm_mbs_elem(a_elem, a_codes, a_scales, a_mbs, b_elem, b_codes, b_scales, b_mbs, out_dtype, out), "mx_gemm_mbs_elem"):
+        return out
     M, N, K = a_codes.shape[0], b_codes.shape[0], a_scales.shape[1] * 32
     if b_scales.shape[1] * 32 != K or a_codes.shape[1] != elem_code_bytes(a_elem, K) or b_codes.shape[1] != elem_code_bytes(b_elem, K):
         raise ValueError("A and B disagree on K, or a code array does not have the row length of its format")
@@ -485,6 +542,9 @@ def mx_gemm_mbs_elem_grouped(a_elem, a_codes, a_scales, a_mbs, b_elem, b_codes, 
                              out_dtype="f32", out=None):
     """Grouped GEMM for operands in 8-bit or 6-bit element formats: rows row_offsets[e]..row_offsets[e+1]-1 of A
     times B_e^T, B stacked [G*N, ...]."""
+    if _native is not None and out is not None and not getattr(_dev, "choices", None) and _done(
+            _native.gemm_mbs_elem_grouped(a_elem, a_codes, a_scales, a_mbs, b_elem, b_codes, b_scales, b_mbs, row_offsets, N, out_dtype, out), "mx_gemm_mbs_elem_grouped"):
+        return out
     torch = _torch_module or _torch()
     M, K = a_codes.shape[0], a_scales.shape[1] * 32
     if row_offsets.dtype != torch.int64 or not row_offsets.is_cuda or not row_offsets.is_contiguous():
@@ -502,6 +562,9 @@ def mx_gemm_mbs_elem_grouped(a_elem, a_codes, a_scales, a_mbs, b_elem, b_codes, 
 
 def mx_gemm_mbs_quantize_a(a, rule, b_codes, b_scales, b_mbs, out_dtype="f32", out=None, a_use_mbs=True):
     """Few-row GEMM with the bf16 activations `a` [M, K] quantized inside the kernel (M <= 64)."""
+    if _native is not None and out is not None and not getattr(_dev, "choices", None) and _done(
+            _native.gemm_mbs_quantize_a(a, rule, a_use_mbs, b_codes, b_scales, b_mbs, out_dtype, out), "mx_gemm_mbs_quantize_a"):
+        return out
     M, K, lda = _rows_ld(a)
     N = b_codes.shape[0]
     if b_codes.shape[1] * 2 != K:
@@ -516,6 +579,9 @@ def mx_gemm_mbs_quantize_a(a, rule, b_codes, b_scales, b_mbs, out_dtype="f32", o
 def mx_gemm_mbs_grouped(a_codes, a_scales, a_mbs, b_codes, b_scales, b_mbs, row_offsets, N, out_dtype="f32",
                         out=None):
     """Grouped GEMM: rows row_offsets[e]..row_offsets[e+1]-1 of A times B_e^T, B stacked [G*N, K]."""
+    if _native is not None and out is not None and not getattr(_dev, "choices", None) and _done(
+            _native.gemm_mbs_grouped(a_codes, a_scales, a_mbs, b_codes, b_scales, b_mbs, row_offsets, N, out_dtype, out), "mx_gemm_mbs_grouped"):
+        return out
     torch = _torch_module or _torch()
     M, K = a_codes.shape[0], a_codes.shape[1] * 2
     if row_offsets.dtype != torch.int64 or not row_offsets.is_cuda or not row_offsets.is_contiguous():

@@ -1,4 +1,5 @@
-"""Build step: compile the HIP sources under csrc/ into libmx4.so for gfx950 with hipcc."""
+"""Build step: compile the HIP sources under csrc/ into libmx4.so for gfx950 with hipcc, and the binding's native marshaller
+under csrc_host/ into _marshal.so with g++."""
 from __future__ import annotations
 
 import glob
@@ -16,6 +17,10 @@ LIB = os.path.join(HERE, "libmx4.so")
 # measurement aids of bench.py (yardstick kernels that allocate their own buffers): a library of their own
 BENCH_CSRC = os.path.join(HERE, "bench_csrc")
 BENCH_LIB = os.path.join(HERE, "libmx4_bench.so")
+
+# the binding's native marshaller: host code against the headers of the torch that is installed
+MARSHAL_SRC = os.path.join(HERE, "csrc_host", "marshal.cpp")
+MARSHAL_LIB = os.path.join(HERE, "_marshal.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -50,6 +55,18 @@ def _run(cmd, verbose):
         print(out)
 
 
+def _marshal_command(out):
+    import sysconfig
+
+    import torch
+
+    top = os.path.dirname(torch.__file__)
+    include = [os.path.join(ROOT, "include"), os.path.join(top, "include"), os.path.join(top, "include", "torch", "csrc", "api", "include"),
+               os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"), sysconfig.get_paths()["include"]]
+    return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1"]
+            + [a for i in include for a in ("-I", i)] + [MARSHAL_SRC, "-L", os.path.join(top, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-o", out])
+
+
 def build(verbose: bool = False) -> str:
     work = tempfile.mkdtemp(prefix="mx4_build_")
     try:
@@ -60,6 +77,8 @@ def build(verbose: bool = False) -> str:
             obj = os.path.join(work, name + ".o")
             objs.append(obj)
             jobs.append([HIPCC] + FLAGS + EXTRA.get(name, VGPR_FORM) + ["-c", src, "-o", obj])
+        marshal = os.path.join(work, "_marshal.so")
+        jobs.append(_marshal_command(marshal))
         with ThreadPoolExecutor(max_workers=min(8, len(jobs))) as pool:
             list(pool.map(lambda c: _run(c, verbose), jobs))
         tmp = os.path.join(work, "libmx4.so")
@@ -70,6 +89,7 @@ def build(verbose: bool = False) -> str:
         if missing:
             raise RuntimeError("libmx4.so has unresolved symbols: " + ", ".join(missing))
         shutil.move(tmp, LIB)
+        shutil.move(marshal, MARSHAL_LIB)
         bench_srcs = sorted(glob.glob(os.path.join(BENCH_CSRC, "*.hip")))
         tmp = os.path.join(work, "libmx4_bench.so")
         _run([HIPCC] + FLAGS + ["-shared"] + bench_srcs + ["-o", tmp], verbose)
