@@ -643,7 +643,7 @@ __global__ __launch_bounds__((F8Shape<kFast, kTile>::NT)) void gemm_f8_kernel(Ge
         constexpr int lanes_per_row = kCols * esz / 16, rows_per_pass = kWave / lanes_per_row;
         const int rd_row = l / lanes_per_row, rd_chunk = l % lanes_per_row;
         const int64_t n = n0 + rd_chunk * per;
-        const bool whole = n + per <= g.N;
+        const bool whole = n + per <= g.N, whole16 = whole && g.vec_store16;
         static_for<FM>([&](auto i_) {
             constexpr int i = decltype(i_)::value;
             static_for<FN * 4>([&](auto q_) {
@@ -662,11 +662,12 @@ __global__ __launch_bounds__((F8Shape<kFast, kTile>::NT)) void gemm_f8_kernel(Ge
                 const int64_t m = m0 + i * 32 + row;
                 if (m < a_end && n < g.N) {
                     uint8_t* o = static_cast<uint8_t*>(g.C) + (m * g.ldc + n) * esz;
-                    if (whole) {
+                    if (whole16) {
+                        __builtin_nontemporal_store(v, reinterpret_cast<v4i*>(o));
+                    } else if (whole) {
                         // (any element: the device serves 16-byte stores at any address; element by element 818 x 3907 x 1152 in
                         // E2M3 with the quantizer took 22.4 us instead of 15.8)
-                        if (g.vec_store16) __builtin_nontemporal_store(v, reinterpret_cast<v4i*>(o));
-                        else *reinterpret_cast<v4i_any*>(o) = v;
+                        *reinterpret_cast<v4i_any*>(o) = v;
                     } else {
 #pragma unroll
                         for (int e = 0; e < per; ++e)

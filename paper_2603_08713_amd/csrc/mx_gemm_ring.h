@@ -909,7 +909,7 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
         constexpr int lanes_per_row = kCols * esz / 16, rows_per_pass = kWave / lanes_per_row;
         const int rd_row = l / lanes_per_row, rd_chunk = l % lanes_per_row;
         const int64_t n = n0 + rd_chunk * per;
-        const bool whole = n + per <= g.N;
+        const bool whole = n + per <= g.N, whole16 = whole && g.vec_store16;
         static_for<FM>([&](auto i_) {
             constexpr int i = decltype(i_)::value;
             static_for<FN * 4>([&](auto q_) {
@@ -928,13 +928,14 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
                 const int64_t m = m0 + i * 32 + row;
                 if (m < a_end && n < g.N) {
                     uint8_t* o = static_cast<uint8_t*>(g.C) + (m * g.ldc + n) * esz;
-                    if (whole) {
+                    if (whole16) {
+                        __builtin_nontemporal_store(v, reinterpret_cast<v4i*>(o));
+                    } else if (whole) {
                         // Rows of C start on any element: the device serves 16-byte stores at any address, so an odd N costs what an
                         // even one does.  (Element by element the store bound such calls: with the quantizer, bf16, 949 x 7899 x 512
                         // 25.2 -> 14.6 us, 2883 x 13259 x 4096 190 -> 141.)  Unaligned stores share lines with their neighbours, so
                         // they are not marked non-temporal.
-                        if (g.vec_store16) __builtin_nontemporal_store(v, reinterpret_cast<v4i*>(o));
-                        else *reinterpret_cast<v4i_any*>(o) = v;
+                        *reinterpret_cast<v4i_any*>(o) = v;
                     } else {
 #pragma unroll
                         for (int e = 0; e < per; ++e)
