@@ -15,7 +15,8 @@ namespace {
 // force_shape (mx_internal_gemm only; the public entry points pass -1 = automatic): 2 / 6 / 7 = fast form without
 // MBS on 256x256 / 256x128 / 128x128 tiles, 3 / 4 = fast form with MBS on 256x128 / 128x128 tiles, 5 = few-row
 // kernel, 8 / 9 = general form (row pieces through registers) on 256x128 / 128x128 tiles, 10 = general form (single bytes, any K:
-// K = 0) on 128x128 tiles, 11 / 12 = fast form with MBS on both operands / general form with MBS on 64x128 tiles.
+// K = 0) on 128x128 tiles, 11 / 12 = fast form with MBS on both operands / general form with MBS on 64x128 tiles, 17 / 18 / 19 = few-row
+// kernel on tiles of 64 rows and 16 / 32 / 64 columns.
 // Grouped problems with words: what the kernels take, in us, from rows, groups and the number of macro blocks; the launch cannot know the
 // routing, so a group is taken to end half a tile-row short and every group to have rows.  Fitted to Zipf and equal routings over 8, 32
 // and 64 groups of 768, 1536 and 2880 squared with 4 to 4096 rows per group.
@@ -52,11 +53,13 @@ bool grouped_small_tile(int64_t M, int64_t N, int64_t K, int64_t num_groups) {
 // The general form fetches a row's pieces through registers, which any K % 32 == 0 at any address can use: it costs what the fast form
 // does, where single bytes (K % 64 = 32 once took them) keep the texture-address unit busy three times as long as the codes and leave
 // LDS for 128 x 128 tiles only.  With the quantizer: 305 x 1205 x 1632 21.8 -> 13.3 us, 5680 x 1130 x 6880 110 -> 75.
-int choose_shape(int64_t M, int64_t N, int64_t K, int64_t num_groups, bool use_mbs, bool ring_ok, bool skinny_ok, bool tile64_ok) {
+int choose_shape(int64_t M, int64_t N, int64_t K, int64_t num_groups, bool use_mbs, bool ring_ok, bool skinny_ok, int row_tile_cols,
+                 bool tile64_ok) {
     const int64_t t256x128 = ((M + 255) / 256) * ((N + 127) / 128), t128 = ((M + 127) / 128) * ((N + 127) / 128);
     const double big = 2.0 * ((t256x128 + 255) / 256) / (use_mbs ? 1.0 : 0.85),
                  small = ((t128 + 255) / 256) / (use_mbs ? 0.8 : 0.72);
     if (skinny_ok) return 5;
+    if (row_tile_cols > 0) return row_tile_cols == 16 ? 17 : row_tile_cols == 32 ? 18 : 19;
     if (num_groups > 0 && use_mbs && K > 0) return grouped_small_tile(M, N, K, num_groups) ? 12 : 8;
     if (tile64_ok && ((M + 63) / 64) * ((N + 127) / 128) <= 256 && K > 0) return ring_ok ? 11 : 12;
     if (ring_ok) return use_mbs ? (big <= small ? 3 : 4) : 2;  // (without MBS the launcher also has 256 x 256 tiles)
@@ -125,6 +128,23 @@ bool takes_few_rows(int64_t M, int64_t N, int64_t K, int64_t num_groups, bool ri
     return M <= 64 && K <= 8192 && few_rows_pay(M, N, K, plan_skinny(M, N, K, ring_ok, pairs_ok), use_mbs);
 }
 
+// More than 64 rows on the few-row kernel: the columns of its tiles of 64 rows (0: the main kernel).  Its eight wavefronts share K and
+// meet no barrier, so a small output with a long K, which leaves most compute units idle on the main kernel's tiles and runs one
+// stage of K after the other there, takes a fraction of the time, as long as one round of workgroups covers it.  The wider the tile, the
+// longer K has to be.  Main kernel (64 x 128 tiles) and this one, words on both sides, us, K = 512, 2048, 4096, 8192:
+//   512 x 512    4.6, 8.1, 14.3, 26.1   16 columns 4.5, 6.0, 7.2, 11.9
+//   512 x 1024   4.8, 8.8, 15.4, 26.3   16 columns (two rounds) 5.4, 8.0, 10.2, 18.9   32 columns 5.0, 7.1, 8.9, 13.9
+//   1024 x 1024  4.9, 9.5, 15.9, 27.1   32 columns (two rounds) 8.1, 12.0, 15.8, 25.0  64 columns 6.7, 9.7, 12.7, 20.3
+// without words 512 x 1024 4.6, 6.7, 13.0, 22.2 and 32 columns 4.6, 6.2, 7.6, 11.8; K = 1056 (single bytes, 16 columns) 512 x 512 7.2 and 5.7.
+int row_tile_columns(int64_t M, int64_t N, int64_t K, int64_t num_groups, bool ring_ok, bool pairs_ok) {
+    if (num_groups > 0 || M <= 64 || K < 512 || K > 8192) return 0;
+    const int64_t rows = (M + 63) / 64, frags = (N + 15) / 16;
+    if (rows * frags <= 256) return 16;
+    if (rows * ((frags + 1) / 2) <= 256 && (ring_ok || pairs_ok) && K >= 768) return 32;
+    if (rows * ((frags + 3) / 4) <= 256 && ring_ok && K >= 3072) return 64;
+    return 0;
+}
+
 int launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* a_mbs, const uint8_t* b_codes,
                 const uint8_t* b_scales, const uint8_t* b_mbs, int num_groups, const int64_t* row_offsets,
                 bool grouped, int64_t M, int64_t N, int64_t K, int c_dtype, void* C, int64_t ldc, bool mbs_entry,
@@ -162,7 +182,7 @@ int launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* 
     const bool pairs_ok = K > 0 && (K % 64) == 0 && aligned(a_scales, 2) && aligned(b_scales, 2);
     const bool skinny_ok = takes_few_rows(M, N, K, g.num_groups, ring_ok, pairs_ok, use_mbs);
     const bool tile64_ok = !grouped && a_mbs && b_mbs && mbs_entry;
-    int shape = choose_shape(M, N, K, g.num_groups, use_mbs, ring_ok, skinny_ok, tile64_ok);
+    int shape = choose_shape(M, N, K, g.num_groups, use_mbs, ring_ok, skinny_ok, row_tile_columns(M, N, K, g.num_groups, ring_ok, pairs_ok), tile64_ok);
     if (force_shape >= 0) shape = force_shape;
     // (the checks below only matter for forced shapes)
     if (shape == 5) {
@@ -170,6 +190,10 @@ int launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* 
         if (grouped) return launch_gemm_skinny_grouped(g, use_mbs, !pairs_ok, s);
         const SkinnyPlan p = plan_skinny(M, N, K, ring_ok, pairs_ok);
         return launch_gemm_skinny_tile(g, use_mbs, p.fm, p.fn, p.form, s);
+    }
+    if (shape >= 17 && shape <= 19) {
+        if (grouped || K == 0 || K > 8192) return MX_EINVAL;
+        return launch_gemm_skinny_tile(g, use_mbs, 4, shape == 17 ? 1 : shape == 18 ? 2 : 4, plan_skinny(64, N, K, ring_ok, pairs_ok).form, s);
     }
     if (shape == 11 || shape == 12) {
         if (!use_mbs || (shape == 11 ? !ring_ok || !a_mbs || !b_mbs : K == 0)) return MX_EINVAL;
@@ -250,6 +274,7 @@ int mx_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int a_has_mbs, int b_
     const bool use_mbs = a_has_mbs || b_has_mbs, grouped = num_groups > 0;
     const bool ring_ok = !grouped && K > 0 && (K % 512) == 0, pairs_ok = K > 0 && (K % 64) == 0;
     const int shape = mx::choose_shape(M, N, K, num_groups, use_mbs, ring_ok, mx::takes_few_rows(M, N, K, num_groups, ring_ok, pairs_ok, use_mbs),
+                                       mx::row_tile_columns(M, N, K, num_groups, ring_ok, pairs_ok),
                                        !grouped && a_has_mbs && b_has_mbs);
     const char* sides = a_has_mbs && b_has_mbs ? "MBS words on A and B" : a_has_mbs ? "MBS words on A" : b_has_mbs ? "MBS words on B" : "no MBS";
     const char* what;
@@ -259,6 +284,9 @@ int mx_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int a_has_mbs, int b_
                                               : "gemm_ring_kernel, fast form, 256x128 tile, 8 wavefronts of 128x32"; break;
         case 4: what = "gemm_ring_kernel, fast form, 128x128 tile, 8 wavefronts of 64x32"; break;
         case 5: what = grouped ? "gemm_skinny_grouped_kernel (few rows per group)" : "gemm_skinny_kernel (few rows)"; break;
+        case 17: what = "gemm_skinny_kernel, tiles of 64 rows and 16 columns"; break;
+        case 18: what = "gemm_skinny_kernel, tiles of 64 rows and 32 columns"; break;
+        case 19: what = "gemm_skinny_kernel, tiles of 64 rows and 64 columns"; break;
         case 11: what = "gemm_ring_kernel, fast form, 64x128 tile, 4 wavefronts of 64x32"; break;
         case 12: what = "gemm_ring_kernel, general form (row pieces through registers), 64x128 tile, 4 wavefronts of 64x32"; break;
         case 10: what = "gemm_ring_kernel, general form (single scale bytes), 128x128 tile"; break;

@@ -50,8 +50,8 @@ int launch_gemm_mbs_ring(const GemmArgs& g, int variant, hipStream_t s);
 // bytes: E8M0 bytes fetched one at a time (needed when K = 0; 128 x 128 tiles only).
 int launch_gemm_mbs_general(const GemmArgs& g, int tile, bool bytes, hipStream_t s);
 int launch_gemm_wide_general(const GemmArgs& g, int tile, bool bytes, hipStream_t s);
-// Few activation rows (mx_gemm_skinny.h): M <= 64, not grouped; fm, fn = fragments of 16 rows of A and of B per
-// workgroup, form as there (mx_gemm_skinny.hip).
+// Few activation rows (mx_gemm_skinny.h), not grouped; fm, fn = fragments of 16 rows of A and of B per
+// workgroup (as many row tiles as M has), form as there (mx_gemm_skinny.hip).
 int launch_gemm_skinny_tile(const GemmArgs& g, bool use_mbs, int fm, int fn, int form, hipStream_t s);
 // The same with A given as bf16 [M, ldx] and quantized inside the kernel (mx_gemm_skinny_fused.hip): rule, MBS-Static words
 // if a_mbs; the a_* members of g are not used.  Also requires K % 512 == 0, x 16-byte aligned, ldx % 8 == 0 and the rows

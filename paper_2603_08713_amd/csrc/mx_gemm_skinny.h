@@ -577,25 +577,26 @@ __device__ __forceinline__ void skinny_tile(const SkinnyArgs& args, uint8_t* sme
     }
 }
 
-// M <= 16 FM rows; a workgroup per column tile.
+// A workgroup per tile of 16 FM rows and 16 FN columns (fused: M <= 16 FM rows).
 template <int NW, int FM, int FN, bool kFused, int kForm, bool kSingle, bool kWords>
 __global__ __launch_bounds__(NW * kWave) void gemm_skinny_kernel(SkinnyArgs args) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const int64_t n0 = (int64_t)blockIdx.x * (16 * FN);
-    skinny_tile<NW, FM, FN, kFused, kForm, kSingle, kWords>(args, smem, 0, args.g.M, n0, args.g.N, n0);
+    const int64_t m0 = kFused ? 0 : (int64_t)blockIdx.y * (16 * FM);
+    skinny_tile<NW, FM, FN, kFused, kForm, kSingle, kWords>(args, smem, m0, kFused ? args.g.M : min(args.g.M, m0 + 16 * FM), n0, args.g.N, n0);
 }
 
 template <int NW, int FM, int FN, bool kFused, int kForm>
 int launch_skinny_variant(const SkinnyArgs& a, hipStream_t s) {
     const GemmArgs& g = a.g;
-    const int64_t blocks = (g.N + 16 * FN - 1) / (16 * FN);
-    if (g.M > 16 * FM || blocks > (int64_t)1 << 30) return MX_EINVAL;
+    const int64_t blocks = (g.N + 16 * FN - 1) / (16 * FN), row_tiles = kFused ? 1 : (g.M + 16 * FM - 1) / (16 * FM);
+    if ((kFused && g.M > 16 * FM) || blocks > (int64_t)1 << 30 || row_tiles > 65535) return MX_EINVAL;
     using S = SkinnyShape<NW, FM, FN, kFused, kForm>;
     auto launch = [&](auto single_, auto words_) {
         auto* fn = gemm_skinny_kernel<NW, FM, FN, kFused, kForm, decltype(single_)::value, decltype(words_)::value>;
         static LdsOptIn opt_in;  // one per kernel instantiation
         if (int st = opt_in.ensure(reinterpret_cast<const void*>(fn), S::kLdsBytes)) return st;
-        hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(S::NT), S::kLdsBytes, s, a);
+        hipLaunchKernelGGL(fn, dim3((unsigned)blocks, (unsigned)row_tiles), dim3(S::NT), S::kLdsBytes, s, a);
         return launch_status();
     };
     if (kFused && g.K > 2 * kSingleChunkK(NW)) return MX_EUNSUPPORTED;  // (the kernel takes two chunks at most)

@@ -19,7 +19,7 @@ int launch_form(const SkinnyArgs& a, int form, hipStream_t s) {
 
 }  // namespace
 
-// M <= 64 rows: fm, fn fragments of 16 rows of A and of B per workgroup; form as in mx_gemm_skinny.h
+// fm, fn fragments of 16 rows of A and of B per workgroup; form as in mx_gemm_skinny.h
 int launch_gemm_skinny_tile(const GemmArgs& g, bool use_mbs, int fm, int fn, int form, hipStream_t s) {
     SkinnyArgs a = {};
     a.g = g;
