@@ -62,6 +62,20 @@ int choose_shape(int64_t M, int64_t N, int64_t K, int64_t num_groups, bool use_m
     if (row_tile_cols > 0) return row_tile_cols == 16 ? 17 : row_tile_cols == 32 ? 18 : 19;
     if (num_groups > 0 && use_mbs && K > 0) return grouped_small_tile(M, N, K, num_groups) ? 12 : 8;
     if (tile64_ok && ((M + 63) / 64) * ((N + 127) / 128) <= 256 && K > 0) return ring_ok ? 11 : 12;
+    // Past one round, with words on both operands or in the general form: by the kernels' prices (mx_gemm_shared.h)
+    // (256 x 128, 128 x 128 and 64 x 128 tiles, us: 2316 x 3815 x 5120 65, 69, 60; 5676 x 1854 x 512 18.2, 19.0, 16.8;
+    // 1579 x 2784 x 1024 11.2, 14.6, 12.5; 1367 x 3890 x 7296 50, 73, 61)
+    if (K > 0 && more_than_a_round_of_64x128(M, N) && (tile64_ok || (!use_mbs && !ring_ok))) {
+        static const TilePrice kFast[3] = {{256, 128, 256, 0.7, 3.40, 0.003, 4.91, 0.726}, {128, 128, 256, 0.8, 2.72, 0.018, 3.26, 0.480}, {64, 128, 512, 0.4, 3.83, 0.098, 2.29, 0.453}};
+        static const TilePrice kGeneral[3] = {{256, 128, 256, 0.7, 2.82, 0.030, 5.48, 0.815}, {128, 128, 256, 0.8, 2.64, 0.021, 3.25, 0.592}, {64, 128, 512, 0.6, 3.27, 0.100, 2.81, 0.523}};
+        static const TilePrice kPlain[2] = {{256, 128, 256, 0.8, 3.27, -0.051, 4.71, 0.651}, {128, 128, 256, 0.4, 3.00, 0.146, 1.93, 0.313}};
+        if (!use_mbs) return kPlain[0].of(M, N, K) <= kPlain[1].of(M, N, K) ? 8 : 9;
+        const TilePrice* t = ring_ok ? kFast : kGeneral;
+        const double a = t[0].of(M, N, K), b = t[1].of(M, N, K), c = t[2].of(M, N, K);
+        if (a <= b && a <= c) return ring_ok ? 3 : 8;
+        if (b <= c) return ring_ok ? 4 : 9;
+        return ring_ok ? 11 : 12;
+    }
     if (ring_ok) return use_mbs ? (big <= small ? 3 : 4) : 2;  // (without MBS the launcher also has 256 x 256 tiles)
     return K == 0 ? 10 : big <= small ? 8 : 9;
 }
@@ -279,7 +293,7 @@ int mx_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int a_has_mbs, int b_
     const char* sides = a_has_mbs && b_has_mbs ? "MBS words on A and B" : a_has_mbs ? "MBS words on A" : b_has_mbs ? "MBS words on B" : "no MBS";
     const char* what;
     switch (shape) {
-        case 2: what = mx::describe_gemm_wide(M, N); break;
+        case 2: what = mx::describe_gemm_wide(M, N, K); break;
         case 3: what = a_has_mbs && b_has_mbs ? "gemm_ring_kernel, fast form, 256x128 tile, 8 wavefronts of 64x64"
                                               : "gemm_ring_kernel, fast form, 256x128 tile, 8 wavefronts of 128x32"; break;
         case 4: what = "gemm_ring_kernel, fast form, 128x128 tile, 8 wavefronts of 64x32"; break;

@@ -43,7 +43,7 @@ struct GemmArgs {
 // Main kernels (mx_gemm_ring.h), fast form: K % 512 == 0 and aligned scale and MBS arrays, not grouped; without MBS
 // (mx_gemm_wide.hip: 256 x 256, 256 x 128 or 128 x 128 tiles) and with MBS (mx_gemm_mbs.hip: 256 x 128 or 128 x 128).
 int launch_gemm_wide(const GemmArgs& g, int tile, hipStream_t s);
-const char* describe_gemm_wide(int64_t M, int64_t N);  // what launch_gemm_wide(tile = 0) does with an M x N problem
+const char* describe_gemm_wide(int64_t M, int64_t N, int64_t K);  // what launch_gemm_wide(tile = 0) does with a problem
 int launch_gemm_mbs_ring(const GemmArgs& g, int variant, hipStream_t s);
 // The same kernels in their general forms (any K % 32 == 0, any alignment of the scale arrays, grouped or not),
 // defined in mx_gemm_general.hip (with MBS) and mx_gemm_wide.hip (without).  tile: 0 = 256 x 128, 1 = 128 x 128;
@@ -76,6 +76,23 @@ int launch_gemm_six_tiny(const GemmArgs& g, bool a32, bool b32, bool use_mbs, hi
 int launch_gemm_six_small(const GemmArgs& g, bool a32, bool b32, bool use_mbs, hipStream_t s);
 int launch_gemm_six(const GemmArgs& g, bool a32, bool b32, bool use_mbs, bool force_general, hipStream_t s);
 int launch_gemm_skinny_elem(const GemmArgs& g, int a_elem, int b_elem, hipStream_t s);
+
+// What a kernel of the main template takes for a problem that is not grouped and has more than one round of 64 x 128 tiles, in us:
+// c0 + c1 st + x (c2 + c3 st) with st stages of K and x rounds of `tiles` tiles of rows x cols, of which a part costs `part` of a
+// whole one and the rest in proportion.  Fitted to 75 problems of 65 to 8190 rows, 300 to 15000 columns and K from 512 to 8192 (even
+// and odd ones, weights from memory): 3 to 7 % off in the mean, 10 % for the kernels without words, and the cheapest by these prices is
+// 0.3 to 0.9 % slower than the fastest of the kernels, where rounds x area at one rate per tile shape was 5 (with words) to 11 % (without).
+struct TilePrice {
+    int rows, cols, tiles;
+    double part, c0, c1, c2, c3;
+    double of(int64_t M, int64_t N, int64_t K) const {
+        const double st = (double)((K + kMacro - 1) / kMacro);
+        const int64_t all = ((M + rows - 1) / rows) * ((N + cols - 1) / cols), whole = all / tiles, rest = all % tiles;
+        const double x = (double)whole + (rest ? part + (1.0 - part) * rest / tiles : 0.0);
+        return c0 + c1 * st + x * (c2 + c3 * st);
+    }
+};
+inline bool more_than_a_round_of_64x128(int64_t M, int64_t N) { return ((M + 63) / 64) * ((N + 127) / 128) > 256; }
 
 namespace {
 

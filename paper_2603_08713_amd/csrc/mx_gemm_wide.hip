@@ -14,7 +14,7 @@ namespace mx {
 // launches where that saves time: 256 x 256 tiles for as many columns as make whole rounds, 256 x 128 tiles
 // (half the cost each) for the rest.
 //
-// Problems with too few large tiles for the device take 256 x 128 or 128 x 128 tiles throughout (four
+// Problems with too few large tiles for the device, or with short K, take 256 x 128 or 128 x 128 tiles throughout (four
 // wavefronts of 128 x 64 or 64 x 64).
 //
 // tile: 0 = choose, 1 = 256 x 256 only, 2 = 256 x 128 only, 3 = 128 x 128 only (development switch).
@@ -32,8 +32,16 @@ struct WidePlan {
     int64_t big_cols, cols;
 };
 
-WidePlan plan_wide(int64_t M, int64_t N, int tile) {
-    if (tile == 0) {
+WidePlan plan_wide(int64_t M, int64_t N, int64_t K, int tile) {
+    if (tile == 0 && more_than_a_round_of_64x128(M, N)) {
+        // (short K: the small tile's stores and prologues overlap with other workgroups' stages.  256 x 256 and 128 x 128 tiles, us: 8026 x
+        // 3161 x 512 30.5 and 21.4, 1354 x 6828 x 512 18.8 and 12.1, 3619 x 2698 x 2048 27.3 and 20.9)
+        static const TilePrice kMain = {256, 256, 256, 0.6, 6.60, 0.004, 9.82, 0.803}, kTail = {256, 128, 256, 0.7, 4.65, -0.016, 4.25, 0.533},
+                               kSmall = {128, 128, 256, 0.3, 4.38, 0.103, 1.395, 0.274};
+        const double a = kMain.of(M, N, K), b = kTail.of(M, N, K), c = kSmall.of(M, N, K);
+        if (b < a && b <= c) return {2, 0, 0};
+        if (c < a) return {3, 0, 0};
+    } else if (tile == 0) {
         // Tiles run in rounds of one per compute unit.  Cost of a launch in units of a 128 x 128 tile's time:
         // rounds x tile area / efficiency, the smaller tiles reaching about 0.85 and 0.78 of the large tile's
         // rate per output (measured; 0.72 is used for the smallest so that an underfilled round of large tiles keeps its edge); the large tile wins ties, and only it is split over two launches.
@@ -62,8 +70,8 @@ WidePlan plan_wide(int64_t M, int64_t N, int tile) {
 
 }  // namespace
 
-const char* describe_gemm_wide(int64_t M, int64_t N) {
-    const WidePlan p = plan_wide(M, N, 0);
+const char* describe_gemm_wide(int64_t M, int64_t N, int64_t K) {
+    const WidePlan p = plan_wide(M, N, K, 0);
     if (p.tile == 2) return "gemm_ring_kernel, fast form, 256x128 tile, 4 wavefronts of 128x64";
     if (p.tile == 3) return "gemm_ring_kernel, fast form, 128x128 tile, 4 wavefronts of 64x64";
     if (p.big_cols == p.cols) return "gemm_ring_kernel, fast form, 256x256 tile, 4 wavefronts of 128x128";
@@ -72,7 +80,7 @@ const char* describe_gemm_wide(int64_t M, int64_t N) {
 }
 
 int launch_gemm_wide(const GemmArgs& g, int tile, hipStream_t s) {
-    const WidePlan p = plan_wide(g.M, g.N, tile);
+    const WidePlan p = plan_wide(g.M, g.N, g.K, tile);
     if (p.tile == 2) return launch_ring<Tail>(g, s);
     if (p.tile == 3) return launch_ring<Small>(g, s);
     if (p.big_cols == p.cols) return launch_ring<Main>(g, s);
