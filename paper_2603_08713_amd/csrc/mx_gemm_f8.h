@@ -706,12 +706,16 @@ int launch_f8_kernel(GemmArgs g, hipStream_t s) {
 // One round of 64 x 128 tiles takes them: a stage's serial chain bounds such a problem, and it is shortest there.  GEMM alone, 128 x 128
 // and 64 x 128 tiles, us: 512 x 4096 x 4096 in E4M3 24.0 and 19.7, without words 18.8 and 15.3, in E2M3 23.0 and 20.0; 1024 x 2048 x 576
 // 8.3 and 7.2; two rounds 512 x 8192 x 2048 15.0 and 16.9.
-// Otherwise tiles run in rounds of one per compute unit: rounds x tile area / efficiency, the 128 x 128 tile taken at 0.75 of
-// the large one's rate per output, 0.55 without words (it reads as many bytes a stage for half the products).  GEMM alone, rounds of large
-// and of small tiles, K = 1536 and 4096, us large and small: 1 and 1 (2048 x 2048) E4M3 16.9, 13.2 and 34.0, 26.7, without words 12.5, 10.7
-// and 26.3, 21.1; 2 and 2 (896 x 9344) 33.2, 25.6 and 72.2, 57.6, without 27.5, 23.4 and 56.4, 48.3; 2 and 3 (600 x 19200)
-// 34.5, 37.3 and 78.1, 84.4, without 27.9, 34.3 and 58.3, 71.2; 3 and 4 (384 x 38400) 52.9, 51.3 and 116, 112, without 43.0, 45.4 and
-// 88.3, 97.0; the 6-bit formats the same within 5 %.
+// Then one round of 128 x 128 tiles: against 64 x 128, with words, us: 347 x 6038 x 3008 in E5M2 20.9 and 24.8, in E3M2 20.6 and 24.0; 1053 x 2205
+// x 1536 in E4M3 13.5 and 15.0; at K = 512 within 4 %.
+// With words and past both, what the three kernels take (TilePrice), fitted to 60 problems in E4M3 and E2M3 of 65 to 4100 rows,
+// 1000 to 15000 columns and K from 512 to 8192, even and odd ones: 5 % off, and the cheapest by these prices is 0.3 % slower than the fastest, where
+// rounds x area at 0.75 of the large tile's rate was 5.2 %.  256 x 128, 128 x 128 and 64 x 128, us: E2M3 784 x 6290 x 512 12.2, 15.7, 13.6; 751
+// x 11471 x 2048 42.4, 41.9, 38.0; E4M3 278 x 12679 x 512 11.9, 14.1, 10.0; 2594 x 3121 x 960 29.4, 30.0, 25.9.
+// Without words that gains 0.4 %: rounds of one tile per compute unit x tile area / efficiency, the 128 x 128 tile taken at 0.55 of the
+// large one's rate per output (it reads as many bytes a stage for half the products).  Rounds of large and of small tiles, E4M3,
+// K = 1536 and 4096, us large and small: 1 and 1 (2048 x 2048) 12.5, 10.7 and 26.3, 21.1; 2 and 2 (896 x 9344) 27.5, 23.4 and 56.4, 48.3;
+// 2 and 3 (600 x 19200) 27.9, 34.3 and 58.3, 71.2; 3 and 4 (384 x 38400) 43.0, 45.4 and 88.3, 97.0; the 6-bit formats the same within 5 %.
 // Grouped: the launch cannot know the routing, so every group is taken to have rows and to end half a tile-row short, and what the
 // three tiles take, in us, is fitted to Zipf routings over 8, 32 and 64 groups of 768, 1536 and 2880 squared in E4M3 and E2M3 (just past a
 // round costs most of a second one; two workgroups of 64 x 128 share a compute unit, so they have no rounds to speak of).  256 x 128, 128 x 128
@@ -731,7 +735,13 @@ inline int f8_tile(const GemmArgs& g, bool use_mbs) {
     }
     const int64_t big = (g.M + 255) / 256 * cols, small = (g.M + 127) / 128 * cols;
     if ((g.M + 63) / 64 * cols <= 256) return 2;
-    return (double)((small + 255) / 256) / (use_mbs ? 0.75 : 0.55) < 2.0 * (double)((big + 255) / 256) ? 1 : 0;
+    if (small <= 256) return 1;
+    if (use_mbs) {
+        static const TilePrice kPrices[3] = {{256, 128, 256, 0.7, 3.25, 0.063, 5.63, 1.034}, {128, 128, 256, 0.8, 2.90, 0.067, 4.09, 0.596}, {64, 128, 512, 0.4, 4.52, 0.108, 2.96, 0.668}};
+        const double t0 = kPrices[0].of(g.M, g.N, g.K), t1 = kPrices[1].of(g.M, g.N, g.K), t2 = kPrices[2].of(g.M, g.N, g.K);
+        return t0 <= t1 && t0 <= t2 ? 0 : t1 <= t2 ? 1 : 2;
+    }
+    return (double)((small + 255) / 256) / 0.55 < 2.0 * (double)((big + 255) / 256) ? 1 : 0;
 }
 
 template <int kFmtA, int kFmtB, int kTile>
