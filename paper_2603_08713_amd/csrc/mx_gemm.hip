@@ -150,11 +150,14 @@ bool takes_few_rows(int64_t M, int64_t N, int64_t K, int64_t num_groups, bool ri
 //   512 x 1024   4.8, 8.8, 15.4, 26.3   16 columns (two rounds) 5.4, 8.0, 10.2, 18.9   32 columns 5.0, 7.1, 8.9, 13.9
 //   1024 x 1024  4.9, 9.5, 15.9, 27.1   32 columns (two rounds) 8.1, 12.0, 15.8, 25.0  64 columns 6.7, 9.7, 12.7, 20.3
 // without words 512 x 1024 4.6, 6.7, 13.0, 22.2 and 32 columns 4.6, 6.2, 7.6, 11.8; K = 1056 (single bytes, 16 columns) 512 x 512 7.2 and 5.7.
+// From nine macro blocks on: below, a wavefront has one at most, its product is rounded before the sum instead of in the main kernel's one
+// multiply-add, and with words the error against 64-bit arithmetic is 7 to 9 % larger (K = 1024 8.1e-8 of the result's norm against 7.5e-8;
+// K = 1056 7.7e-8 against 7.8e-8, K = 4096 8.5e-8 against 1.14e-7, K = 8192 9.2e-8 against 1.53e-7; without words the same sums).
 int row_tile_columns(int64_t M, int64_t N, int64_t K, int64_t num_groups, bool ring_ok, bool pairs_ok) {
-    if (num_groups > 0 || M <= 64 || K < 512 || K > 8192) return 0;
+    if (num_groups > 0 || M <= 64 || K <= 1024 || K > 8192) return 0;
     const int64_t rows = (M + 63) / 64, frags = (N + 15) / 16;
     if (rows * frags <= 256) return 16;
-    if (rows * ((frags + 1) / 2) <= 256 && (ring_ok || pairs_ok) && K >= 768) return 32;
+    if (rows * ((frags + 1) / 2) <= 256 && (ring_ok || pairs_ok)) return 32;
     if (rows * ((frags + 3) / 4) <= 256 && ring_ok && K >= 3072) return 64;
     return 0;
 }
