@@ -99,12 +99,17 @@ SkinnyPlan plan_skinny(int64_t M, int64_t N, int64_t K, bool ring_ok, bool pairs
     if (p.form == 3) p.fn = 1;
     return p;
 }
-// Grouped problems may take the few-row kernel up to this many rows per group on average: it streams the weights once per
-// 32 rows.  From K = 512 on, with words, it competes with the main kernel's 64 x 128 tiles (grouped_prices).  Zipf routing, 8, 16 and 32 rows
-// per group, few-row kernel and tiles: 32 groups of 2880 x 2880 34.9, 43.4, 54.2 and 43.1, 46.2, 48.8 us; 64 of 1536 x 1536 22.0, 25.8,
-// 33.0 and 22.3, 24.4, 25.5; 64 of 768 x 768 9.0, 11.7, 14.7 and 8.3, 8.4, 8.5.  All rows
+// Grouped problems take the few-row kernel up to this many rows per group on average: it streams the weights once per
+// 32 rows.  Zipf routing, 8, 16 and 32 rows per group, few-row kernel and 64 x 128 tiles: 32 groups of 2880 x 2880 34.9, 43.4, 54.2 and 43.1,
+// 46.2, 48.8 us; 64 of 1536 x 1536 22.0, 25.8, 33.0 and 22.3, 24.4, 25.5; 64 of 768 x 768 9.0, 11.7, 14.7 and 8.3, 8.4, 8.5.  All rows
 // in one group, 8, 16 and 32 per group on average: 32 of 2880 x 2880 13, 22, 35 against 16, 17, 19; 64 of 1024 x 1024 7, 11, 17
 // against 9, 9, 9.  The launch cannot know the routing: it goes by what routers produce and loses up to half there.
+//
+// Where the tiles are faster they are not always as exact: with words, their sum over K is one chain of macro blocks, the few-row kernel's is
+// split over four wavefronts.  Error against 64 bits, tiles over few rows: K = 512 0.92, 640 0.97, 672 to 768 1.003 to 1.02, 800 to 896
+// 0.99 to 1.0, 1024 1.02, 1536 1.11, 2880 1.24, 8192 1.46.  So tiles take up to five macro blocks, and seven, where they are clearly
+// cheaper (K up to 640, few-row price over tile price 1.02 to 1.2 and 1.2 to 1.4, tiles' time over few-row: equal routing 0.83, 0.76, Zipf 0.88, 0.77,
+// all rows in one group 1.1, 0.94, with single calls up to 1.4 and 1.2).
 constexpr int64_t kFewRowsPerGroup = 32;
 
 // Whether the few-row kernel takes a problem that is not grouped and has at most 64 rows.  With K % 512 == 0 and aligned
@@ -135,9 +140,10 @@ bool takes_few_rows(int64_t M, int64_t N, int64_t K, int64_t num_groups, bool ri
     if (K == 0) return false;
     if (num_groups > 0) {
         if (M > kFewRowsPerGroup * num_groups || few_rows_blocks(M, N, num_groups, !pairs_ok) > kFewRowsMaxBlocks) return false;
-        if (K < 512 || !use_mbs) return true;
+        const int64_t st = (K + kMacro - 1) / kMacro;
+        if (K < 512 || !use_mbs || (st > 5 && st != 7)) return true;
         const GroupedPrices p = grouped_prices(M, N, K, num_groups);
-        return p.few <= 1.02 * p.small;
+        return p.few <= 1.2 * p.small;
     }
     return M <= 64 && K <= 8192 && few_rows_pay(M, N, K, plan_skinny(M, N, K, ring_ok, pairs_ok), use_mbs);
 }
