@@ -122,7 +122,8 @@ constexpr int64_t kFewRowsPerGroup = 32;
 //   K = 4128   N =  4096  5.8, 8.0, 11.5      and 18.1, 20.5, 19.8;   N = 28672  23.4, 41.1, 67.1   and 26.5, 27.3, 28.9
 // Over K of 64 to 8160, N of 1024 to 57344 and 1 to 64 rows the few-row kernel is chosen where it is at most 4 % slower, the
 // main kernel where it is at most a third slower: the prices lean to the kernel that had all of these problems before.
-bool few_rows_pay(int64_t M, int64_t N, int64_t K, const SkinnyPlan& p, bool use_mbs) {
+bool few_rows_pay(int64_t M, int64_t N, int64_t K, const SkinnyPlan& p, int sides) {
+    const bool use_mbs = sides > 0;
     if (p.form <= 1) return true;
     const bool bytes = p.form == 3;
     const int64_t rounds = ((N + 15) / 16 + p.fn * 256 - 1) / (p.fn * 256), tile_rounds = ((N + 127) / 128 + 255) / 256;
@@ -130,22 +131,27 @@ bool few_rows_pay(int64_t M, int64_t N, int64_t K, const SkinnyPlan& p, bool use
     const int at = p.fm == 1 ? 0 : p.fm == 2 ? 1 : 2;
     static const double kRound[2][3] = {{1.6, 2.2, 2.8}, {0.8, 1.1, 1.4}}, kRoundPerK[2][3] = {{0.92e-3, 1.14e-3, 1.6e-3}, {0.6e-3, 1.15e-3, 2.0e-3}};
     const double few = 1.7 + rounds * (kRound[bytes][at] + kRoundPerK[bytes][at] * K);
+    // Single bytes, K > 1024: tiles only far behind the line of their time.  Their one chain over K is less exact with words than the few-row
+    // kernel's eight shares (error against 64 bits, tiles over few rows: K = 992 0.93, 1056 1.01, 2080 1.15, 4128 1.36).
+    if (bytes && K > 1024) return few <= (use_mbs ? 4.5 + 6.2e-3 * K : 3.5 + 5.2e-3 * K) * tile_rounds;
     const double tile = use_mbs ? std::max(4.3, 1.5 + 5.5e-3 * K) : std::max(4.0, 1.4 + 4.7e-3 * K);
     // (a further round of the tiles starts while the one before ends, where two workgroups fit a compute unit)
-    // (single bytes: the quarter is what the few-row prices above are too high for one row and long K)
-    return few <= tile * (bytes ? 1.25 : 1.0) * (0.5 + 0.5 * tile_rounds);
+    // (single bytes: the few-row prices are a quarter too high for one row; words on one side only and none take 128 x 128 tiles, for which the
+    // tile price is too low.  Few rows and tiles: 45 x 5264 x 352 with words on A 5.9 and 6.8 us, 20 x 8415 x 224 6.1 and 6.5; without words
+    // 25 x 6218 x 512 4.9 and 5.7; on the tiles' side of the line 9 x 14974 x 640 with words on B 7.8 and 7.6)
+    return few <= tile * (bytes ? (sides == 2 ? 1.25 : sides == 1 ? 1.5 : 1.3) : 1.0) * (0.5 + 0.5 * tile_rounds);
 }
-// Whether the few-row kernel takes a problem (num_groups: 0 = not grouped).
-bool takes_few_rows(int64_t M, int64_t N, int64_t K, int64_t num_groups, bool ring_ok, bool pairs_ok, bool use_mbs) {
+// Whether the few-row kernel takes a problem (num_groups: 0 = not grouped; sides: how many operands have words).
+bool takes_few_rows(int64_t M, int64_t N, int64_t K, int64_t num_groups, bool ring_ok, bool pairs_ok, int sides) {
     if (K == 0) return false;
     if (num_groups > 0) {
         if (M > kFewRowsPerGroup * num_groups || few_rows_blocks(M, N, num_groups, !pairs_ok) > kFewRowsMaxBlocks) return false;
         const int64_t st = (K + kMacro - 1) / kMacro;
-        if (K < 512 || !use_mbs || (st > 5 && st != 7)) return true;
+        if (K < 512 || sides == 0 || (st > 5 && st != 7)) return true;
         const GroupedPrices p = grouped_prices(M, N, K, num_groups);
         return p.few <= 1.2 * p.small;
     }
-    return M <= 64 && K <= 8192 && few_rows_pay(M, N, K, plan_skinny(M, N, K, ring_ok, pairs_ok), use_mbs);
+    return M <= 64 && K <= 8192 && few_rows_pay(M, N, K, plan_skinny(M, N, K, ring_ok, pairs_ok), sides);
 }
 
 // More than 64 rows on the few-row kernel: the columns of its tiles of 64 rows (0: the main kernel).  Its eight wavefronts share K and
@@ -203,7 +209,7 @@ int launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* 
                          (!use_mbs || ((!a_mbs || aligned(a_mbs, 4)) && (!b_mbs || aligned(b_mbs, 4))));
     // (few-row kernel: pairs of E8M0 bytes; else single ones)
     const bool pairs_ok = K > 0 && (K % 64) == 0 && aligned(a_scales, 2) && aligned(b_scales, 2);
-    const bool skinny_ok = takes_few_rows(M, N, K, g.num_groups, ring_ok, pairs_ok, use_mbs);
+    const bool skinny_ok = takes_few_rows(M, N, K, g.num_groups, ring_ok, pairs_ok, use_mbs ? (a_mbs != nullptr) + (b_mbs != nullptr) : 0);
     const bool tile64_ok = !grouped && a_mbs && b_mbs && mbs_entry;
     int shape = choose_shape(M, N, K, g.num_groups, use_mbs, ring_ok, skinny_ok, row_tile_columns(M, N, K, g.num_groups, ring_ok, pairs_ok), tile64_ok);
     if (force_shape >= 0) shape = force_shape;
@@ -296,7 +302,7 @@ int mx_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int a_has_mbs, int b_
     if (!out || cap <= 0 || M < 0 || N < 0 || K < 0 || (K % mx::kBlock) != 0 || num_groups < 0) return MX_EINVAL;
     const bool use_mbs = a_has_mbs || b_has_mbs, grouped = num_groups > 0;
     const bool ring_ok = !grouped && K > 0 && (K % 512) == 0, pairs_ok = K > 0 && (K % 64) == 0;
-    const int shape = mx::choose_shape(M, N, K, num_groups, use_mbs, ring_ok, mx::takes_few_rows(M, N, K, num_groups, ring_ok, pairs_ok, use_mbs),
+    const int shape = mx::choose_shape(M, N, K, num_groups, use_mbs, ring_ok, mx::takes_few_rows(M, N, K, num_groups, ring_ok, pairs_ok, (a_has_mbs != 0) + (b_has_mbs != 0)),
                                        mx::row_tile_columns(M, N, K, num_groups, ring_ok, pairs_ok),
                                        !grouped && a_has_mbs && b_has_mbs);
     const char* sides = a_has_mbs && b_has_mbs ? "MBS words on A and B" : a_has_mbs ? "MBS words on A" : b_has_mbs ? "MBS words on B" : "no MBS";

@@ -14,3 +14,14 @@ def test_groups_of_few_rows_on_tiles():
     assert "64x128" in mx.gemm_plan(64 * 32, 2048, 640, grouped=True, num_groups=64)
     assert "64x128" in mx.gemm_plan(64 * 32, 2048, 896, grouped=True, num_groups=64)
     assert "few rows" in mx.gemm_plan(64 * 32, 2048, 672, grouped=True, num_groups=64)
+
+
+@pytest.mark.parametrize("M,N,K,a,b", [(32, 33556, 1824, 1, 1), (2, 50884, 2592, 1, 1), (27, 12681, 1312, 1, 1), (5, 33505, 1184, 1, 0), (16, 56399, 5152, 1, 0), (8, 20000, 1696, 0, 0),
+                                       (45, 5264, 352, 1, 0), (25, 6218, 480, 0, 0)])
+def test_single_bytes_stay_on_the_few_row_kernel(M, N, K, a, b):
+    """K % 64 = 32: past K = 1024 the split sum is the more exact one; below, where tiles take longer."""
+    assert "few rows" in mx.gemm_plan(M, N, K, bool(a), bool(b))
+
+
+def test_single_bytes_on_tiles():
+    assert "few rows" not in mx.gemm_plan(56, 14000, 864) and "few rows" not in mx.gemm_plan(64, 28672, 4128)

@@ -35,3 +35,17 @@ def test_groups(mx, G, rows, N, K):  # noqa: F811
     want = torch.cat([x[e * rows:(e + 1) * rows] @ w[e * N:(e + 1) * N].T.contiguous() for e in range(G)])
     assert torch.equal(got, few)
     assert error(got, want) < error(tiles, want) < 2e-7
+
+
+@pytest.mark.parametrize("M,N,K", [(32, 33556, 1824), (2, 50884, 2592)])
+def test_single_scale_bytes(mx, M, N, K):  # noqa: F811
+    """K % 64 = 32 in several rounds of workgroups."""
+    a, b = quantized(mx, 1, M, K), quantized(mx, 2, N, K, scale=0.02)
+    got = mx.mx_gemm_mbs(*a, *b, "f32")
+    with mx.forced(gemm_shape=5):
+        few = mx.mx_gemm_mbs(*a, *b, "f32")
+    with mx.forced(gemm_shape=12):
+        tiles = mx.mx_gemm_mbs(*a, *b, "f32")
+    want = value(mx, a) @ value(mx, b).T.contiguous()
+    assert torch.equal(got, few)
+    assert error(got, want) < error(tiles, want) < 2e-7
