@@ -49,3 +49,18 @@ def test_single_scale_bytes(mx, M, N, K):  # noqa: F811
     want = value(mx, a) @ value(mx, b).T.contiguous()
     assert torch.equal(got, few)
     assert error(got, want) < error(tiles, want) < 2e-7
+
+
+@pytest.mark.parametrize("a_elem,b_elem,M,N,K", [("e2m3", "e2m3", 64, 4224, 1024), ("e2m3", "e3m2", 33, 8200, 2048), ("e3m2", "e2m3", 8, 16896, 4096)])
+def test_e2m3(mx, a_elem, b_elem, M, N, K):  # noqa: F811
+    """E2M3 on either side: its products are exact in the matrix unit, so the order of the sum over K decides the error."""
+    a, b = quantized(mx, 1, M, K, a_elem), quantized(mx, 2, N, K, b_elem, scale=0.02)
+    call = lambda: mx.mx_gemm_mbs_elem(a_elem, *a, b_elem, *b, "f32")  # noqa: E731
+    got = call()
+    with mx.forced(gemm_elem=3):
+        few = call()
+    with mx.forced(gemm_elem=18):
+        tiles = call()
+    want = value(mx, a, a_elem) @ value(mx, b, b_elem).T.contiguous()
+    assert torch.equal(got, few)
+    assert error(got, want) < error(tiles, want) < 2e-7
