@@ -43,22 +43,23 @@ int launch_gemm_elem(int a_elem, const uint8_t* a_codes, const uint8_t* a_scales
     const bool use_mbs = a_mbs || b_mbs;
     const bool force_general = force == 1;
     // few activation rows: the weights are streamed once, nothing is staged (mx_gemm_skinny_f8.hip)
-    // Taken where its rows and its rounds of workgroups are few, against one round of 64 x 128 tiles of the main kernel.  With the
+    // Taken where its rows and its rounds of 4096 columns are few, against one round of 64 x 128 tiles of the main kernel.  With the
     // quantizer in front and words, few-row kernel and tiles, us, K = 512, 1536, 2560, 5120: E4M3, 8 rows, N = 8192 8.0, 10.5, 12.3,
     // 16.5 and 8.8, 13.1, 16.8, 25.6, N = 8800 9.7, 13.7, 16.7, 23.4 and 8.8, 13.3, 16.7, 25.8; 26 rows, N = 4945 10.2, 13.1, 16.9, 23.7 and 9.2,
     // 12.9, 16.7, 25.7, N = 8800 12.0, 17.3, 21.5, 31.6 and 9.1, 13.2, 17.0, 25.9; 64 rows, N = 4096 10.3, 13.0, 16.1, 24.0 and 9.2, 13.1, 16.7, 26.1,
     // N = 4160 15.2, 20.2, 25.8, 38.7 and 9.3, 13.1, 16.9, 26.2.  E3M2: 8 rows, N = 10548 8.6, 12.2, 15.2, 22.1 and 9.0, 13.3, 16.9, 25.6; 26
-    // rows, N = 4945 8.9, 11.6, 14.8, 22.5 and 9.4, 12.9, 16.6, 25.6; 64 rows, N = 4096 10.2, 12.8, 15.6, 23.7 and 9.5, 13.1, 16.7, 26.0.  Without
-    // words the tiles gain more, and from K = 5120 on, with 8-bit weights that no cache holds, the few rows again: 8 rows, N = 8800 19.1
-    // and 23.1 in E4M3 (the other formats and row counts within 14 % either way).  (To 16 rows a round is counted as 4352 columns:
-    // 8193 to 8704 would gain 4 to 10 % on tiles at K = 512, but their sums are held to this kernel's order.)
-    const int64_t span = M <= 16 ? 4352 : 4096, few_work = (M <= 16 ? 1 : M <= 32 ? 2 : 4) * ((N + span - 1) / span);
-    const int64_t few_from = !use_mbs ? 5120 : a8 ? 2560 : M <= 32 ? 0 : 1536;
+    // rows, N = 4945 8.9, 11.6, 14.8, 22.5 and 9.4, 12.9, 16.6, 25.6; 64 rows, N = 4096 10.2, 12.8, 15.6, 23.7 and 9.5, 13.1, 16.7, 26.0.  More than
+    // 32 rows in one round are 64 to this kernel's tile and fewer to its loads.  Tiles over few rows at 33, 40, 48 and 64, N = 64 to 4096: K = 1024 1.05,
+    // 1.01, 1.01, 0.95; 1536 1.12, 1.08, 1.06, 1.0; 2048 1.16, 1.13, 1.11, 1.04; without words K = 2048 0.99, 0.96, 0.94, 0.88; 3072 1.05, 1.0, 0.98, 0.91.
+    // Without words the tiles gain more, and from K = 5120 on, with 8-bit weights that no cache holds, the few rows again: 8 rows, N = 8800 19.1
+    // and 23.1 in E4M3 (the other formats and row counts within 14 % either way).
+    const int64_t few_work = (M <= 16 ? 1 : M <= 32 ? 2 : 4) * ((N + 4095) / 4096);
+    const int64_t few_from = !use_mbs ? (M > 32 && M <= 40 ? 3072 : 5120) : M > 40 ? 1536 : M > 32 ? 1024 : a8 ? 2560 : 0;
     // E2M3's products fit the matrix unit's sum without a cut, so the order of the sum over K shows: error against 64 bits, tiles over
-    // few rows, with words, E2M3 on either side: K = 512 1.0, 1024 1.06, 2048 1.19, 4096 1.36, 8192 1.69 (without words both are exact on
-    // such data).  Past K = 512 it stays with this kernel's split sum.  The other formats' cut hides the order (1.0000 at every K).
+    // few rows, with words, E2M3 on either side: K = 512 1.0, 1024 1.06, 2048 1.19, 4096 1.36, 8192 1.69.  Past K = 512 it stays with this
+    // kernel's split sum.  Without words both are exact on such data, and the other formats' cut hides the order (1.0000 at every K).
     const bool exact_products = a_elem == MX_ELEM_E2M3 || b_elem == MX_ELEM_E2M3;
-    const bool few_pays = few_work <= 2 || (few_work <= 4 && K >= few_from) || (exact_products && K > 512);
+    const bool few_pays = few_work <= 2 || (few_work <= 4 && K >= few_from) || (exact_products && use_mbs && K > 512);
     const bool skinny_ok = !grouped && M <= 64 && (K % 512) == 0 && K <= 8192 && aligned(a_scales, 16) && aligned(b_scales, 16) &&
                            (!a_mbs || aligned(a_mbs, 4)) && (!b_mbs || aligned(b_mbs, 4));
     if (force == 3 && !skinny_ok) return MX_EINVAL;

@@ -518,7 +518,10 @@ def test_gemm_elem_few_rows(mx, oracle, ea, eb):
             pa1, pb1 = (pa[0], pa[1], pa[2] if wa else None), (pb[0], pb[1], pb[2] if wb else None)
             got = gpu_gemm(mx, ea, pa1, eb, pb1, kernel=3)
             assert_gemm_elem_ok(oracle, host(got), ea, a1, eb, b1, "few rows %s x %s %dx%dx%d words %d%d" % (ea, eb, M, N, K, wa, wb))
-            if (wa, wb) == (True, True):
+            if (wa, wb) == (True, True) and N > 8192:
+                # just past two rounds of workgroups the library may pick the main kernel, with sums in another order
+                assert_gemm_elem_ok(oracle, host(gpu_gemm(mx, ea, pa1, eb, pb1, kernel=None)), ea, a1, eb, b1, "chosen %s x %s %dx%dx%d" % (ea, eb, M, N, K))
+            elif (wa, wb) == (True, True):
                 # what the library picks for this shape is this kernel, and bf16 is the rounding of its fp32
                 assert torch.equal(gpu_gemm(mx, ea, pa1, eb, pb1, kernel=None), got)
                 assert torch.equal(gpu_gemm(mx, ea, pa1, eb, pb1, "bf16", kernel=None), got.to(torch.bfloat16))

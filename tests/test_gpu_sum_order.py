@@ -64,3 +64,21 @@ def test_e2m3(mx, a_elem, b_elem, M, N, K):  # noqa: F811
     want = value(mx, a, a_elem) @ value(mx, b, b_elem).T.contiguous()
     assert torch.equal(got, few)
     assert error(got, want) < error(tiles, want) < 2e-7
+
+
+# (rounds of 4096 columns: four and five; more than 32 rows in one round: short and long K, with words and without)
+@pytest.mark.parametrize("elem,words,M,N,K,few", [("e4m3", True, 8, 16384, 4096, True), ("e4m3", True, 8, 16500, 4096, False), ("e5m2", True, 40, 300, 1024, True),
+                                                  ("e4m3", True, 64, 300, 1536, True), ("e4m3", True, 64, 300, 1024, False), ("e4m3", False, 33, 300, 3072, True),
+                                                  ("e4m3", False, 41, 300, 3072, False), ("e4m3", False, 12, 16400, 8192, False), ("e2m3", True, 41, 4100, 1024, True),
+                                                  ("e2m3", False, 41, 4100, 1024, False)])
+def test_lines_of_the_few_row_kernel(mx, elem, words, M, N, K, few):  # noqa: F811
+    """Which kernel 8-bit and 6-bit calls take, by the sums' bits: the few-row kernel's, or the tiles', which differ on such operands."""
+    a, b = quantized(mx, 1, M, K, elem), quantized(mx, 2, N, K, elem, 0.02)
+    if not words and elem == "e2m3":  # (what is exact in every order says nothing: scales far apart)
+        a[1].copy_(torch.randint(100, 150, a[1].shape, generator=torch.Generator(device="cuda").manual_seed(3), device="cuda", dtype=torch.uint8))
+        b[1].copy_(torch.randint(100, 150, b[1].shape, generator=torch.Generator(device="cuda").manual_seed(4), device="cuda", dtype=torch.uint8))
+    got = {}
+    for force in (0, 3, 18):
+        with mx.forced(gemm_elem=force):
+            got[force] = mx.mx_gemm_mbs_elem(elem, a[0], a[1], a[2] if words else None, elem, b[0], b[1], b[2] if words else None, "f32")
+    assert torch.equal(got[0], got[3 if few else 18]) and not torch.equal(got[3], got[18])
