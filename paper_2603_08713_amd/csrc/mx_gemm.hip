@@ -39,6 +39,8 @@ GroupedPrices grouped_prices(int64_t M, int64_t N, int64_t K, int64_t num_groups
 // 45.8; 64 of 2880 x 2880, 4096 rows 157 and 111; 8 of 768 x 768, 1024 rows 7.4 and 6.4; past the line 32 of 1536 x 1536, 16384 rows
 // 55 and 63, 8 of 2880 x 2880, 2048 rows 24 and 32.
 bool grouped_small_tile(int64_t M, int64_t N, int64_t K, int64_t num_groups) {
+    // (their grid, two workgroups of 256 for one of 512, has to stay below 2^32 work-items: 3.3 million groups of 300 rows do not)
+    if ((M / 64 + num_groups) * ((N + 127) / 128) >= (int64_t)1 << 24) return false;
     const GroupedPrices p = grouped_prices(M, N, K, num_groups);
     return M <= 128 * num_groups || p.small < 0.85 * p.big;
 }

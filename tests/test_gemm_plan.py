@@ -25,3 +25,9 @@ def test_single_bytes_stay_on_the_few_row_kernel(M, N, K, a, b):
 
 def test_single_bytes_on_tiles():
     assert "few rows" not in mx.gemm_plan(56, 14000, 864) and "few rows" not in mx.gemm_plan(64, 28672, 4128)
+
+
+def test_tiles_whose_grid_a_launch_takes():
+    """Twice as many work-items as on 256 x 128 tiles: from 2^32 on the launch would be refused."""
+    assert "256x128" in mx.gemm_plan(300 * 3300000, 100, 32, grouped=True, num_groups=3300000)
+    assert "64x128" in mx.gemm_plan(300 * 33000, 100, 32, grouped=True, num_groups=33000)
