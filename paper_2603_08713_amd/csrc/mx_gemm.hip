@@ -1,7 +1,7 @@
 // Block-scaled MXFP4 GEMM  C = A * B^T  with the Macro Block Scaling correction, for gfx950: argument checks and
 // the choice of kernel.  The kernels are the main template (mx_gemm_ring.h: fast form in mx_gemm_wide.hip and
 // mx_gemm_mbs.hip, general forms in mx_gemm_general.hip and mx_gemm_wide.hip) and the few-row kernel
-// (mx_gemm_skinny.h; mx_gemm_skinny.hip, mx_gemm_skinny_fused.hip, mx_gemm_skinny_grouped.hip).
+// (mx_gemm_skinny.h; mx_gemm_skinny.hip, mx_gemm_skinny_rows.hip, mx_gemm_skinny_fused.hip, mx_gemm_skinny_grouped.hip).
 #include "mx_gemm_shared.h"
 #include "mx_internal.h"
 
@@ -224,7 +224,7 @@ int launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* 
     }
     if (shape >= 17 && shape <= 19) {
         if (grouped || K == 0 || K > 8192) return MX_EINVAL;
-        return launch_gemm_skinny_tile(g, use_mbs, 4, shape == 17 ? 1 : shape == 18 ? 2 : 4, plan_skinny(64, N, K, ring_ok, pairs_ok).form, s);
+        return launch_gemm_skinny_rows(g, use_mbs, shape == 17 ? 1 : shape == 18 ? 2 : 4, plan_skinny(64, N, K, ring_ok, pairs_ok).form, s);
     }
     if (shape == 11 || shape == 12) {
         if (!use_mbs || (shape == 11 ? !ring_ok || !a_mbs || !b_mbs : K == 0)) return MX_EINVAL;

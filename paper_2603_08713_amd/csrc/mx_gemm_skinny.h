@@ -577,23 +577,24 @@ __device__ __forceinline__ void skinny_tile(const SkinnyArgs& args, uint8_t* sme
     }
 }
 
-// A workgroup per tile of 16 FM rows and 16 FN columns (fused: M <= 16 FM rows).
-template <int NW, int FM, int FN, bool kFused, int kForm, bool kSingle, bool kWords>
+// A workgroup per 16 FN columns; M <= 16 FM rows or, kTall, as many tiles of 16 FM rows as M has (compiled apart: the second grid dimension
+// costs the calls of a few microseconds, which have one, 0.04 to 0.08 us, 1 % of 16 x 4096 x 512).
+template <int NW, int FM, int FN, bool kFused, int kForm, bool kSingle, bool kWords, bool kTall>
 __global__ __launch_bounds__(NW * kWave) void gemm_skinny_kernel(SkinnyArgs args) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const int64_t n0 = (int64_t)blockIdx.x * (16 * FN);
-    const int64_t m0 = kFused ? 0 : (int64_t)blockIdx.y * (16 * FM);
-    skinny_tile<NW, FM, FN, kFused, kForm, kSingle, kWords>(args, smem, m0, kFused ? args.g.M : min(args.g.M, m0 + 16 * FM), n0, args.g.N, n0);
+    const int64_t m0 = kTall ? (int64_t)blockIdx.y * (16 * FM) : 0;
+    skinny_tile<NW, FM, FN, kFused, kForm, kSingle, kWords>(args, smem, m0, kTall ? min(args.g.M, m0 + 16 * FM) : args.g.M, n0, args.g.N, n0);
 }
 
-template <int NW, int FM, int FN, bool kFused, int kForm>
+template <int NW, int FM, int FN, bool kFused, int kForm, bool kTall = false>
 int launch_skinny_variant(const SkinnyArgs& a, hipStream_t s) {
     const GemmArgs& g = a.g;
-    const int64_t blocks = (g.N + 16 * FN - 1) / (16 * FN), row_tiles = kFused ? 1 : (g.M + 16 * FM - 1) / (16 * FM);
-    if ((kFused && g.M > 16 * FM) || blocks > (int64_t)1 << 30 || row_tiles > 65535) return MX_EINVAL;
+    const int64_t blocks = (g.N + 16 * FN - 1) / (16 * FN), row_tiles = (g.M + 16 * FM - 1) / (16 * FM);
+    if (row_tiles > (kTall ? 65535 : 1) || blocks > (int64_t)1 << 30) return MX_EINVAL;
     using S = SkinnyShape<NW, FM, FN, kFused, kForm>;
     auto launch = [&](auto single_, auto words_) {
-        auto* fn = gemm_skinny_kernel<NW, FM, FN, kFused, kForm, decltype(single_)::value, decltype(words_)::value>;
+        auto* fn = gemm_skinny_kernel<NW, FM, FN, kFused, kForm, decltype(single_)::value, decltype(words_)::value, kTall>;
         static LdsOptIn opt_in;  // one per kernel instantiation
         if (int st = opt_in.ensure(reinterpret_cast<const void*>(fn), S::kLdsBytes)) return st;
         hipLaunchKernelGGL(fn, dim3((unsigned)blocks, (unsigned)row_tiles), dim3(S::NT), S::kLdsBytes, s, a);

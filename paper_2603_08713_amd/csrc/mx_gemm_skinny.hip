@@ -19,7 +19,7 @@ int launch_form(const SkinnyArgs& a, int form, hipStream_t s) {
 
 }  // namespace
 
-// fm, fn fragments of 16 rows of A and of B per workgroup; form as in mx_gemm_skinny.h
+// M <= 16 fm rows: fm, fn fragments of 16 rows of A and of B per workgroup; form as in mx_gemm_skinny.h
 int launch_gemm_skinny_tile(const GemmArgs& g, bool use_mbs, int fm, int fn, int form, hipStream_t s) {
     SkinnyArgs a = {};
     a.g = g;
