@@ -43,16 +43,17 @@ struct GemmArgs {
 // Main kernels (mx_gemm_ring.h), fast form: K % 512 == 0 and aligned scale and MBS arrays, not grouped; without MBS
 // (mx_gemm_wide.hip: 256 x 256, 256 x 128 or 128 x 128 tiles) and with MBS (mx_gemm_mbs.hip: 256 x 128 or 128 x 128).
 int launch_gemm_wide(const GemmArgs& g, int tile, hipStream_t s);
-const char* describe_gemm_wide(int64_t M, int64_t N, int64_t K);  // what launch_gemm_wide(tile = 0) does with a problem
+const char* describe_gemm_wide(int64_t M, int64_t N, int64_t K);  // what launch_gemm_wide(tile = 0) does with a problem, C in bf16 and whole
 int launch_gemm_mbs_ring(const GemmArgs& g, int variant, hipStream_t s);
 // The same kernels in their general forms (any K % 32 == 0, any alignment of the scale arrays, grouped or not),
 // defined in mx_gemm_general.hip (with MBS) and mx_gemm_wide.hip (without).  tile: 0 = 256 x 128, 1 = 128 x 128;
 // bytes: E8M0 bytes fetched one at a time (needed when K = 0; 128 x 128 tiles only).
 int launch_gemm_mbs_general(const GemmArgs& g, int tile, bool bytes, hipStream_t s);
 int launch_gemm_wide_general(const GemmArgs& g, int tile, bool bytes, hipStream_t s);
-// Few activation rows (mx_gemm_skinny.h), not grouped; fm, fn = fragments of 16 rows of A and of B per
-// workgroup (as many row tiles as M has), form as there (mx_gemm_skinny.hip).
+// Few activation rows (mx_gemm_skinny.h): M <= 16 fm, not grouped; fm, fn = fragments of 16 rows of A and of B per
+// workgroup, form as there (mx_gemm_skinny.hip).  More rows, in tiles of 64 (mx_gemm_skinny_rows.hip).
 int launch_gemm_skinny_tile(const GemmArgs& g, bool use_mbs, int fm, int fn, int form, hipStream_t s);
+int launch_gemm_skinny_rows(const GemmArgs& g, bool use_mbs, int fn, int form, hipStream_t s);
 // The same with A given as bf16 [M, ldx] and quantized inside the kernel (mx_gemm_skinny_fused.hip): rule, MBS-Static words
 // if a_mbs; the a_* members of g are not used.  Also requires K % 512 == 0, x 16-byte aligned, ldx % 8 == 0 and the rows
 // of x to span less than 2 GiB.

@@ -25,15 +25,26 @@ using Tail = RingShape<2, 2, 4, 2, 0>;
 using Small = RingShape<2, 2, 2, 2, 0>;
 constexpr int64_t kUnits = 256;  // compute units of the device
 
-// What launch_gemm_wide does with an M x N problem: the tile (1, 2, 3 as above) and, for the large tile, how many
+// Whether the tile goes by prices, from where the rows of C start (their bytes, and the address of the first).  The prices were fitted to
+// rows on any element.  Rows on 16 bytes are stored past the caches, which costs the small tiles, with half the bytes per piece of a row,
+// up to half their time where rows straddle lines, and the large tile nothing: 4826 x 15920 x 1024 in bf16 133 us by price and 77 by area, 1777 x
+// 5004 x 2048 in fp32 23.6 and 20.1.  Means over 1368 problems in each type, of the fastest tile's time, K = 512, 1024 to 1536, 2048 to 3072, from 4096:
+// rows on any element 1.00, 1.00, 1.01, 1.015 by price, 1.10, 1.04, 1.02, 1.005 by area; on 16 bytes 1.02, 1.06, 1.03, 1.03 and 1.05, 1.03, 1.015, 1.005;
+// on whole lines at K = 512 the price is 0.94 of the area's time.
+bool goes_by_price(int64_t K, uintptr_t first, int64_t row_bytes) {
+    const uintptr_t both = first | (uintptr_t)row_bytes;
+    return both % 16 != 0 ? K < 4096 : both % 128 == 0 && K < 1024;
+}
+
+// What launch_gemm_wide does with a problem: the tile (1, 2, 3 as above) and, for the large tile, how many
 // of its tile columns go to the large tile (the rest to 256 x 128 tiles in a second launch).
 struct WidePlan {
     int tile;
     int64_t big_cols, cols;
 };
 
-WidePlan plan_wide(int64_t M, int64_t N, int64_t K, int tile) {
-    if (tile == 0 && more_than_a_round_of_64x128(M, N)) {
+WidePlan plan_wide(int64_t M, int64_t N, int64_t K, bool by_price, int tile) {
+    if (tile == 0 && by_price && more_than_a_round_of_64x128(M, N)) {
         // (short K: the small tile's stores and prologues overlap with other workgroups' stages.  256 x 256 and 128 x 128 tiles, us: 8026 x
         // 3161 x 512 30.5 and 21.4, 1354 x 6828 x 512 18.8 and 12.1, 3619 x 2698 x 2048 27.3 and 20.9)
         static const TilePrice kMain = {256, 256, 256, 0.6, 6.60, 0.004, 9.82, 0.803}, kTail = {256, 128, 256, 0.7, 4.65, -0.016, 4.25, 0.533},
@@ -71,7 +82,7 @@ WidePlan plan_wide(int64_t M, int64_t N, int64_t K, int tile) {
 }  // namespace
 
 const char* describe_gemm_wide(int64_t M, int64_t N, int64_t K) {
-    const WidePlan p = plan_wide(M, N, K, 0);
+    const WidePlan p = plan_wide(M, N, K, goes_by_price(K, 0, 2 * N), 0);
     if (p.tile == 2) return "gemm_ring_kernel, fast form, 256x128 tile, 4 wavefronts of 128x64";
     if (p.tile == 3) return "gemm_ring_kernel, fast form, 128x128 tile, 4 wavefronts of 64x64";
     if (p.big_cols == p.cols) return "gemm_ring_kernel, fast form, 256x256 tile, 4 wavefronts of 128x128";
@@ -80,7 +91,7 @@ const char* describe_gemm_wide(int64_t M, int64_t N, int64_t K) {
 }
 
 int launch_gemm_wide(const GemmArgs& g, int tile, hipStream_t s) {
-    const WidePlan p = plan_wide(g.M, g.N, g.K, tile);
+    const WidePlan p = plan_wide(g.M, g.N, g.K, goes_by_price(g.K, reinterpret_cast<uintptr_t>(g.C), g.ldc * (g.c_bf16 ? 2 : 4)), tile);
     if (p.tile == 2) return launch_ring<Tail>(g, s);
     if (p.tile == 3) return launch_ring<Small>(g, s);
     if (p.big_cols == p.cols) return launch_ring<Main>(g, s);
