@@ -324,8 +324,10 @@ int mx_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int a_has_mbs, int b_
         case 8: what = use_mbs ? "gemm_ring_kernel, general form (row pieces through registers), 256x128 tile, 8 wavefronts" : "gemm_ring_kernel, general form (row pieces through registers), 256x128 tile, 4 wavefronts"; break;
         default: what = "gemm_ring_kernel, general form (row pieces through registers), 128x128 tile"; break;
     }
-    // (K % 64 = 32: the rows of E8M0 bytes have an odd length)
-    snprintf(out, (size_t)cap, "%s%s; %s", what, K % 64 != 0 ? ", single scale bytes at the end of K" : "", sides);
+    // (how the few-row kernel fetches E8M0 bytes where a row's pieces are not aligned)
+    const bool few = shape == 5 || shape >= 17;
+    const char* pieces = !few || ring_ok ? "" : pairs_ok ? ", pairs of scale bytes" : ", single scale bytes";
+    snprintf(out, (size_t)cap, "%s%s; %s", what, pieces, sides);
     return MX_OK;
 }
 

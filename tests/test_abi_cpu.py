@@ -96,7 +96,9 @@ def test_gemm_plan_names_the_kernel_a_problem_takes(lib):
     assert "128x128" in plan(2048, 2048, 2048)                      # too few large tiles for 256 compute units
     assert "few rows" in plan(16, 4096, 4096)                       # decode
     assert "general form" in plan(32768, 2880, 2880, 1, 1, 1)       # grouped, K % 512 != 0
-    assert "single scale bytes" in plan(512, 512, 2016)             # K % 64 == 32
+    assert "tiles of 64 rows and 16 columns, single scale bytes" in plan(512, 512, 2016)           # K % 64 == 32: few-row kernel ...
+    assert "row pieces through registers" in plan(4000, 4000, 2016) and "single" not in plan(4000, 4000, 2016)  # ... and general form
+    assert "pairs of scale bytes" in plan(16, 4096, 2880) and "scale bytes" not in plan(16, 4096, 4096)
     assert lib.mx_internal_gemm_plan(8, 8, 48, 1, 1, 0, ctypes.create_string_buffer(8), 8) == -1   # K % 32
     assert lib.mx_internal_gemm_plan(8, 8, 64, 1, 1, 0, None, 0) == -1
     # grouped: the choice goes by the rows per group
@@ -104,7 +106,7 @@ def test_gemm_plan_names_the_kernel_a_problem_takes(lib):
     assert "general form" in plan(32 * 32 + 1, 2880, 2880, grouped=32)
     # ... and by what fits a launch of fewer than 2^32 work-items
     assert "few rows per group" in plan(2048, 1 << 22, 64, grouped=64) and "general form" in plan(2048, 1 << 23, 64, grouped=64)
-    assert "few rows per group" in plan(64, 1 << 21, 32, grouped=64) and "single scale bytes" in plan(64, 1 << 23, 32, grouped=64)
+    assert "few rows per group" in plan(64, 1 << 21, 32, grouped=64) and "general form" in plan(64, 1 << 23, 32, grouped=64)
     import paper_2603_08713_amd as mx
 
     assert "few rows per group" in mx.gemm_plan(256, 2880, 2880, grouped=True, num_groups=32)
