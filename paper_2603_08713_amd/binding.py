@@ -320,7 +320,7 @@ def mx_quantize_mbs(x, rule="oas", codes=None, scales=None, mbs=None):
 
 def mx_quantize_mbs_pair(x0, x1, rule="oas", out0=None, out1=None):
     """MBS-Static quantization of two tensors with the same K in one launch -> ((codes, scales, mbs), (...))."""
-    if _native is not None and type(out0) is tuple and type(out1) is tuple and _done(
+    if _native is not None and type(out0) is tuple and type(out1) is tuple and len(out0) == len(out1) == 3 and _done(
             _native.quantize_mbs_pair(x0, x1, rule, *out0, *out1), "mx_quantize_mbs_pair"):
         return out0, out1
     rows0, K, ld0 = _rows_ld(x0)

@@ -105,3 +105,15 @@ def test_declines(mx):
     # inside a transform the tensor is a wrapper without an address: declined, and the Python path raises as it always has
     with pytest.raises(Exception):
         torch.vmap(lambda v: mx.mx_quantize_mbs(v, "oas", *q)[0])(x.unsqueeze(0))
+
+
+def test_pair_outputs_of_other_lengths(mx):
+    """Outputs are given per tensor: an empty tuple asks for them to be allocated, any other number than three is refused."""
+    x = torch.randn((4, 512), generator=torch.Generator(device="cuda").manual_seed(1), device="cuda").to(torch.bfloat16)
+    q = lambda: (u8(4, 256), u8(4, 16), u8(4, 4))  # noqa: E731
+    want = mx.mx_quantize_mbs(x, "oas")
+    o0, o1 = mx.mx_quantize_mbs_pair(x, x, "oas", (), q())
+    assert all(torch.equal(s, t) for o in (o0, o1) for s, t in zip(o, want, strict=True))
+    for out0, out1 in (((), q() + q()), (q()[:2], q()[:1] + q()), (q() + q()[:1], q()[:2])):
+        with pytest.raises(TypeError):
+            mx.mx_quantize_mbs_pair(x, x, "oas", out0, out1)
