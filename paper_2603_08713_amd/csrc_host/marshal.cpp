@@ -7,6 +7,8 @@
 // returns None and nothing has happened: the binding's Python code then does the call or raises.
 #include <Python.h>
 
+#include <string.h>
+
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <ATen/core/Tensor.h>
 #include <c10/hip/HIPStream.h>
@@ -38,8 +40,8 @@ void need(bool ok) {
     if (!ok) throw Declined();
 }
 
+// (the types of the arguments have been looked at: `served`)
 const at::Tensor& tensor(PyObject* o) {
-    need(THPVariable_CheckExact(o));
     const at::Tensor& t = THPVariable_Unpack(o);
     using K = c10::DispatchKey;
     need(t.defined() && t.is_cuda() && t.layout() == c10::kStrided && t.has_storage() && !t.unsafeGetTensorImpl()->is_python_dispatch() &&
@@ -83,7 +85,6 @@ mx_dtype_t out_type(PyObject* o) {
         need(PyUnicode_CompareWithASCIIString(o, "f32") == 0 || PyUnicode_CompareWithASCIIString(o, "fp32") == 0);
         return MX_OUT_F32;
     }
-    need(THPDtype_Check(o));
     const at::ScalarType s = reinterpret_cast<THPDtype*>(o)->scalar_type;
     need(s == at::kFloat || s == at::kBFloat16);
     return s == at::kFloat ? MX_OUT_F32 : MX_OUT_BF16;
@@ -102,7 +103,6 @@ Out out_matrix(PyObject* type, PyObject* o, int64_t rows, int64_t cols) {
 }
 
 int64_t integer(PyObject* o) {
-    need(PyLong_CheckExact(o));
     const long long v = PyLong_AsLongLong(o);
     if (v == -1 && PyErr_Occurred()) {
         PyErr_Clear();
@@ -112,7 +112,6 @@ int64_t integer(PyObject* o) {
 }
 template <int N>
 int name_of(PyObject* o, const char* const (&names)[N]) {
-    need(PyUnicode_CheckExact(o));
     for (int i = 0; i < N; ++i)
         if (PyUnicode_CompareWithASCIIString(o, names[i]) == 0) return i;
     throw Declined();
@@ -126,23 +125,42 @@ mx_elem_t elem(PyObject* o) {
     return (mx_elem_t)name_of(o, kNames);
 }
 int64_t code_bytes(mx_elem_t e, int64_t K) { return e == MX_ELEM_E2M3 || e == MX_ELEM_E3M2 ? K * 3 / 4 : K; }
-bool flag(PyObject* o) {
-    need(PyBool_Check(o));
-    return o == Py_True;
-}
+bool flag(PyObject* o) { return o == Py_True; }
 
 void* stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
+// Whether the arguments have the types that are served: t = tensor, o = tensor or None, s = text, d = text or torch dtype, i = int,
+// b = bool.  Looked at before anything that throws: an exception costs 2 us, a third of the call that the binding's Python code then makes.
+bool served(PyObject* const* a, Py_ssize_t n, const char* kinds) {
+    for (Py_ssize_t i = 0; i < n; ++i) {
+        bool ok = false;
+        switch (kinds[i]) {
+            case 'o': ok = a[i] == Py_None || THPVariable_CheckExact(a[i]); break;
+            case 't': ok = THPVariable_CheckExact(a[i]); break;
+            case 's': ok = PyUnicode_CheckExact(a[i]); break;
+            case 'd': ok = PyUnicode_CheckExact(a[i]) || THPDtype_Check(a[i]); break;
+            case 'i': ok = PyLong_CheckExact(a[i]); break;
+            case 'b': ok = PyBool_Check(a[i]); break;
+        }
+        if (!ok) return false;
+    }
+    return true;
+}
+
 // Runs a call's marshalling; the entry point itself runs without the interpreter's lock, as it did through ctypes.
 template <typename F>
-PyObject* run(Py_ssize_t given, Py_ssize_t wanted, F&& marshal) {
-    if (given == wanted && !at::impl::torch_function_mode_enabled()) {
+PyObject* run(PyObject* const* a, Py_ssize_t n, const char* kinds, F&& marshal) {
+    if (n == (Py_ssize_t)strlen(kinds) && served(a, n, kinds) && !at::impl::torch_function_mode_enabled()) {
         try {
             auto call = marshal();
-            int status;
-            Py_BEGIN_ALLOW_THREADS
-            status = call();
-            Py_END_ALLOW_THREADS
+            // (noexcept: an exception out of the C entry point would leave here without the lock)
+            const int status = [&]() noexcept {
+                int st;
+                Py_BEGIN_ALLOW_THREADS
+                st = call();
+                Py_END_ALLOW_THREADS
+                return st;
+            }();
             return PyLong_FromLong(status);
         } catch (...) {  // declined, or a tensor that has no address: nothing has been called
         }
@@ -153,7 +171,7 @@ PyObject* run(Py_ssize_t given, Py_ssize_t wanted, F&& marshal) {
 #define MX_CALL(name) PyObject* name(PyObject*, PyObject* const* a, Py_ssize_t n)
 
 MX_CALL(quantize) {  // x, rule, codes, scales
-    return run(n, 4, [&] {
+    return run(a, n, "tstt", [&] {
         const Rows x = bf16_rows(a[0]);
         const mx_rule_t r = rule(a[1]);
         uint8_t *c = bytes(a[2], x.rows, x.K / 2), *s = bytes(a[3], x.rows, x.K / 32);
@@ -162,7 +180,7 @@ MX_CALL(quantize) {  // x, rule, codes, scales
     });
 }
 MX_CALL(quantize_mbs) {  // x, rule, codes, scales, mbs
-    return run(n, 5, [&] {
+    return run(a, n, "tsttt", [&] {
         const Rows x = bf16_rows(a[0]);
         const mx_rule_t r = rule(a[1]);
         uint8_t *c = bytes(a[2], x.rows, x.K / 2), *s = bytes(a[3], x.rows, x.K / 32), *m = bytes(a[4], x.rows, (x.K + 127) / 128);
@@ -171,7 +189,7 @@ MX_CALL(quantize_mbs) {  // x, rule, codes, scales, mbs
     });
 }
 MX_CALL(quantize_mbs_pair) {  // x0, x1, rule, codes0, scales0, mbs0, codes1, scales1, mbs1
-    return run(n, 9, [&] {
+    return run(a, n, "ttstttttt", [&] {
         const Rows x = bf16_rows(a[0]), y = bf16_rows(a[1]);
         need(x.K == y.K);
         const mx_rule_t r = rule(a[2]);
@@ -182,7 +200,7 @@ MX_CALL(quantize_mbs_pair) {  // x0, x1, rule, codes0, scales0, mbs0, codes1, sc
     });
 }
 MX_CALL(quantize_mbs_dynamic) {  // x, rule, first, count, stride, codes, scales, mbs
-    return run(n, 8, [&] {
+    return run(a, n, "tsiiittt", [&] {
         const Rows x = bf16_rows(a[0]);
         const mx_rule_t r = rule(a[1]);
         const int64_t first = integer(a[2]), count = integer(a[3]), stride = integer(a[4]);
@@ -193,7 +211,7 @@ MX_CALL(quantize_mbs_dynamic) {  // x, rule, first, count, stride, codes, scales
     });
 }
 MX_CALL(quantize_elem) {  // x, elem, rule, use_mbs, codes, scales, mbs (looked at with use_mbs only)
-    return run(n, 7, [&] {
+    return run(a, n, "tssbtto", [&] {
         const Rows x = bf16_rows(a[0]);
         const mx_elem_t e = elem(a[1]);
         const mx_rule_t r = rule(a[2]);
@@ -204,7 +222,7 @@ MX_CALL(quantize_elem) {  // x, elem, rule, use_mbs, codes, scales, mbs (looked 
     });
 }
 MX_CALL(dequantize) {  // codes, scales, mbs, type, out
-    return run(n, 5, [&] {
+    return run(a, n, "toodt", [&] {
         const at::Tensor& c = matrix(a[0]);
         const int64_t rows = c.size(0), K = c.size(1) * 2;
         const uint8_t *s = optional(a[1]), *m = optional(a[2]), *cp = address(c);
@@ -224,7 +242,7 @@ Operands operands(PyObject* ac, PyObject* as, PyObject* am, PyObject* bc, PyObje
     return {address(x), optional(as), optional(am), address(w), optional(bs), optional(bm), x.size(0), w.size(0), x.size(1) * 2};
 }
 MX_CALL(gemm) {  // a_codes, a_scales, b_codes, b_scales, type, out
-    return run(n, 6, [&] {
+    return run(a, n, "totodt", [&] {
         const Operands p = operands(a[0], a[1], Py_None, a[2], a[3], Py_None);
         const Out o = out_matrix(a[4], a[5], p.M, p.N);
         void* st = stream();
@@ -232,7 +250,7 @@ MX_CALL(gemm) {  // a_codes, a_scales, b_codes, b_scales, type, out
     });
 }
 MX_CALL(gemm_mbs) {  // a_codes, a_scales, a_mbs, b_codes, b_scales, b_mbs, type, out
-    return run(n, 8, [&] {
+    return run(a, n, "tootoodt", [&] {
         const Operands p = operands(a[0], a[1], a[2], a[3], a[4], a[5]);
         const Out o = out_matrix(a[6], a[7], p.M, p.N);
         void* st = stream();
@@ -247,11 +265,12 @@ Groups groups(PyObject* offsets, PyObject* N, int64_t b_rows) {
     const at::Tensor& t = tensor(offsets);
     need(t.scalar_type() == at::kLong && t.is_contiguous());
     const int64_t count = t.numel() - 1;
-    need(count == (int32_t)count && b_rows == count * integer(N));
+    int64_t rows;
+    need(count == (int32_t)count && !__builtin_mul_overflow(count, integer(N), &rows) && rows == b_rows);
     return {address<const int64_t>(t), (int32_t)count};
 }
 MX_CALL(gemm_mbs_grouped) {  // a_codes, a_scales, a_mbs, b_codes, b_scales, b_mbs, row_offsets, N, type, out
-    return run(n, 10, [&] {
+    return run(a, n, "tootootidt", [&] {
         const Operands p = operands(a[0], a[1], a[2], a[3], a[4], a[5]);
         const Groups g = groups(a[6], a[7], p.N);
         const int64_t N = integer(a[7]);
@@ -261,7 +280,7 @@ MX_CALL(gemm_mbs_grouped) {  // a_codes, a_scales, a_mbs, b_codes, b_scales, b_m
     });
 }
 MX_CALL(gemm_mbs_quantize_a) {  // a, rule, a_use_mbs, b_codes, b_scales, b_mbs, type, out
-    return run(n, 8, [&] {
+    return run(a, n, "tsbtoodt", [&] {
         const Rows x = bf16_rows(a[0]);
         const mx_rule_t r = rule(a[1]);
         const bool words = flag(a[2]);
@@ -289,7 +308,7 @@ ElemOperands elem_operands(PyObject* const* a) {  // a_elem, a_codes, a_scales, 
     return q;
 }
 MX_CALL(gemm_mbs_elem) {  // a_elem .. b_mbs, type, out
-    return run(n, 10, [&] {
+    return run(a, n, "sttosttodt", [&] {
         const ElemOperands q = elem_operands(a);
         const Out o = out_matrix(a[8], a[9], q.p.M, q.p.N);
         void* st = stream();
@@ -300,7 +319,7 @@ MX_CALL(gemm_mbs_elem) {  // a_elem .. b_mbs, type, out
     });
 }
 MX_CALL(gemm_mbs_elem_grouped) {  // a_elem .. b_mbs, row_offsets, N, type, out
-    return run(n, 12, [&] {
+    return run(a, n, "sttosttotidt", [&] {
         const ElemOperands q = elem_operands(a);
         const Groups g = groups(a[8], a[9], q.p.N);
         const int64_t N = integer(a[9]);
