@@ -174,7 +174,7 @@ def _torch():
         for names, value in (((MX_OUT_F32, "f32", "fp32", torch.float32), (MX_OUT_F32, torch.float32)),
                              ((MX_OUT_BF16, "bf16", torch.bfloat16), (MX_OUT_BF16, torch.bfloat16))):
             _out_dtypes.update((name, value) for name in names)
-        _native = _load_native()
+        _native = _load_native(torch)
         _torch_module = torch
     return _torch_module
 
@@ -184,17 +184,34 @@ _NATIVE_CALLS = ("mx_quantize", "mx_quantize_mbs", "mx_quantize_mbs_pair", "mx_q
                  "mx_gemm_mbs", "mx_gemm_mbs_grouped", "mx_gemm_mbs_quantize_a", "mx_gemm_mbs_elem", "mx_gemm_mbs_elem_grouped")
 
 
-def _load_native():
-    """The native marshaller (the build step makes it beside libmx4.so); without it every call goes through ctypes."""
+def marshal_tag(torch) -> str:
+    """What a native marshaller has to have been compiled against to be loaded here: this interpreter and this torch."""
+    import sysconfig
+
+    return "%s torch-%s" % (sysconfig.get_config_var("SOABI"), torch.__version__)
+
+
+def _load_native(torch):
+    """The native marshaller (the build step makes it beside libmx4.so).  Without one, or with one made for another torch or
+    interpreter, every call goes through ctypes."""
     if not os.path.exists(_MARSHAL_PATH):
         return None
     import importlib.machinery
     import importlib.util
+    import warnings
 
     L = load_library()
     loader = importlib.machinery.ExtensionFileLoader("_marshal", _MARSHAL_PATH)
-    module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_marshal", _MARSHAL_PATH, loader=loader))
-    loader.exec_module(module)
+    try:
+        module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_marshal", _MARSHAL_PATH, loader=loader))
+        loader.exec_module(module)
+        built_for = module.built_for()
+    except (ImportError, AttributeError) as e:
+        warnings.warn("%s does not load, calls go through ctypes: %s" % (_MARSHAL_PATH, e))
+        return None
+    if built_for != marshal_tag(torch):
+        warnings.warn("%s was built for %s, not for %s: calls go through ctypes" % (_MARSHAL_PATH, built_for, marshal_tag(torch)))
+        return None
     module.use(*(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in _NATIVE_CALLS))
     return module
 

@@ -50,7 +50,7 @@ def _run(cmd, verbose):
     # the host pass warns that it does not know the packed-fp32 target feature; that is harmless
     out = "\n".join(l for l in proc.stdout.splitlines() if "packed-fp32-ops" not in l)
     if proc.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + " ".join(cmd) + "\n" + out)
+        raise RuntimeError(os.path.basename(cmd[0]) + " failed:\n" + " ".join(cmd) + "\n" + out)
     if verbose and out.strip():
         print(out)
 
@@ -60,11 +60,37 @@ def _marshal_command(out):
 
     import torch
 
+    from .binding import marshal_tag
+
     top = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(shutil.which(HIPCC) or HIPCC)))
     include = [os.path.join(ROOT, "include"), os.path.join(top, "include"), os.path.join(top, "include", "torch", "csrc", "api", "include"),
-               os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"), sysconfig.get_paths()["include"]]
-    return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1"]
+               os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]
+    return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", '-DMX_BUILT_FOR="%s"' % marshal_tag(torch)]
             + [a for i in include for a in ("-I", i)] + [MARSHAL_SRC, "-L", os.path.join(top, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-o", out])
+
+
+def build_marshal(verbose: bool = False) -> None:
+    """The native marshaller.  The C-ABI library needs neither torch nor g++, so it is built first and stands where this fails; where
+    one of the two is missing there is nothing to build, and the binding goes through ctypes."""
+    work = tempfile.mkdtemp(prefix="mx4_marshal_")
+    try:
+        # (one made for an older library would be called with its entry points)
+        if os.path.exists(MARSHAL_LIB):
+            os.remove(MARSHAL_LIB)
+        tmp = os.path.join(work, "_marshal.so")
+        try:
+            command = _marshal_command(tmp)
+        except ImportError as e:
+            print("native marshaller not built: %s" % e, flush=True)
+            return
+        if shutil.which(command[0]) is None:
+            print("native marshaller not built: no %s" % command[0], flush=True)
+            return
+        _run(command, verbose)
+        shutil.move(tmp, MARSHAL_LIB)
+    finally:
+        shutil.rmtree(work, ignore_errors=True)
 
 
 def build(verbose: bool = False) -> str:
@@ -77,8 +103,6 @@ def build(verbose: bool = False) -> str:
             obj = os.path.join(work, name + ".o")
             objs.append(obj)
             jobs.append([HIPCC] + FLAGS + EXTRA.get(name, VGPR_FORM) + ["-c", src, "-o", obj])
-        marshal = os.path.join(work, "_marshal.so")
-        jobs.append(_marshal_command(marshal))
         with ThreadPoolExecutor(max_workers=min(8, len(jobs))) as pool:
             list(pool.map(lambda c: _run(c, verbose), jobs))
         tmp = os.path.join(work, "libmx4.so")
@@ -89,13 +113,13 @@ def build(verbose: bool = False) -> str:
         if missing:
             raise RuntimeError("libmx4.so has unresolved symbols: " + ", ".join(missing))
         shutil.move(tmp, LIB)
-        shutil.move(marshal, MARSHAL_LIB)
         bench_srcs = sorted(glob.glob(os.path.join(BENCH_CSRC, "*.hip")))
         tmp = os.path.join(work, "libmx4_bench.so")
         _run([HIPCC] + FLAGS + ["-shared"] + bench_srcs + ["-o", tmp], verbose)
         shutil.move(tmp, BENCH_LIB)
     finally:
         shutil.rmtree(work, ignore_errors=True)
+    build_marshal(verbose)
     return LIB
 
 

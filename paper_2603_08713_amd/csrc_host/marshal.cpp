@@ -351,8 +351,12 @@ PyObject* use(PyObject*, PyObject* const* a, Py_ssize_t n) {
     Py_RETURN_NONE;
 }
 
+// what this module was compiled against: the binding compares it before any other call (torch's objects are read through inline
+// headers, at the offsets of that torch)
+PyObject* built_for(PyObject*, PyObject* const*, Py_ssize_t) { return PyUnicode_FromString(MX_BUILT_FOR); }
+
 #define MX_METHOD(name) {#name, (PyCFunction)(void (*)(void))name, METH_FASTCALL, nullptr}
-PyMethodDef methods[] = {MX_METHOD(use), MX_METHOD(quantize), MX_METHOD(quantize_mbs), MX_METHOD(quantize_mbs_pair), MX_METHOD(quantize_mbs_dynamic),
+PyMethodDef methods[] = {MX_METHOD(built_for), MX_METHOD(use), MX_METHOD(quantize), MX_METHOD(quantize_mbs), MX_METHOD(quantize_mbs_pair), MX_METHOD(quantize_mbs_dynamic),
                          MX_METHOD(quantize_elem), MX_METHOD(dequantize), MX_METHOD(gemm), MX_METHOD(gemm_mbs), MX_METHOD(gemm_mbs_grouped),
                          MX_METHOD(gemm_mbs_quantize_a), MX_METHOD(gemm_mbs_elem), MX_METHOD(gemm_mbs_elem_grouped), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
