@@ -1,9 +1,10 @@
 """The 8-bit and 6-bit GEMM on 64 x 128 tiles, where they can go wrong: the edges of a tile, K's last group of four stages whole,
 one block pair long and one short, rows of scales at any address, groups that end inside a tile.  The tile shapes and the
-general form, which other tests hold to the oracle, add the same products in the same order: their results are the same bits."""
+general form add the same products in the same order: their results are the same bits.  The tiles themselves are held to the oracle too."""
 import numpy as np
 import pytest
 
+from test_gpu_parity_elem import ALL_PAIRS, assert_gemm_elem_ok, gpu_gemm, random_operand_any
 from test_gpu_row_pieces import dev, mx, torch  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -45,3 +46,16 @@ def test_groups_of_few_rows(mx, elem):  # noqa: F811
             with mx.forced(gemm_elem=16):
                 want = mx.mx_gemm_mbs_elem(elem, *[t[lo:hi].contiguous() for t in da], elem, *[t[e * N:(e + 1) * N].contiguous() for t in dw], "f32")
             assert torch.equal(got[lo:hi], want), (elem, e)
+
+
+# (one group of four stages whole, a group of one block pair, three stages, several groups with a short one; with words on both sides, one, none)
+@pytest.mark.parametrize("ea,eb", ALL_PAIRS)
+def test_against_the_oracle(mx, oracle, ea, eb):  # noqa: F811
+    rng = np.random.default_rng(64)
+    hi = 132 if "e5m2" in (ea, eb) else 140
+    for M, N, K in ((63, 129, 512), (65, 40, 576), (130, 131, 896), (33, 257, 2880)):
+        (a, pa), (b, pb) = random_operand_any(rng, ea, M, K, 110, hi), random_operand_any(rng, eb, N, K, 110, hi)
+        for wa, wb in ((True, True), (False, True), (False, False)):
+            got = gpu_gemm(mx, ea, (pa[0], pa[1], pa[2] if wa else None), eb, (pb[0], pb[1], pb[2] if wb else None), kernel=18)
+            assert_gemm_elem_ok(oracle, got.cpu().numpy(), ea, (a[0], a[1], a[2] if wa else None), eb, (b[0], b[1], b[2] if wb else None),
+                                "64 x 128 tiles %s x %s %dx%dx%d words %d%d" % (ea, eb, M, N, K, wa, wb))
