@@ -14,8 +14,7 @@ namespace {
 
 // force_shape (mx_internal_gemm only; the public entry points pass -1 = automatic): 2 / 6 / 7 = fast form without
 // MBS on 256x256 / 256x128 / 128x128 tiles, 3 / 4 = fast form with MBS on 256x128 / 128x128 tiles, 5 = few-row
-// kernel, 8 / 9 = general form (row pieces through registers) on 256x128 / 128x128 tiles, 10 = general form (single bytes, any K:
-// K = 0) on 128x128 tiles, 11 / 12 = fast form with MBS on both operands / general form with MBS on 64x128 tiles, 17 / 18 / 19 = few-row
+// kernel, 8 / 9 = general form (row pieces through registers) on 256x128 / 128x128 tiles, 11 / 12 = fast form with MBS on both operands / general form with MBS on 64x128 tiles, 17 / 18 / 19 = few-row
 // kernel on tiles of 64 rows and 16 / 32 / 64 columns.
 // Grouped problems with words: what the kernels take, in us, from rows, groups and the number of macro blocks; the launch cannot know the
 // routing, so a group is taken to end half a tile-row short and every group to have rows.  Fitted to Zipf and equal routings over 8, 32
@@ -45,7 +44,7 @@ bool grouped_small_tile(int64_t M, int64_t N, int64_t K, int64_t num_groups) {
     return M <= 128 * num_groups || p.small < 0.85 * p.big;
 }
 
-// Which kernel form and tile shape (the codes above) takes a problem.  Tiles run in rounds of one per compute
+// Which kernel form and tile shape (the codes above) takes a problem with K > 0.  Tiles run in rounds of one per compute
 // unit: rounds x tile area / efficiency (the small tile reaches about 0.8 of the large tile's rate per output
 // with MBS, 0.85 / 0.72 without; measured) picks the tile.  With words on both operands, ungrouped, 64 x 128 tiles
 // take what they cover in one round: twice the compute units have work, and a tile of few rows is bound by a stage's serial chain
@@ -62,12 +61,12 @@ int choose_shape(int64_t M, int64_t N, int64_t K, int64_t num_groups, bool use_m
                  small = ((t128 + 255) / 256) / (use_mbs ? 0.8 : 0.72);
     if (skinny_ok) return 5;
     if (row_tile_cols > 0) return row_tile_cols == 16 ? 17 : row_tile_cols == 32 ? 18 : 19;
-    if (num_groups > 0 && use_mbs && K > 0) return grouped_small_tile(M, N, K, num_groups) ? 12 : 8;
-    if (tile64_ok && ((M + 63) / 64) * ((N + 127) / 128) <= 256 && K > 0) return ring_ok ? 11 : 12;
+    if (num_groups > 0 && use_mbs) return grouped_small_tile(M, N, K, num_groups) ? 12 : 8;
+    if (tile64_ok && ((M + 63) / 64) * ((N + 127) / 128) <= 256) return ring_ok ? 11 : 12;
     // Past one round, with words on both operands or in the general form: by the kernels' prices (mx_gemm_shared.h)
     // (256 x 128, 128 x 128 and 64 x 128 tiles, us: 2316 x 3815 x 5120 65, 69, 60; 5676 x 1854 x 512 18.2, 19.0, 16.8;
     // 1579 x 2784 x 1024 11.2, 14.6, 12.5; 1367 x 3890 x 7296 50, 73, 61)
-    if (K > 0 && more_than_a_round_of_64x128(M, N) && (tile64_ok || (!use_mbs && !ring_ok))) {
+    if (more_than_a_round_of_64x128(M, N) && (tile64_ok || (!use_mbs && !ring_ok))) {
         static const TilePrice kFast[3] = {{256, 128, 256, 0.7, 3.40, 0.003, 4.91, 0.726}, {128, 128, 256, 0.8, 2.72, 0.018, 3.26, 0.480}, {64, 128, 512, 0.4, 3.83, 0.098, 2.29, 0.453}};
         static const TilePrice kGeneral[3] = {{256, 128, 256, 0.7, 2.82, 0.030, 5.48, 0.815}, {128, 128, 256, 0.8, 2.64, 0.021, 3.25, 0.592}, {64, 128, 512, 0.6, 3.27, 0.100, 2.81, 0.523}};
         static const TilePrice kPlain[2] = {{256, 128, 256, 0.8, 3.27, -0.051, 4.71, 0.651}, {128, 128, 256, 0.4, 3.00, 0.146, 1.93, 0.313}};
@@ -79,7 +78,7 @@ int choose_shape(int64_t M, int64_t N, int64_t K, int64_t num_groups, bool use_m
         return ring_ok ? 11 : 12;
     }
     if (ring_ok) return use_mbs ? (big <= small ? 3 : 4) : 2;  // (without MBS the launcher also has 256 x 256 tiles)
-    return K == 0 ? 10 : big <= small ? 8 : 9;
+    return big <= small ? 8 : 9;
 }
 
 // The few-row kernel's tile for M <= 64: the smallest fm that covers the rows; fn so that the launch has about one
@@ -145,7 +144,6 @@ bool few_rows_pay(int64_t M, int64_t N, int64_t K, const SkinnyPlan& p, int side
 }
 // Whether the few-row kernel takes a problem (num_groups: 0 = not grouped; sides: how many operands have words).
 bool takes_few_rows(int64_t M, int64_t N, int64_t K, int64_t num_groups, bool ring_ok, bool pairs_ok, int sides) {
-    if (K == 0) return false;
     if (num_groups > 0) {
         if (M > kFewRowsPerGroup * num_groups || few_rows_blocks(M, N, num_groups, !pairs_ok) > kFewRowsMaxBlocks) return false;
         const int64_t st = (K + kMacro - 1) / kMacro;
@@ -174,6 +172,29 @@ int row_tile_columns(int64_t M, int64_t N, int64_t K, int64_t num_groups, bool r
     if (rows * ((frags + 1) / 2) <= 256 && (ring_ok || pairs_ok)) return 32;
     if (rows * ((frags + 3) / 4) <= 256 && ring_ok && K >= 3072) return 64;
     return 0;
+}
+
+// K = 0, an empty sum: the rows of C become zero, of a grouped problem those that belong to a group.
+template <typename T>
+__global__ __launch_bounds__(256) void gemm_zero_kernel(GemmArgs g) {
+    constexpr int per = 16 / sizeof(T);
+    const int64_t rows = g.num_groups > 0 ? min(g.row_offsets[g.num_groups], g.M) : g.M, pieces = (g.N + per - 1) / per;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < rows * pieces; i += (int64_t)gridDim.x * 256) {
+        const int64_t n = i % pieces * per;
+        T* o = static_cast<T*>(g.C) + i / pieces * g.ldc + n;
+        if (n + per <= g.N) {
+            *reinterpret_cast<v4i_any*>(o) = v4i{0, 0, 0, 0};
+        } else {
+            for (int e = 0; n + e < g.N; ++e) o[e] = 0;
+        }
+    }
+}
+int launch_gemm_zero(const GemmArgs& g, hipStream_t s) {
+    const int64_t pieces = g.c_bf16 ? (g.N + 7) / 8 : (g.N + 3) / 4;
+    const unsigned blocks = (unsigned)std::min<int64_t>((g.M * pieces + 255) / 256, 8192);
+    if (g.c_bf16) gemm_zero_kernel<uint16_t><<<dim3(blocks), dim3(256), 0, s>>>(g);
+    else gemm_zero_kernel<uint32_t><<<dim3(blocks), dim3(256), 0, s>>>(g);
+    return launch_status();
 }
 
 int launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* a_mbs, const uint8_t* b_codes,
@@ -205,36 +226,33 @@ int launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* 
     g.vec_store16 = aligned(C, 16) && (ldc * esz) % 16 == 0;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (K == 0) return force_shape < 0 ? launch_gemm_zero(g, s) : MX_EINVAL;
     const bool use_mbs = mbs_entry && (a_mbs || b_mbs);
     // Fast form: K in whole groups of four macro blocks and aligned per-row arrays.
-    const bool ring_ok = !grouped && K > 0 && (K % 512) == 0 && aligned(a_scales, 16) && aligned(b_scales, 16) &&
+    const bool ring_ok = !grouped && (K % 512) == 0 && aligned(a_scales, 16) && aligned(b_scales, 16) &&
                          (!use_mbs || ((!a_mbs || aligned(a_mbs, 4)) && (!b_mbs || aligned(b_mbs, 4))));
     // (few-row kernel: pairs of E8M0 bytes; else single ones)
-    const bool pairs_ok = K > 0 && (K % 64) == 0 && aligned(a_scales, 2) && aligned(b_scales, 2);
+    const bool pairs_ok = (K % 64) == 0 && aligned(a_scales, 2) && aligned(b_scales, 2);
     const bool skinny_ok = takes_few_rows(M, N, K, g.num_groups, ring_ok, pairs_ok, use_mbs ? (a_mbs != nullptr) + (b_mbs != nullptr) : 0);
     const bool tile64_ok = !grouped && a_mbs && b_mbs && mbs_entry;
     int shape = choose_shape(M, N, K, g.num_groups, use_mbs, ring_ok, skinny_ok, row_tile_columns(M, N, K, g.num_groups, ring_ok, pairs_ok), tile64_ok);
     if (force_shape >= 0) shape = force_shape;
     // (the checks below only matter for forced shapes)
     if (shape == 5) {
-        if (K == 0 || (!grouped && (M > 64 || K > 8192))) return MX_EINVAL;
+        if (!grouped && (M > 64 || K > 8192)) return MX_EINVAL;
         if (grouped) return launch_gemm_skinny_grouped(g, use_mbs, !pairs_ok, s);
         const SkinnyPlan p = plan_skinny(M, N, K, ring_ok, pairs_ok);
         return launch_gemm_skinny_tile(g, use_mbs, p.fm, p.fn, p.form, s);
     }
     if (shape >= 17 && shape <= 19) {
-        if (grouped || K == 0 || K > 8192) return MX_EINVAL;
+        if (grouped || K > 8192) return MX_EINVAL;
         return launch_gemm_skinny_rows(g, use_mbs, shape == 17 ? 1 : shape == 18 ? 2 : 4, plan_skinny(64, N, K, ring_ok, pairs_ok).form, s);
     }
     if (shape == 11 || shape == 12) {
-        if (!use_mbs || (shape == 11 ? !ring_ok || !a_mbs || !b_mbs : K == 0)) return MX_EINVAL;
-        return shape == 11 ? launch_gemm_mbs_ring(g, 2, s) : launch_gemm_mbs_general(g, 2, false, s);
+        if (!use_mbs || (shape == 11 && (!ring_ok || !a_mbs || !b_mbs))) return MX_EINVAL;
+        return shape == 11 ? launch_gemm_mbs_ring(g, 2, s) : launch_gemm_mbs_general(g, 2, s);
     }
-    if (shape == 8 || shape == 9) {
-        if (K == 0) return MX_EINVAL;
-        return use_mbs ? launch_gemm_mbs_general(g, shape - 8, false, s) : launch_gemm_wide_general(g, shape - 8, false, s);
-    }
-    if (shape == 10) return use_mbs ? launch_gemm_mbs_general(g, 1, true, s) : launch_gemm_wide_general(g, 1, true, s);
+    if (shape == 8 || shape == 9) return use_mbs ? launch_gemm_mbs_general(g, shape - 8, s) : launch_gemm_wide_general(g, shape - 8, s);
     const bool plain_shape = shape == 2 || shape == 6 || shape == 7;
     if (shape < 2 || shape > 7 || !ring_ok || plain_shape == use_mbs) return MX_EINVAL;
     if (plain_shape) return launch_gemm_wide(g, force_shape < 0 ? 0 : shape == 2 ? 1 : shape == 6 ? 2 : 3, s);
@@ -303,7 +321,8 @@ int mx_gemm_mbs_grouped(const uint8_t* a_codes, const uint8_t* a_scales, const u
 int mx_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int a_has_mbs, int b_has_mbs, int num_groups, char* out, int cap) {
     if (!out || cap <= 0 || M < 0 || N < 0 || K < 0 || (K % mx::kBlock) != 0 || num_groups < 0) return MX_EINVAL;
     const bool use_mbs = a_has_mbs || b_has_mbs, grouped = num_groups > 0;
-    const bool ring_ok = !grouped && K > 0 && (K % 512) == 0, pairs_ok = K > 0 && (K % 64) == 0;
+    if (K == 0) return snprintf(out, (size_t)cap, "gemm_zero_kernel"), MX_OK;
+    const bool ring_ok = !grouped && (K % 512) == 0, pairs_ok = (K % 64) == 0;
     const int shape = mx::choose_shape(M, N, K, num_groups, use_mbs, ring_ok, mx::takes_few_rows(M, N, K, num_groups, ring_ok, pairs_ok, (a_has_mbs != 0) + (b_has_mbs != 0)),
                                        mx::row_tile_columns(M, N, K, num_groups, ring_ok, pairs_ok),
                                        !grouped && a_has_mbs && b_has_mbs);
@@ -320,7 +339,6 @@ int mx_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int a_has_mbs, int b_
         case 19: what = "gemm_skinny_kernel, tiles of 64 rows and 64 columns"; break;
         case 11: what = "gemm_ring_kernel, fast form, 64x128 tile, 4 wavefronts of 64x32"; break;
         case 12: what = "gemm_ring_kernel, general form (row pieces through registers), 64x128 tile, 4 wavefronts of 64x32"; break;
-        case 10: what = "gemm_ring_kernel, general form (single scale bytes), 128x128 tile"; break;
         case 8: what = use_mbs ? "gemm_ring_kernel, general form (row pieces through registers), 256x128 tile, 8 wavefronts" : "gemm_ring_kernel, general form (row pieces through registers), 256x128 tile, 4 wavefronts"; break;
         default: what = "gemm_ring_kernel, general form (row pieces through registers), 128x128 tile"; break;
     }

@@ -142,7 +142,7 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
         const int row = ((i * NW + w) * 16 + (l >> 2)) - (i * NW * 16 < TM ? 0 : TM);  // row within its operand
         code_off[i] = row * row_bytes + (((l & 3) ^ ((row >> 2) & 3)) * 16);
     }
-    // Per-row loads (not in single bytes): load i of wavefront w serves row (i * NW + w) * 64 + l with the 16 E8M0
+    // Per-row loads: load i of wavefront w serves row (i * NW + w) * 64 + l with the 16 E8M0
     // bytes, or the 4 MBS words, of a group of four stages; rows past the tile are padding and read zero.
     int scale_off[kRowDma], m8_off[kRowDma];
     bool row_is_a[kRowDma];
@@ -154,17 +154,13 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
         scale_off[i] = grow >= kRows ? kOob : row * scale_bytes;
         m8_off[i] = grow >= kRows ? kOob : row * nmac;
     }
-    // Single bytes: E8M0 load i of wavefront w serves rows (i * NW + w) * 4 .. + 3, lane l byte l % 16 of row l / 16;
-    // MBS load i serves rows (i * NW + w) * 16 .. + 15, lane l word l % 4 of row l / 4.
     const int gen_code_col = ((l & 3) ^ ((l >> 4) & 3)) * 16;  // this lane's chunk of the 64-byte stage piece
-    const int gen_scale_col = l & 15, gen_scale_off = (w * 4 + (l >> 4)) * scale_bytes + gen_scale_col;
-    const int gen_m8_off = (w * 16 + (l >> 2)) * nmac + (l & 3), gen_m8_col = l & 3;
-    // Form 1 takes any K % 32 == 0: a chunk of codes is one E8M0 block, so the blocks of the last stage that do not exist are chunks
+    // The general form takes any K % 32 == 0: a chunk of codes is one E8M0 block, so the blocks of the last stage that do not exist are chunks
     // past the end of the row, and their E8M0 bytes are zeros like the rest of a partial group.
     // The groups of four stages that K fills, and the slot of a group (the partial last one has its own).
     const int nwhole = K / (kRingGroup * kRingStageK);
-    auto group_slot = [&](int grp) { return S::kRegs && grp >= nwhole ? 2 : grp & 1; };
-    // A row's E8M0 bytes and MBS words on their way through registers (form 1): requested in one stage with a barrier,
+    auto group_slot = [&](int grp) { return S::kGen && grp >= nwhole ? 2 : grp & 1; };
+    // A row's E8M0 bytes and MBS words on their way through registers (general form): requested in one stage with a barrier,
     // written in the next.  Loads into registers serve rows at any address and cost the texture-address unit one
     // pass per row and group; fetched direct to LDS in 2-byte and 1-byte pieces, as this form once did, they cost nine
     // passes of 64 clocks per wavefront and group, three times what the codes cost.  Without MBS words that was what
@@ -192,18 +188,9 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
     };
     auto dma_scale = [&](int grp, auto i_) {  // load i of the E8M0 bytes of stages 4 grp .. 4 grp + 3
         constexpr int i = decltype(i_)::value;
-        if constexpr (S::kRegs) {
+        if constexpr (S::kGen) {
             const __amdgpu_buffer_rsrc_t rsrc = row_is_a[i] ? opa.scales : opb.scales;
             reg_scale[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, grp < nwhole ? scale_off[i] : kOob, grp * 16, 0);
-        } else if constexpr (S::kBytes) {
-            constexpr int kPer = 4;
-            constexpr bool is_a = i * NW * kPer < TM;
-            uint8_t* dst = smem + S::kScaleBase + (grp & 1) * S::kScaleGroup + (i * NW + w) * 256;
-            // (the row goes into the per-lane offset, which is what the hardware checks against the valid rows)
-            const int in_range = gen_scale_off + (i * NW * kPer - (is_a ? 0 : TM)) * scale_bytes;
-            const int voff = grp * 16 + gen_scale_col < scale_bytes ? in_range : kOob;  // past K: zero
-            const __amdgpu_buffer_rsrc_t rsrc = is_a ? opa.scales : opb.scales;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)dst, 1, voff, grp * 16, 0, 0);
         } else {
             uint8_t* dst = smem + S::kScaleBase + (grp & 1) * S::kScaleGroup + (i * NW + w) * 1024;
             const int voff = scale_off[i];
@@ -213,16 +200,9 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
     };
     auto dma_m8 = [&](int grp, auto i_) {  // load i of the MBS words of stages 4 grp .. 4 grp + 3
         constexpr int i = decltype(i_)::value;
-        if constexpr (S::kRegs) {
+        if constexpr (S::kGen) {
             const __amdgpu_buffer_rsrc_t rsrc = row_is_a[i] ? opa.mbs : opb.mbs;
             reg_m8[i] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, grp < nwhole ? m8_off[i] : kOob, grp * 4, 0);
-        } else if constexpr (S::kBytes) {
-            constexpr bool is_a = i * NW * 16 < TM;
-            uint8_t* dst = smem + S::kM8Base + (grp & 1) * S::kM8Group + (i * NW + w) * 256;
-            const int in_range = gen_m8_off + (i * NW * 16 - (is_a ? 0 : TM)) * nmac;
-            const int voff = grp * 4 + gen_m8_col < nmac ? in_range : kOob;  // past K: zero
-            const __amdgpu_buffer_rsrc_t rsrc = is_a ? opa.mbs : opb.mbs;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)dst, 1, voff, grp * 4, 0, 0);
         } else {
             uint8_t* dst = smem + S::kM8Base + (grp & 1) * S::kM8Group + (i * NW + w) * 256;
             const int voff = m8_off[i];
@@ -230,7 +210,7 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)dst, 4, voff, min(grp, ngroups - 1) * 4, 0, 0);
         }
     };
-    // form 1: what has arrived in registers to its group's slot
+    // general form: what has arrived in registers to its group's slot
     auto put_scale = [&](int slot, const v4i (&v)[kRowDma]) {
 #pragma unroll
         for (int i = 0; i < kRowDma; ++i)
@@ -243,7 +223,7 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
                 *reinterpret_cast<uint32_t*>(smem + S::kM8Base + slot * S::kM8Group + (i * NT + tid) * 4) = v[i];
         }
     };
-    // form 1: the partial last group of K, zeros behind its end: a row's last 16 bytes (requested ahead of everything
+    // general form: the partial last group of K, zeros behind its end: a row's last 16 bytes (requested ahead of everything
     // else), shifted down by those of the group before when they have arrived.  Rows of fewer than 16 bytes (K < 512) come as
     // the dwords, the pair and the byte that they have, all requested at once when they are put together (byte by byte, each waited for, 128 x
     // 4096 x 448 took 7.2 us instead of 5.2).  Not ahead of everything else: a branch for them in front of the prologue gains
@@ -310,9 +290,7 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
         for (int i = 0; i < kConv; ++i) {
             const int q = i * NT + tid;  // (a side without words reads zero and stores sigma = 1, which nobody reads)
             const int p = (kRows % NT == 0 || q < kRows) ? q : 0;
-            // a row's four words in one dword; single bytes: one word per dword, [row][4]
-            r.first[i] = S::kBytes ? raw[p * kRingGroup + s % kRingGroup] : raw[p];
-            r.second[i] = S::kBytes ? raw[p * kRingGroup + s % kRingGroup + 1] : r.first[i];
+            r.first[i] = r.second[i] = raw[p];  // (a row's four words in one dword)
         }
     };
     auto store_sigma = [&](int s, const uint32_t (&words)[kConv]) {
@@ -321,7 +299,7 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
         for (int i = 0; i < kConv; ++i) {
             const int q = i * NT + tid;
             const bool live = kRows % NT == 0 || q < kRows;
-            const uint32_t m8 = S::kBytes ? words[i] & 0xFFu : (words[i] >> (8 * (s % kRingGroup))) & 0xFFu;
+            const uint32_t m8 = (words[i] >> (8 * (s % kRingGroup))) & 0xFFu;
             float* dst = live ? sig + (live ? q : 0) : reinterpret_cast<float*>(smem + S::kDummy);
             *dst = __builtin_amdgcn_rcpf(1.0f + (float)m8 * (1.0f / 256.0f));
         }
@@ -334,7 +312,7 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
         const uint8_t* tab = smem + S::kRcpBase;
 #pragma unroll
         for (int i = 0; i < kConv; ++i) {
-            const uint32_t at = S::kBytes ? (words[i] & 0xFFu) << 2 : ((words[i] >> (8 * (s % kRingGroup))) & 0xFFu) << 2;
+            const uint32_t at = ((words[i] >> (8 * (s % kRingGroup))) & 0xFFu) << 2;
             val[i] = *reinterpret_cast<const float*>(tab + at);
         }
     };
@@ -405,7 +383,7 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
             asm volatile("" : "+v"(code_base[o][kk][1]));
         }
     }
-    const int lane_scale = S::kBytes ? lr * 64 + lh * 8 : lr * 16 + lh * 2;
+    const int lane_scale = lr * 16 + lh * 2;
 
     // LDS read `idx` of the kReads that fetch the fragments of a stage in ring slot `slot`: per fragment (A's
     // FM, then B's FN) the two 16-byte code pieces and the 16-bit scale pair.
@@ -422,19 +400,9 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
             else f.n[q][part] = v;
         } else {
             const int row0 = is_m ? (wm * FM + q) * 32 : TM + (wn * FN + q) * 32;  // in the A-then-B row space
-            // [row][16 bytes of the group]; single bytes: one byte per dword (the lane's two bytes come as two dwords
-            // and are packed)
-            uint32_t v;
+            // [row][16 bytes of the group]
             const uint8_t* grp_base = smem + S::kScaleBase + (gp < 0 ? group_slot(s / kRingGroup) : gp) * S::kScaleGroup;
-            if constexpr (S::kBytes) {
-                // (a plain vector type: before a read through HIP's uint2 the compiler waits for every
-                // outstanding direct-to-LDS load)
-                typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-                const u32x2 two = *reinterpret_cast<const u32x2*>(grp_base + (s % kRingGroup) * 16 + lane_scale + row0 * 64);
-                v = (two.x & 0xFFu) | ((two.y & 0xFFu) << 8);
-            } else {
-                v = *(lds_half_ptr_t)(grp_base + (s % kRingGroup) * 4 + lane_scale + row0 * 16);
-            }
+            const uint32_t v = *(lds_half_ptr_t)(grp_base + (s % kRingGroup) * 4 + lane_scale + row0 * 16);
             if constexpr (is_m) f.scl_m[q] = v;
             else f.scl_n[q] = v;
         }
@@ -493,25 +461,25 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
     };
 
     // ---- prologue: fill the ring, fetch the operands of stage 0 --------------------------------------
-    if constexpr (S::kRegs) fetch_tail();
-    uint32_t first_m8[kRowDma];  // form 1: the words of group 0 (reg_m8 takes those of group 1)
+    if constexpr (S::kGen) fetch_tail();
+    uint32_t first_m8[kRowDma];  // general form: the words of group 0 (reg_m8 takes those of group 1)
     static_for<Sched::prologue_count()>([&](auto n_) {
         constexpr LoadItem it = Sched::prologue_item(decltype(n_)::value);
         using Index = std::integral_constant<int, it.index>;
         if constexpr (it.kind == kLoadCode) dma_code(it.what, Index{});
         else if constexpr (it.kind == kLoadScale) dma_scale(it.what, Index{});
         else dma_m8(it.what, Index{});
-        if constexpr (S::kRegs && it.kind == kLoadWords && it.what == 0) first_m8[it.index] = reg_m8[it.index];
+        if constexpr (S::kGen && it.kind == kLoadWords && it.what == 0) first_m8[it.index] = reg_m8[it.index];
     });
     if constexpr (kSigmaLut) {
         static_assert(NT >= 256, "one thread per table entry");
         if (tid < 256) reinterpret_cast<float*>(smem + S::kRcpBase)[tid] = __builtin_amdgcn_rcpf(1.0f + (float)tid * (1.0f / 256.0f));
         __builtin_amdgcn_s_waitcnt(kWaitLds);  // the barrier below publishes the table
     }
-    // (form 1: the compiler may issue group 1's words, which go to a register, earlier than the schedule has them; they are
+    // (general form: the compiler may issue group 1's words, which go to a register, earlier than the schedule has them; they are
     // not counted on to be among the youngest)
-    __builtin_amdgcn_s_waitcnt(wait_imm(Sched::prologue_wait_first() - (S::kRegs && kMbs ? kM8Dma : 0)));
-    if constexpr (S::kRegs) {
+    __builtin_amdgcn_s_waitcnt(wait_imm(Sched::prologue_wait_first() - (S::kGen && kMbs ? kM8Dma : 0)));
+    if constexpr (S::kGen) {
         put_scale(0, reg_scale);
         put_m8(0, first_m8);
         put_tail();
@@ -527,7 +495,7 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
         read_sigma_m(0, std::integral_constant<int, 0>{});
         read_sigma_n(0, std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
     }
-    static_for<kReads>([&](auto idx_) { read_item(f0, 0, std::integral_constant<int, 0>{}, idx_, std::integral_constant<int, S::kRegs ? -1 : 0>{}); });
+    static_for<kReads>([&](auto idx_) { read_item(f0, 0, std::integral_constant<int, 0>{}, idx_, std::integral_constant<int, S::kGen ? -1 : 0>{}); });
 
     // ---- the matrix instructions of one stage ---------------------------------------------------------
     // Plain: instruction t is half kk = t / (FM FN) of fragment pair (i, j); the two halves of a pair are
@@ -614,12 +582,12 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
             __builtin_amdgcn_s_waitcnt(wait_imm(Sched::wait_count(kPhase)));
             bare_barrier();
             // the words requested two stages ago: this thread alone reads them, from the next stage on
-            if constexpr (S::kRegs && kIssue && kPhase == 1) put_m8(kGp < 0 ? (s / kRingGroup + 1) & 1 : 1 - kGp, reg_m8);
+            if constexpr (S::kGen && kIssue && kPhase == 1) put_m8(kGp < 0 ? (s / kRingGroup + 1) & 1 : 1 - kGp, reg_m8);
         }
-        // form 1: the E8M0 bytes requested in the stage before (the compiler waits for them and lets the codes fly), written in the
+        // general form: the E8M0 bytes requested in the stage before (the compiler waits for them and lets the codes fly), written in the
         // middle of the stage so that the next one's barrier, which publishes them, does not wait for the LDS
         auto put_next_scale = [&]() {
-            if constexpr (S::kRegs && kIssue && kPhase == 2) put_scale(kGp < 0 ? (s / kRingGroup + 1) & 1 : 1 - kGp, reg_scale);
+            if constexpr (S::kGen && kIssue && kPhase == 2) put_scale(kGp < 0 ? (s / kRingGroup + 1) & 1 : 1 - kGp, reg_scale);
         };
         // a stage without a barrier converts the words of the stages s + 2 and s + 3 at its end (published by the
         // next stage's barrier, into the tables that the stages s - 2 and s - 1 were read from)
@@ -828,7 +796,7 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
     // Stages whose iteration still has a stage s + 4 to request, rounded up to whole groups (the extra ones
     // fetch the last stage again into slots that are no longer read); the rest runs without loads.
     const int n_issue = (max(nstages - kRingSlots, 0) + kRingGroup - 1) / kRingGroup * kRingGroup;
-    constexpr bool kSkip = S::kRegs;
+    constexpr bool kSkip = S::kGen;
     static_assert(!kSkip || !kMbs || kSurface, "the product left over is folded in with the last stage's parity below");
     auto run = [&](auto late_) {
         using Yes = std::integral_constant<bool, true>;
@@ -846,8 +814,8 @@ __global__ __launch_bounds__(S::NT) void gemm_ring_kernel(GemmArgs g) {
         if constexpr (kTwoGroups) {
             // two groups per turn: which of the two slots a group's E8M0 bytes and MBS words sit in is then a
             // constant of the LDS instructions that read them, which saves the vector ALUs the address additions
-            // (form 1: a partial last group has a slot of its own and is first read in the stage before it)
-            const int n_paired = S::kRegs ? min(n_issue, (nwhole - 1) * kRingGroup) : n_issue;
+            // (general form: a partial last group has a slot of its own and is first read in the stage before it)
+            const int n_paired = S::kGen ? min(n_issue, (nwhole - 1) * kRingGroup) : n_issue;
             for (; s + 8 <= n_paired; s += 8) {
                 stage(s, fa, fb, P0{}, late_, Yes{}, G0{});
                 stage(s + 1, fb, fa, P1{}, late_, Yes{}, G0{});

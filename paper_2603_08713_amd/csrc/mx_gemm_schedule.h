@@ -37,34 +37,31 @@ constexpr int kSigmaSlots = 4;                  // as many as ring slots: a stag
 
 // kSides: which operands carry MBS words (0 none, 1 A only, 2 B only, 3 both).
 // kForm: 0 = fast form, which wants K % 512 == 0 and 16-byte (E8M0) / 4-byte (MBS) aligned rows, so that a row's
-// bytes of four stages travel as one piece per lane.  1, 2 = general forms for everything else, grouped problems
-// included; the last stage may be partly empty and the stage count is padded to whole groups with stages that read
-// zeros.  1 (any K % 32 == 0, K > 0, any address): the same 16-byte and 4-byte pieces, one row per
+// bytes of four stages travel as one piece per lane.  1 = general form for everything else (any K % 32 == 0, K > 0, any
+// address), grouped problems included; the last stage may be partly empty and the stage count is padded to whole groups
+// with stages that read zeros.  The same 16-byte and 4-byte pieces, one row per
 // lane, but through registers - a load into registers takes any address, a direct-to-LDS load of 16 bytes does not -
 // and the thread writes them to LDS; K's last group, where it is not whole, is fetched in the prologue into a slot of
-// its own.  2 (any K, 0 among them, any address): E8M0 bytes and MBS words travel direct to LDS as single bytes, each in
-// an LDS dword of its own.
+// its own.
 template <int NWM_, int NWN_, int FM_, int FN_, int kSides_, int kForm_ = 0>
 struct RingShape {
     static constexpr int NWM = NWM_, NWN = NWN_, FM = FM_, FN = FN_, kSides = kSides_;
-    static constexpr bool kMbs = kSides != 0, kGen = kForm_ != 0, kBytes = kForm_ == 2, kRegs = kForm_ == 1;
+    static constexpr bool kMbs = kSides != 0, kGen = kForm_ == 1;
     // (couples of A fragments against one B fragment at a time; instantiated with one and with two B fragments)
     static constexpr bool kSurface = kSides == 3 && FM_ % 2 == 0 && (FN_ == 1 || FN_ == 2);
     static constexpr int NW = NWM * NWN, NT = NW * kWave;
     static constexpr int TM = NWM * FM * 32, TN = NWN * FN * 32;
     static constexpr int kRows = TM + TN;             // rows of A followed by rows of B
     static constexpr int kCodeDma = kRows / 16 / NW;  // per wavefront and stage: 16 rows x 64 B per load
-    // per wavefront and group of four stages: E8M0 bytes (one row per lane; single bytes: 4 rows x 16 bytes per
-    // load) and MBS words (one row per lane; single bytes: 16 rows x 4 words per load)
+    // per wavefront and group of four stages: E8M0 bytes and MBS words, one row per lane
     static constexpr int kRowDma = ceil_div(kRows, kWave * NW);
-    static constexpr int kScaleDma = kBytes ? kRows / 4 / NW : kRowDma;
-    static constexpr int kM8Dma = kBytes ? kRows / 16 / NW : kRowDma;
+    static constexpr int kScaleDma = kRowDma, kM8Dma = kRowDma;
     static constexpr int kRowsPadded = kRowDma * NW * kWave;
     static constexpr int kCodesStage = kRows * kRingRowStage;
-    static constexpr int kScaleGroup = kBytes ? kRows * 64 : kRowsPadded * 16;
-    static constexpr int kM8Group = !kMbs ? 0 : kBytes ? kRows * 16 : kRowsPadded * 4;
-    // group g sits in slot g % 2; with kRegs K's last, partial group in slot 2
-    static constexpr int kGroupSlots = kRegs ? 3 : 2;
+    static constexpr int kScaleGroup = kRowsPadded * 16;
+    static constexpr int kM8Group = kMbs ? kRowsPadded * 4 : 0;
+    // group g sits in slot g % 2; in the general form K's last, partial group in slot 2
+    static constexpr int kGroupSlots = kGen ? 3 : 2;
     static constexpr int kSigmaStage = kMbs ? kRows * 4 : 0;
     // The small arrays come first: their addresses then fit the 16-bit constant of an LDS instruction.
     static constexpr int kM8Base = 0;
@@ -80,7 +77,6 @@ struct RingShape {
     static constexpr int kStageRegion = 32 * (FN * 32 * 4 + 16);  // per wavefront, epilogue staging
     static_assert(NW == 4 || NW == 8, "one or two wavefronts per SIMD");
     static_assert((TM / 16) % NW == 0 && (TN / 16) % NW == 0, "16-row code loads: operand fixed per load index");
-    static_assert(!kBytes || (TM % 128 == 0 && TN % 128 == 0 && kRows % (16 * NW) == 0), "single bytes: operand fixed per load index");
     static_assert(TM % kWave == 0 && TN % kWave == 0, "a wavefront's rows belong to one operand");
     static_assert(kLdsBytes <= 160 * 1024, "LDS capacity of a gfx950 compute unit");
     static_assert(NW * kStageRegion <= kLdsBytes, "epilogue staging fits the LDS of the main loop");

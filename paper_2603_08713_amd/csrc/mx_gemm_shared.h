@@ -45,11 +45,10 @@ struct GemmArgs {
 int launch_gemm_wide(const GemmArgs& g, int tile, hipStream_t s);
 const char* describe_gemm_wide(int64_t M, int64_t N, int64_t K);  // what launch_gemm_wide(tile = 0) does with a problem, C in bf16 and whole
 int launch_gemm_mbs_ring(const GemmArgs& g, int variant, hipStream_t s);
-// The same kernels in their general forms (any K % 32 == 0, any alignment of the scale arrays, grouped or not),
-// defined in mx_gemm_general.hip (with MBS) and mx_gemm_wide.hip (without).  tile: 0 = 256 x 128, 1 = 128 x 128;
-// bytes: E8M0 bytes fetched one at a time (needed when K = 0; 128 x 128 tiles only).
-int launch_gemm_mbs_general(const GemmArgs& g, int tile, bool bytes, hipStream_t s);
-int launch_gemm_wide_general(const GemmArgs& g, int tile, bool bytes, hipStream_t s);
+// The same kernels in their general form (any K % 32 == 0, K > 0, any alignment of the scale arrays, grouped or not),
+// defined in mx_gemm_general.hip (with MBS) and mx_gemm_wide.hip (without).  tile: 0 = 256 x 128, 1 = 128 x 128, 2 = 64 x 128 (with MBS).
+int launch_gemm_mbs_general(const GemmArgs& g, int tile, hipStream_t s);
+int launch_gemm_wide_general(const GemmArgs& g, int tile, hipStream_t s);
 // Few activation rows (mx_gemm_skinny.h): M <= 16 fm, not grouped; fm, fn = fragments of 16 rows of A and of B per
 // workgroup, form as there (mx_gemm_skinny.hip).  More rows, in tiles of 64 (mx_gemm_skinny_rows.hip).
 int launch_gemm_skinny_tile(const GemmArgs& g, bool use_mbs, int fm, int fn, int form, hipStream_t s);

@@ -404,7 +404,6 @@ int main() {
     SHAPE(2, 2, 2, 2, 0);
     SHAPE(2, 2, 4, 2, 0, 1);
     SHAPE(2, 2, 2, 2, 0, 1);
-    SHAPE(2, 2, 2, 2, 0, 2);
     SHAPE(4, 2, 2, 2, 3);
     SHAPE(2, 4, 4, 1, 1);
     SHAPE(2, 4, 4, 1, 2);
@@ -413,7 +412,6 @@ int main() {
     SHAPE(2, 4, 2, 1, 2);
     SHAPE(4, 2, 2, 2, 3, 1);
     SHAPE(2, 4, 2, 1, 3, 1);
-    SHAPE(2, 4, 2, 1, 3, 2);
     SHAPE(1, 4, 2, 1, 3);
     SHAPE(1, 4, 2, 1, 3, 1);
     // the forms of the kernel for 8-bit and 6-bit operands, with and without MBS words

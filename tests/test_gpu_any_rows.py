@@ -43,3 +43,20 @@ def test_odd_blocks_and_addresses(mx, oracle, shape, K, shift):  # noqa: F811
         if rows:
             want = oracle.gemm(tuple(t[rows] for t in a), tuple(t[e * N:(e + 1) * N] for t in w))
             close(got[rows], want, (K, "group", e))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,N", [(1, 1), (5, 130), (261, 139), (3, 4096)])
+def test_empty_sum(mx, dtype, M, N):  # noqa: F811
+    """K = 0: zeros in C's rows and nothing beside them; grouped, in the rows that belong to a group."""
+    empty = lambda rows: [torch.empty((rows, 0), dtype=torch.uint8, device="cuda") for _ in range(3)]  # noqa: E731
+    full = torch.full((M + 2, N + 3), -3.0, dtype=torch.float32 if dtype == "f32" else torch.bfloat16, device="cuda")
+    offsets = torch.tensor([0, 0, M // 2, M - M // 3], device="cuda")
+    for call, rows in ((lambda out: mx.mx_gemm(*empty(M)[:2], *empty(N)[:2], dtype, out=out), M), (lambda out: mx.mx_gemm_mbs(*empty(M), *empty(N), dtype, out=out), M),
+                       (lambda out: mx.mx_gemm_mbs_grouped(*empty(M), *empty(3 * N), offsets, N, dtype, out=out), M - M // 3)):
+        big = full.clone()
+        call(big[1:M + 1, 1:N + 1])
+        want = full.clone()
+        want[1:rows + 1, 1:N + 1] = 0
+        assert torch.equal(big, want)
+    assert mx.gemm_plan(M, N, 0) == "gemm_zero_kernel"
