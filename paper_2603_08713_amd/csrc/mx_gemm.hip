@@ -108,9 +108,9 @@ SkinnyPlan plan_skinny(int64_t M, int64_t N, int64_t K, bool ring_ok, bool pairs
 //
 // Where the tiles are faster they are not always as exact: with words, their sum over K is one chain of macro blocks, the few-row kernel's is
 // split over four wavefronts.  Error against 64 bits, tiles over few rows: K = 512 0.92, 640 0.97, 672 to 768 1.003 to 1.02, 800 to 896
-// 0.99 to 1.0, 1024 1.02, 1536 1.11, 2880 1.24, 8192 1.46.  So tiles take up to five macro blocks, and seven, where they are clearly
-// cheaper (K up to 640, few-row price over tile price 1.02 to 1.2 and 1.2 to 1.4, tiles' time over few-row: equal routing 0.83, 0.76, Zipf 0.88, 0.77,
-// all rows in one group 1.1, 0.94, with single calls up to 1.4 and 1.2).
+// 0.99 to 1.0, 1024 1.02, 1536 1.11, 2880 1.24, 8192 1.46.  So tiles take up to five macro blocks, and seven, where their price
+// is lower by more than the microsecond that prices of small launches are off (few rows and tiles, K = 512: 64 groups, 91 rows in all, N = 4687 47.3 and
+// 27.3 us; 128, 211 rows, N = 2582 54.2 and 32.0; within the microsecond 16, 92 rows, N = 2026 5.2 and 7.0; 32, 143 rows, N = 963 5.2 and 6.2).
 constexpr int64_t kFewRowsPerGroup = 32;
 
 // Whether the few-row kernel takes a problem that is not grouped and has at most 64 rows.  With K % 512 == 0 and aligned
@@ -149,7 +149,7 @@ bool takes_few_rows(int64_t M, int64_t N, int64_t K, int64_t num_groups, bool ri
         const int64_t st = (K + kMacro - 1) / kMacro;
         if (K < 512 || sides == 0 || (st > 5 && st != 7)) return true;
         const GroupedPrices p = grouped_prices(M, N, K, num_groups);
-        return p.few <= 1.2 * p.small;
+        return p.few <= 1.02 * p.small + 1.0;
     }
     return M <= 64 && K <= 8192 && few_rows_pay(M, N, K, plan_skinny(M, N, K, ring_ok, pairs_ok), sides);
 }
