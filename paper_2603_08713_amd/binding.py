@@ -117,7 +117,8 @@ _dev = threading.local()
 def forced(**choices):
     """quantize_hw / quantize_elem_hw = 0 or 1 (rounding implementation), gemm_shape = a kernel form and
     tile shape code of mx_gemm.hip, gemm_elem = which kernel takes an 8-/6-bit GEMM (1 = the main kernel's general
-    form, 2 = the main kernel in the form the problem allows, 3 = the few-row kernel)."""
+    form, 2 = the main kernel in the form the problem allows, 3 = the few-row kernel, 16 / 17 / 18 = the main kernel on 256 x 128 /
+    128 x 128 / 64 x 128 tiles, the last two for K >= 512)."""
     allowed = {"quantize_hw", "quantize_elem_hw", "gemm_shape", "gemm_elem"}
     if set(choices) - allowed:
         raise TypeError("unknown choice: %s" % sorted(set(choices) - allowed))

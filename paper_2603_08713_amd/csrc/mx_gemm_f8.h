@@ -709,8 +709,8 @@ int launch_f8_kernel(GemmArgs g, hipStream_t s) {
 // Then one round of 128 x 128 tiles: against 64 x 128, with words, us: 347 x 6038 x 3008 in E5M2 20.9 and 24.8, in E3M2 20.6 and 24.0; 1053 x 2205
 // x 1536 in E4M3 13.5 and 15.0; at K = 512 within 4 %.
 // With words and past both, what the three kernels take (TilePrice), fitted to 60 problems in E4M3 and E2M3 of 65 to 4100 rows,
-// 1000 to 15000 columns and K from 512 to 8192, even and odd ones: 5 % off, and the cheapest by these prices is 0.3 % slower than the fastest, where
-// rounds x area at 0.75 of the large tile's rate was 5.2 %.  256 x 128, 128 x 128 and 64 x 128, us: E2M3 784 x 6290 x 512 12.2, 15.7, 13.6; 751
+// 1000 to 15000 columns and K from 512 to 8192, even and odd ones: 5 % off, and the cheapest by these prices is 0.3 % slower than the fastest (2 % over
+// 80 problems it was not fitted to), where rounds x area at 0.75 of the large tile's rate was 5.2 %.  256 x 128, 128 x 128 and 64 x 128, us: E2M3 784 x 6290 x 512 12.2, 15.7, 13.6; 751
 // x 11471 x 2048 42.4, 41.9, 38.0; E4M3 278 x 12679 x 512 11.9, 14.1, 10.0; 2594 x 3121 x 960 29.4, 30.0, 25.9.
 // Without words that gains 0.4 %: rounds of one tile per compute unit x tile area / efficiency, the 128 x 128 tile taken at 0.55 of the
 // large one's rate per output (it reads as many bytes a stage for half the products).  Rounds of large and of small tiles, E4M3,

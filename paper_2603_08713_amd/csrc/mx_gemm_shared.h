@@ -81,7 +81,8 @@ int launch_gemm_skinny_elem(const GemmArgs& g, int a_elem, int b_elem, hipStream
 // c0 + c1 st + x (c2 + c3 st) with st stages of K and x rounds of `tiles` tiles of rows x cols, of which a part costs `part` of a
 // whole one and the rest in proportion.  Fitted to 75 problems of 65 to 8190 rows, 300 to 15000 columns and K from 512 to 8192 (even
 // and odd ones, weights from memory): 3 to 7 % off in the mean, 10 % for the kernels without words, and the cheapest by these prices is
-// 0.3 to 0.9 % slower than the fastest of the kernels, where rounds x area at one rate per tile shape was 5 (with words) to 11 % (without).
+// 0.3 to 0.9 % slower than the fastest of the kernels, where rounds x area at one rate per tile shape was 5 (with words) to 11 % (without).  240 problems
+// they were not fitted to, each with its measured times and prices, are in profiles/tile_prices.txt.
 struct TilePrice {
     int rows, cols, tiles;
     double part, c0, c1, c2, c3;
