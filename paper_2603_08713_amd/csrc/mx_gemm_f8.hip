@@ -49,12 +49,16 @@ int launch_gemm_elem(int a_elem, const uint8_t* a_codes, const uint8_t* a_scales
     // 12.9, 16.7, 25.7, N = 8800 12.0, 17.3, 21.5, 31.6 and 9.1, 13.2, 17.0, 25.9; 64 rows, N = 4096 10.3, 13.0, 16.1, 24.0 and 9.2, 13.1, 16.7, 26.1,
     // N = 4160 15.2, 20.2, 25.8, 38.7 and 9.3, 13.1, 16.9, 26.2.  E3M2: 8 rows, N = 10548 8.6, 12.2, 15.2, 22.1 and 9.0, 13.3, 16.9, 25.6; 26
     // rows, N = 4945 8.9, 11.6, 14.8, 22.5 and 9.4, 12.9, 16.6, 25.6; 64 rows, N = 4096 10.2, 12.8, 15.6, 23.7 and 9.5, 13.1, 16.7, 26.0.  More than
-    // 32 rows in one round are 64 to this kernel's tile and fewer to its loads.  Tiles over few rows at 33, 40, 48 and 64, N = 64 to 4096: K = 1024 1.05,
-    // 1.01, 1.01, 0.95; 1536 1.12, 1.08, 1.06, 1.0; 2048 1.16, 1.13, 1.11, 1.04; without words K = 2048 0.99, 0.96, 0.94, 0.88; 3072 1.05, 1.0, 0.98, 0.91.
+    // 32 rows in one round are 64 to this kernel's tile and fewer to its loads.  Tiles over few rows, words, GEMM alone, 14000 problems of N = 128 to 4096, rows 33
+    // to 40, to 48, to 56, to 64: K = 512 0.98, 0.97, 0.94, 0.92 in E4M3 and 1.01, 1.00, 0.98, 0.96 in E3M2; 1024 1.10, 1.07, 1.03, 1.00 (0.97 in bf16) and
+    // 1.13, 1.11, 1.07, 1.04; 1536 1.19, 1.16, 1.10, 1.08 and 1.22, 1.19, 1.14, 1.10; without words K = 2048 0.99, 0.96, 0.94, 0.88 at 33,
+    // 40, 48 and 64, 3072 1.05, 1.0, 0.98, 0.91.
     // Without words the tiles gain more, and from K = 5120 on, with 8-bit weights that no cache holds, the few rows again: 8 rows, N = 8800 19.1
-    // and 23.1 in E4M3 (the other formats and row counts within 14 % either way).
+    // and 23.1 in E4M3 (the other formats and row counts within 14 % either way).  In six bits short K leaves tiles little to gain: tiles over few rows, three
+    // and four rounds, to 8 and to 16 rows: K = 512 1.11, 1.06, 1024 1.05, 0.99, 1536 1.00, 0.95 (8 bits 0.88, 0.86; 0.86, 0.82; 0.86, 0.81).
     const int64_t few_work = (M <= 16 ? 1 : M <= 32 ? 2 : 4) * ((N + 4095) / 4096);
-    const int64_t few_from = !use_mbs ? (M > 32 && M <= 40 ? 3072 : 5120) : M > 40 ? 1536 : M > 32 ? 1024 : a8 ? 2560 : 0;
+    const bool short_six = !use_mbs && !a8 && M <= 16 && K <= (M <= 8 ? 1024 : 512);
+    const int64_t few_from = !use_mbs ? (short_six ? 0 : M > 32 && M <= 40 ? 3072 : 5120) : M > 56 && a8 ? 1536 : M > 32 ? 1024 : a8 ? 2560 : 0;
     // E2M3's products fit the matrix unit's sum without a cut, so the order of the sum over K shows: error against 64 bits, tiles over
     // few rows, with words, E2M3 on either side: K = 512 1.0, 1024 1.06, 2048 1.19, 4096 1.36, 8192 1.69.  Past K = 512 it stays with this
     // kernel's split sum.  Without words both are exact on such data, and the other formats' cut hides the order (1.0000 at every K).

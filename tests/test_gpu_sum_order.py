@@ -70,11 +70,14 @@ def test_e2m3(mx, a_elem, b_elem, M, N, K):  # noqa: F811
 @pytest.mark.parametrize("elem,words,M,N,K,few", [("e4m3", True, 8, 16384, 4096, True), ("e4m3", True, 8, 16500, 4096, False), ("e5m2", True, 40, 300, 1024, True),
                                                   ("e4m3", True, 64, 300, 1536, True), ("e4m3", True, 64, 300, 1024, False), ("e4m3", False, 33, 300, 3072, True),
                                                   ("e4m3", False, 41, 300, 3072, False), ("e4m3", False, 12, 16400, 8192, False), ("e2m3", True, 41, 4100, 1024, True),
-                                                  ("e2m3", False, 41, 4100, 1024, False)])
+                                                  ("e2m3", False, 41, 4100, 1024, False),
+                                                  ("e4m3", True, 56, 300, 1024, True), ("e3m2", True, 64, 4096, 1024, True),
+                                                  ("e3m2", False, 8, 16384, 1024, True), ("e3m2", False, 9, 16384, 512, True), ("e3m2", False, 9, 8200, 1024, False),
+                                                  ("e3m2", False, 8, 16385, 512, False), ("e3m2", False, 8, 8200, 1536, False), ("e4m3", False, 8, 8200, 1024, False)])
 def test_lines_of_the_few_row_kernel(mx, elem, words, M, N, K, few):  # noqa: F811
     """Which kernel 8-bit and 6-bit calls take, by the sums' bits: the few-row kernel's, or the tiles', which differ on such operands."""
     a, b = quantized(mx, 1, M, K, elem), quantized(mx, 2, N, K, elem, 0.02)
-    if not words and elem == "e2m3":  # (what is exact in every order says nothing: scales far apart)
+    if not words:  # (what is exact in every order says nothing: scales far apart)
         a[1].copy_(torch.randint(100, 150, a[1].shape, generator=torch.Generator(device="cuda").manual_seed(3), device="cuda", dtype=torch.uint8))
         b[1].copy_(torch.randint(100, 150, b[1].shape, generator=torch.Generator(device="cuda").manual_seed(4), device="cuda", dtype=torch.uint8))
     got = {}
