@@ -235,7 +235,7 @@ int mx_dequantize_elem(mx_elem_t elem, const uint8_t* codes, const uint8_t* scal
  * points), codes 16-byte aligned, scale arrays 4-byte aligned (2-byte where K % 128 == 64); anything else
  * returns MX_EUNSUPPORTED and nothing is launched.  (K % 512 == 0,
  * 16-byte aligned scale arrays and 4-byte aligned MBS arrays take a faster form of the kernel; with M <= 64 and
- * K <= 8192 besides, a kernel that streams the weights once.)
+ * K <= 8192 besides, where it is faster or more exact, a kernel that streams the weights once.)
  *
  * Accumulation contract.  The exact result is  C[m, n] = sum over macro blocks g of sigma_A[m, g] sigma_B[n, g]
  * P_g[m, n],  P_g = the sum over the 128 K-elements of g of the products of the dequantized elements.  What is

@@ -1,6 +1,6 @@
 // Block-scaled MXFP4 GEMM  C = A * B^T  with the Macro Block Scaling correction, for gfx950: argument checks and
 // the choice of kernel.  The kernels are the main template (mx_gemm_ring.h: fast form in mx_gemm_wide.hip and
-// mx_gemm_mbs.hip, general forms in mx_gemm_general.hip and mx_gemm_wide.hip) and the few-row kernel
+// mx_gemm_mbs.hip, general form in mx_gemm_general.hip and mx_gemm_wide.hip) and the few-row kernel
 // (mx_gemm_skinny.h; mx_gemm_skinny.hip, mx_gemm_skinny_rows.hip, mx_gemm_skinny_fused.hip, mx_gemm_skinny_grouped.hip).
 #include "mx_gemm_shared.h"
 #include "mx_internal.h"
@@ -55,7 +55,7 @@ bool grouped_small_tile(int64_t M, int64_t N, int64_t K, int64_t num_groups) {
 // does, where single bytes (K % 64 = 32 once took them) keep the texture-address unit busy three times as long as the codes and leave
 // LDS for 128 x 128 tiles only.  With the quantizer: 305 x 1205 x 1632 21.8 -> 13.3 us, 5680 x 1130 x 6880 110 -> 75.
 int choose_shape(int64_t M, int64_t N, int64_t K, int64_t num_groups, bool use_mbs, bool ring_ok, bool skinny_ok, int row_tile_cols,
-                 bool tile64_ok) {
+                 bool tile64_ok, bool c_lines) {
     const int64_t t256x128 = ((M + 255) / 256) * ((N + 127) / 128), t128 = ((M + 127) / 128) * ((N + 127) / 128);
     const double big = 2.0 * ((t256x128 + 255) / 256) / (use_mbs ? 1.0 : 0.85),
                  small = ((t128 + 255) / 256) / (use_mbs ? 0.8 : 0.72);
@@ -66,6 +66,12 @@ int choose_shape(int64_t M, int64_t N, int64_t K, int64_t num_groups, bool use_m
     // Past one round, with words on both operands or in the general form: by the kernels' prices (mx_gemm_shared.h)
     // (256 x 128, 128 x 128 and 64 x 128 tiles, us: 2316 x 3815 x 5120 65, 69, 60; 5676 x 1854 x 512 18.2, 19.0, 16.8;
     // 1579 x 2784 x 1024 11.2, 14.6, 12.5; 1367 x 3890 x 7296 50, 73, 61)
+    // The prices were fitted to rows of C on any element.  Rows on whole 128-byte lines (c_lines) cost the larger tile's epilogue less, and near a tie
+    // the price picks the smaller: one round of 256 x 128 against more than one of 64 x 128 (two on a compute unit), K = 512, in bf16 1.00 and 1.11 of the fastest
+    // tile's time in the mean of 103 problems (784 x 6272 x 512 7.9 and 9.1 us), longer K more; in the general form one round of 128 x 128 against 64 x 128,
+    // K < 640, to 1024, to 1536, to 2560 1.00 and 1.05, 1.03, 1.03, 1.01 (from 2560 on even, then 64 x 128 gains).
+    if (c_lines && tile64_ok && t256x128 <= 256 && ((M + 63) / 64) * ((N + 127) / 128) > 512) return ring_ok ? 3 : 8;
+    if (c_lines && tile64_ok && !ring_ok && t128 <= 256 && K < 2048) return 9;
     if (more_than_a_round_of_64x128(M, N) && (tile64_ok || (!use_mbs && !ring_ok))) {
         static const TilePrice kFast[3] = {{256, 128, 256, 0.7, 3.40, 0.003, 4.91, 0.726}, {128, 128, 256, 0.8, 2.72, 0.018, 3.26, 0.480}, {64, 128, 512, 0.4, 3.83, 0.098, 2.29, 0.453}};
         static const TilePrice kGeneral[3] = {{256, 128, 256, 0.7, 2.82, 0.030, 5.48, 0.815}, {128, 128, 256, 0.8, 2.64, 0.021, 3.25, 0.592}, {64, 128, 512, 0.6, 3.27, 0.100, 2.81, 0.523}};
@@ -235,7 +241,8 @@ int launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* 
     const bool pairs_ok = (K % 64) == 0 && aligned(a_scales, 2) && aligned(b_scales, 2);
     const bool skinny_ok = takes_few_rows(M, N, K, g.num_groups, ring_ok, pairs_ok, use_mbs ? (a_mbs != nullptr) + (b_mbs != nullptr) : 0);
     const bool tile64_ok = !grouped && a_mbs && b_mbs && mbs_entry;
-    int shape = choose_shape(M, N, K, g.num_groups, use_mbs, ring_ok, skinny_ok, row_tile_columns(M, N, K, g.num_groups, ring_ok, pairs_ok), tile64_ok);
+    int shape = choose_shape(M, N, K, g.num_groups, use_mbs, ring_ok, skinny_ok, row_tile_columns(M, N, K, g.num_groups, ring_ok, pairs_ok), tile64_ok,
+                             aligned(C, 128) && (ldc * esz) % 128 == 0);
     if (force_shape >= 0) shape = force_shape;
     // (the checks below only matter for forced shapes)
     if (shape == 5) {
@@ -325,7 +332,7 @@ int mx_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int a_has_mbs, int b_
     const bool ring_ok = !grouped && (K % 512) == 0, pairs_ok = (K % 64) == 0;
     const int shape = mx::choose_shape(M, N, K, num_groups, use_mbs, ring_ok, mx::takes_few_rows(M, N, K, num_groups, ring_ok, pairs_ok, (a_has_mbs != 0) + (b_has_mbs != 0)),
                                        mx::row_tile_columns(M, N, K, num_groups, ring_ok, pairs_ok),
-                                       !grouped && a_has_mbs && b_has_mbs);
+                                       !grouped && a_has_mbs && b_has_mbs, N % 64 == 0);  // (C in bf16 and whole)
     const char* sides = a_has_mbs && b_has_mbs ? "MBS words on A and B" : a_has_mbs ? "MBS words on A" : b_has_mbs ? "MBS words on B" : "no MBS";
     const char* what;
     switch (shape) {

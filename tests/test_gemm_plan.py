@@ -39,3 +39,10 @@ def test_tiles_whose_grid_a_launch_takes():
 def test_plain_tiles_by_the_rows_of_c(M, N, K, tile):
     """Without words: rows of C on 16 bytes go by area, others and whole lines by price as long as K is short."""
     assert tile in mx.gemm_plan(M, N, K, False, False)
+
+
+@pytest.mark.parametrize("M,N,K,tile", [(784, 6272, 512, "256x128"), (784, 6280, 512, "64x128"), (1500, 2048, 576, "128x128"), (1500, 2048, 1984, "128x128"), (1500, 2048, 7744, "64x128"),
+                                        (1024, 2048, 576, "64x128"), (1300, 2500, 1088, "64x128"), (1300, 2496, 1088, "128x128"), (1024, 8192, 1088, "256x128")])
+def test_tiles_for_rows_of_c_on_lines(M, N, K, tile):
+    """With words: near a tie of the prices, rows of C on whole lines go to the larger tile."""
+    assert " " + tile in mx.gemm_plan(M, N, K)

@@ -265,7 +265,7 @@ print("first launch ok")
 @pytest.mark.parametrize("M,N,K", [(4096, 14336, 4096), (2048, 2048, 2048), (3000, 2880, 2880), (700, 530, 2016)])
 def test_gemm_repeated_launches_are_bit_identical(mx, M, N, K):
     """The kernels have no atomics and a fixed summation order, so every launch on the same operands must give
-    the same bits; a difference means a synchronisation hole (fast form, small tiles, both general forms)."""
+    the same bits; a difference means a synchronisation hole (fast form, small tiles, general form)."""
     rng = np.random.default_rng(M + N + K)
     a, b = [dev_u8(t) for t in random_operand(rng, M, K, 120, 134)], [dev_u8(t) for t in random_operand(rng, N, K, 120, 134)]
     first_m = mx.mx_gemm_mbs(*a, *b, "bf16")
