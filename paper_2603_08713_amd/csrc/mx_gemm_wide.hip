@@ -26,14 +26,15 @@ using Small = RingShape<2, 2, 2, 2, 0>;
 constexpr int64_t kUnits = 256;  // compute units of the device
 
 // Whether the tile goes by prices, from where the rows of C start (their bytes, and the address of the first).  The prices were fitted to
-// rows on any element.  Rows on 16 bytes are stored past the caches, which costs the small tiles, with half the bytes per piece of a row,
-// up to half their time where rows straddle lines, and the large tile nothing: 4826 x 15920 x 1024 in bf16 133 us by price and 77 by area, 1777 x
-// 5004 x 2048 in fp32 23.6 and 20.1.  Means over 1368 problems in each type, of the fastest tile's time, K = 512, 1024 to 1536, 2048 to 3072, from 4096:
-// rows on any element 1.00, 1.00, 1.01, 1.015 by price, 1.10, 1.04, 1.02, 1.005 by area; on 16 bytes 1.02, 1.06, 1.03, 1.03 and 1.05, 1.03, 1.015, 1.005;
-// on whole lines at K = 512 the price is 0.94 of the area's time.
+// rows on any element.  Rows on 16 bytes are stored past the caches, which favours the large tile as K grows: it writes twice the bytes per piece of a row.
+// Means of the fastest tile's time over 7000 other problems, by price and by area, K = 512, 1024, 1536, 2048, 3072: rows on 16 bytes
+// 1.01, 1.01, 1.01, 1.01, 1.01 and 1.05, 1.04, 1.02, 1.02, 1.01; on whole lines 1.00, 1.00, 1.00, 1.01, 1.01 and 1.09, 1.06, 1.03, 1.02, 1.01; on any element, 1368
+// problems, 1.00, 1.00, 1.01 by price, 1.10, 1.04, 1.02 by area, and from K = 4096 1.015 and 1.005.  Where rows on 16 bytes straddle lines, K = 1024 took the
+// small tile up to twice its time in some runs and not in others (4826 x 15920 x 1024 in bf16 133 us in one, 72 in another, the large tile 77 and 75; why is
+// not known), so these go by area from there on.
 bool goes_by_price(int64_t K, uintptr_t first, int64_t row_bytes) {
     const uintptr_t both = first | (uintptr_t)row_bytes;
-    return both % 16 != 0 ? K < 4096 : both % 128 == 0 && K < 1024;
+    return K < (both % 16 != 0 ? 4096 : both % 128 != 0 ? 1024 : 2048);
 }
 
 // What launch_gemm_wide does with a problem: the tile (1, 2, 3 as above) and, for the large tile, how many

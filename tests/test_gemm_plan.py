@@ -35,9 +35,10 @@ def test_tiles_whose_grid_a_launch_takes():
 
 @pytest.mark.parametrize("M,N,K,tile", [(4826, 15920, 1024, "256x256"), (7130, 11368, 1024, "256x256"), (2939, 8592, 1024, "256x256"), (3000, 3000, 4096, "256x256"),
                                         (4826, 15917, 1024, "128x128"), (718, 11043, 8192, "256x256"),
-                                        (4096, 14336, 512, "128x128"), (4096, 14344, 512, "256x256")])
+                                        (4096, 14336, 512, "128x128"), (4096, 14344, 512, "128x128"),
+                                        (3498, 3584, 1024, "128x128"), (4096, 14336, 1536, "128x128"), (3498, 3584, 2048, "256x256")])
 def test_plain_tiles_by_the_rows_of_c(M, N, K, tile):
-    """Without words: rows of C on 16 bytes go by area, others and whole lines by price as long as K is short."""
+    """Without words: by price as long as K is short, longest where rows of C start on any element, shortest where they start on 16 bytes; else by area."""
     assert tile in mx.gemm_plan(M, N, K, False, False)
 
 
